@@ -217,6 +217,7 @@ static Shape make_shape(const fastocr_kv_view *kv, const fastocr_batch_view *bv,
     auto m16 = [&](int64_t elems) { return (elems * esz) % 16 == 0; };
     s.vec16 = a16(kv->k) && a16(kv->v) && m16(kv->stride_token) && m16(kv->stride_head) && m16(kv->stride_seq) &&
               m16(kv->stride_page) && m16(kv->head_dim);
+    s.fast32 = kv->dtype == FASTOCR_F32 && (kv->head_dim == 128 || kv->head_dim == 64) && n_q_heads / kv->n_kv_heads <= 16 && s.vec16;
     return s;
 }
 
@@ -257,7 +258,7 @@ static int choose_splits(int op, const Shape &s, int max_positions, bool *partia
     if (forced > 0) {
         nsplit = forced;
     } else {
-        const int streams = s.batch * (fast ? s.kv.n_kv_heads : s.n_q_heads);
+        const int streams = s.batch * (fast || s.fast32 ? s.kv.n_kv_heads : s.n_q_heads);
         // Measured on MI355X: the streaming kernels run best with about one workgroup per compute
         // unit (few, long, equally sized streams), the plain-FMA kernels with many small ones.
         const int target_wg = fast ? kNumCU : 8 * kNumCU;
@@ -293,7 +294,16 @@ static int choose_splits(int op, const Shape &s, int max_positions, bool *partia
                 return n;
             }
         }
-        nsplit = (target_wg + streams - 1) / (streams > 0 ? streams : 1);
+        // fp64 matrix-core kernels: two workgroups of four waves per compute unit (rounded down: no more partials
+        // than the plain kernels left, which bounds the shapes the static scratch serves)
+        if (s.fast32) {
+            nsplit = 2 * kNumCU / (streams > 0 ? streams : 1);
+            // a list of up to two (head_dim 64: three) tiles per wave is not cut: the one launch then writes the
+            // output itself (head_dim 128: 100 tokens 10.1 us uncut, 12.3 cut; 160 tokens 12.8, 12.3; head_dim 64: 160
+            // tokens 9.8, 12.5; replayed from a graph 9.8, 9.2; 12.8, 9.4; 8.0, 7.6)
+            if (op != FASTOCR_OP_FOCAL_SCORE && by_work <= (s.kv.head_dim == 64 ? 3 : 2)) nsplit = 1;
+        }
+        else nsplit = (target_wg + streams - 1) / (streams > 0 ? streams : 1);
         // pruned attention is short: when eight waves get at most eight tiles each, or at least half
         // a chip of streams exists, one eight-wave workgroup per stream writes the final output
         // itself (no partials, no merge kernel -- a second launch costs more than it saves here)
@@ -352,6 +362,10 @@ size_t fastocr_workspace_bytes(int op, const fastocr_kv_view *kv, const fastocr_
         size_t need = fastocr_workspace_bytes(FASTOCR_OP_FOCAL_SCORE, kv, bv, n_q_heads, 0);
         const size_t dense = fastocr_workspace_bytes(FASTOCR_OP_DENSE_DECODE_ATTN, kv, bv, n_q_heads, 0);
         need = need > dense ? need : dense;
+        if (s.fast32) {
+            const size_t one = round256(focal_f32_workspace_bytes(s, choose_splits(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len)) + 256);
+            need = need > one ? need : one;
+        }
         ResidentPlan rp;
         if (s.kv.head_dim == 128 && resident_plan(s, plan_cu_count(), &rp)) {
             const size_t fused = round256(focal_fused_workspace_bytes(s, rp) + 256);
@@ -601,6 +615,14 @@ static int focal_attn_score_impl(const fastocr_kv_view *kv, const fastocr_batch_
         hipError_t e = launch_focal_fused(s, rp, slot, flag, q, scale, out, scores, lse, img_mass, ws, (hipStream_t)hip_stream,
                                           fuse ? select : nullptr, hand_on ? defer : nullptr);
         if (fused) *fused = fuse;
+        if (hand_on) *deferred = true;
+        return e == hipSuccess ? FASTOCR_OK : FASTOCR_EHIP;
+    }
+    if (s.fast32 && g_tune_focal_fused.load(std::memory_order_relaxed) != 0) {
+        const bool hand_on = defer && deferred && topk_takes_combine(bv->max_vis_len, kv->head_dim);
+        const int nsplit = choose_splits(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len);
+        const hipError_t e = launch_focal_f32(s, q, scale, out, scores, lse, img_mass, ws, nsplit, (hipStream_t)hip_stream,
+                                              hand_on ? defer : nullptr);
         if (hand_on) *deferred = true;
         return e == hipSuccess ? FASTOCR_OK : FASTOCR_EHIP;
     }

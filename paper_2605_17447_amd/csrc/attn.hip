@@ -460,7 +460,7 @@ tiles_done:
 // everything a long chain of roundings could spoil runs in fp64: the q.k sums (dot_row), the
 // difference between a logit and the running maximum (exact in double; only the small difference
 // is rounded to fp32 for the exponential), the sum of the weights and the p.V accumulators.  The
-// kernel is off the hot path (none of the paper's models takes it) and stays latency-bound.
+// kernel is off the hot path and stays latency-bound; fp32 caches of head_dim 128 and 64 take attn_f32.hip.
 // -----------------------------------------------------------------------------------------
 // acc[x] += sum_j p_j V[j][lane + 64 x] over the nv tokens of a tile; lane j holds token j's
 // probability pj and row offset off.  Eight tokens' rows are requested before any is used (a row's
@@ -673,6 +673,11 @@ hipError_t launch_attn(const Shape &s, const void *q, float scale, const int32_t
         else        { if (s.paged) FN<__VA_ARGS__ false, true>(kid, s, q, scale_log2, sel_idx, sel_cnt, kmax, part_o, part_ml, nsplit, merge_slot, gave_up_flag, out, lse, stream); \
                       else         FN<__VA_ARGS__ false, false>(kid, s, q, scale_log2, sel_idx, sel_cnt, kmax, part_o, part_ml, nsplit, merge_slot, gave_up_flag, out, lse, stream); } \
     } while (0)
+    if (f32_mfma_path(s)) {
+        const hipError_t e = launch_attn_f32(kid, s, q, scale, sel_idx, sel_cnt, kmax, part_o, part_ml, nsplit, out, lse, nullptr, 0, stream);
+        if (e != hipSuccess || nsplit == 1) return e;                         // one range: the kernel wrote the final output itself
+        return launch_attn_combine(s, part_o, part_ml, nsplit, out, lse, stream);
+    }
     if (mfma_path(s)) {
         FASTOCR_DISPATCH(launch_mfma, scale_log2f, );
     } else if (s.dtype == DT_BF16) {

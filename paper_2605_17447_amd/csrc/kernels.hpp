@@ -39,9 +39,11 @@ struct Shape {
                     // 16-byte aligned rows (decided once from the views by the C-ABI layer); the
                     // one-pass focal kernel and the in-launch merge need head_dim 128, register-resident
                     // scoring takes both
+    bool fast32;    // the fp64 matrix-core kernels of attn_f32.hip cover it: fp32, head_dim 128 or 64, group size <= 16, vec16
 };
 
 inline bool mfma_path(const Shape &s) { return s.fast; }
+inline bool f32_mfma_path(const Shape &s) { return s.fast32; }
 
 // ---- host-side state shared by the launchers (api.hip) --------------------------------------
 // Launch-shape overrides (fastocr_set_tuning); atomics, so that callers on several threads may
@@ -93,12 +95,26 @@ hipError_t launch_attn_combine(const Shape &s, const float *part_o, const float 
                                void *out, float *lse, hipStream_t stream, const int32_t *seq_meta = nullptr,
                                int wpk = 1);
 
+// ---- fp32 caches on the fp64 matrix cores (attn_f32.hip; shapes with s.fast32) --------------
+// sel_idx: pruned attention.  part_o == nullptr: no attention output.  logits: the logits are parked there (with
+// row pitch `pitch`) for the score kernels.  nsplit == 1 without logits: the kernel writes the final output itself.
+hipError_t launch_attn_f32(int kid, const Shape &s, const void *q, float scale, const int32_t *sel_idx, const int32_t *sel_cnt,
+                           int64_t kmax, float *part_o, float *part_ml, int nsplit, void *out, float *lse, float *logits,
+                           int64_t pitch, hipStream_t stream);
+
 // ---- focal scoring (score.hip) ----------------------------------------------------------
 // Workspace: logits fp32 [B][Hq][pitch], part_ml fp32 [B][Hq][nsplit][2], mass partials.
 int score_tile_tokens(const Shape &s);
 size_t score_workspace_bytes(const Shape &s, int nsplit);
 hipError_t launch_score(const Shape &s, const void *q, float scale, float *scores, float *lse,
                         float *img_mass, void *ws, int nsplit, hipStream_t stream);
+
+// A focal layer of an fp32 cache in one pass (s.fast32): attention partials and parked logits from one read of K
+// and V, then the scores.  nsplit: that of dense attention.  defer: see launch_focal_fused.
+size_t focal_f32_workspace_bytes(const Shape &s, int nsplit);
+struct CombineArgs;
+hipError_t launch_focal_f32(const Shape &s, const void *q, float scale, void *out, float *scores, float *lse, float *img_mass,
+                            void *ws, int nsplit, hipStream_t stream, CombineArgs *defer = nullptr);
 
 // ---- focal scoring with register-resident logits (score_resident.hip) ---------------------
 // The plan gives the grid (nranges * batch workgroups, at most one per compute unit) and the
@@ -129,8 +145,9 @@ size_t focal_fused_workspace_bytes(const Shape &s, const ResidentPlan &p);
 struct CombineArgs {
     const float *part_o, *part_ml;
     int nsplit, d, n_q_heads, wpk;
-    const int32_t *seq_meta;
-    uint16_t *out;              // bf16 [B, Hq, d]
+    const int32_t *seq_meta;    // null: nsplit partials per (sequence, head), see launch_attn
+    void *out;                  // [B, Hq, d]: bf16, or fp32 with out_f32
+    bool out_f32;
 };
 // defer != nullptr: the merge of the output's partials is not launched; *defer describes it and the
 // caller passes it to launch_topk, whose launch then does both (the top-k and that merge depend on

@@ -227,7 +227,7 @@ stream_done:
     }
 }
 
-// Generic: one wave per (range, query head, sequence), lanes over tokens.  The q.k sums run in
+// Generic (fp32 caches of head_dim 128 and 64 take attn_f32.hip): one wave per (range, query head, sequence), lanes over tokens.  The q.k sums run in
 // fp64 (dot_row) and are scaled there; the logit is rounded to fp32 once, when it is parked.
 template <typename T, bool PAGED>
 __global__ __launch_bounds__(64) void score_generic_kernel(
@@ -281,7 +281,9 @@ __global__ __launch_bounds__(kFinThreads) void score_finalize_kernel(
     const float *__restrict__ part_ml, int nsplit, float *__restrict__ scores,
     float *__restrict__ lse, float *__restrict__ mass_part)
 {
-    extern __shared__ float lse2[];                    // [Hq]
+    // [Hq][2]: a head's maximum M and 1/Z over the sequence.  A weight is 2^(logit - M) / Z: the difference of two
+    // logits of like size is nearly exact, where logit - (M + log2 Z) would carry the rounding of that sum
+    extern __shared__ float norm[];
     __shared__ float red[kFinThreads / 64];
     const int b = blockIdx.y;
     const SeqGeom geo = seq_geom(bv, b);
@@ -297,9 +299,9 @@ __global__ __launch_bounds__(kFinThreads) void score_finalize_kernel(
 #pragma unroll
         for (int o = 1; o < 8; o <<= 1) softmax_merge(M, Z, __shfl_xor(M, o), __shfl_xor(Z, o));
         if (h < Hq && part == 0) {
-            const float l2 = Z > 0.f ? M + log2f(Z) : -INFINITY;
-            lse2[h] = l2;
-            if (lse && blockIdx.x == 0) lse[(int64_t)b * Hq + h] = l2 * kLn2;
+            norm[2 * h] = M;
+            norm[2 * h + 1] = 1.0f / Z;
+            if (lse && blockIdx.x == 0) lse[(int64_t)b * Hq + h] = (Z > 0.f ? M + log2f(Z) : -INFINITY) * kLn2;
         }
     }
     __syncthreads();
@@ -318,7 +320,7 @@ __global__ __launch_bounds__(kFinThreads) void score_finalize_kernel(
                 const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(row + x0));
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    if (x0 + r < G) acc += fast_exp2(v[r] - lse2[g * G + x0 + r]);
+                    if (x0 + r < G) acc += fast_exp2(v[r] - norm[2 * (g * G + x0 + r)]) * norm[2 * (g * G + x0 + r) + 1];
             }
         }
     }
@@ -373,6 +375,17 @@ size_t score_workspace_bytes(const Shape &s, int nsplit)
     return bytes;
 }
 
+static hipError_t launch_finalize(const Shape &s, const float *logits, int64_t pitch, const float *part_ml, int nsplit,
+                                  float *scores, float *lse, float *img_mass, float *mass_part, hipStream_t stream)
+{
+    const int nblk = fin_blocks(s);
+    dim3 fgrid(nblk, s.batch), fblock(kFinThreads);
+    FASTOCR_LAUNCH(K_SCORE_FINALIZE, score_finalize_kernel, fgrid, fblock, (size_t)s.n_q_heads * 2 * sizeof(float), stream,
+        s.bv, s.n_q_heads, s.kv.n_kv_heads, logits, pitch, part_ml, nsplit, scores, lse, img_mass ? mass_part : nullptr);
+    if (img_mass) mass_reduce_kernel<<<s.batch, 64, 0, stream>>>(mass_part, nblk, img_mass);
+    return hipGetLastError();
+}
+
 hipError_t launch_score(const Shape &s, const void *q, float scale, float *scores, float *lse,
                         float *img_mass, void *ws, int nsplit, hipStream_t stream)
 {
@@ -395,6 +408,10 @@ hipError_t launch_score(const Shape &s, const void *q, float scale, float *score
         else if (s.paged) { if (G <= 8) FASTOCR_SCORE(128, true, 8); else FASTOCR_SCORE(128, true, 16); }
         else              { if (G <= 8) FASTOCR_SCORE(128, false, 8); else FASTOCR_SCORE(128, false, 16); }
 #undef FASTOCR_SCORE
+    } else if (f32_mfma_path(s)) {
+        const hipError_t e = launch_attn_f32(K_SCORE_LOGITS, s, q, scale, nullptr, nullptr, 0, nullptr, part_ml, nsplit, nullptr, nullptr,
+                                             logits, pitch, stream);
+        if (e != hipSuccess) return e;
     } else {
         dim3 grid(nsplit, s.n_q_heads, s.batch), block(64);
 #define FASTOCR_SCORE(T, P) FASTOCR_LAUNCH(K_SCORE_LOGITS, (score_generic_kernel<T, P>), grid, block, 0, stream, \
@@ -406,12 +423,33 @@ hipError_t launch_score(const Shape &s, const void *q, float scale, float *score
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
 
-    const int nblk = fin_blocks(s);
-    dim3 fgrid(nblk, s.batch), fblock(kFinThreads);
-    FASTOCR_LAUNCH(K_SCORE_FINALIZE, score_finalize_kernel, fgrid, fblock, (size_t)s.n_q_heads * sizeof(float), stream,
-        s.bv, s.n_q_heads, s.kv.n_kv_heads, logits, pitch, part_ml, nsplit, scores, lse, img_mass ? mass_part : nullptr);
-    if (img_mass) mass_reduce_kernel<<<s.batch, 64, 0, stream>>>(mass_part, nblk, img_mass);
-    return hipGetLastError();
+    return launch_finalize(s, logits, pitch, part_ml, nsplit, scores, lse, img_mass, mass_part, stream);
+}
+
+// Workspace: as launch_score's, then the attention partials fp32 [B][Hq][nsplit][d] (the softmax statistics serve both).
+size_t focal_f32_workspace_bytes(const Shape &s, int nsplit)
+{
+    return (score_workspace_bytes(s, nsplit) + 255) / 256 * 256 + (size_t)s.batch * s.n_q_heads * nsplit * s.kv.head_dim * sizeof(float);
+}
+
+hipError_t launch_focal_f32(const Shape &s, const void *q, float scale, void *out, float *scores, float *lse, float *img_mass,
+                            void *ws, int nsplit, hipStream_t stream, CombineArgs *defer)
+{
+    const int64_t pitch = logit_pitch(s.bv.max_seq_len);
+    float *logits = reinterpret_cast<float *>(ws);
+    float *part_ml = logits + parked_floats(s);
+    float *mass_part = part_ml + (size_t)s.batch * s.n_q_heads * nsplit * 2;
+    float *part_o = logits + (score_workspace_bytes(s, nsplit) + 255) / 256 * 256 / sizeof(float);
+    hipError_t e = launch_attn_f32(K_FOCAL_FUSED, s, q, scale, nullptr, nullptr, 0, part_o, part_ml, nsplit, nullptr, nullptr, logits,
+                                   pitch, stream);
+    if (e != hipSuccess) return e;
+    e = launch_finalize(s, logits, pitch, part_ml, nsplit, scores, lse, img_mass, mass_part, stream);
+    if (e != hipSuccess) return e;
+    if (defer) {
+        *defer = CombineArgs{part_o, part_ml, nsplit, s.kv.head_dim, s.n_q_heads, 1, nullptr, out, true};
+        return hipSuccess;
+    }
+    return launch_attn_combine(s, part_o, part_ml, nsplit, out, nullptr, stream);
 }
 
 }  // namespace fastocr

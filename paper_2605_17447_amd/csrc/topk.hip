@@ -249,8 +249,9 @@ __global__ __launch_bounds__(kTopkThreads) void focal_tail_kernel(
     } else {
         const int x = (int)blockIdx.x - batch;
         const int b = x / c.n_q_heads, h = x - b * c.n_q_heads;
-        combine_wide_body<uint16_t>(c.part_o, c.part_ml, c.nsplit, c.d, c.out, nullptr, c.seq_meta, c.wpk, h, b, c.n_q_heads,
-                                    CombineShared{sm_max, sm_z, sm_o});
+        const CombineShared cs{sm_max, sm_z, sm_o};
+        if (c.out_f32) combine_wide_body<float>(c.part_o, c.part_ml, c.nsplit, c.d, (float *)c.out, nullptr, c.seq_meta, c.wpk, h, b, c.n_q_heads, cs);
+        else combine_wide_body<uint16_t>(c.part_o, c.part_ml, c.nsplit, c.d, (uint16_t *)c.out, nullptr, c.seq_meta, c.wpk, h, b, c.n_q_heads, cs);
     }
 }
 
