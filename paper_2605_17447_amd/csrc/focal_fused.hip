@@ -5,6 +5,10 @@
 // either computation's traffic, so reading it twice (dense attention, then scoring) wastes a
 // third of the bytes.
 //
+// head_dim 128 and 64.  At 64 the tiles are half as large, so two tiles of K and of V are in flight per wave instead of one;
+// batch 16, 16384 image tokens, 64/8 heads: 99 us for 563 MB (5.7 TB/s) where dense attention, its merge and scoring
+// took 89 + 5 + 54 us and read K twice.
+//
 // Structure (shared with the scoring-only kernel in score_resident.hip):
 //   - one 512-thread workgroup per (image-token range, sequence), at most one per compute unit,
 //     so the whole grid is resident; wave w streams KV head w % Hkv in 32-token tiles;
@@ -43,7 +47,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x32 __attribute__((ext_vector_type(32)));
 static_assert(kResTmax == 32, "one f32x32 per logit row holds kResTmax tiles");
 
-template <bool PAGED, bool SELECT>
+template <int D, bool PAGED, bool SELECT>
 __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     SelectArgs sel_args /* first: read straight from the kernel-argument segment when the select starts */,
     KvDev kv, BatchDev bv, const uint16_t *__restrict__ q, int Hq, int G, float scale_log2,
@@ -53,14 +57,25 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     uint32_t *__restrict__ gave_up_flag)
 {
     static_assert(sizeof(unsigned char[kResWaves][2][8192]) >= (size_t)kSelLdsBytes, "the select reuses the tile buffers");
-    __shared__ __align__(16) unsigned char smem[kResWaves][2][8192];      // [wave][K, V]
+    __shared__ __align__(16) unsigned char smem[kResWaves][2][8192];      // [wave][K, V][slot]
+
+    static_assert(D == 128 || D == 64, "head_dim 128 or 64");
+    constexpr int KS = D / 32;             // k-steps of a logit
+    constexpr int NACC = D / 16;           // 16-dim blocks of the output
+    constexpr int NL = D / 16;             // 1 KB load instructions per 32-token K (or V) tile
+    constexpr int RPL = 32 / NL;           // rows one load instruction brings
+    constexpr int CPR = D / 8;             // 16-byte chunks of a row
+    constexpr int ROWB = 2 * D;            // bytes of a row
+    constexpr int NSLOT = 128 / D;         // tiles of K (and of V) in flight: 8 KB each way, whatever the head_dim
+    constexpr int NV = D == 128 ? 4 : 2;   // distinct chunk permutations over the loads of a K tile
     __shared__ float sm_m[kResWaves][8], sm_z[kResWaves][8];
     __shared__ float sm_red[kResWaves];
     __shared__ int sm_met, sm_last;
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    const int li = lane & 15, lg = lane >> 4;
+    const int li = lane & 15, lg = lane >> 4;                      // the lane in the matrix products
+    const int lrow = lane / CPR, lslot = lane % CPR;               // the lane in a load: row of the load's group, chunk slot in LDS
     const int Hkv = kv.n_kv_heads;
     const int wpk = kResWaves / Hkv;
     const int kvh = wave % Hkv, sub = wave / Hkv;
@@ -87,12 +102,12 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     // Q as the B operand of the logits: column n = li holds head n & 7 of the group
     const int hcol = li & 7;
     const bool hi = li >= 8;                     // this lane's logits belong to the tile's last 16 tokens
-    u32x4 qq[4];
+    u32x4 qq[KS];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
+    for (int kk = 0; kk < KS; ++kk) {
         qq[kk] = u32x4{0u, 0u, 0u, 0u};
         if (hcol < G)
-            qq[kk] = *reinterpret_cast<const u32x4 *>(q + ((int64_t)b * Hq + (int64_t)kvh * G + hcol) * 128 + 8 * (4 * kk + lg));
+            qq[kk] = *reinterpret_cast<const u32x4 *>(q + ((int64_t)b * Hq + (int64_t)kvh * G + hcol) * D + 8 * (4 * kk + lg));
     }
     const uint16_t *kbase = reinterpret_cast<const uint16_t *>(kv.k);
     const uint16_t *vbase = reinterpret_cast<const uint16_t *>(kv.v);
@@ -105,22 +120,25 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     };
     auto text_first = [&](int x) { return (slot + x * nslots) * kResTile; };       // text-relative
 
-    // A tile goes into the wave's K or V slot: load e brings rows 4e .. 4e+3, lane (lg, li) one
-    // 16-byte chunk of row 4e + lg, which lands at slot + 1024 e + 16 lane.  For K the chunk is
-    // li ^ (row & 15) (the swizzle that makes the MFMA operand reads conflict-free); V stays
-    // row-major (chunk li).  Rows past the end of a ragged tile are clamped to its last row.
+    // Tile number n of the wave goes into slot n % NSLOT of its K and V buffers: load e brings rows RPL e ..
+    // RPL e + RPL - 1, lane (lrow, lslot) one 16-byte chunk of row r = RPL e + lrow, which lands at slot + 1024 e +
+    // 16 lane.  For K the chunk is lslot ^ f(r), f(r) = r & 15 (D 128) or (r >> 1) & 7 (D 64): the swizzle that
+    // makes the MFMA operand reads conflict-free; V stays row-major (chunk lslot).  Rows past the end of a
+    // ragged tile are clamped to its last row.
     const int64_t seq_base = row_offset<false>(kv, b, 0, kvh);
     const uint32_t stride_b = (uint32_t)kv.stride_token * 2u;            // bytes; 32 rows fit 32 bits (host-checked)
-    const uint32_t rowoff_lg = (uint32_t)lg * stride_b;
-    uint32_t chunk_k[4];
+    const uint32_t rowoff_row = (uint32_t)lrow * stride_b;
+    const int fl = D == 128 ? lrow : (lrow >> 1);
+    uint32_t chunk_k[NV];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) chunk_k[k] = 16u * (uint32_t)((li ^ lg) ^ (4 * k));
-    const uint32_t chunk_v = 16u * (uint32_t)li;
+    for (int k = 0; k < NV; ++k) chunk_k[k] = 16u * (uint32_t)((lslot ^ fl) ^ (4 * k));
+    const uint32_t chunk_v = 16u * (uint32_t)lslot;
     const unsigned char *kbytes = reinterpret_cast<const unsigned char *>(kv.k);
     const unsigned char *vbytes = reinterpret_cast<const unsigned char *>(kv.v);
 
-    auto issue_run = [&](int first_tok, int rv, bool isv) {
-        unsigned char *dst = smem[wave][isv ? 1 : 0];
+    auto slot_of = [&](int n, bool isv) { return smem[wave][isv ? 1 : 0] + (n & (NSLOT - 1)) * (8192 / NSLOT); };
+    auto issue_run = [&](int first_tok, int rv, int n, bool isv) {
+        unsigned char *dst = slot_of(n, isv);
         const unsigned char *bytes = isv ? vbytes : kbytes;
         const uint32_t limit = (uint32_t)(rv - 1) * stride_b;
         if (PAGED) {
@@ -132,43 +150,43 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
             const unsigned char *base_b = bytes + 2 * (pb * kv.stride_page + (int64_t)kvh * kv.stride_head + (int64_t)(in0 - pt) * kv.stride_token);
             const uint32_t split = (uint32_t)(pt - in0) * stride_b;      // first byte offset of the second page
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const uint32_t ro = min(rowoff_lg + (uint32_t)(4 * e) * stride_b, limit);
+            for (int e = 0; e < NL; ++e) {
+                const uint32_t ro = min(rowoff_row + (uint32_t)(RPL * e) * stride_b, limit);
                 const unsigned char *base = ro >= split ? base_b : base_a;
-                lds_dma16(reinterpret_cast<const uint16_t *>(base + (ro + (isv ? chunk_v : chunk_k[e & 3]))), dst + 1024 * e);
+                lds_dma16(reinterpret_cast<const uint16_t *>(base + (ro + (isv ? chunk_v : chunk_k[e & (NV - 1)]))), dst + 1024 * e);
             }
         } else {
             const unsigned char *base = bytes + 2 * (seq_base + (int64_t)first_tok * kv.stride_token);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const uint32_t ro = min(rowoff_lg + (uint32_t)(4 * e) * stride_b, limit);
-                lds_dma16(reinterpret_cast<const uint16_t *>(base + (ro + (isv ? chunk_v : chunk_k[e & 3]))), dst + 1024 * e);
+            for (int e = 0; e < NL; ++e) {
+                const uint32_t ro = min(rowoff_row + (uint32_t)(RPL * e) * stride_b, limit);
+                lds_dma16(reinterpret_cast<const uint16_t *>(base + (ro + (isv ? chunk_v : chunk_k[e & (NV - 1)]))), dst + 1024 * e);
             }
         }
     };
-    // Past the wave's last tile the refill stays unconditional (the readers' "at most 8 loads
-    // outstanding" waits count on it) but fetches 256 bytes of the query, which are in cache.
-    const uint16_t *qrow = q + ((int64_t)b * Hq + (int64_t)kvh * G) * 128;
-    auto issue_dummy = [&](bool isv) {
-        unsigned char *dst = smem[wave][isv ? 1 : 0];
+    // Past the wave's last tile the refill stays unconditional (the readers' counts of outstanding
+    // loads rely on it) but fetches one row of the query, which is in cache.
+    const uint16_t *qrow = q + ((int64_t)b * Hq + (int64_t)kvh * G) * D;
+    auto issue_dummy = [&](int n, bool isv) {
+        unsigned char *dst = slot_of(n, isv);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) lds_dma16(qrow + chunk_v / 2, dst + 1024 * e);
+        for (int e = 0; e < NL; ++e) lds_dma16(qrow + chunk_v / 2, dst + 1024 * e);
     };
     auto issue_img = [&](int x, bool isv) {
-        if (x >= nimg) { issue_dummy(isv); return; }
+        if (x >= nimg) { issue_dummy(ntext + x, isv); return; }
         const int jf = img_first(x);
-        issue_run(v0 + jf, min(kResTile, r1 - jf), isv);
+        issue_run(v0 + jf, min(kResTile, r1 - jf), ntext + x, isv);
     };
     // text positions map to tokens with a gap at the image span, so the rows are addressed one by one
     auto issue_text = [&](int x, bool isv) {
         const int tf = text_first(x);
-        unsigned char *dst = smem[wave][isv ? 1 : 0];
+        unsigned char *dst = slot_of(x, isv);
         const uint16_t *base = isv ? vbase : kbase;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int tc = min(tf + 4 * e + lg, Tn - 1);
+        for (int e = 0; e < NL; ++e) {
+            const int tc = min(tf + RPL * e + lrow, Tn - 1);
             const int tok = tc < v0 ? tc : tc + N;
-            lds_dma16(base + row_offset<PAGED>(kv, b, tok, kvh) + (isv ? chunk_v : chunk_k[e & 3]) / 2, dst + 1024 * e);
+            lds_dma16(base + row_offset<PAGED>(kv, b, tok, kvh) + (isv ? chunk_v : chunk_k[e & (NV - 1)]) / 2, dst + 1024 * e);
         }
     };
     // tile number n of the wave (text tiles first, then image tiles), or the dummy past the end
@@ -179,25 +197,36 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
 
     const int tt0 = 16 * (li >> 3) + 4 * lg;        // tile-relative token of this lane's first logit
     float m = kMinusHuge, z = 0.f;                  // running max (uniform over the head's lanes), this lane's sum
-    f32x4 acc[8];
+    f32x4 acc[NACC];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < NACC; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // LDS byte addresses: K rows li and 16 + li as the A operand, V rows 4lg.. and 16 + 4lg..
-    uint32_t rd_addr[4];
+    // LDS byte addresses in slot 0: K rows li and 16 + li as the A operand, V rows 4lg.. and 16 + 4lg..
+    uint32_t rd_addr[KS];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-        rd_addr[kk] = lds_address(&smem[wave][0][0]) + li * 256 + ((((4 * kk + lg) ^ li) & 15) << 4);
-    const uint32_t rd_v = lds_address(&smem[wave][1][0]) + (4 * lg) * 256 + li * 16;
+    for (int kk = 0; kk < KS; ++kk)
+        rd_addr[kk] = lds_address(&smem[wave][0][0]) + li * ROWB + ((((4 * kk + lg) ^ (D == 128 ? li : (li >> 1))) & (CPR - 1)) << 4);
+    const uint32_t rd_v = lds_address(&smem[wave][1][0]) + (4 * lg) * ROWB + (li & (CPR - 1)) * 16;
 
-    // The newest outstanding loads are always the 8 of the other slot's refill, so "at most 8
-    // outstanding" means the tile wanted here has landed.  Reads and waits are written in assembly:
-    // the compiler neither orders LDS reads after loads that land in LDS by themselves without
-    // draining ALL of them, nor may it move the products above the wait.
+    // Loads are sent in the order K(n), V(n), K(n+1), ..; when K(n) is wanted the newest ones outstanding
+    // are V(n) and, with two slots, K(n+1) and V(n+1); when V(n) is wanted, K and V of the tiles between
+    // and the K refill just sent: 8 loads with one slot (D 128), 12 with two (D 64), so "at most that many
+    // outstanding" means the tile has landed.  Reads and waits are written in assembly: the compiler
+    // neither orders LDS reads after loads that land in LDS by themselves without draining ALL of them, nor
+    // may it move the products above the wait.
     // rows li (first call) and 16 + li (second call) of the K tile, in two halves so that only
     // four operand registers are live at a time
-    auto read_k_lo = [&](u32x4(&kb)[4]) {
-        asm volatile(
+    auto read_k_lo = [&](uint32_t so, u32x4(&kb)[KS]) {
+        if constexpr (D == 64)
+            asm volatile(
+                "s_waitcnt vmcnt(12)\n\t"
+                "ds_read_b128 %0, %2\n\t"
+                "ds_read_b128 %1, %3\n\t"
+                "s_waitcnt lgkmcnt(0)"
+                : "=&v"(kb[0]), "=&v"(kb[1])
+                : "v"(rd_addr[0] + so), "v"(rd_addr[1] + so)
+                : "memory");
+        else asm volatile(
             "s_waitcnt vmcnt(8)\n\t"
             "ds_read_b128 %0, %4\n\t"
             "ds_read_b128 %1, %5\n\t"
@@ -208,8 +237,16 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
             : "v"(rd_addr[0]), "v"(rd_addr[1]), "v"(rd_addr[2]), "v"(rd_addr[3])
             : "memory");
     };
-    auto read_k_hi = [&](u32x4(&kb)[4]) {
-        asm volatile(
+    auto read_k_hi = [&](uint32_t so, u32x4(&kb)[KS]) {
+        if constexpr (D == 64)
+            asm volatile(
+                "ds_read_b128 %0, %2 offset:2048\n\t"
+                "ds_read_b128 %1, %3 offset:2048\n\t"
+                "s_waitcnt lgkmcnt(0)"
+                : "=&v"(kb[0]), "=&v"(kb[1])
+                : "v"(rd_addr[0] + so), "v"(rd_addr[1] + so)
+                : "memory");
+        else asm volatile(
             "ds_read_b128 %0, %4 offset:4096\n\t"
             "ds_read_b128 %1, %5 offset:4096\n\t"
             "ds_read_b128 %2, %6 offset:4096\n\t"
@@ -219,9 +256,24 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
             : "v"(rd_addr[0]), "v"(rd_addr[1]), "v"(rd_addr[2]), "v"(rd_addr[3])
             : "memory");
     };
-    // vv[e]: dims 8li .. 8li+7 of token 4lg + e (e < 4) or 16 + 4lg + e - 4 of the tile
-    auto read_v = [&](u32x4(&vv)[8]) {
-        asm volatile(
+    // vv[e]: chunk li (D 64: li & 7) of the row of token 4lg + e (e < 4) or 16 + 4lg + e - 4 of the tile
+    auto read_v = [&](uint32_t so, u32x4(&vv)[8]) {
+        if constexpr (D == 64)
+            asm volatile(
+                "s_waitcnt vmcnt(12)\n\t"
+                "ds_read_b128 %0, %8\n\t"
+                "ds_read_b128 %1, %8 offset:128\n\t"
+                "ds_read_b128 %2, %8 offset:256\n\t"
+                "ds_read_b128 %3, %8 offset:384\n\t"
+                "ds_read_b128 %4, %8 offset:2048\n\t"
+                "ds_read_b128 %5, %8 offset:2176\n\t"
+                "ds_read_b128 %6, %8 offset:2304\n\t"
+                "ds_read_b128 %7, %8 offset:2432\n\t"
+                "s_waitcnt lgkmcnt(0)"
+                : "=&v"(vv[0]), "=&v"(vv[1]), "=&v"(vv[2]), "=&v"(vv[3]), "=&v"(vv[4]), "=&v"(vv[5]), "=&v"(vv[6]), "=&v"(vv[7])
+                : "v"(rd_v + so)
+                : "memory");
+        else asm volatile(
             "s_waitcnt vmcnt(8)\n\t"
             "ds_read_b128 %0, %8\n\t"
             "ds_read_b128 %1, %8 offset:256\n\t"
@@ -239,18 +291,19 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
 
     // One tile: logits, online softmax, P*V.  nlive = tokens of the tile that exist (may exceed 32).
     // Returns this lane's 4 logits (log2 domain; -inf for tokens past the end).
-    auto tile_step = [&](int nlive, auto &&next_k, auto &&next_v) -> f32x4 {
-        u32x4 kb[4];
+    auto tile_step = [&](int n, int nlive, auto &&next_k, auto &&next_v) -> f32x4 {
+        const uint32_t so = (uint32_t)(n & (NSLOT - 1)) * (8192 / NSLOT);
+        u32x4 kb[KS];
         f32x4 c0 = f32x4{0.f, 0.f, 0.f, 0.f}, c1 = c0;
-        read_k_lo(kb);
+        read_k_lo(so, kb);
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
+        for (int kk = 0; kk < KS; ++kk)
             c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kb[kk]),
                                                          __builtin_bit_cast(bf16x8, qq[kk]), c0, 0, 0, 0);
-        read_k_hi(kb);
+        read_k_hi(so, kb);
         next_k();
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
+        for (int kk = 0; kk < KS; ++kk)
             c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kb[kk]),
                                                          __builtin_bit_cast(bf16x8, qq[kk]), c1, 0, 0, 0);
         f32x4 s;
@@ -267,7 +320,7 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
             const float alpha = fast_exp2(m - m_new);
             z *= alpha;
 #pragma unroll
-            for (int t = 0; t < 8; ++t) acc[t] *= alpha;
+            for (int t = 0; t < NACC; ++t) acc[t] *= alpha;
             m = m_new;
         }
         float p[4];
@@ -280,12 +333,14 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
         const u32x4 pb = u32x4{hi ? 0u : w0, hi ? 0u : w1, hi ? w0 : 0u, hi ? w1 : 0u};
 
         u32x4 vv[8];
-        read_v(vv);
+        read_v(so, vv);
         next_v();
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const int w = t >> 1;
-            const uint32_t selb = (t & 1) ? 0x07060302u : 0x05040100u;
+        for (int t = 0; t < NACC; ++t) {
+            // D 128: row i of block t is dim 8i + t; D 64: rows i and i + 8 share chunk i & 7 and take its even and
+            // odd elements, dim 8 (i & 7) + 2t + (i >> 3)
+            const int w = D == 128 ? t >> 1 : t;
+            const uint32_t selb = (D == 128 ? (t & 1) != 0 : hi) ? 0x07060302u : 0x05040100u;
             u32x4 a;
 #pragma unroll
             for (int pp = 0; pp < 4; ++pp) a[pp] = __builtin_amdgcn_perm(vv[2 * pp + 1][w], vv[2 * pp][w], selb);
@@ -300,10 +355,11 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     if (ntext + nimg > 0) {
         issue_any(0, false);
         issue_any(0, true);
+        if constexpr (NSLOT == 2) { issue_any(1, false); issue_any(1, true); }
         for (int x = 0; x < ntext; ++x)
-            (void)tile_step(Tn - text_first(x), [&]() { issue_any(x + 1, false); }, [&]() { issue_any(x + 1, true); });
+            (void)tile_step(x, Tn - text_first(x), [&]() { issue_any(x + NSLOT, false); }, [&]() { issue_any(x + NSLOT, true); });
         for (int J = 0; J < nimg; ++J) {
-            const f32x4 s = tile_step(r1 - img_first(J), [&]() { issue_img(J + 1, false); }, [&]() { issue_img(J + 1, true); });
+            const f32x4 s = tile_step(ntext + J, r1 - img_first(J), [&]() { issue_img(J + NSLOT, false); }, [&]() { issue_img(J + NSLOT, true); });
             park0[J] = s[0];
             park1[J] = s[1];
             park2[J] = s[2];
@@ -323,17 +379,44 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     z += dpp_move<kDppRor8>(z);
     z = rows_sum(z);
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
+    for (int t = 0; t < NACC; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[t][r] += dpp_move<kDppRor8>(acc[t][r]);
-    if (li_p < 8 && li_p < G) {
-        // lane_p (head li_p, group lg_p) holds dims 32lg + 8r + t in acc[t][r]
-        const int64_t row = ((int64_t)(wg0 + rng) * wpk + sub) * Hq + kvh * G + li_p;      // [workgroup][sub][head]
-        float *po = att_o + row * 128 + 32 * lg_p;
+    if constexpr (D == 64) {
+        // operand row 4lg + r: lane groups 0 and 1 hold the even dims of chunks 4 (lg & 1) + r, groups 2 and 3 the odd
+        // ones; after the half swaps acc[0..3][r] are four consecutive dims of the chunk, its first four in
+        // groups 0 and 1, its last four in groups 2 and 3
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            *reinterpret_cast<f32x4 *>(po + 8 * r) = f32x4{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
-            *reinterpret_cast<f32x4 *>(po + 8 * r + 4) = f32x4{acc[4][r], acc[5][r], acc[6][r], acc[7][r]};
+            float x[4];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                // (copies: a bit cast of a vector element itself reads element 0)
+                const float even = acc[t][r], later = acc[t + 2][r];
+                const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, even), __builtin_bit_cast(uint32_t, later),
+                                                                 false, false);
+                x[2 * t] = __builtin_bit_cast(float, (uint32_t)sw[0]);
+                x[2 * t + 1] = __builtin_bit_cast(float, (uint32_t)sw[1]);
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[t][r] = x[t];
+        }
+    }
+    if (li_p < 8 && li_p < G) {
+        const int64_t row = ((int64_t)(wg0 + rng) * wpk + sub) * Hq + kvh * G + li_p;      // [workgroup][sub][head]
+        if constexpr (D == 128) {
+            // lane_p (head li_p, group lg_p) holds dims 32lg + 8r + t in acc[t][r]
+            float *po = att_o + row * 128 + 32 * lg_p;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                *reinterpret_cast<f32x4 *>(po + 8 * r) = f32x4{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+                *reinterpret_cast<f32x4 *>(po + 8 * r + 4) = f32x4{acc[4][r], acc[5][r], acc[6][r], acc[7][r]};
+            }
+        } else {
+            float *po = att_o + row * 64 + 32 * (lg_p & 1) + 4 * (lg_p >> 1);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                *reinterpret_cast<f32x4 *>(po + 8 * r) = f32x4{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
         }
         if (lg_p == 0) {
             att_ml[2 * row] = m;
@@ -352,7 +435,10 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     unsigned long long *stats = g_fus_stats[sync_slot] + (int64_t)wg0 * Hq;
     resident_publish(stats + (int64_t)rng * Hq, sm_m, sm_z, Hq, G, Hkv, wpk);
     // the log-sum-exp of this wave's heads over the whole sequence (lane 8s + x: head x of the group)
-    float lh;
+    // (D 64: a weight is 2^(logit - M) / Z: the difference of two logits of like size is nearly exact, where
+    // logit - (M + log2 Z) carries the rounding of that sum -- a sixth of the scores' error; at D 128 the extra
+    // product costs 1 us of 196)
+    float lh, sh, rz = 1.0f;
     {
         float M, Z;
         const bool ok = resident_heads_gather<4>(stats, rng, nranges, Hq, G, Hkv, wpk, kvh, sm_m, sm_z, spin_ticks, M, Z);
@@ -362,6 +448,11 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
             if (gave_up_flag) __hip_atomic_store(gave_up_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
         lh = (hcol_p < G && Z > 0.f) ? M + log2f(Z) : (hcol_p < G ? -INFINITY : INFINITY);
+        sh = lh;
+        if constexpr (D == 64) {
+            rz = hcol_p < G ? 1.0f / Z : 0.f;
+            sh = hcol_p < G ? M : INFINITY;               // (columns without a head: weight 0)
+        }
     }
     __syncthreads();      // whether every wave has met its ranges
     // This range is done reading: count it out.  The last one of the sequence clears the
@@ -392,7 +483,8 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
         f32x4 v = f32x4{park0[J], park1[J], park2[J], park3[J]};
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            float x = fast_exp2(v[r] - lh);
+            float x = fast_exp2(v[r] - sh);
+            if constexpr (D == 64) x *= rz;
             x += dpp_move<kDppXor1>(x);
             x += dpp_move<kDppXor2>(x);
             x += dpp_move<kDppHalfMirror>(x);
@@ -435,13 +527,13 @@ __global__ void fused_mass_kernel(const float *__restrict__ mass_part, const int
     if (threadIdx.x == 0) img_mass[b] = t;
 }
 
-// Workspace, with W = nranges * batch workgroups: attention partials fp32 [W][wpk][Hq][128] and
+// Workspace, with W = nranges * batch workgroups: attention partials fp32 [W][wpk][Hq][d] and
 // [W][wpk][Hq][2], image-mass partials [W], and per sequence
 // its first workgroup and range count int32 [B][2].
 size_t focal_fused_workspace_bytes(const Shape &s, const ResidentPlan &p)
 {
     const size_t W = (size_t)p.nranges * s.batch;
-    size_t bytes = W * p.wpk * s.n_q_heads * (128 + 2) * sizeof(float);
+    size_t bytes = W * p.wpk * s.n_q_heads * (s.kv.head_dim + 2) * sizeof(float);
     bytes += W * sizeof(float);
     bytes += (size_t)s.batch * 2 * sizeof(int32_t);
     return bytes;
@@ -456,7 +548,7 @@ hipError_t launch_focal_fused(const Shape &s, const ResidentPlan &p, int sync_sl
     if (sync_slot < 0 || sync_slot >= kResSlots) return hipErrorInvalidValue;
     const int W = p.nranges * s.batch;
     float *att_o = reinterpret_cast<float *>(ws);
-    float *att_ml = att_o + (size_t)W * p.wpk * s.n_q_heads * 128;
+    float *att_ml = att_o + (size_t)W * p.wpk * s.n_q_heads * s.kv.head_dim;
     float *mass_part = att_ml + (size_t)W * p.wpk * s.n_q_heads * 2;
     int32_t *seq_meta = reinterpret_cast<int32_t *>(mass_part + W);
     const float scale_log2 = scale * kLog2e;
@@ -467,11 +559,14 @@ hipError_t launch_focal_fused(const Shape &s, const ResidentPlan &p, int sync_sl
     const bool fuse = select && select->sel_idx;
     if (fuse && !resident_select_fits(s)) return hipErrorInvalidValue;
     const SelectArgs sa = fuse ? *select : SelectArgs{0.0, nullptr, nullptr, nullptr, nullptr, 0};
-#define FASTOCR_FUS(P, S) FASTOCR_LAUNCH(K_FOCAL_FUSED, (focal_fused_kernel<P, S>), grid, block, 0, stream, sa, s.kv, s.bv, \
+#define FASTOCR_FUS(D, P, S) FASTOCR_LAUNCH(K_FOCAL_FUSED, (focal_fused_kernel<D, P, S>), grid, block, 0, stream, sa, s.kv, s.bv, \
                        (const uint16_t *)q, s.n_q_heads, G, scale_log2, s.batch, p.nranges, p.range_tokens, \
                        sync_slot, spin_ticks, scores, lse, img_mass ? mass_part : nullptr, att_o, att_ml, seq_meta, flag)
-    if (s.paged) { if (fuse) FASTOCR_FUS(true, true); else FASTOCR_FUS(true, false); }
-    else         { if (fuse) FASTOCR_FUS(false, true); else FASTOCR_FUS(false, false); }
+#define FASTOCR_FUS_D(D) \
+    if (s.paged) { if (fuse) FASTOCR_FUS(D, true, true); else FASTOCR_FUS(D, true, false); } \
+    else         { if (fuse) FASTOCR_FUS(D, false, true); else FASTOCR_FUS(D, false, false); }
+    if (s.kv.head_dim == 64) { FASTOCR_FUS_D(64) } else { FASTOCR_FUS_D(128) }
+#undef FASTOCR_FUS_D
 #undef FASTOCR_FUS
     if (img_mass) fused_mass_kernel<<<s.batch, 64, 0, stream>>>(mass_part, seq_meta, img_mass);
     // every sequence's partials: workgroups seq_meta[b][0] .. + seq_meta[b][1], wpk of them each

@@ -36,9 +36,7 @@ struct Shape {
     bool paged;
     bool vec16;     // every cache row starts 16-byte aligned and head_dim covers whole 16-byte pieces
     bool fast;      // the MFMA kernels cover this shape: bf16, head_dim 128 or 64, group size <= 16,
-                    // 16-byte aligned rows (decided once from the views by the C-ABI layer); the
-                    // one-pass focal kernel and the in-launch merge need head_dim 128, register-resident
-                    // scoring takes both
+                    // 16-byte aligned rows (decided once from the views by the C-ABI layer)
     bool fast32;    // the fp64 matrix-core kernels of attn_f32.hip cover it: fp32, head_dim 128 or 64, group size <= 16, vec16
 };
 
