@@ -610,7 +610,7 @@ static int focal_attn_score_impl(const fastocr_kv_view *kv, const fastocr_batch_
     uint32_t *flag = nullptr;
     if (use_resident(EX_FUSED, g_tune_focal_fused.load(std::memory_order_relaxed), s, &rp, kFusedMinTiles, (hipStream_t)hip_stream, &slot, &flag)) {
         const bool fuse = select && g_tune_select_fused.load(std::memory_order_relaxed) != 0 && resident_select_fits(s);
-        const bool hand_on = defer && deferred && !fuse && topk_takes_combine(bv->max_vis_len, kv->head_dim);
+        const bool hand_on = defer && deferred && !fuse && !img_mass && topk_takes_combine(bv->max_vis_len, kv->head_dim);
         hipError_t e = launch_focal_fused(s, rp, slot, flag, q, scale, out, scores, lse, img_mass, ws, (hipStream_t)hip_stream,
                                           fuse ? select : nullptr, hand_on ? defer : nullptr);
         if (fused) *fused = fuse;
@@ -618,7 +618,7 @@ static int focal_attn_score_impl(const fastocr_kv_view *kv, const fastocr_batch_
         return e == hipSuccess ? FASTOCR_OK : FASTOCR_EHIP;
     }
     if (s.fast32 && g_tune_focal_fused.load(std::memory_order_relaxed) != 0) {
-        const bool hand_on = defer && deferred && topk_takes_combine(bv->max_vis_len, kv->head_dim);
+        const bool hand_on = defer && deferred && !img_mass && topk_takes_combine(bv->max_vis_len, kv->head_dim);
         const int nsplit = choose_splits(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len);
         const hipError_t e = launch_focal_f32(s, q, scale, out, scores, lse, img_mass, ws, nsplit, (hipStream_t)hip_stream,
                                               hand_on ? defer : nullptr);

@@ -584,12 +584,18 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(
 template <typename T>
 __global__ __launch_bounds__(256) void attn_combine_wide_kernel(
     const float *__restrict__ part_o, const float *__restrict__ part_ml, int nsplit, int d,
-    T *__restrict__ out, float *__restrict__ lse, const int32_t *__restrict__ seq_meta, int wpk)
+    T *__restrict__ out, float *__restrict__ lse, const int32_t *__restrict__ seq_meta, int wpk, MassArgs mass)
 {
     __shared__ float sm_max[4];
     __shared__ float sm_z[256];
     __shared__ __align__(16) float sm_o[1024];
-    combine_wide_body<T>(part_o, part_ml, nsplit, d, out, lse, seq_meta, wpk, blockIdx.x, blockIdx.y, gridDim.x,
+    // with image mass to sum, one more workgroup per sequence, behind those of its heads
+    const int Hq = (int)gridDim.x - (mass.out ? 1 : 0);
+    if ((int)blockIdx.x == Hq) {
+        image_mass_sum(mass, seq_meta, blockIdx.y);
+        return;
+    }
+    combine_wide_body<T>(part_o, part_ml, nsplit, d, out, lse, seq_meta, wpk, blockIdx.x, blockIdx.y, Hq,
                          CombineShared{sm_max, sm_z, sm_o});
 }
 
@@ -694,18 +700,18 @@ hipError_t launch_attn(const Shape &s, const void *q, float scale, const int32_t
 }
 
 hipError_t launch_attn_combine(const Shape &s, const float *part_o, const float *part_ml, int nsplit,
-                               void *out, float *lse, hipStream_t stream, const int32_t *seq_meta, int wpk)
+                               void *out, float *lse, hipStream_t stream, const int32_t *seq_meta, int wpk, MassArgs mass)
 {
     const int d = s.kv.head_dim;
-    dim3 grid(s.n_q_heads, s.batch), block(256);
-    if (seq_meta && d % 4 != 0) return hipErrorInvalidValue;
-    if (d % 4 == 0 && (nsplit >= 2 || seq_meta)) {
+    dim3 grid(s.n_q_heads + (mass.out ? 1 : 0), s.batch), block(256);
+    if ((seq_meta || mass.out) && d % 4 != 0) return hipErrorInvalidValue;
+    if (d % 4 == 0 && (nsplit >= 2 || seq_meta || mass.out)) {
         // several partials per head: spread them over the workgroup's threads (two partials as well: its
         // form for few partials needs one memory round trip where the plain walk below needs two)
         if (s.dtype == DT_BF16)
-            FASTOCR_LAUNCH(K_ATTN_COMBINE, attn_combine_wide_kernel<uint16_t>, grid, block, 0, stream, part_o, part_ml, nsplit, d, (uint16_t *)out, lse, seq_meta, wpk);
+            FASTOCR_LAUNCH(K_ATTN_COMBINE, attn_combine_wide_kernel<uint16_t>, grid, block, 0, stream, part_o, part_ml, nsplit, d, (uint16_t *)out, lse, seq_meta, wpk, mass);
         else
-            FASTOCR_LAUNCH(K_ATTN_COMBINE, attn_combine_wide_kernel<float>, grid, block, 0, stream, part_o, part_ml, nsplit, d, (float *)out, lse, seq_meta, wpk);
+            FASTOCR_LAUNCH(K_ATTN_COMBINE, attn_combine_wide_kernel<float>, grid, block, 0, stream, part_o, part_ml, nsplit, d, (float *)out, lse, seq_meta, wpk, mass);
         return hipGetLastError();
     }
     if (s.dtype == DT_BF16)

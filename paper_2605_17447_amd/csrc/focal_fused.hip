@@ -516,17 +516,6 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     leave();
 }
 
-__global__ void fused_mass_kernel(const float *__restrict__ mass_part, const int32_t *__restrict__ seq_meta,
-                                  float *__restrict__ img_mass)
-{
-    const int b = blockIdx.x;
-    const int first = seq_meta[2 * b], n = seq_meta[2 * b + 1];
-    float t = 0.f;
-    for (int x = threadIdx.x; x < n; x += 64) t += mass_part[first + x];
-    t = wave_sum(t);
-    if (threadIdx.x == 0) img_mass[b] = t;
-}
-
 // Workspace, with W = nranges * batch workgroups: attention partials fp32 [W][wpk][Hq][d] and
 // [W][wpk][Hq][2], image-mass partials [W], and per sequence
 // its first workgroup and range count int32 [B][2].
@@ -568,13 +557,13 @@ hipError_t launch_focal_fused(const Shape &s, const ResidentPlan &p, int sync_sl
     if (s.kv.head_dim == 64) { FASTOCR_FUS_D(64) } else { FASTOCR_FUS_D(128) }
 #undef FASTOCR_FUS_D
 #undef FASTOCR_FUS
-    if (img_mass) fused_mass_kernel<<<s.batch, 64, 0, stream>>>(mass_part, seq_meta, img_mass);
+    const MassArgs mass{mass_part, img_mass, 0};          // summed by the launch that merges the output's partials
     // every sequence's partials: workgroups seq_meta[b][0] .. + seq_meta[b][1], wpk of them each
     if (defer) {
         *defer = CombineArgs{att_o, att_ml, p.nranges * p.wpk, s.kv.head_dim, s.n_q_heads, p.wpk, seq_meta, out, false};
         return hipGetLastError();
     }
-    return launch_attn_combine(s, att_o, att_ml, p.nranges * p.wpk, out, nullptr, stream, seq_meta, p.wpk);
+    return launch_attn_combine(s, att_o, att_ml, p.nranges * p.wpk, out, nullptr, stream, seq_meta, p.wpk, mass);
 }
 
 }  // namespace fastocr

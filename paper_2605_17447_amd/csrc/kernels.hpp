@@ -73,6 +73,14 @@ constexpr int kMergeEagerSlots = 4;
 int exchange_slot(int kind, hipStream_t stream, uint32_t **gave_up_flag);
 bool exchange_trusted();               // false once a wave has given up (or "exchange_fallback" 1)
 
+// Image-mass partials to be summed per sequence (out == nullptr: none): n_part per sequence, or with seq_meta one
+// per workgroup of the one-pass focal kernel.
+struct MassArgs {
+    const float *part;
+    float *out;                 // [B]
+    int n_part;
+};
+
 // ---- attention (attn.hip) ---------------------------------------------------------------
 // Workspace: part_o fp32 [B][Hq][nsplit][d] followed by part_ml fp32 [B][Hq][nsplit][2].
 int attn_tile_tokens(const Shape &s);
@@ -89,9 +97,10 @@ hipError_t launch_attn(const Shape &s, const void *q, float scale, const int32_t
 // merge of nsplit partials per (sequence, head) in the layout above into the final output.
 // With seq_meta (device int32 [B][2]: first workgroup, workgroup count) the partials are instead
 // those of the fused focal kernel, [workgroup][wpk][Hq][d] / [..][2], wpk per workgroup.
+// mass: the launch also sums the image-mass partials of every sequence.
 hipError_t launch_attn_combine(const Shape &s, const float *part_o, const float *part_ml, int nsplit,
                                void *out, float *lse, hipStream_t stream, const int32_t *seq_meta = nullptr,
-                               int wpk = 1);
+                               int wpk = 1, MassArgs mass = MassArgs{nullptr, nullptr, 0});
 
 // ---- fp32 caches on the fp64 matrix cores (attn_f32.hip; shapes with s.fast32) --------------
 // sel_idx: pruned attention.  part_o == nullptr: no attention output.  logits: the logits are parked there (with
@@ -149,7 +158,7 @@ struct CombineArgs {
 };
 // defer != nullptr: the merge of the output's partials is not launched; *defer describes it and the
 // caller passes it to launch_topk, whose launch then does both (the top-k and that merge depend on
-// this kernel only, not on each other).
+// this kernel only, not on each other).  Not together with img_mass, which the merge's own launch sums.
 hipError_t launch_focal_fused(const Shape &s, const ResidentPlan &p, int sync_slot, uint32_t *gave_up_flag, const void *q, float scale,
                               void *out, float *scores, float *lse, float *img_mass, void *ws, hipStream_t stream,
                               const SelectArgs *select = nullptr, CombineArgs *defer = nullptr);

@@ -382,7 +382,6 @@ static hipError_t launch_finalize(const Shape &s, const float *logits, int64_t p
     dim3 fgrid(nblk, s.batch), fblock(kFinThreads);
     FASTOCR_LAUNCH(K_SCORE_FINALIZE, score_finalize_kernel, fgrid, fblock, (size_t)s.n_q_heads * 2 * sizeof(float), stream,
         s.bv, s.n_q_heads, s.kv.n_kv_heads, logits, pitch, part_ml, nsplit, scores, lse, img_mass ? mass_part : nullptr);
-    if (img_mass) mass_reduce_kernel<<<s.batch, 64, 0, stream>>>(mass_part, nblk, img_mass);
     return hipGetLastError();
 }
 
@@ -423,7 +422,10 @@ hipError_t launch_score(const Shape &s, const void *q, float scale, float *score
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
 
-    return launch_finalize(s, logits, pitch, part_ml, nsplit, scores, lse, img_mass, mass_part, stream);
+    e = launch_finalize(s, logits, pitch, part_ml, nsplit, scores, lse, img_mass, mass_part, stream);
+    if (e != hipSuccess || !img_mass) return e;
+    mass_reduce_kernel<<<s.batch, 64, 0, stream>>>(mass_part, fin_blocks(s), img_mass);
+    return hipGetLastError();
 }
 
 // Workspace: as launch_score's, then the attention partials fp32 [B][Hq][nsplit][d] (the softmax statistics serve both).
@@ -445,11 +447,12 @@ hipError_t launch_focal_f32(const Shape &s, const void *q, float scale, void *ou
     if (e != hipSuccess) return e;
     e = launch_finalize(s, logits, pitch, part_ml, nsplit, scores, lse, img_mass, mass_part, stream);
     if (e != hipSuccess) return e;
-    if (defer) {
+    const MassArgs mass{mass_part, img_mass, fin_blocks(s)};
+    if (defer) {                                       // (no image mass then)
         *defer = CombineArgs{part_o, part_ml, nsplit, s.kv.head_dim, s.n_q_heads, 1, nullptr, out, true};
         return hipSuccess;
     }
-    return launch_attn_combine(s, part_o, part_ml, nsplit, out, nullptr, stream);
+    return launch_attn_combine(s, part_o, part_ml, nsplit, out, nullptr, stream, nullptr, 1, mass);
 }
 
 }  // namespace fastocr

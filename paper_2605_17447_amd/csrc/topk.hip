@@ -228,7 +228,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(
 // The same, with batch * Hq more workgroups behind the selecting ones: each merges the attention
 // partials of one (sequence, query head) of the focal layer whose scores are being selected from.
 // The two kinds of workgroup share nothing but the launch.
-template <bool VEC, int PER>
+template <typename T, bool VEC, int PER>
 __global__ __launch_bounds__(kTopkThreads) void focal_tail_kernel(
     const float *__restrict__ scores, BatchDev bv, double tau, const int32_t *prev_idx,
     const int32_t *prev_cnt, int32_t *sel_idx, int32_t *sel_cnt, int64_t kmax, int batch, CombineArgs c)
@@ -249,9 +249,8 @@ __global__ __launch_bounds__(kTopkThreads) void focal_tail_kernel(
     } else {
         const int x = (int)blockIdx.x - batch;
         const int b = x / c.n_q_heads, h = x - b * c.n_q_heads;
-        const CombineShared cs{sm_max, sm_z, sm_o};
-        if (c.out_f32) combine_wide_body<float>(c.part_o, c.part_ml, c.nsplit, c.d, (float *)c.out, nullptr, c.seq_meta, c.wpk, h, b, c.n_q_heads, cs);
-        else combine_wide_body<uint16_t>(c.part_o, c.part_ml, c.nsplit, c.d, (uint16_t *)c.out, nullptr, c.seq_meta, c.wpk, h, b, c.n_q_heads, cs);
+        combine_wide_body<T>(c.part_o, c.part_ml, c.nsplit, c.d, (T *)c.out, nullptr, c.seq_meta, c.wpk, h, b, c.n_q_heads,
+                             CombineShared{sm_max, sm_z, sm_o});
     }
 }
 
@@ -303,12 +302,14 @@ hipError_t launch_topk(const float *scores, const BatchDev &bv, int batch, doubl
                                               bv, tau, prev_idx, prev_cnt, sel_idx, sel_cnt, kmax)
         if (combine) {
             const dim3 grid(batch + batch * combine->n_q_heads);
-#define FASTOCR_TAIL(V, P) FASTOCR_LAUNCH(K_TOPK, (focal_tail_kernel<V, P>), grid, dim3(kTopkThreads), 0, stream, scores, \
+#define FASTOCR_TAIL_T(T, V, P) FASTOCR_LAUNCH(K_TOPK, (focal_tail_kernel<T, V, P>), grid, dim3(kTopkThreads), 0, stream, scores, \
                                           bv, tau, prev_idx, prev_cnt, sel_idx, sel_cnt, kmax, batch, *combine)
+#define FASTOCR_TAIL(V, P) do { if (combine->out_f32) FASTOCR_TAIL_T(float, V, P); else FASTOCR_TAIL_T(uint16_t, V, P); } while (0)
             if (bv.max_vis_len <= kTopkThreads * 4) { if (vec) FASTOCR_TAIL(true, 4); else FASTOCR_TAIL(false, 4); }
             else if (bv.max_vis_len <= kTopkThreads * 8) { if (vec) FASTOCR_TAIL(true, 8); else FASTOCR_TAIL(false, 8); }
             else { if (vec) FASTOCR_TAIL(true, kTopkPer); else FASTOCR_TAIL(false, kTopkPer); }
 #undef FASTOCR_TAIL
+#undef FASTOCR_TAIL_T
             return hipGetLastError();
         }
         if (bv.max_vis_len <= kTopkThreads * 4) { if (vec) FASTOCR_TOPK_REG(true, 4); else FASTOCR_TOPK_REG(false, 4); }
