@@ -211,7 +211,15 @@ class SeqBatch:
         return view
 
 
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(stream: Optional[torch.cuda.Stream]):
+    # the current stream's handle is read without building a Stream object for it (3.0 -> 0.3 us of host time,
+    # of the 9.9 us that a call took: more than its kernel at small sizes)
+    if stream is None and _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(_current_device()) or None
     s = stream if stream is not None else torch.cuda.current_stream()
     return s.cuda_stream or None          # the default stream's handle is 0 = NULL
 
@@ -246,12 +254,12 @@ def focal_score(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scale: float, 
                 ws: torch.Tensor, lse: Optional[torch.Tensor] = None,
                 img_mass: Optional[torch.Tensor] = None, stream=None) -> None:
     """fastocr_focal_score: q [B,Hq,d]; scores fp32 [B, max_vis_len] (written in place)."""
-    lib = load_library()
+    lib = _lib or load_library()
     kv, bv = cache.view(), batch.view()
     assert q.is_contiguous() and scores.is_contiguous() and scores.dtype == torch.float32
-    assert scores.shape[0] == bv.batch and (scores.shape[1] == bv.max_vis_len or bv.batch == 0)
-    _check(lib.fastocr_focal_score(ctypes.byref(kv), ctypes.byref(bv), _ptr(q), q.shape[1], float(scale),
-                                   _ptr(scores), _ptr(lse), _ptr(img_mass), _ptr(ws), ws.numel(),
+    assert scores.size(0) == bv.batch and (scores.size(1) == bv.max_vis_len or bv.batch == 0)
+    _check(lib.fastocr_focal_score(ctypes.byref(kv), ctypes.byref(bv), q.data_ptr(), q.size(1), float(scale),
+                                   scores.data_ptr(), _ptr(lse), _ptr(img_mass), ws.data_ptr(), ws.numel(),
                                    _stream_handle(stream)), "fastocr_focal_score")
 
 
@@ -260,15 +268,15 @@ def topk_fixation(scores: torch.Tensor, batch: SeqBatch, tau: float, sel_idx: to
                   prev_idx: Optional[torch.Tensor] = None, prev_cnt: Optional[torch.Tensor] = None,
                   stream=None) -> None:
     """fastocr_topk_fixation: sel_idx int32 [B,kmax], sel_cnt int32 [B] (written in place)."""
-    lib = load_library()
+    lib = _lib or load_library()
     bv = batch.view()
     assert sel_idx.dtype == torch.int32 and sel_idx.is_contiguous() and sel_cnt.dtype == torch.int32
     assert scores.dtype == torch.float32 and scores.is_contiguous()
-    assert scores.shape[1] == bv.max_vis_len or bv.batch == 0
+    assert scores.size(1) == bv.max_vis_len or bv.batch == 0
     if prev_idx is not None:
         assert prev_idx.shape == sel_idx.shape and prev_idx.dtype == torch.int32 and prev_idx.is_contiguous()
-    _check(lib.fastocr_topk_fixation(_ptr(scores), ctypes.byref(bv), float(tau), _ptr(prev_idx),
-                                     _ptr(prev_cnt), _ptr(sel_idx), _ptr(sel_cnt), sel_idx.shape[1],
+    _check(lib.fastocr_topk_fixation(scores.data_ptr(), ctypes.byref(bv), float(tau), _ptr(prev_idx),
+                                     _ptr(prev_cnt), sel_idx.data_ptr(), sel_cnt.data_ptr(), sel_idx.size(1),
                                      _ptr(ws), 0 if ws is None else ws.numel(), _stream_handle(stream)),
            "fastocr_topk_fixation")
 
@@ -277,35 +285,35 @@ def sparse_decode_attn(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scale: 
                        sel_idx: torch.Tensor, sel_cnt: torch.Tensor, out: torch.Tensor,
                        ws: torch.Tensor, stream=None) -> None:
     """fastocr_sparse_decode_attn: out [B,Hq,d] in the cache dtype (written in place)."""
-    lib = load_library()
+    lib = _lib or load_library()
     kv, bv = cache.view(), batch.view()
     assert q.is_contiguous() and out.is_contiguous() and out.shape == q.shape and out.dtype == q.dtype
     assert sel_idx.dtype == torch.int32 and sel_idx.is_contiguous() and sel_cnt.dtype == torch.int32
-    _check(lib.fastocr_sparse_decode_attn(ctypes.byref(kv), ctypes.byref(bv), _ptr(q), q.shape[1],
-                                          float(scale), _ptr(sel_idx), _ptr(sel_cnt), sel_idx.shape[1],
-                                          _ptr(out), _ptr(ws), ws.numel(), _stream_handle(stream)),
+    _check(lib.fastocr_sparse_decode_attn(ctypes.byref(kv), ctypes.byref(bv), q.data_ptr(), q.size(1),
+                                          float(scale), sel_idx.data_ptr(), sel_cnt.data_ptr(), sel_idx.size(1),
+                                          out.data_ptr(), ws.data_ptr(), ws.numel(), _stream_handle(stream)),
            "fastocr_sparse_decode_attn")
 
 
 def dense_decode_attn(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scale: float, out: torch.Tensor,
                       ws: torch.Tensor, lse: Optional[torch.Tensor] = None, stream=None) -> None:
     """fastocr_dense_decode_attn: out [B,Hq,d] in the cache dtype (written in place)."""
-    lib = load_library()
+    lib = _lib or load_library()
     kv, bv = cache.view(), batch.view()
     assert q.is_contiguous() and out.is_contiguous() and out.shape == q.shape and out.dtype == q.dtype
-    _check(lib.fastocr_dense_decode_attn(ctypes.byref(kv), ctypes.byref(bv), _ptr(q), q.shape[1],
-                                         float(scale), _ptr(out), _ptr(lse), _ptr(ws), ws.numel(),
+    _check(lib.fastocr_dense_decode_attn(ctypes.byref(kv), ctypes.byref(bv), q.data_ptr(), q.size(1),
+                                         float(scale), out.data_ptr(), _ptr(lse), ws.data_ptr(), ws.numel(),
                                          _stream_handle(stream)), "fastocr_dense_decode_attn")
 
 
 def dense_decode_attn_static(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scale: float, out: torch.Tensor,
                              lse: Optional[torch.Tensor] = None, stream=None) -> None:
     """fastocr_dense_decode_attn_static: as dense_decode_attn, scratch in the library's static device buffer."""
-    lib = load_library()
+    lib = _lib or load_library()
     kv, bv = cache.view(), batch.view()
     assert q.is_contiguous() and out.is_contiguous() and out.shape == q.shape and out.dtype == q.dtype
-    _check(lib.fastocr_dense_decode_attn_static(ctypes.byref(kv), ctypes.byref(bv), _ptr(q), q.shape[1],
-                                                float(scale), _ptr(out), _ptr(lse), _stream_handle(stream)),
+    _check(lib.fastocr_dense_decode_attn_static(ctypes.byref(kv), ctypes.byref(bv), q.data_ptr(), q.size(1),
+                                                float(scale), out.data_ptr(), _ptr(lse), _stream_handle(stream)),
            "fastocr_dense_decode_attn_static")
 
 
@@ -313,13 +321,13 @@ def focal_attn_score(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scale: fl
                      scores: torch.Tensor, ws: torch.Tensor, lse: Optional[torch.Tensor] = None,
                      img_mass: Optional[torch.Tensor] = None, stream=None) -> None:
     """fastocr_focal_attn_score: dense output [B,Hq,d] and scores fp32 [B, max_vis_len] in one call."""
-    lib = load_library()
+    lib = _lib or load_library()
     kv, bv = cache.view(), batch.view()
     assert q.is_contiguous() and out.is_contiguous() and out.shape == q.shape and out.dtype == q.dtype
     assert scores.is_contiguous() and scores.dtype == torch.float32
-    assert scores.shape[0] == bv.batch and (scores.shape[1] == bv.max_vis_len or bv.batch == 0)
-    _check(lib.fastocr_focal_attn_score(ctypes.byref(kv), ctypes.byref(bv), _ptr(q), q.shape[1], float(scale),
-                                        _ptr(out), _ptr(scores), _ptr(lse), _ptr(img_mass), _ptr(ws), ws.numel(),
+    assert scores.size(0) == bv.batch and (scores.size(1) == bv.max_vis_len or bv.batch == 0)
+    _check(lib.fastocr_focal_attn_score(ctypes.byref(kv), ctypes.byref(bv), q.data_ptr(), q.size(1), float(scale),
+                                        out.data_ptr(), scores.data_ptr(), _ptr(lse), _ptr(img_mass), ws.data_ptr(), ws.numel(),
                                         _stream_handle(stream)), "fastocr_focal_attn_score")
 
 
@@ -328,16 +336,16 @@ def focal_score_topk(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scale: fl
                      prev_idx: Optional[torch.Tensor] = None, prev_cnt: Optional[torch.Tensor] = None,
                      lse: Optional[torch.Tensor] = None, img_mass: Optional[torch.Tensor] = None, stream=None) -> None:
     """fastocr_focal_score_topk: scores and the selected set from one call."""
-    lib = load_library()
+    lib = _lib or load_library()
     kv, bv = cache.view(), batch.view()
     assert q.is_contiguous() and scores.is_contiguous() and scores.dtype == torch.float32
-    assert scores.shape[0] == bv.batch and (scores.shape[1] == bv.max_vis_len or bv.batch == 0)
+    assert scores.size(0) == bv.batch and (scores.size(1) == bv.max_vis_len or bv.batch == 0)
     assert sel_idx.dtype == torch.int32 and sel_idx.is_contiguous() and sel_cnt.dtype == torch.int32
     if prev_idx is not None:
         assert prev_idx.shape == sel_idx.shape and prev_idx.dtype == torch.int32 and prev_idx.is_contiguous()
-    _check(lib.fastocr_focal_score_topk(ctypes.byref(kv), ctypes.byref(bv), _ptr(q), q.shape[1], float(scale), float(tau),
-                                        _ptr(prev_idx), _ptr(prev_cnt), _ptr(sel_idx), _ptr(sel_cnt), sel_idx.shape[1],
-                                        _ptr(scores), _ptr(lse), _ptr(img_mass), _ptr(ws), ws.numel(),
+    _check(lib.fastocr_focal_score_topk(ctypes.byref(kv), ctypes.byref(bv), q.data_ptr(), q.size(1), float(scale), float(tau),
+                                        _ptr(prev_idx), _ptr(prev_cnt), sel_idx.data_ptr(), sel_cnt.data_ptr(), sel_idx.size(1),
+                                        scores.data_ptr(), _ptr(lse), _ptr(img_mass), ws.data_ptr(), ws.numel(),
                                         _stream_handle(stream)), "fastocr_focal_score_topk")
 
 
@@ -346,17 +354,17 @@ def focal_attn_score_topk(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scal
                           prev_idx: Optional[torch.Tensor] = None, prev_cnt: Optional[torch.Tensor] = None,
                           lse: Optional[torch.Tensor] = None, img_mass: Optional[torch.Tensor] = None, stream=None) -> None:
     """fastocr_focal_attn_score_topk: a focal layer's dense output, its scores and the selected set from one call."""
-    lib = load_library()
+    lib = _lib or load_library()
     kv, bv = cache.view(), batch.view()
     assert q.is_contiguous() and out.is_contiguous() and out.shape == q.shape and out.dtype == q.dtype
     assert scores.is_contiguous() and scores.dtype == torch.float32
-    assert scores.shape[0] == bv.batch and (scores.shape[1] == bv.max_vis_len or bv.batch == 0)
+    assert scores.size(0) == bv.batch and (scores.size(1) == bv.max_vis_len or bv.batch == 0)
     assert sel_idx.dtype == torch.int32 and sel_idx.is_contiguous() and sel_cnt.dtype == torch.int32
     if prev_idx is not None:
         assert prev_idx.shape == sel_idx.shape and prev_idx.dtype == torch.int32 and prev_idx.is_contiguous()
-    _check(lib.fastocr_focal_attn_score_topk(ctypes.byref(kv), ctypes.byref(bv), _ptr(q), q.shape[1], float(scale), float(tau),
-                                             _ptr(prev_idx), _ptr(prev_cnt), _ptr(sel_idx), _ptr(sel_cnt), sel_idx.shape[1],
-                                             _ptr(out), _ptr(scores), _ptr(lse), _ptr(img_mass), _ptr(ws), ws.numel(),
+    _check(lib.fastocr_focal_attn_score_topk(ctypes.byref(kv), ctypes.byref(bv), q.data_ptr(), q.size(1), float(scale), float(tau),
+                                             _ptr(prev_idx), _ptr(prev_cnt), sel_idx.data_ptr(), sel_cnt.data_ptr(), sel_idx.size(1),
+                                             out.data_ptr(), scores.data_ptr(), _ptr(lse), _ptr(img_mass), ws.data_ptr(), ws.numel(),
                                              _stream_handle(stream)), "fastocr_focal_attn_score_topk")
 
 
