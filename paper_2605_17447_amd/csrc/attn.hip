@@ -182,28 +182,24 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
 
     // D = 64: which of the k-block's halves this lane loads of V, and its chunk of a row
     const int vh = li >> 3, lc = lane & 7;
+    // K first: its products and the exponentials run while V is still arriving
     auto load_tile = [&](int i, int64_t off, u32x4(&K)[NL], u32x4(&V)[NL]) {
+        auto row = [&](int r) -> int64_t {
+            if (GATHER || PAGED) return __shfl(off, r);
+            return seq_base + (int64_t)min(tile_pos(i) + r, L - 1) * kv.stride_token;
+        };
+        if constexpr (D == 128) {
+            int64_t ro[NL];
 #pragma unroll
-        for (int e = 0; e < NL; ++e) {
-            if constexpr (D == 128) {
-                const int r = tile_row(lg, e);
-                int64_t ro;
-                if (GATHER || PAGED) ro = __shfl(off, r);
-                else ro = seq_base + (int64_t)min(tile_pos(i) + r, L - 1) * kv.stride_token;
-                V[e] = stream_load(vbase + ro + 8 * li);
-                K[e] = stream_load(kbase + ro + 8 * li);
-            } else {
-                // V: row 16 vh + 4 lg + e (the k-block's tokens); K: rows 8e .. 8e+7, one per 8 lanes
-                const int rv = 16 * vh + 4 * lg + e, rk = 8 * e + (lane >> 3);
-                int64_t rov, rok;
-                if (GATHER || PAGED) { rov = __shfl(off, rv); rok = __shfl(off, rk); }
-                else {
-                    rov = seq_base + (int64_t)min(tile_pos(i) + rv, L - 1) * kv.stride_token;
-                    rok = seq_base + (int64_t)min(tile_pos(i) + rk, L - 1) * kv.stride_token;
-                }
-                V[e] = stream_load(vbase + rov + 8 * lc);
-                K[e] = stream_load(kbase + rok + 8 * lc);
-            }
+            for (int e = 0; e < NL; ++e) { ro[e] = row(tile_row(lg, e)); K[e] = stream_load(kbase + ro[e] + 8 * li); }
+#pragma unroll
+            for (int e = 0; e < NL; ++e) V[e] = stream_load(vbase + ro[e] + 8 * li);
+        } else {
+            // V: row 16 vh + 4 lg + e (the k-block's tokens); K: rows 8e .. 8e+7, one per 8 lanes
+#pragma unroll
+            for (int e = 0; e < NL; ++e) K[e] = stream_load(kbase + row(8 * e + (lane >> 3)) + 8 * lc);
+#pragma unroll
+            for (int e = 0; e < NL; ++e) V[e] = stream_load(vbase + row(16 * vh + 4 * lg + e) + 8 * lc);
         }
     };
 
@@ -367,15 +363,14 @@ tiles_done:
     __syncthreads();
     const uint32_t tag = MODE == kMerge ? sm_tag : 0u;
 
-    const int np = nsplit - 1;                                       // ranges that publish (kMerge)
-    // the stream's published partials: kMergeMaxSplits - 1 fixed places of kMergePitch words
-    unsigned long long *words = MODE == kMerge ? g_merge_words[merge_slot] + (int64_t)stream_id * (kMergeMaxSplits - 1) * kMergePitch : nullptr;
-    for (int idx = threadIdx.x; idx < G * D; idx += 64 * kWaves) {
+    // this workgroup's own (o, M, Z) for element idx = (head, dim) of the group's output
+    auto own = [&](int idx, float &o, float &M, float &Z) {
         const int hh = idx / D, c = idx % D;
-        float M = sm_m[0][hh];
+        M = sm_m[0][hh];
 #pragma unroll
         for (int w = 1; w < kWaves; ++w) M = fmaxf(M, sm_m[w][hh]);
-        float o = 0.f, Z = 0.f;
+        o = 0.f;
+        Z = 0.f;
         if (M > -INFINITY) {
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) {
@@ -384,54 +379,75 @@ tiles_done:
                 Z += f * sm_z[w][hh];
             }
         }
-        const int64_t bh = (int64_t)b * Hq + (int64_t)kvh * G + hh;
-        if (MODE == kMerge && split < np) {
-            unsigned long long *w = words + (int64_t)split * kMergePitch;
-            __hip_atomic_store(w + idx, tagged(o, tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (c == 0) {
-                __hip_atomic_store(w + kMergeStatsAt + hh, tagged(M, tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(w + kMergeStatsAt + kMergeMaxG + hh, tagged(Z, tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        } else if (MODE == kMerge) {
-            // the stream's last range: every other range's (o, m, Z) for this element, all requested
-            // at once, again until each word carries this call's tag
-            unsigned long long wo[kMergeMaxSplits - 1], wm[kMergeMaxSplits - 1], wz[kMergeMaxSplits - 1];
-            const long long t_start = wall_clock64();
-            bool ok = true;
-            while (true) {
+    };
+    const int np = nsplit - 1;                                       // ranges that publish (kMerge)
+    // the stream's published partials: kMergeMaxSplits - 1 fixed places of kMergePitch words
+    unsigned long long *words = MODE == kMerge ? g_merge_words[merge_slot] + (int64_t)stream_id * (kMergeMaxSplits - 1) * kMergePitch : nullptr;
+    if (MODE == kMerge && split == np) {
+        // The stream's last range: every other range's (o, m, Z) for this thread's elements, all requested at
+        // once -- before its own partial is computed, so that the round trip passes behind that -- and
+        // again until each word carries this call's tag.
+        constexpr int EPT = (kMergeMaxG * D + 64 * kWaves - 1) / (64 * kWaves);
+        constexpr int NP = kMergeMaxSplits - 1;
+        unsigned long long wo[EPT][NP], wm[EPT][NP], wz[EPT][NP];
+        auto request = [&]() {
 #pragma unroll
-                for (int x = 0; x < kMergeMaxSplits - 1; ++x) {
-                    if (x < np) {
+            for (int u = 0; u < EPT; ++u) {
+                const int idx = threadIdx.x + 64 * kWaves * u;
+#pragma unroll
+                for (int x = 0; x < NP; ++x) {
+                    if (x < np && idx < G * D) {
                         const unsigned long long *w = words + (int64_t)x * kMergePitch;
-                        wo[x] = __hip_atomic_load(w + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        wm[x] = __hip_atomic_load(w + kMergeStatsAt + hh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        wz[x] = __hip_atomic_load(w + kMergeStatsAt + kMergeMaxG + hh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        wo[u][x] = __hip_atomic_load(w + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        wm[u][x] = __hip_atomic_load(w + kMergeStatsAt + idx / D, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        wz[u][x] = __hip_atomic_load(w + kMergeStatsAt + kMergeMaxG + idx / D, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     }
                 }
-                bool all = true;
-#pragma unroll
-                for (int x = 0; x < kMergeMaxSplits - 1; ++x)
-                    if (x < np)
-                        all = all && (uint32_t)(wo[x] >> 32) == tag && (uint32_t)(wm[x] >> 32) == tag && (uint32_t)(wz[x] >> 32) == tag;
-                if (all) break;
-                __builtin_amdgcn_s_sleep(1);
-                if (wall_clock64() - t_start > spin_ticks) { ok = false; break; }
             }
-            float Mt = M;
+        };
+        request();
+        float o[EPT], M[EPT], Z[EPT];
 #pragma unroll
-            for (int x = 0; x < kMergeMaxSplits - 1; ++x)
-                if (x < np) Mt = fmaxf(Mt, __uint_as_float((uint32_t)wm[x]));
+        for (int u = 0; u < EPT; ++u)
+            own(min((int)threadIdx.x + 64 * kWaves * u, G * D - 1), o[u], M[u], Z[u]);
+        const long long t_start = wall_clock64();
+        bool ok = true;
+        while (true) {
+            bool all = true;
+#pragma unroll
+            for (int u = 0; u < EPT; ++u) {
+                const int idx = threadIdx.x + 64 * kWaves * u;
+#pragma unroll
+                for (int x = 0; x < NP; ++x)
+                    if (x < np && idx < G * D)
+                        all = all && (uint32_t)(wo[u][x] >> 32) == tag && (uint32_t)(wm[u][x] >> 32) == tag && (uint32_t)(wz[u][x] >> 32) == tag;
+            }
+            if (all) break;
+            __builtin_amdgcn_s_sleep(1);
+            if (wall_clock64() - t_start > spin_ticks) { ok = false; break; }
+            request();
+        }
+#pragma unroll
+        for (int u = 0; u < EPT; ++u) {
+            const int idx = threadIdx.x + 64 * kWaves * u;
+            if (idx >= G * D) continue;
+            const int hh = idx / D, c = idx % D;
+            const int64_t bh = (int64_t)b * Hq + (int64_t)kvh * G + hh;
+            float Mt = M[u];
+#pragma unroll
+            for (int x = 0; x < NP; ++x)
+                if (x < np) Mt = fmaxf(Mt, __uint_as_float((uint32_t)wm[u][x]));
             float ot = 0.f, Zt = 0.f;
             if (Mt > -INFINITY) {
-                const float f = fast_exp2(M - Mt);
-                ot = f * o;
-                Zt = f * Z;
+                const float f = fast_exp2(M[u] - Mt);
+                ot = f * o[u];
+                Zt = f * Z[u];
 #pragma unroll
-                for (int x = 0; x < kMergeMaxSplits - 1; ++x) {
+                for (int x = 0; x < NP; ++x) {
                     if (x < np) {
-                        const float fx = fast_exp2(__uint_as_float((uint32_t)wm[x]) - Mt);
-                        ot += fx * __uint_as_float((uint32_t)wo[x]);
-                        Zt += fx * __uint_as_float((uint32_t)wz[x]);
+                        const float fx = fast_exp2(__uint_as_float((uint32_t)wm[u][x]) - Mt);
+                        ot += fx * __uint_as_float((uint32_t)wo[u][x]);
+                        Zt += fx * __uint_as_float((uint32_t)wz[u][x]);
                     }
                 }
             }
@@ -441,6 +457,21 @@ tiles_done:
             if (idx == 0 && !ok) {
                 __hip_atomic_fetch_add(&g_merge_timeouts, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (gave_up_flag) __hip_atomic_store(gave_up_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+        }
+        return;
+    }
+    for (int idx = threadIdx.x; idx < G * D; idx += 64 * kWaves) {
+        const int hh = idx / D, c = idx % D;
+        float o, M, Z;
+        own(idx, o, M, Z);
+        const int64_t bh = (int64_t)b * Hq + (int64_t)kvh * G + hh;
+        if (MODE == kMerge) {
+            unsigned long long *w = words + (int64_t)split * kMergePitch;
+            __hip_atomic_store(w + idx, tagged(o, tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (c == 0) {
+                __hip_atomic_store(w + kMergeStatsAt + hh, tagged(M, tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(w + kMergeStatsAt + kMergeMaxG + hh, tagged(Z, tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         } else if (MODE == kDirect) {
             out[bh * D + c] = f32_to_bf16_bits(Z > 0.f ? o / Z : 0.f);
