@@ -264,15 +264,15 @@ static int choose_splits(int op, const Shape &s, int max_positions, bool *partia
         const int target_wg = fast ? kNumCU : 8 * kNumCU;
         if (fast && op == FASTOCR_OP_SPARSE_DECODE_ATTN && g_tune_attn_merge.load(std::memory_order_relaxed)) {
             // pruned attention is short: one launch whose eight-wave workgroups fill the chip once,
-            // the ranges of a stream merged inside the launch.  Up to 12 tiles one workgroup has the whole list
+            // the ranges of a stream merged inside the launch.  Up to 14 tiles one workgroup has the whole list
             // in flight at once (two tiles per wave) and a cut only adds the merge; beyond that a compute
             // unit's load path is the bound, and the ranges that leave a wave at most one tile win until four
-            // of them no longer do (us per call with 1 / 2 / 3 / 4 ranges, 32 streams: 12 tiles 8.9 / 9.5 / 9.9 / 9.8,
-            // 15 tiles 10.1 / 9.4 / 9.8 / 10.4, 20 tiles 11.2 / 10.9 / 10.0 / 10.5, 27 tiles 14.2 / 12.0 / 11.1 / 10.6,
-            // 40 tiles 17.4 / 14.1 / 12.6 / 12.9, 52 tiles 21.3 / 16.1 / 13.5 / 13.1; 4, 24 and 128 streams
+            // of them no longer do (us per call with 1 / 2 / 3 / 4 ranges, 32 streams: 12 tiles 8.0 / 8.7 / 9.0 / 9.0,
+            // 15 tiles 8.9 / 8.8 / 8.9 / 9.5, 20 tiles 10.5 / 10.0 / 9.0 / 9.6, 27 tiles 13.2 / 10.8 / 9.7 / 9.4,
+            // 40 tiles 16.1 / 13.1 / 11.3 / 11.7, 52 tiles 20.2 / 14.9 / 12.6 / 11.7; 4, 24 and 128 streams
             // order alike)
             int n = kNumCU / (streams > 0 ? streams : 1);
-            const int by_len = ntile <= 12 ? 1 : (ntile <= 16 ? 2 : (ntile <= 24 ? 3 : (ntile <= 32 || ntile >= 48 ? 4 : 3)));
+            const int by_len = ntile <= 14 ? 1 : (ntile <= 16 ? 2 : (ntile <= 24 ? 3 : (ntile <= 32 || ntile >= 48 ? 4 : 3)));
             n = n < by_len ? n : by_len;
             n = n < 1 ? 1 : n;
             if (n == 1 || attn_merges_in_kernel(s, n)) {
