@@ -6,7 +6,7 @@
 // third of the bytes.
 //
 // head_dim 128 and 64.  At 64 the tiles are half as large, so two tiles of K and of V are in flight per wave instead of one;
-// batch 16, 16384 image tokens, 64/8 heads: 99 us for 563 MB (5.7 TB/s) where dense attention, its merge and scoring
+// batch 16, 16384 image tokens, 64/8 heads: 100 us for 563 MB (5.6 TB/s) where dense attention, its merge and scoring
 // took 89 + 5 + 54 us and read K twice.
 //
 // Structure (shared with the scoring-only kernel in score_resident.hip):
@@ -196,7 +196,13 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     };
 
     const int tt0 = 16 * (li >> 3) + 4 * lg;        // tile-relative token of this lane's first logit
-    float m = kMinusHuge, z = 0.f;                  // running max (uniform over the head's lanes), this lane's sum
+    float m = kMinusHuge, z = 0.f;                  // running max (uniform over the head's lanes), this lane's sum (D 128)
+    // D 64: what is parked is not the logit but its softmax weight, in the scoring kernel's arithmetic step by step
+    // (score_resident.hip: per token slot of the tile a reference fixed by the slot's first live logit,
+    // the sums joined in the same order), so that both kernels' scores are the same bits and a set never
+    // depends on which of them a focal layer ran.  Head_dim 128 has no registers for the references.
+    float ref[4] = {kMinusHuge, kMinusHuge, kMinusHuge, kMinusHuge}, zr[4] = {0.f, 0.f, 0.f, 0.f};
+    f32x32 park0, park1, park2, park3;              // logit (D 64: weight) r of image tile J in park<r>[J]
     f32x4 acc[NACC];
 #pragma unroll
     for (int t = 0; t < NACC; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -290,7 +296,7 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     };
 
     // One tile: logits, online softmax, P*V.  nlive = tokens of the tile that exist (may exceed 32).
-    // Returns this lane's 4 logits (log2 domain; -inf for tokens past the end).
+    // Returns this lane's 4 logits (log2 domain; -inf for tokens past the end), for D 64 their weights.
     auto tile_step = [&](int n, int nlive, auto &&next_k, auto &&next_v) -> f32x4 {
         const uint32_t so = (uint32_t)(n & (NSLOT - 1)) * (8192 / NSLOT);
         u32x4 kb[KS];
@@ -318,7 +324,7 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
         const float m_new = fmaxf(m, mx);
         if (__builtin_amdgcn_ballot_w64(m_new != m) != 0ull) {
             const float alpha = fast_exp2(m - m_new);
-            z *= alpha;
+            if constexpr (D == 128) z *= alpha;
 #pragma unroll
             for (int t = 0; t < NACC; ++t) acc[t] *= alpha;
             m = m_new;
@@ -326,7 +332,7 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
         float p[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) p[r] = fast_exp2(s[r] - m);
-        z += (p[0] + p[1]) + (p[2] + p[3]);
+        if constexpr (D == 128) z += (p[0] + p[1]) + (p[2] + p[3]);
         const uint32_t w0 = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)p[0], (__bf16)p[1]});
         const uint32_t w1 = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)p[2], (__bf16)p[3]});
         // contraction slots of lane group lg: tokens 4lg..4lg+3, then 16+4lg..16+4lg+3
@@ -347,11 +353,37 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
             acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
                                                              __builtin_bit_cast(bf16x8, pb), acc[t], 0, 0, 0);
         }
+        if constexpr (D == 64) {
+            bool moved = false;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (ref[r] == kMinusHuge) ref[r] = fmaxf(s[r], kMinusHuge);          // the first live logit
+                moved = moved || s[r] - ref[r] > kRefSlack;
+            }
+            if (__builtin_amdgcn_ballot_w64(moved) != 0ull) {
+                float a[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const bool mv = s[r] - ref[r] > kRefSlack;
+                    a[r] = mv ? fast_exp2(ref[r] - s[r]) : 1.f;
+                    ref[r] = mv ? s[r] : ref[r];
+                    zr[r] *= a[r];
+                }
+                park0 *= a[0];
+                park1 *= a[1];
+                park2 *= a[2];
+                park3 *= a[3];
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                s[r] = fast_exp2(s[r] - ref[r]);
+                zr[r] += s[r];
+            }
+        }
         return s;
     };
 
     // ---- stream: text tiles, then image tiles (logits parked in registers) ----------------------
-    f32x32 park0, park1, park2, park3;          // logit r of image tile J in park<r>[J]
     if (ntext + nimg > 0) {
         issue_any(0, false);
         issue_any(0, true);
@@ -376,8 +408,27 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     const int tt0_p = 16 * (li_p >> 3) + 4 * lg_p;
 
     // ---- attention partial of this wave: O^T columns n and n + 8 are the same head's halves -----
-    z += dpp_move<kDppRor8>(z);
-    z = rows_sum(z);
+    // mref, zref: what the sums are relative to and their total, per head (lanes li and li + 8, all lane groups)
+    float mref = m, zref;
+    if constexpr (D == 128) {
+        z += dpp_move<kDppRor8>(z);
+        z = rows_sum(z);
+        zref = z;
+    } else {
+        mref = fmaxf(fmaxf(ref[0], ref[1]), fmaxf(ref[2], ref[3]));
+        mref = rows_max(mref);
+        mref = fmaxf(mref, dpp_move<kDppRor8>(mref));
+        // the scoring kernel's first step adds a product to its neighbour's rounded one, and the lane whose total
+        // counts meets the odd quads of a half mirrored (reductions over score_resident.hip's lanes li)
+        float e[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) e[r] = fast_exp2(ref[r] - mref);
+        zref = (lg_p & 1) ? fmaf(zr[3], e[3], zr[2] * e[2]) + fmaf(zr[1], e[1], zr[0] * e[0])
+                          : fmaf(zr[0], e[0], zr[1] * e[1]) + fmaf(zr[2], e[2], zr[3] * e[3]);
+        zref = rows_sum(zref);
+        zref += dpp_move<kDppRor8>(zref);
+        z = zref * fast_exp2(mref - m);             // the same sum relative to the running maximum, as the partial has it
+    }
 #pragma unroll
     for (int t = 0; t < NACC; ++t)
 #pragma unroll
@@ -421,8 +472,8 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
         if (lg_p == 0) {
             att_ml[2 * row] = m;
             att_ml[2 * row + 1] = z;
-            sm_m[wave][li_p] = m;
-            sm_z[wave][li_p] = z;
+            sm_m[wave][li_p] = mref;
+            sm_z[wave][li_p] = zref;
         }
     }
     if (threadIdx.x == 0) sm_met = 1;
@@ -435,10 +486,7 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     unsigned long long *stats = g_fus_stats[sync_slot] + (int64_t)wg0 * Hq;
     resident_publish(stats + (int64_t)rng * Hq, sm_m, sm_z, Hq, G, Hkv, wpk);
     // the log-sum-exp of this wave's heads over the whole sequence (lane 8s + x: head x of the group)
-    // (D 64: a weight is 2^(logit - M) / Z: the difference of two logits of like size is nearly exact, where
-    // logit - (M + log2 Z) carries the rounding of that sum -- a sixth of the scores' error; at D 128 the extra
-    // product costs 1 us of 196)
-    float lh, sh, rz = 1.0f;
+    float lh;
     {
         float M, Z;
         const bool ok = resident_heads_gather<4>(stats, rng, nranges, Hq, G, Hkv, wpk, kvh, sm_m, sm_z, spin_ticks, M, Z);
@@ -448,11 +496,6 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
             if (gave_up_flag) __hip_atomic_store(gave_up_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
         lh = (hcol_p < G && Z > 0.f) ? M + log2f(Z) : (hcol_p < G ? -INFINITY : INFINITY);
-        sh = lh;
-        if constexpr (D == 64) {
-            rz = hcol_p < G ? 1.0f / Z : 0.f;
-            sh = hcol_p < G ? M : INFINITY;               // (columns without a head: weight 0)
-        }
     }
     __syncthreads();      // whether every wave has met its ranges
     // This range is done reading: count it out.  The last one of the sequence clears the
@@ -477,27 +520,56 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     if (lse_out && rng == 0 && sub == 0 && lane_p < G) lse_out[(int64_t)b * Hq + kvh * G + lane_p] = lh * kLn2;
 
     // ---- probabilities of the parked logits, summed over the heads of each token ---------------
-    float *red = reinterpret_cast<float *>(&smem[0][0][0]);          // [Hkv][R], at most 32 KB
-    for (int J = 0; J < nimg; ++J) {
-        // this lane_p's 4 tokens of tile J, one head each on 8 neighbouring lanes
-        f32x4 v = f32x4{park0[J], park1[J], park2[J], park3[J]};
+    // D 128: one row of sums per kv head, [Hkv][R], at most 32 KB; D 64: one per four heads, [2 Hkv][R], at most 64 KB
+    float *red = reinterpret_cast<float *>(&smem[0][0][0]);
+    if constexpr (D == 128) {
+        for (int J = 0; J < nimg; ++J) {
+            // this lane_p's 4 tokens of tile J, one head each on 8 neighbouring lanes
+            f32x4 v = f32x4{park0[J], park1[J], park2[J], park3[J]};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float x = fast_exp2(v[r] - lh);
+                x += dpp_move<kDppXor1>(x);
+                x += dpp_move<kDppXor2>(x);
+                x += dpp_move<kDppHalfMirror>(x);
+                v[r] = x;
+            }
+            if ((li_p & 7) == 0) *reinterpret_cast<f32x4 *>(&red[kvh * R + img_first(J) - r0 + tt0_p]) = v;
+        }
+    } else {
+        // from the slot's reference to the head's normaliser (lane x's for head x, as in the scoring kernel: the lanes of
+        // a head agree only up to the rounding of the gather's last merges), for the four heads of this lane's quad
+        lh = __shfl(lh, hcol_p);
+        float cf[4][4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            float x = fast_exp2(v[r] - sh);
-            if constexpr (D == 64) x *= rz;
-            x += dpp_move<kDppXor1>(x);
-            x += dpp_move<kDppXor2>(x);
-            x += dpp_move<kDppHalfMirror>(x);
-            v[r] = x;
+            const float c = hcol_p < G ? fast_exp2(ref[r] - lh) : 0.f;
+            cf[r][0] = dpp_move<kDppQuad0>(c);
+            cf[r][1] = dpp_move<kDppQuad1>(c);
+            cf[r][2] = dpp_move<kDppQuad2>(c);
+            cf[r][3] = dpp_move<kDppQuad3>(c);
         }
-        if ((li_p & 7) == 0) *reinterpret_cast<f32x4 *>(&red[kvh * R + img_first(J) - r0 + tt0_p]) = v;
+        for (int J = 0; J < nimg; ++J) {
+            f32x4 v = f32x4{park0[J], park1[J], park2[J], park3[J]};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float w = v[r];
+                float x = dpp_move<kDppQuad0>(w) * cf[r][0];
+                x = fmaf(dpp_move<kDppQuad1>(w), cf[r][1], x);
+                x = fmaf(dpp_move<kDppQuad2>(w), cf[r][2], x);
+                x = fmaf(dpp_move<kDppQuad3>(w), cf[r][3], x);
+                v[r] = x;
+            }
+            if ((li_p & 3) == 0) *reinterpret_cast<f32x4 *>(&red[(2 * kvh + ((li_p >> 2) & 1)) * R + img_first(J) - r0 + tt0_p]) = v;
+        }
     }
     __syncthreads();
     float local = 0.f;
     const float inv = 1.0f / (float)Hq;
+    const int rows = D == 128 ? Hkv : 2 * Hkv;
     for (int i = threadIdx.x; i < r1 - r0; i += kResThreads) {
         float a = 0.f;
-        for (int g = 0; g < Hkv; ++g) a += red[g * R + i];
+        for (int g = 0; g < rows; ++g) a += red[g * R + i];
         a *= inv;
         store_score<SELECT>(&scores[(int64_t)b * bv.max_vis_len + r0 + i], a);
         local += a;

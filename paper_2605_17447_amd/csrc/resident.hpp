@@ -13,6 +13,7 @@ constexpr int kResTmax = 32;          // image tiles per wave held in registers
 constexpr int kResTile = 32;
 constexpr int kResMaxHq = 64;
 constexpr int kResMaxBatch = 256;
+constexpr float kRefSlack = 16.f;       // how far (log2 units) a logit may rise above its lane's reference before the reference moves
 
 #define RES_EACH_TILE(M)                                                                            \
     M(0) M(1) M(2) M(3) M(4) M(5) M(6) M(7) M(8) M(9) M(10) M(11) M(12) M(13) M(14) M(15)               \
@@ -44,6 +45,7 @@ constexpr int kDppXor2 = 0x4E;          // quad_perm [2,3,0,1]
 constexpr int kDppHalfMirror = 0x141;   // lane i <-> 7 - i within each 8 lanes
 constexpr int kDppRowMirror = 0x140;    // lane i <-> 15 - i within each 16 lanes
 constexpr int kDppRor8 = 0x128;         // lane i <- lane i ^ 8
+constexpr int kDppQuad0 = 0x00, kDppQuad1 = 0x55, kDppQuad2 = 0xAA, kDppQuad3 = 0xFF;      // quad_perm: lane k of each quad to its four lanes
 
 // ---- which (sequence, image-token range) a workgroup of a register-resident kernel works on ------
 // The grid has W workgroups (at most one per compute unit).  With sequences of equal length every

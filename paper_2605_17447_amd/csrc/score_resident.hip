@@ -32,7 +32,6 @@
 namespace fastocr {
 
 constexpr int kResGatherGroup = 8;      // ranges whose statistics a wave asks for at a time
-constexpr float kRefSlack = 16.f;       // how far (log2 units) a logit may rise above its lane's reference before the reference moves
 
 #define RES_DECLARE(J) f32x4 park_##J = f32x4{0.f, 0.f, 0.f, 0.f};
 // image tile J of the wave: multiply, keep the weights, refill the tile's LDS slot
@@ -397,8 +396,8 @@ img_done:
         M = fmaxf(M, dpp_move<kDppHalfMirror>(M));
         M = fmaxf(M, dpp_move<kDppRowMirror>(M));
         M = with_lane_xor32(M, [](float a, float b) { return fmaxf(a, b); });
-        float Z = z[r] * fast_exp2(ref[r] - M);
-        Z += dpp_move<kDppXor1>(Z);
+        const float e = fast_exp2(ref[r] - M);
+        float Z = fmaf(z[r], e, dpp_move<kDppXor1>(z[r] * e));       // (spelt out: focal_fused.hip repeats these roundings)
         Z += dpp_move<kDppXor2>(Z);
         Z += dpp_move<kDppHalfMirror>(Z);
         Z += dpp_move<kDppRowMirror>(Z);

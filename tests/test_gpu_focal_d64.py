@@ -27,6 +27,11 @@ def _check(p, what, tau=0.05):
     check_scores(sc, ref_sc, p.vis_len, what)
     assert np.allclose(lse.cpu().numpy(), ref_lse, rtol=2e-5, atol=2e-5)
     assert np.allclose(mass.cpu().numpy(), ref_mass, atol=2e-5)
+    # the scoring kernel's scores, bit for bit: which of the two ran never changes a set
+    alone, alone_lse, alone_mass = p.scores(want_lse=True, want_mass=True)
+    for b, n in enumerate(p.vis_len):
+        assert torch.equal(alone[b, :n], sc[b, :n]), f"{what}: sequence {b}'s scores differ from the scoring kernel's"
+    assert torch.equal(alone_lse, lse) and torch.equal(alone_mass, mass)
     # with the top-k: the same output and scores bit for bit, and the exact set of these scores
     kmax = max(1, fo.keep_count(p.batch.max_vis_len, tau))
     out2, sc2 = torch.full_like(p.q, 3.0), torch.full_like(sc, -7.0)
@@ -42,6 +47,7 @@ def _check(p, what, tau=0.05):
 @pytest.mark.parametrize("Hq,Hkv", [(64, 8), (28, 4), (16, 2), (5, 1)])
 def test_one_pass_focal_layer_head_dim_64(Hq, Hkv):
     fb.set_tuning("focal_fused", 2)
+    fb.set_tuning("score_resident", 2)
     fb.kernel_timer_enable(fb.KERNEL_FOCAL_FUSED, 8)
     try:
         many = TinyCase(seed=900 + Hq, B=24, Hq=Hq, Hkv=Hkv, d=64, n_vis=[1500 + 61 * i for i in range(24)],
@@ -51,6 +57,8 @@ def test_one_pass_focal_layer_head_dim_64(Hq, Hkv):
         few = TinyCase(seed=901 + Hq, B=3, Hq=Hq, Hkv=Hkv, d=64, n_vis=[64, 200, 33], pre=[3000, 1500, 0],
                        post=[500, 2100, 4000], dtype="bf16", spread=2.0)
         _check(problem_from_case(few), f"d64 {Hq}/{Hkv} long text")
+        steep = TinyCase(seed=903 + Hq, B=2, Hq=Hq, Hkv=Hkv, d=64, n_vis=[2000, 700], pre=[9, 0], post=[3, 100], dtype="bf16", spread=6.0)
+        _check(problem_from_case(steep), f"d64 {Hq}/{Hkv} logits far above the first ones")
         one = TinyCase(seed=902 + Hq, B=2, Hq=Hq, Hkv=Hkv, d=64, n_vis=[31, 1], pre=[0, 0], post=[0, 1], dtype="bf16")
         _check(problem_from_case(one), f"d64 {Hq}/{Hkv} one tile", tau=0.25)
         wl = fs.config(5, batch=12, steps=4, n_visual=(600, 3000), grid_w=(20, 60), text_prefix=(3, 300), page_tokens=64,
@@ -62,3 +70,4 @@ def test_one_pass_focal_layer_head_dim_64(Hq, Hkv):
     finally:
         fb.kernel_timer_enable(fb.KERNEL_FOCAL_FUSED, 0)
         fb.set_tuning("focal_fused", 1)
+        fb.set_tuning("score_resident", 1)
