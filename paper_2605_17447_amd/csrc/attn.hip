@@ -626,8 +626,8 @@ __global__ __launch_bounds__(256) void attn_combine_wide_kernel(
     T *__restrict__ out, float *__restrict__ lse, const int32_t *__restrict__ seq_meta, int wpk, MassArgs mass)
 {
     __shared__ float sm_max[4];
-    __shared__ float sm_z[256];
-    __shared__ __align__(16) float sm_o[1024];
+    __shared__ typename CombineAcc<T>::type sm_z[256];
+    __shared__ __align__(32) typename CombineAcc<T>::type sm_o[1024];
     // with image mass to sum, one more workgroup per sequence, behind those of its heads
     const int Hq = (int)gridDim.x - (mass.out ? 1 : 0);
     if ((int)blockIdx.x == Hq) {
@@ -635,7 +635,7 @@ __global__ __launch_bounds__(256) void attn_combine_wide_kernel(
         return;
     }
     combine_wide_body<T>(part_o, part_ml, nsplit, d, out, lse, seq_meta, wpk, blockIdx.x, blockIdx.y, Hq,
-                         CombineShared{sm_max, sm_z, sm_o});
+                         CombineShared<T>{sm_max, sm_z, sm_o});
 }
 
 // -----------------------------------------------------------------------------------------

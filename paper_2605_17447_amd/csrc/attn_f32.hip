@@ -169,7 +169,9 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void attn_f32_kernel(
                 if (PARK && li < Gp) lpark[(int64_t)(wp0 + i * kF32Tile + 4 * r + lg) * Gp] = f;      // inside the pitch
             }
             mx = rows_max(mx);
-            const float m_new = fmaxf(m, mx);
+            // a whole number: the factors between maxima, here and where waves and ranges are merged, are then exact
+            // powers of two instead of exponentials off by an ulp each
+            const float m_new = fmaxf(m, ceilf(mx));
             if (__builtin_amdgcn_ballot_w64(m_new != m) != 0ull) {
                 const double alpha = (double)fast_exp2(m - m_new);
                 z *= alpha;
@@ -179,13 +181,14 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void attn_f32_kernel(
                 }
                 m = m_new;
             }
-            // the weight from the exact difference: rounding it to fp32 costs 2^-24 of a number that is small
-            // wherever the weight matters
+            // The weight from the exact difference, its whole part apart: fp32 holds the rest to 2^-25, where the
+            // difference itself (10 and more octaves for most tokens of a flat distribution) would be rounded to 2^-21.
             double p[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float w = fast_exp2((float)(s[r] - (double)m));
-                p[r] = (wp0 + i * kF32Tile + 4 * r + lg < pend) ? (double)w : 0.0;
+                const double x = s[r] - (double)m, whole = rint(x);
+                const double w = ldexp((double)fast_exp2((float)(x - whole)), (int)whole);
+                p[r] = (wp0 + i * kF32Tile + 4 * r + lg < pend) ? w : 0.0;
                 z += p[r];
             }
             if constexpr (PV) {

@@ -8,10 +8,17 @@ namespace fastocr {
 
 constexpr int kCombineFew = 32;        // up to this many partials per head the merge takes its one-round-trip form
 
+// What the partials are added up in: fp64 for fp32 outputs (up to 32 and more fp32 partials in an fp32 chain were the
+// largest part of those outputs' error), else fp32.
+template <typename T> struct CombineAcc { typedef float type; };
+template <> struct CombineAcc<float> { typedef double type; };
+
+template <typename T>
 struct CombineShared {
+    typedef typename CombineAcc<T>::type A;
     float *max4;        // [4]
-    float *z;           // [256]
-    float *o;           // [1024], 16-byte aligned: [split lane][d], SL * d <= 1024 as DL >= d/4
+    A *z;               // [256]
+    A *o;               // [1024], 16-byte aligned: [split lane][d], SL * d <= 1024 as DL >= d/4
 };
 
 // out = sum_s 2^(m_s - M) acc_s / sum_s 2^(m_s - M) Z_s for head h of sequence b (head_dim a multiple
@@ -24,9 +31,11 @@ struct CombineShared {
 template <typename T>
 __device__ __forceinline__ void combine_wide_body(const float *__restrict__ part_o, const float *__restrict__ part_ml, int nsplit, int d,
                                                   T *__restrict__ out, float *__restrict__ lse, const int32_t *__restrict__ seq_meta,
-                                                  int wpk, int h, int b, int Hq, const CombineShared &sh)
+                                                  int wpk, int h, int b, int Hq, const CombineShared<T> &sh)
 {
-    float *sm_max = sh.max4, *sm_z = sh.z, *sm_o = sh.o;
+    typedef typename CombineAcc<T>::type A;
+    float *sm_max = sh.max4;
+    A *sm_z = sh.z, *sm_o = sh.o;
     const int64_t bh = (int64_t)b * Hq + h;
     const int t = threadIdx.x;
     const bool works = t < 256;
@@ -50,8 +59,10 @@ __device__ __forceinline__ void combine_wide_body(const float *__restrict__ part
     const int dl = t & (DL - 1), sl = t / DL;
     const bool live = works && dl < nd4;          // this thread holds a (split lane, dim lane) of the merge
 
-    float Z = 0.f, M;
-    f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+    A Z = 0;
+    float M;
+    typedef A Ax4 __attribute__((ext_vector_type(4)));
+    Ax4 o = Ax4{0, 0, 0, 0};
     if (nsplit <= kCombineFew && nsplit <= 4 * SL) {
         // A handful of partials (a short list cut fine): one memory round trip instead of two.  The
         // thread's (at most four) accumulators are requested first, from clamped addresses; then every
@@ -73,9 +84,9 @@ __device__ __forceinline__ void combine_wide_body(const float *__restrict__ part
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 if (sl + k * SL < nsplit) {
-                    const float f = fast_exp2(mm[k] - M);
+                    const A f = fast_exp2(mm[k] - M);
                     Z += f * zz[k];
-                    o += a[k] * f;
+                    o += __builtin_convertvector(a[k], Ax4) * f;
                 }
             }
         }
@@ -91,21 +102,21 @@ __device__ __forceinline__ void combine_wide_body(const float *__restrict__ part
             const float *po = pbase + 4 * dl;
 #pragma unroll 4
             for (int s = sl; s < nsplit; s += SL) {
-                const float f = fast_exp2(ml[s * ml_step] - M);
+                const A f = fast_exp2(ml[s * ml_step] - M);
                 Z += f * ml[s * ml_step + 1];
                 const f32x4 a = *reinterpret_cast<const f32x4 *>(po + s * o_step);
-                o += a * f;
+                o += __builtin_convertvector(a, Ax4) * f;
             }
         }
     }
-    if (live) *reinterpret_cast<f32x4 *>(&sm_o[sl * d + 4 * dl]) = o;
+    if (live) *reinterpret_cast<Ax4 *>(&sm_o[sl * d + 4 * dl]) = o;
     if (works && dl == 0) sm_z[sl] = Z;
     __syncthreads();
     if (t < d) {
-        float acc = 0.f, zt = 0.f;
+        A acc = 0, zt = 0;
         for (int x = 0; x < SL; ++x) { acc += sm_o[x * d + t]; zt += sm_z[x]; }
-        store_elem<T>(out + bh * d + t, zt > 0.f ? acc / zt : 0.f);
-        if (lse && t == 0) lse[bh] = zt > 0.f ? (M + log2f(zt)) * kLn2 : -INFINITY;
+        store_elem<T>(out + bh * d + t, zt > 0 ? (float)(acc / zt) : 0.f);
+        if (lse && t == 0) lse[bh] = zt > 0 ? (M + log2f((float)zt)) * kLn2 : -INFINITY;
     }
 
 }

@@ -238,8 +238,8 @@ __global__ __launch_bounds__(kTopkThreads) void focal_tail_kernel(
     __shared__ int s_pick[4];
     __shared__ __align__(16) int w_ac[4 * kTopkWaves];
     __shared__ float sm_max[4];
-    __shared__ float sm_z[256];
-    __shared__ __align__(16) float sm_o[1024];
+    __shared__ typename CombineAcc<T>::type sm_z[256];
+    __shared__ __align__(32) typename CombineAcc<T>::type sm_o[1024];
 
     if ((int)blockIdx.x < batch) {
         TopkRegShared sh;
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(kTopkThreads) void focal_tail_kernel(
         const int x = (int)blockIdx.x - batch;
         const int b = x / c.n_q_heads, h = x - b * c.n_q_heads;
         combine_wide_body<T>(c.part_o, c.part_ml, c.nsplit, c.d, (T *)c.out, nullptr, c.seq_meta, c.wpk, h, b, c.n_q_heads,
-                             CombineShared{sm_max, sm_z, sm_o});
+                             CombineShared<T>{sm_max, sm_z, sm_o});
     }
 }
 
