@@ -282,10 +282,11 @@ static int choose_splits(int op, const Shape &s, int max_positions, bool *partia
                 // plain store of the partial).  Replayed from a graph, where the merge kernel starts
                 // 0.4 us after the launch before it (eager: 2 - 3 us), partials over four-wave workgroups
                 // of one tile per wave plus that kernel win as long as those workgroups find a compute
-                // unit each (28- and 36-layer stacks, batch 4 - 16, 8 - 64 streams of 15 - 47 tiles:
-                // 356 -> 331, 391 -> 376, 495 -> 443, 364 -> 323, 548 -> 452, 403 -> 327 us per decode
-                // step; with 96 and 128 streams of 15 tiles, where they would not: 418 -> 464 and
-                // 449 -> 506 us, so those keep the single launch; eager the fine cut costs 2 us per call).
+                // unit each (a captured step of 28 layers, single launches / fine cut: 296 / 291 us with 32 streams of
+                // 15 tiles, 325 / 297 and 307 / 283 with 24 of 27, 371 / 292 and 354 / 280 with 8 of 47, 265 / 240
+                // with 4 of 17; with 96 and 128 streams of 15 tiles, where they would not, an earlier form of
+                // the kernel took 418 / 464 and 449 / 506 us, so those keep the single launch; eager the fine cut costs
+                // 2 us per call).
                 bool fits = false;
                 const int fine = finest_splits(s, max_positions, &fits);
                 if (replay == 1 && fits && fine > n) {
