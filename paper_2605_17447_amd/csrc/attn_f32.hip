@@ -32,6 +32,8 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kF32Tile = 16;       // tokens per wave tile
 constexpr int kF32Waves = 4;
+constexpr float kLowest = -3.402823466e+38f;
+constexpr double kRound = 6755399441055744.0;      // 1.5 * 2^52
 
 __device__ __forceinline__ f32x4 stream_load_f32(const float *p)
 {
@@ -125,7 +127,9 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void attn_f32_kernel(
         }
     };
 
-    float m = -INFINITY;                 // running maximum of head li: an fp32 value, exact as a double
+    // Running maximum of head li: an fp32 value, exact as a double.  It starts finite, so that a tile of keys that are all
+    // masked out (logits of -inf, or below the type's lowest value) leaves weights of 0 behind, not of 2^(inf - inf).
+    float m = kLowest;
     double z = 0.0;                      // this lane's share of head li's weight sum
     f64x4 acc[PV ? 4 * NH : 1];
     if constexpr (PV) {
@@ -183,12 +187,15 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void attn_f32_kernel(
             }
             // The weight from the exact difference, its whole part apart: fp32 holds the rest to 2^-25, where the
             // difference itself (10 and more octaves for most tokens of a flat distribution) would be rounded to 2^-21.
+            // Rounded by adding and taking off 1.5 * 2^52, whose low word then holds the whole part: defined for every
+            // value, where the conversion to an integer is not.  Below -2000 the weight is 0 in fp64 anyway and
+            // taken as that: a logit of -inf has no whole part and no rest.  A NaN passes and stays one.
             double p[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const double x = s[r] - (double)m, whole = rint(x);
-                const double w = ldexp((double)fast_exp2((float)(x - whole)), (int)whole);
-                p[r] = (wp0 + i * kF32Tile + 4 * r + lg < pend) ? w : 0.0;
+                const double x = s[r] - (double)m, y = x + kRound, whole = y - kRound;
+                const double w = ldexp((double)fast_exp2((float)(x - whole)), (int)(uint32_t)__builtin_bit_cast(uint64_t, y));
+                p[r] = (wp0 + i * kF32Tile + 4 * r + lg < pend) && !(x < -2000.0) ? w : 0.0;
                 z += p[r];
             }
             if constexpr (PV) {
