@@ -296,8 +296,7 @@ static int choose_splits(int op, const Shape &s, int max_positions, bool *partia
                 return n;
             }
         }
-        // fp64 matrix-core kernels: two workgroups of four waves per compute unit (rounded down: no more partials
-        // than the plain kernels left, which bounds the shapes the static scratch serves)
+        // fp64 matrix-core kernels: two workgroups of four waves per compute unit (rounded down, see partial_rows)
         if (s.fast32) {
             nsplit = 2 * kNumCU / (streams > 0 ? streams : 1);
             // a list of up to two (head_dim 64: three) tiles per wave is not cut: the one launch then writes the
@@ -315,6 +314,20 @@ static int choose_splits(int op, const Shape &s, int max_positions, bool *partia
     if (nsplit > 256) nsplit = 256;
     if (nsplit < 1) nsplit = 1;
     return nsplit;
+}
+
+// Partial rows (sequence, query head, range) to size a workspace for.  For fp32 caches on the matrix cores the most that
+// a call with this many sequences or fewer leaves (a call's own count goes up and down with the batch, by the rounding
+// of its range count): at most 2 CU workgroups, each a row per query head of its group, or one range per sequence. That is
+// at most 8192 rows of 256 CUs and 16 heads, 4.3 MB at head_dim 128, unless the batch itself has more, so every
+// shape whose single ranges fit the static scratch is served from it.
+static size_t partial_rows(int op, const Shape &s, int max_positions, int nsplit)
+{
+    const size_t heads = (size_t)s.batch * s.n_q_heads;
+    if (!s.fast32 || g_tune_splits[op].load(std::memory_order_relaxed) > 0) return heads * nsplit;
+    const size_t by_work = (size_t)std::min(256, std::max(1, (max_positions + 63) / 64));
+    const size_t filled = (size_t)(2 * plan_cu_count() / s.kv.n_kv_heads) * s.n_q_heads;
+    return std::min(heads * by_work, std::max(heads, filled));
 }
 
 // Upper bound of the positions a pruned-attention call attends: all text plus kmax image tokens
@@ -365,18 +378,17 @@ size_t fastocr_workspace_bytes(int op, const fastocr_kv_view *kv, const fastocr_
         const size_t dense = fastocr_workspace_bytes(FASTOCR_OP_DENSE_DECODE_ATTN, kv, bv, n_q_heads, 0);
         need = need > dense ? need : dense;
         if (s.fast32) {
-            const size_t one = round256(focal_f32_workspace_bytes(s, choose_splits(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len)) + 256);
+            const int nsplit = choose_splits(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len);
+            const size_t rows = partial_rows(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len, nsplit);
+            const size_t one = round256(focal_f32_workspace_bytes(s, rows) + 256);
             need = need > one ? need : one;
         }
-        ResidentPlan rp;
-        if (resident_plan(s, plan_cu_count(), &rp)) {
-            const size_t fused = round256(focal_fused_workspace_bytes(s, rp) + 256);
-            need = need > fused ? need : fused;
-        }
-        return need;
+        const size_t fused = focal_fused_workspace_bytes(s, plan_cu_count());
+        return fused > 0 ? std::max(need, round256(fused + 256)) : need;
     }
-    // fewer positions never need more ranges, so a bound taken with a larger kmax (or none) also covers;
-    // pruned attention: sized for the finest cut as well, whether or not "graph_replay" asks for it
+    // Pruned attention (bf16): sized for the finest cut as well, whether or not "graph_replay" asks for it.  That cut is
+    // monotone in the list's length and as fine as any that is merged inside the launch (whose own count falls from four
+    // ranges to three after 32 tiles), so a size taken with a larger kmax (or none) also covers.
     const int positions = op == FASTOCR_OP_SPARSE_DECODE_ATTN ? sparse_positions(bv, kmax) : bv->max_seq_len;
     int nsplit = choose_splits(op, s, positions, nullptr, 0);
     if (op == FASTOCR_OP_SPARSE_DECODE_ATTN && s.fast && g_tune_splits[op].load(std::memory_order_relaxed) <= 0) {
@@ -385,12 +397,12 @@ size_t fastocr_workspace_bytes(int op, const fastocr_kv_view *kv, const fastocr_
     }
     if (op == FASTOCR_OP_FOCAL_SCORE) {
         // sized for either scoring path, so that the choice can be made at launch
-        size_t need = score_workspace_bytes(s, nsplit);
+        size_t need = score_workspace_bytes(s, partial_rows(op, s, positions, nsplit));
         ResidentPlan rp;
         if (resident_plan(s, plan_cu_count(), &rp)) need = need > resident_workspace_bytes(s, rp) ? need : resident_workspace_bytes(s, rp);
         return round256(need + 256);
     }
-    return round256(attn_workspace_bytes(s, nsplit) + 256);
+    return round256(attn_workspace_bytes(s, partial_rows(op, s, positions, nsplit)) + 256);
 }
 
 static int check_ws(const void *ws, size_t ws_bytes, size_t need)

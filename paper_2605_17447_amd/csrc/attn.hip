@@ -643,9 +643,8 @@ __global__ __launch_bounds__(256) void attn_combine_wide_kernel(
 // -----------------------------------------------------------------------------------------
 int attn_tile_tokens(const Shape &s) { return mfma_path(s) ? kTile * 4 : 64; }
 
-size_t attn_workspace_bytes(const Shape &s, int nsplit)
+size_t attn_workspace_bytes(const Shape &s, size_t rows)
 {
-    const size_t rows = (size_t)s.batch * s.n_q_heads * nsplit;
     return rows * (size_t)(s.kv.head_dim + 2) * sizeof(float);
 }
 

@@ -591,10 +591,14 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
 // Workspace, with W = nranges * batch workgroups: attention partials fp32 [W][wpk][Hq][d] and
 // [W][wpk][Hq][2], image-mass partials [W], and per sequence
 // its first workgroup and range count int32 [B][2].
-size_t focal_fused_workspace_bytes(const Shape &s, const ResidentPlan &p)
+// Sized for the most workgroups that this or a smaller problem's plan can have: a plan's own count goes up and
+// down as its range length is rounded, and a size asked for once has to serve shorter sequences as well.
+size_t focal_fused_workspace_bytes(const Shape &s, int num_cu)
 {
-    const size_t W = (size_t)p.nranges * s.batch;
-    size_t bytes = W * p.wpk * s.n_q_heads * (s.kv.head_dim + 2) * sizeof(float);
+    const size_t W = (size_t)resident_max_workgroups(s, num_cu);
+    if (W == 0) return 0;
+    const size_t wpk = (size_t)(kResWaves / s.kv.n_kv_heads);
+    size_t bytes = W * wpk * s.n_q_heads * (s.kv.head_dim + 2) * sizeof(float);
     bytes += W * sizeof(float);
     bytes += (size_t)s.batch * 2 * sizeof(int32_t);
     return bytes;

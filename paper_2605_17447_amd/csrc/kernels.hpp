@@ -84,7 +84,7 @@ struct MassArgs {
 // ---- attention (attn.hip) ---------------------------------------------------------------
 // Workspace: part_o fp32 [B][Hq][nsplit][d] followed by part_ml fp32 [B][Hq][nsplit][2].
 int attn_tile_tokens(const Shape &s);
-size_t attn_workspace_bytes(const Shape &s, int nsplit);
+size_t attn_workspace_bytes(const Shape &s, size_t rows);             // rows = B * Hq * nsplit
 // With 2 .. 4 ranges per stream on the MFMA path the stream's last range can merge the others'
 // partials inside the launch (through static device memory) when the shape fits
 // (attn_merges_in_kernel) and an exchange slot is given; otherwise partials go to the workspace
@@ -112,13 +112,13 @@ hipError_t launch_attn_f32(int kid, const Shape &s, const void *q, float scale, 
 // ---- focal scoring (score.hip) ----------------------------------------------------------
 // Workspace: logits fp32 [B][Hq][pitch], part_ml fp32 [B][Hq][nsplit][2], mass partials.
 int score_tile_tokens(const Shape &s);
-size_t score_workspace_bytes(const Shape &s, int nsplit);
+size_t score_workspace_bytes(const Shape &s, size_t rows);            // rows = B * Hq * nsplit
 hipError_t launch_score(const Shape &s, const void *q, float scale, float *scores, float *lse,
                         float *img_mass, void *ws, int nsplit, hipStream_t stream);
 
 // A focal layer of an fp32 cache in one pass (s.fast32): attention partials and parked logits from one read of K
 // and V, then the scores.  nsplit: that of dense attention.  defer: see launch_focal_fused.
-size_t focal_f32_workspace_bytes(const Shape &s, int nsplit);
+size_t focal_f32_workspace_bytes(const Shape &s, size_t rows);        // rows = B * Hq * nsplit
 struct CombineArgs;
 hipError_t launch_focal_f32(const Shape &s, const void *q, float scale, void *out, float *scores, float *lse, float *img_mass,
                             void *ws, int nsplit, hipStream_t stream, CombineArgs *defer = nullptr);
@@ -140,6 +140,8 @@ struct SelectArgs {
 // whether the fused select covers the shape (image spans of up to 16384 tokens)
 bool resident_select_fits(const Shape &s);
 bool resident_plan(const Shape &s, int num_cu, ResidentPlan *plan);
+// The most workgroups a plan of this cache for at most these sequences has, in number and length (0: never a plan).
+int resident_max_workgroups(const Shape &s, int num_cu);
 size_t resident_workspace_bytes(const Shape &s, const ResidentPlan &p);
 hipError_t launch_score_resident(const Shape &s, const ResidentPlan &p, int sync_slot, uint32_t *gave_up_flag, const void *q, float scale,
                                  float *scores, float *lse, float *img_mass, void *ws, hipStream_t stream,
@@ -147,7 +149,7 @@ hipError_t launch_score_resident(const Shape &s, const ResidentPlan &p, int sync
 
 // ---- focal layer in one pass: dense attention output + scores (focal_fused.hip) -----------
 // Uses the same plan as the register-resident scoring kernel.
-size_t focal_fused_workspace_bytes(const Shape &s, const ResidentPlan &p);
+size_t focal_fused_workspace_bytes(const Shape &s, int num_cu);
 // A merge of attention partials handed on to the launch that follows (see launch_topk).
 struct CombineArgs {
     const float *part_o, *part_ml;

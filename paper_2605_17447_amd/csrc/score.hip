@@ -367,10 +367,10 @@ static size_t parked_floats(const Shape &s)
     return (size_t)s.batch * s.kv.n_kv_heads * (size_t)logit_pitch(s.bv.max_seq_len) * Gp;
 }
 
-size_t score_workspace_bytes(const Shape &s, int nsplit)
+size_t score_workspace_bytes(const Shape &s, size_t rows)
 {
     size_t bytes = parked_floats(s) * sizeof(float);
-    bytes += (size_t)s.batch * s.n_q_heads * (size_t)nsplit * 2 * sizeof(float);
+    bytes += rows * 2 * sizeof(float);
     bytes += (size_t)s.batch * fin_blocks(s) * sizeof(float);
     return bytes;
 }
@@ -429,9 +429,9 @@ hipError_t launch_score(const Shape &s, const void *q, float scale, float *score
 }
 
 // Workspace: as launch_score's, then the attention partials fp32 [B][Hq][nsplit][d] (the softmax statistics serve both).
-size_t focal_f32_workspace_bytes(const Shape &s, int nsplit)
+size_t focal_f32_workspace_bytes(const Shape &s, size_t rows)
 {
-    return (score_workspace_bytes(s, nsplit) + 255) / 256 * 256 + (size_t)s.batch * s.n_q_heads * nsplit * s.kv.head_dim * sizeof(float);
+    return (score_workspace_bytes(s, rows) + 255) / 256 * 256 + rows * s.kv.head_dim * sizeof(float);
 }
 
 hipError_t launch_focal_f32(const Shape &s, const void *q, float scale, void *out, float *scores, float *lse, float *img_mass,
@@ -440,8 +440,9 @@ hipError_t launch_focal_f32(const Shape &s, const void *q, float scale, void *ou
     const int64_t pitch = logit_pitch(s.bv.max_seq_len);
     float *logits = reinterpret_cast<float *>(ws);
     float *part_ml = logits + parked_floats(s);
-    float *mass_part = part_ml + (size_t)s.batch * s.n_q_heads * nsplit * 2;
-    float *part_o = logits + (score_workspace_bytes(s, nsplit) + 255) / 256 * 256 / sizeof(float);
+    const size_t rows = (size_t)s.batch * s.n_q_heads * nsplit;
+    float *mass_part = part_ml + rows * 2;
+    float *part_o = logits + (score_workspace_bytes(s, rows) + 255) / 256 * 256 / sizeof(float);
     hipError_t e = launch_attn_f32(K_FOCAL_FUSED, s, q, scale, nullptr, nullptr, 0, part_o, part_ml, nsplit, nullptr, nullptr, logits,
                                    pitch, stream);
     if (e != hipSuccess) return e;

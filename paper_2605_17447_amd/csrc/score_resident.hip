@@ -26,6 +26,8 @@
 // head_dim 128 or 64 (a template parameter: rows of 256 or 128 bytes, 4 or 2 k-steps per logit).
 // Shapes that do not fit (group size > 8, Hkv not dividing 8, more sequences than compute
 // units, more than 32 tiles per wave, pages shorter than a tile) take the two-kernel path.
+#include <algorithm>
+
 #include "kernels.hpp"
 #include "resident.hpp"
 
@@ -74,16 +76,31 @@ __device__ uint32_t g_res_done[kResSlots][kResMaxBatch];     // fused top-k: ran
 
 bool resident_select_fits(const Shape &s) { return s.bv.max_vis_len <= kSelMaxKeys; }
 
-bool resident_plan(const Shape &s, int num_cu, ResidentPlan *plan)
+// What the register-resident kernels ask of a cache and its heads, whatever the sequences.
+static bool resident_cache(const Shape &s)
 {
     const int Hkv = s.kv.n_kv_heads;
     if (!s.fast || (s.kv.head_dim != 128 && s.kv.head_dim != 64) || Hkv < 1 || s.n_q_heads % Hkv != 0) return false;
     const int G = s.n_q_heads / Hkv;
     if (G > 8 || s.n_q_heads > kResMaxHq) return false;
     if (Hkv != 1 && Hkv != 2 && Hkv != 4 && Hkv != 8) return false;
-    if (s.batch < 1 || s.batch > num_cu || s.batch > kResMaxBatch) return false;
     if (s.paged && s.kv.page_tokens < kResTile) return false;        // a tile may touch two pages at most
-    if (s.kv.stride_token > (1 << 24)) return false;                 // 32 rows of bytes must fit 32 bits
+    return s.kv.stride_token <= (1 << 24);                           // 32 rows of bytes must fit 32 bits
+}
+
+int resident_max_workgroups(const Shape &s, int num_cu)
+{
+    if (!resident_cache(s)) return 0;
+    const int unit = kResTile * (kResWaves / s.kv.n_kv_heads);
+    const int64_t cuts = ((int64_t)s.bv.max_vis_len + unit - 1) / unit;
+    return (int)std::min<int64_t>(num_cu, (int64_t)s.batch * std::max<int64_t>(cuts, 1));
+}
+
+bool resident_plan(const Shape &s, int num_cu, ResidentPlan *plan)
+{
+    if (!resident_cache(s)) return false;
+    const int Hkv = s.kv.n_kv_heads;
+    if (s.batch < 1 || s.batch > num_cu || s.batch > kResMaxBatch) return false;
     const int wpk = kResWaves / Hkv;
     const int unit = kResTile * wpk;                       // tokens of one round of a head's waves
     int nranges = num_cu / s.batch;
