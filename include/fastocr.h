@@ -137,11 +137,12 @@ size_t fastocr_workspace_bytes(int op, const fastocr_kv_view *kv, const fastocr_
  *   scores   fp32 [batch, max_vis_len]
  *   lse      fp32 [batch, n_q_heads] natural-log sum-exp of each head's logits, or NULL
  *   img_mass fp32 [batch] sum_i scores[b,i] = the image-attention ratio of Eq. 1, or NULL
- * Kernels: bf16 caches with head_dim 128 or 64 and at most 16 query heads per kv head run on the
- * matrix-core kernels (all calls); every other shape (fp32 caches, other head dimensions up to 256,
- * larger groups) runs on plain-FMA kernels that accumulate in fp64, to the same error bars.
+ * Kernels: caches with head_dim 128 or 64, rows that start 16-byte aligned and at most 16 query heads per
+ * kv head run on matrix-core kernels (all calls): bf16 products for bf16 caches, fp64 products for fp32
+ * caches.  Every other shape (other head dimensions up to 256, larger groups, unaligned rows) runs on
+ * plain-FMA kernels that accumulate in fp64, to the same error bars.
  * Concurrency: when the shape fits (bf16, head_dim 128 or 64, 1/2/4/8 kv heads with at most 8 query heads
- * each, batch <= 256 and <= the compute-unit count) this call (and, at head_dim 128, fastocr_focal_attn_score) runs as ONE kernel whose
+ * each, batch <= 256 and <= the compute-unit count) this call and fastocr_focal_attn_score run as ONE kernel whose
  * workgroups -- at most one per compute unit -- wait for each other's softmax statistics, so
  * all of them must be on the chip together.  Launched alone on the GPU (any number of calls in
  * order on one stream, HIP graphs included) that always holds.  If other kernels occupy compute
@@ -150,7 +151,8 @@ size_t fastocr_workspace_bytes(int op, const fastocr_kv_view *kv, const fastocr_
  * itself takes the forms built from separate kernels for the rest of the process
  * (fastocr_set_tuning("exchange_fallback", 0) re-arms the single-launch forms).  Callers that
  * overlap other GPU work by design should select the separate kernels up front with
- * fastocr_set_tuning("score_resident", 0) and ("focal_fused", 0).
+ * fastocr_set_tuning("score_resident", 0) and ("focal_fused", 0) (at head_dim 64 the first alone also
+ * keeps fastocr_focal_attn_score to separate kernels).  No call on an fp32 cache waits in this way.
  */
 int fastocr_focal_score(const fastocr_kv_view *kv, const fastocr_batch_view *bv, const void *q,
                         int n_q_heads, float scale, float *scores, float *lse, float *img_mass,
@@ -232,9 +234,12 @@ int fastocr_dense_decode_attn_static(const fastocr_kv_view *kv, const fastocr_ba
  * A focal layer in one call (Alg. 1, focal branch; Eq. 1 and Eq. 2 with the full cache): the
  * dense attention output of fastocr_dense_decode_attn AND the scores, lse and img_mass of
  * fastocr_focal_score for the same q, computed from a single pass over K and V where the
- * shape allows it (bf16, head_dim 128, group size <= 8, 1/2/4/8 KV heads, batch <= compute
- * units, at most 32 tiles of 32 image tokens per wave); other shapes run the two separate
- * kernels one after the other on the same stream, with identical results up to rounding order.
+ * shape allows it: bf16, head_dim 128 or 64, group size <= 8, 1/2/4/8 KV heads, batch <= compute
+ * units, at most 32 tiles of 32 image tokens per wave (one kernel that waits for itself, see
+ * Concurrency above); fp32, head_dim 128 or 64, group size <= 16, 16-byte aligned rows (attention
+ * partials and parked logits from one kernel, scores from a second, nothing waits).  Other shapes, and
+ * all of them with fastocr_set_tuning("focal_fused", 0), run the two separate calls' kernels one after the
+ * other on the same stream, with identical results up to rounding order.
  * Arguments as in those two calls; out and scores are both required, lse and img_mass optional.
  * Workspace: fastocr_workspace_bytes(FASTOCR_OP_FOCAL_ATTN_SCORE, ...).
  */
@@ -326,7 +331,8 @@ int fastocr_stream_probe(const void *src, void *dst, size_t bytes, void *sink, v
 
 /* Launch-shape overrides for measurement sweeps and deployment choices (value >= 0):
  *   "splits_score" | "splits_dense" | "splits_sparse"   ranges per stream; 0 = automatic
- *   "score_resident" | "focal_fused"   0 = always the separate kernels; 1 = chosen by the library
+ *   "score_resident" | "focal_fused"   0 = always the separate kernels (score_resident 0 at head_dim 64: in
+ *       the focal layer's call too); 1 = chosen by the library
  *       (default: the single-kernel form whenever the shape fits, the stream has an exchange slot
  *       and no wave of such a form has ever given up waiting in this process); 2 = the
  *       single-kernel form whenever the shape fits and the stream has a slot

@@ -622,7 +622,10 @@ static int focal_attn_score_impl(const fastocr_kv_view *kv, const fastocr_batch_
     ResidentPlan rp;
     int slot = -1;
     uint32_t *flag = nullptr;
-    if (use_resident(EX_FUSED, g_tune_focal_fused.load(std::memory_order_relaxed), s, &rp, kFusedMinTiles, (hipStream_t)hip_stream, &slot, &flag)) {
+    // At head_dim 64 the layer has long been dense attention and then scoring: callers who overlap other work and keep its
+    // scoring off the waiting grid ("score_resident" 0) have no such grid in this call either.
+    const bool apart = kv->head_dim == 64 && g_tune_score_resident.load(std::memory_order_relaxed) == 0;
+    if (!apart && use_resident(EX_FUSED, g_tune_focal_fused.load(std::memory_order_relaxed), s, &rp, kFusedMinTiles, (hipStream_t)hip_stream, &slot, &flag)) {
         const bool fuse = select && g_tune_select_fused.load(std::memory_order_relaxed) != 0 && resident_select_fits(s);
         const bool hand_on = defer && deferred && !fuse && !img_mass && topk_takes_combine(bv->max_vis_len, kv->head_dim);
         hipError_t e = launch_focal_fused(s, rp, slot, flag, q, scale, out, scores, lse, img_mass, ws, (hipStream_t)hip_stream,

@@ -71,3 +71,22 @@ def test_one_pass_focal_layer_head_dim_64(Hq, Hkv):
         fb.kernel_timer_enable(fb.KERNEL_FOCAL_FUSED, 0)
         fb.set_tuning("focal_fused", 1)
         fb.set_tuning("score_resident", 1)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_scoring_kept_off_the_waiting_grid_keeps_the_head_dim_64_layer_off_it(d):
+    case = TinyCase(seed=950, B=2, Hq=28, Hkv=4, d=d, n_vis=[900, 2000], pre=[9, 0], post=[3, 100], dtype="bf16")
+    p = problem_from_case(case)
+    want, _ = oracle.decode_attn(*p.oracle_args())
+    ref_sc, _, _ = oracle.focal_score(*p.oracle_args())
+    fb.kernel_timer_enable(fb.KERNEL_FOCAL_FUSED, 8)
+    try:
+        for scoring, launches in ((1, 1), (0, 0 if d == 64 else 1)):
+            fb.set_tuning("score_resident", scoring)
+            out, sc, _, _ = p.focal_attn()
+            assert len(fb.kernel_timer_read(fb.KERNEL_FOCAL_FUSED)) == launches, f"score_resident {scoring}"
+            check_out(out, want, f"score_resident {scoring}")
+            check_scores(sc, ref_sc, p.vis_len, f"score_resident {scoring}")
+    finally:
+        fb.kernel_timer_enable(fb.KERNEL_FOCAL_FUSED, 0)
+        fb.set_tuning("score_resident", 1)
