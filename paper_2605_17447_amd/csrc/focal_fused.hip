@@ -636,7 +636,7 @@ hipError_t launch_focal_fused(const Shape &s, const ResidentPlan &p, int sync_sl
     const MassArgs mass{mass_part, img_mass, 0};          // summed by the launch that merges the output's partials
     // every sequence's partials: workgroups seq_meta[b][0] .. + seq_meta[b][1], wpk of them each
     if (defer) {
-        *defer = CombineArgs{att_o, att_ml, p.nranges * p.wpk, s.kv.head_dim, s.n_q_heads, p.wpk, seq_meta, out, false};
+        *defer = CombineArgs{att_o, att_ml, p.nranges * p.wpk, s.kv.head_dim, s.n_q_heads, p.wpk, seq_meta, out, false, mass};
         return hipGetLastError();
     }
     return launch_attn_combine(s, att_o, att_ml, p.nranges * p.wpk, out, nullptr, stream, seq_meta, p.wpk, mass);

@@ -157,10 +157,11 @@ struct CombineArgs {
     const int32_t *seq_meta;    // null: nsplit partials per (sequence, head), see launch_attn
     void *out;                  // [B, Hq, d]: bf16, or fp32 with out_f32
     bool out_f32;
+    MassArgs mass;              // the image-mass partials to sum on the way (mass.out null: none)
 };
 // defer != nullptr: the merge of the output's partials is not launched; *defer describes it and the
 // caller passes it to launch_topk, whose launch then does both (the top-k and that merge depend on
-// this kernel only, not on each other).  Not together with img_mass, which the merge's own launch sums.
+// this kernel only, not on each other), and sums the image mass.
 hipError_t launch_focal_fused(const Shape &s, const ResidentPlan &p, int sync_slot, uint32_t *gave_up_flag, const void *q, float scale,
                               void *out, float *scores, float *lse, float *img_mass, void *ws, hipStream_t stream,
                               const SelectArgs *select = nullptr, CombineArgs *defer = nullptr);

@@ -449,8 +449,8 @@ hipError_t launch_focal_f32(const Shape &s, const void *q, float scale, void *ou
     e = launch_finalize(s, logits, pitch, part_ml, nsplit, scores, lse, img_mass, mass_part, stream);
     if (e != hipSuccess) return e;
     const MassArgs mass{mass_part, img_mass, fin_blocks(s)};
-    if (defer) {                                       // (no image mass then)
-        *defer = CombineArgs{part_o, part_ml, nsplit, s.kv.head_dim, s.n_q_heads, 1, nullptr, out, true};
+    if (defer) {
+        *defer = CombineArgs{part_o, part_ml, nsplit, s.kv.head_dim, s.n_q_heads, 1, nullptr, out, true, mass};
         return hipSuccess;
     }
     return launch_attn_combine(s, part_o, part_ml, nsplit, out, nullptr, stream, nullptr, 1, mass);

@@ -227,8 +227,9 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(
 
 // The same, with batch * Hq more workgroups behind the selecting ones: each merges the attention
 // partials of one (sequence, query head) of the focal layer whose scores are being selected from.
-// The two kinds of workgroup share nothing but the launch.
-template <typename T, bool VEC, int PER>
+// The two kinds of workgroup share nothing but the launch.  MASS: `batch` workgroups between the two sum the image mass
+// (a template parameter: the argument's load and a branch in front of every merge cost 3 us at 2048 merges).
+template <typename T, bool VEC, int PER, bool MASS>
 __global__ __launch_bounds__(kTopkThreads) void focal_tail_kernel(
     const float *__restrict__ scores, BatchDev bv, double tau, const int32_t *prev_idx,
     const int32_t *prev_cnt, int32_t *sel_idx, int32_t *sel_cnt, int64_t kmax, int batch, CombineArgs c)
@@ -246,8 +247,10 @@ __global__ __launch_bounds__(kTopkThreads) void focal_tail_kernel(
         sh.hist = hist; sh.list = list; sh.pick = s_pick; sh.w_ac = w_ac;
         topk_reg_body<kTopkThreads, PER, false, VEC>(scores, bv, blockIdx.x, tau, prev_idx, prev_cnt, sel_idx, sel_cnt, kmax, sh,
                                               [](int, int) {});
+    } else if (MASS && (int)blockIdx.x < 2 * batch) {
+        image_mass_sum(c.mass, c.seq_meta, (int)blockIdx.x - batch);
     } else {
-        const int x = (int)blockIdx.x - batch;
+        const int x = (int)blockIdx.x - (MASS ? 2 * batch : batch);
         const int b = x / c.n_q_heads, h = x - b * c.n_q_heads;
         combine_wide_body<T>(c.part_o, c.part_ml, c.nsplit, c.d, (T *)c.out, nullptr, c.seq_meta, c.wpk, h, b, c.n_q_heads,
                              CombineShared<T>{sm_max, sm_z, sm_o});
@@ -301,15 +304,17 @@ hipError_t launch_topk(const float *scores, const BatchDev &bv, int batch, doubl
 #define FASTOCR_TOPK_REG(V, P) FASTOCR_LAUNCH(K_TOPK, (topk_reg_kernel<V, P>), dim3(batch), dim3(kTopkThreads), 0, stream, scores, \
                                               bv, tau, prev_idx, prev_cnt, sel_idx, sel_cnt, kmax)
         if (combine) {
-            const dim3 grid(batch + batch * combine->n_q_heads);
-#define FASTOCR_TAIL_T(T, V, P) FASTOCR_LAUNCH(K_TOPK, (focal_tail_kernel<T, V, P>), grid, dim3(kTopkThreads), 0, stream, scores, \
+            const dim3 grid(batch + batch * combine->n_q_heads + (combine->mass.out ? batch : 0));
+#define FASTOCR_TAIL_M(T, V, P, M) FASTOCR_LAUNCH(K_TOPK, (focal_tail_kernel<T, V, P, M>), grid, dim3(kTopkThreads), 0, stream, scores, \
                                           bv, tau, prev_idx, prev_cnt, sel_idx, sel_cnt, kmax, batch, *combine)
+#define FASTOCR_TAIL_T(T, V, P) do { if (combine->mass.out) FASTOCR_TAIL_M(T, V, P, true); else FASTOCR_TAIL_M(T, V, P, false); } while (0)
 #define FASTOCR_TAIL(V, P) do { if (combine->out_f32) FASTOCR_TAIL_T(float, V, P); else FASTOCR_TAIL_T(uint16_t, V, P); } while (0)
             if (bv.max_vis_len <= kTopkThreads * 4) { if (vec) FASTOCR_TAIL(true, 4); else FASTOCR_TAIL(false, 4); }
             else if (bv.max_vis_len <= kTopkThreads * 8) { if (vec) FASTOCR_TAIL(true, 8); else FASTOCR_TAIL(false, 8); }
             else { if (vec) FASTOCR_TAIL(true, kTopkPer); else FASTOCR_TAIL(false, kTopkPer); }
 #undef FASTOCR_TAIL
 #undef FASTOCR_TAIL_T
+#undef FASTOCR_TAIL_M
             return hipGetLastError();
         }
         if (bv.max_vis_len <= kTopkThreads * 4) { if (vec) FASTOCR_TOPK_REG(true, 4); else FASTOCR_TOPK_REG(false, 4); }
