@@ -265,7 +265,8 @@ int fastocr_focal_attn_score(const fastocr_kv_view *kv, const fastocr_batch_view
  * fastocr_focal_attn_score_topk by default: when the layer runs as its one-pass kernel and no image span
  * exceeds 16384 tokens, the merge of the dense output's partials (and the sum of the image mass) is done by
  * extra workgroups of the select's launch (both depend on the one-pass kernel only): two launches instead of
- * three, same bits.  With many sequences and heads and the image mass wanted, the merge keeps a launch of its own.
+ * three, same bits.  With many sequences and heads (more than five merges per compute unit) the merge keeps
+ * a launch of its own.
  */
 int fastocr_focal_score_topk(const fastocr_kv_view *kv, const fastocr_batch_view *bv, const void *q,
                              int n_q_heads, float scale, double tau, const int32_t *prev_idx,

@@ -601,9 +601,9 @@ int fastocr_dense_decode_attn_static(const fastocr_kv_view *kv, const fastocr_ba
 
 // Whether a focal layer's top-k and the merge of its output's partials share a launch.  They do as long as the merges, each
 // a workgroup of that launch's 1024 threads, pass through the chip in two or three rounds; in workgroups of 256 threads
-// and a launch of their own (3 us) they are done sooner beyond that (us per call with image mass, shared / apart, 1024 image tokens:
+// and a launch of their own (3 us) they are done sooner beyond that (us per call, shared / apart, 1024 image tokens:
 // head_dim 128, 896 merges 32.4 / 34.6, 1024 35.2 / 36.0, 1680 43.9 / 42.2, 2048 49.1 / 46.3; head_dim 64, 1024 26.4 / 27.2,
-// 1680 31.9 / 30.3, 2048 35.0 / 32.2).
+// 1680 31.9 / 30.3, 2048 35.0 / 32.2, 6400 77.8 / 60.0).
 static bool merge_shares_topk(const Shape &s)
 {
     return topk_takes_combine(s.bv.max_vis_len, s.kv.head_dim) && (int64_t)s.batch * s.n_q_heads <= 5 * plan_cu_count();
@@ -637,7 +637,7 @@ static int focal_attn_score_impl(const fastocr_kv_view *kv, const fastocr_batch_
     const bool apart = kv->head_dim == 64 && g_tune_score_resident.load(std::memory_order_relaxed) == 0;
     if (!apart && use_resident(EX_FUSED, g_tune_focal_fused.load(std::memory_order_relaxed), s, &rp, kFusedMinTiles, (hipStream_t)hip_stream, &slot, &flag)) {
         const bool fuse = select && g_tune_select_fused.load(std::memory_order_relaxed) != 0 && resident_select_fits(s);
-        const bool hand_on = defer && deferred && !fuse && (img_mass ? merge_shares_topk(s) : topk_takes_combine(bv->max_vis_len, kv->head_dim));
+        const bool hand_on = defer && deferred && !fuse && merge_shares_topk(s);
         hipError_t e = launch_focal_fused(s, rp, slot, flag, q, scale, out, scores, lse, img_mass, ws, (hipStream_t)hip_stream,
                                           fuse ? select : nullptr, hand_on ? defer : nullptr);
         if (fused) *fused = fuse;
@@ -645,7 +645,7 @@ static int focal_attn_score_impl(const fastocr_kv_view *kv, const fastocr_batch_
         return e == hipSuccess ? FASTOCR_OK : FASTOCR_EHIP;
     }
     if (s.fast32 && g_tune_focal_fused.load(std::memory_order_relaxed) != 0) {
-        const bool hand_on = defer && deferred && (img_mass ? merge_shares_topk(s) : topk_takes_combine(bv->max_vis_len, kv->head_dim));
+        const bool hand_on = defer && deferred && merge_shares_topk(s);
         const int nsplit = choose_splits(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len);
         const hipError_t e = launch_focal_f32(s, q, scale, out, scores, lse, img_mass, ws, nsplit, (hipStream_t)hip_stream,
                                               hand_on ? defer : nullptr);

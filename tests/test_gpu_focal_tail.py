@@ -21,6 +21,29 @@ def _layer(p, tau, mass):
     return out, sc, idx, cnt
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64)])
+@pytest.mark.parametrize("B,apart", [(20, 0), (21, 1)])          # 1280 and 1344 merges of 64 heads, 256 compute units
+def test_many_merges_keep_their_own_launch(dtype, d, B, apart):
+    n = [40 + 7 * (b % 9) for b in range(B)]
+    case = TinyCase(seed=700 + d + B, B=B, Hq=64, Hkv=8, d=d, n_vis=n, pre=[b % 5 for b in range(B)], post=[b % 11 for b in range(B)], dtype=dtype)
+    p = problem_from_case(case)
+    tau = 0.1
+    want_out, want_sc, _, want_mass = p.focal_attn(want_mass=True)
+    want_idx, want_cnt = p.topk(want_sc, tau)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    fb.kernel_timer_enable(fb.KERNEL_ATTN_COMBINE, 16)
+    try:
+        for mass in (None, torch.full((B,), -3.0, dtype=torch.float32, device=DEV)):
+            out, sc, idx, cnt = _layer(p, tau, mass)
+            assert len(fb.kernel_timer_read(fb.KERNEL_ATTN_COMBINE)) == (apart if cus == 256 else int(64 * B > 5 * cus))
+            assert torch.equal(out, want_out) and torch.equal(cnt, want_cnt) and (mass is None or torch.equal(mass, want_mass))
+            for b in range(B):
+                assert torch.equal(sc[b, : n[b]], want_sc[b, : n[b]])
+                assert torch.equal(idx[b, : int(cnt[b])], want_idx[b, : int(cnt[b])])
+    finally:
+        fb.kernel_timer_enable(fb.KERNEL_ATTN_COMBINE, 0)
+
+
 @pytest.mark.parametrize("dtype,d,Hq,Hkv,B", [("bf16", 128, 28, 4, 3), ("bf16", 64, 64, 8, 5), ("bf16", 128, 8, 1, 40),
                                               ("f32", 128, 28, 4, 3), ("f32", 64, 4, 1, 7)])
 def test_the_image_mass_is_summed_by_the_shared_launch(dtype, d, Hq, Hkv, B):
