@@ -241,6 +241,24 @@ static int finest_splits(const Shape &s, int max_positions, bool *fits = nullptr
     return n < 1 ? 1 : n;
 }
 
+// Ranges per stream of the fp64 matrix-core kernels: two workgroups of four waves per compute unit, rounded down (see
+// partial_rows).  Where that leaves at most 1.7 workgroups per compute unit, some hold two and the others one, with half
+// the loads in flight; with one query head per kv head, where the kernels are bound by bytes and the plain kernels
+// read no row twice either, a finer cut evens that out (head_dim 128, caches too large for the last-level cache, us: 264 streams
+// of 700 tokens, 1 / 3 ranges, scoring 56.2 / 46.5, dense attention 60.3 / 51.2; 384 of 1700, 124.7 / 104.8, 141.0 / 127.6;
+// 192 of 1700, 2 / 4 ranges, 65.3 / 55.6, 77.9 / 65.6; from 448 streams on one range is as good or better: 131.4 / 126.7, 141.7 / 148.7).
+// A range keeps two blocks of 64 tokens (scoring, which ends in a second launch anyway: one and a half): 384 streams of 280, dense
+// attention 31.0 / 35.4, 264 of them, scoring 33.2 / 30.7.
+static int f32_ranges(int op, const Shape &s, int num_cu, int blocks)
+{
+    const int64_t streams = std::max<int64_t>(1, (int64_t)s.batch * s.kv.n_kv_heads);
+    const int n = (int)std::max<int64_t>(1, 2 * num_cu / streams);
+    const int64_t filled = n * streams;
+    const bool uneven = s.n_q_heads == s.kv.n_kv_heads && filled > num_cu && 10 * filled <= 17 * num_cu;
+    const int finer = n + std::max(2, n);
+    return uneven && 2 * blocks >= (op == FASTOCR_OP_FOCAL_SCORE ? 3 : 4) * finer ? finer : n;
+}
+
 // replay: 0 / 1 = as if "graph_replay" were that, -1 = the tuning's value.  *partials (if given) is set
 // when the choice only holds as partials in the workspace followed by the merge kernel.
 static int choose_splits(int op, const Shape &s, int max_positions, bool *partials = nullptr, int replay = -1)
@@ -296,9 +314,8 @@ static int choose_splits(int op, const Shape &s, int max_positions, bool *partia
                 return n;
             }
         }
-        // fp64 matrix-core kernels: two workgroups of four waves per compute unit (rounded down, see partial_rows)
         if (s.fast32) {
-            nsplit = 2 * kNumCU / (streams > 0 ? streams : 1);
+            nsplit = f32_ranges(op, s, kNumCU, by_work);
             // a list of up to two (head_dim 64: three) tiles per wave is not cut: the one launch then writes the
             // output itself (head_dim 128: 100 tokens 10.1 us uncut, 12.3 cut; 160 tokens 12.8, 12.3; head_dim 64: 160
             // tokens 9.8, 12.5; replayed from a graph 9.8, 9.2; 12.8, 9.4; 8.0, 7.6)
@@ -318,15 +335,22 @@ static int choose_splits(int op, const Shape &s, int max_positions, bool *partia
 
 // Partial rows (sequence, query head, range) to size a workspace for.  For fp32 caches on the matrix cores the most that
 // a call with this many sequences or fewer leaves (a call's own count goes up and down with the batch, by the rounding
-// of its range count): at most 2 CU workgroups, each a row per query head of its group, or one range per sequence. That is
-// at most 8192 rows of 256 CUs and 16 heads, 4.3 MB at head_dim 128, unless the batch itself has more, so every
-// shape whose single ranges fit the static scratch is served from it.
+// of its range count, see f32_ranges): at most 2 CU workgroups with a row per query head of their group, or with one
+// head per group 3.4 CU of them, or three ranges of up to 1.7 CU streams, or one range per sequence.  That is at most 8192
+// rows of 256 CUs and 16 heads, 4.3 MB at head_dim 128, unless the batch itself has more, so every shape whose single
+// ranges fit the static scratch is served from it.
 static size_t partial_rows(int op, const Shape &s, int max_positions, int nsplit)
 {
     const size_t heads = (size_t)s.batch * s.n_q_heads;
     if (!s.fast32 || g_tune_splits[op].load(std::memory_order_relaxed) > 0) return heads * nsplit;
     const size_t by_work = (size_t)std::min(256, std::max(1, (max_positions + 63) / 64));
-    const size_t filled = (size_t)(2 * plan_cu_count() / s.kv.n_kv_heads) * s.n_q_heads;
+    const size_t cus = (size_t)plan_cu_count(), Hkv = (size_t)s.kv.n_kv_heads;
+    size_t filled = 2 * cus / Hkv;                                        // sequences times ranges
+    if ((size_t)s.n_q_heads == Hkv) {
+        filled = 34 * cus / 10 / Hkv;
+        if (s.batch * Hkv > cus) filled = std::max(filled, 3 * std::min((size_t)s.batch, 17 * cus / 10 / Hkv));
+    }
+    filled *= (size_t)s.n_q_heads;
     return std::min(heads * by_work, std::max(heads, filled));
 }
 

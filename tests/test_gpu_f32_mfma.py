@@ -59,6 +59,24 @@ def test_forced_range_counts(nsplit, d):
             fb.set_tuning(key, 0)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,Hq,Hkv,merges", [(24, 8, 8, 1), (32, 8, 8, 1), (33, 8, 8, 1), (54, 8, 8, 1), (55, 8, 8, 0), (33, 16, 8, 0)])
+def test_streams_that_fill_the_chip_unevenly_are_cut(B, Hq, Hkv, merges, d):
+    # up to 256 streams are cut to fill the chip (192 of them in four), 257 to 435 of one query head each in three, more not at all
+    n = [330 + 11 * (b % 7) for b in range(B)]
+    case = TinyCase(seed=90 + B, B=B, Hq=Hq, Hkv=Hkv, d=d, n_vis=n, pre=[b % 5 for b in range(B)], post=[9 + b % 3 for b in range(B)], dtype="f32")
+    p = problem_from_case(case)
+    fb.kernel_timer_enable(fb.KERNEL_ATTN_COMBINE, 8)
+    try:
+        p.dense()
+        got = len(fb.kernel_timer_read(fb.KERNEL_ATTN_COMBINE))
+    finally:
+        fb.kernel_timer_enable(fb.KERNEL_ATTN_COMBINE, 0)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert got == merges
+    full_check(p, 0.5, f"{B * Hkv} streams d={d}")
+
+
 @pytest.mark.parametrize("d,n", [(64, 300), (128, 5000)])
 def test_focal_layer_in_one_call_selects_like_the_separate_calls(d, n):
     case = TinyCase(seed=71, B=3, Hq=28, Hkv=4, d=d, n_vis=[n, n // 3, 0], pre=[5, 0, 4], post=[11, 70, 3], dtype="f32")
