@@ -566,11 +566,11 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     __syncthreads();
     // Where the rest of the kernel starts in a 64-byte instruction line makes up to 1.2 us of difference at a few tiles per wave (it
     // runs once, on all compute units at about the same time, after a stream that leaves little of it in the caches), so its
-    // start is fixed at byte 40, whatever comes before it.  Measured in steps of 8 bytes, 36 to 44 are best in all forms of
-    // the kernel; us with the merge's launch at byte 4 / 20 / 40 / 52: 12/2 heads, batch 8, 3000 image tokens, head_dim 128
-    // 21.2 / 21.1 / 20.4 / 21.2, 64 17.5 / 17.5 / 16.6 / 17.5; 28/4 heads, batch 10, 1392 image tokens 23.1 / 22.6 / 22.2 / 23.0 and
-    // 18.3 / 17.6 / 17.6 / 18.2; 64/8 heads, batch 16, 16384: no difference.
-    asm volatile(".p2align 6\n\t.rept 10\n\ts_nop 0\n\t.endr");
+    // start is fixed at byte 36, whatever comes before it.  Measured in steps of 4 and 8 bytes, 36 to 44 are best in all forms of
+    // the kernel (36 by up to 0.5 us with one sequence); us with the merge's launch at byte 4 / 20 / 36 / 52: 12/2 heads, batch 8, 3000 image tokens, head_dim 128
+    // 21.2 / 21.1 / 20.4 / 21.2, 64 17.5 / 17.5 / 16.5 / 17.5; 28/4 heads, batch 10, 1392 image tokens 23.1 / 22.6 / 22.3 / 23.0 and
+    // 18.3 / 17.6 / 17.3 / 18.2; 64/8 heads, batch 16, 16384: no difference.
+    asm volatile(".p2align 6\n\t.rept 9\n\ts_nop 0\n\t.endr");
     float local = 0.f;
     const float inv = 1.0f / (float)Hq;
     const int rows = D == 128 ? Hkv : 2 * Hkv;
