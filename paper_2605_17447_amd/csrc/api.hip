@@ -316,9 +316,10 @@ static int choose_splits(int op, const Shape &s, int max_positions, bool *partia
         }
         if (s.fast32) {
             nsplit = f32_ranges(op, s, kNumCU, by_work);
-            // a list of up to two (head_dim 64: three) tiles per wave is not cut: the one launch then writes the
-            // output itself (head_dim 128: 100 tokens 10.1 us uncut, 12.3 cut; 160 tokens 12.8, 12.3; head_dim 64: 160
-            // tokens 9.8, 12.5; replayed from a graph 9.8, 9.2; 12.8, 9.4; 8.0, 7.6)
+            // a list of up to two (head_dim 64: three) tiles per wave is not cut: the one launch then writes the output
+            // itself (us uncut / cut, launched one by one and replayed from a graph: head_dim 128, 100 tokens 10.1 / 12.3 and 9.8 /
+            // 9.2, 160 tokens -- three tiles, cut -- 12.8 / 12.3 and 12.8 / 9.4; head_dim 64, 160 tokens 9.8 / 12.5 and 8.0 / 7.6:
+            // a replay would gain half a microsecond from a cut, single launches lose two, so the line is theirs for both)
             if (op != FASTOCR_OP_FOCAL_SCORE && by_work <= (s.kv.head_dim == 64 ? 3 : 2)) nsplit = 1;
         }
         else nsplit = (target_wg + streams - 1) / (streams > 0 ? streams : 1);

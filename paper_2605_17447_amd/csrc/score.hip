@@ -6,10 +6,11 @@
 //   logits   : streams K once.  Per (sequence, kv head, token range) it computes the G query
 //              heads' logits, parks them (fp32, log2 domain) in the workspace and reduces a
 //              per-range (max, sum-exp) per head.
-//   finalize : merges the per-range statistics into each head's log-sum-exp and writes
-//              score_i = (1/Hq) sum_h 2^(logit_h,i - lse_h) for the image tokens.
+//   finalize : merges the per-range statistics into each head's maximum M and sum Z and writes
+//              score_i = (1/Hq) sum_h 2^(logit_h,i - M_h) / Z_h for the image tokens.
 // The K stream uses the same MFMA tiling as the attention kernel (tokens x heads tiles of
-// v_mfma_f32_16x16x32_bf16) for bf16 / head_dim 128, and a plain fp32 kernel otherwise.
+// v_mfma_f32_16x16x32_bf16) for bf16 caches of head_dim 128 and 64, the fp64 matrix-core kernel of attn_f32.hip for
+// fp32 caches of these, and a plain kernel otherwise.
 #include "kernels.hpp"
 
 namespace fastocr {

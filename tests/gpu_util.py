@@ -116,6 +116,22 @@ def problem_from_case(case, layout="bhsd") -> GpuProblem:
     return GpuProblem(k, v, q, case.seq_len, case.vis_start, case.vis_len, case.scale, layout)
 
 
+def paged_twin(p: GpuProblem, page: int, seed: int) -> GpuProblem:
+    """A contiguous head-major problem with its rows scattered over shuffled pages of `page` tokens."""
+    B, H, S, d = p.k.shape
+    per = -(-S // page)
+    order = torch.from_numpy(np.random.default_rng(seed).permutation(B * per).astype(np.int32))
+    table = order.reshape(B, per).contiguous()
+    pools = []
+    for t in (p.k, p.v):
+        full = torch.zeros((B, H, per * page, d), dtype=t.dtype, device=t.device)
+        full[:, :, :S] = t
+        pool = torch.empty((B * per, H, page, d), dtype=t.dtype, device=t.device)
+        pool[table.reshape(-1).long().to(t.device)] = full.reshape(B, H, per, page, d).transpose(1, 2).reshape(B * per, H, page, d)
+        pools.append(pool)
+    return GpuProblem(pools[0], pools[1], p.q, p.seq_len, p.vis_start, p.vis_len, p.scale, block_table=table.to(DEV))
+
+
 def row_rel_err(out: torch.Tensor, ref: np.ndarray) -> float:
     o = out.detach().float().cpu().numpy().astype(np.float64)
     num = np.abs(o - ref).max(axis=-1)

@@ -11,7 +11,7 @@ from util import TinyCase
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
-    from gpu_util import DEV, GpuProblem, check_out, problem_from_case
+    from gpu_util import DEV, check_out, paged_twin, problem_from_case
 
 
 @pytest.mark.parametrize("d", [128, 64])
@@ -24,17 +24,7 @@ def test_tiles_per_wave(tiles, d):
     for layout, paged in (("bhsd", False), ("bshd", False), ("bhsd", True)):
         p = problem_from_case(case, layout)
         if paged:
-            B, H, S, _ = p.k.shape
-            per = -(-S // 16)
-            table = torch.randperm(B * per, generator=torch.Generator().manual_seed(tiles)).int().reshape(B, per).to(DEV)
-            pools = []
-            for t in (p.k, p.v):
-                full = torch.zeros((B, H, per * 16, d), dtype=t.dtype, device=DEV)
-                full[:, :, :S] = t
-                pool = torch.empty((B * per, H, 16, d), dtype=t.dtype, device=DEV)
-                pool[table.reshape(-1).long()] = full.reshape(B, H, per, 16, d).transpose(1, 2).reshape(B * per, H, 16, d)
-                pools.append(pool)
-            p = GpuProblem(pools[0], pools[1], p.q, p.seq_len, p.vis_start, p.vis_len, p.scale, block_table=table)
+            p = paged_twin(p, 16, tiles)
         oc = p.oracle_args()
         rng = np.random.default_rng(tiles)
         kmax = max(p.vis_len)

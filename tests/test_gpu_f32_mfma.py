@@ -12,24 +12,8 @@ from util import TinyCase
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
-    from gpu_util import DEV, GpuProblem, check_out, check_scores, problem_from_case, row_rel_err, to_np
+    from gpu_util import DEV, GpuProblem, check_out, check_scores, paged_twin, problem_from_case, row_rel_err, to_np
     from test_gpu_parity import full_check
-
-
-def _paged(p, page, seed):
-    """The same problem with its rows scattered over shuffled pages."""
-    B, H, S, d = p.k.shape
-    per = -(-S // page)
-    order = torch.from_numpy(np.random.default_rng(seed).permutation(B * per).astype(np.int32))
-    table = order.reshape(B, per).contiguous()
-    pools = []
-    for t in (p.k, p.v):
-        full = torch.zeros((B, H, per * page, d), dtype=t.dtype, device=t.device)
-        full[:, :, :S] = t
-        pool = torch.empty((B * per, H, page, d), dtype=t.dtype, device=t.device)
-        pool[table.reshape(-1).long().to(t.device)] = full.reshape(B, H, per, page, d).transpose(1, 2).reshape(B * per, H, page, d)
-        pools.append(pool)
-    return GpuProblem(pools[0], pools[1], p.q, p.seq_len, p.vis_start, p.vis_len, p.scale, block_table=table.to(DEV))
 
 
 @pytest.mark.parametrize("d", [64, 128])
@@ -41,8 +25,8 @@ def test_every_call_on_ragged_batches(Hq, Hkv, d):
     for tau in (0.05, 1.0):
         full_check(problem_from_case(case, "bhsd"), tau, f"f32 {Hq}/{Hkv} d={d} tau={tau}")
     full_check(problem_from_case(case, "bshd"), 0.05, "token-major")
-    full_check(_paged(problem_from_case(case), 16, 3), 0.05, "paged, 16-token pages")
-    full_check(_paged(problem_from_case(case), 24, 4), 0.05, "paged, pages that are no multiple of a tile")
+    full_check(paged_twin(problem_from_case(case), 16, 3), 0.05, "paged, 16-token pages")
+    full_check(paged_twin(problem_from_case(case), 24, 4), 0.05, "paged, pages that are no multiple of a tile")
 
 
 @pytest.mark.parametrize("d", [64, 128])
@@ -85,8 +69,12 @@ def test_focal_layer_in_one_call_selects_like_the_separate_calls(d, n):
     dense, _ = oracle.decode_attn(*p.oracle_args())
     tau = 0.05
     kmax = fo.keep_count(p.batch.max_vis_len, tau)
+    timers = (fb.KERNEL_FOCAL_FUSED, fb.KERNEL_DENSE_ATTN, fb.KERNEL_SCORE_LOGITS)
+    results = []
     for mode in (1, 0):                                    # one pass; the separate calls
         fb.set_tuning("focal_fused", mode)
+        for k in timers:
+            fb.kernel_timer_enable(k, 8)
         try:
             out = torch.full_like(p.q, 3.0)
             sc = torch.zeros((p.B, p.batch.max_vis_len), dtype=torch.float32, device=DEV)
@@ -96,8 +84,13 @@ def test_focal_layer_in_one_call_selects_like_the_separate_calls(d, n):
             fo.focal_attn_score_topk(p.cache, p.batch, p.q, p.scale, tau, out, sc, idx, cnt,
                                      p.ws(fb.OP_FOCAL_ATTN_SCORE_TOPK, kmax), img_mass=mass)
             torch.cuda.synchronize()
+            launches = tuple(len(fb.kernel_timer_read(k)) for k in timers)
         finally:
             fb.set_tuning("focal_fused", 1)
+            for k in timers:
+                fb.kernel_timer_enable(k, 0)
+        assert launches == ((1, 0, 0) if mode else (0, 1, 1))
+        results.append((to_np(sc), idx.cpu().numpy()))
         check_out(out, dense, f"mode {mode}")
         check_scores(sc, ref, p.vis_len, f"mode {mode}")
         assert np.abs(mass.cpu().numpy() - ref_mass).max() <= 1e-5
@@ -106,6 +99,17 @@ def test_focal_layer_in_one_call_selects_like_the_separate_calls(d, n):
             assert int(cnt[b]) == k
             want = oracle.topk(to_np(sc)[b, : p.vis_len[b]], k) if k else np.zeros(0, np.int32)
             assert np.array_equal(idx[b, :k].cpu().numpy(), want)
+    # The logits are the same bits; the two forms cut the list into other ranges, so a head's sum differs by the roundings of
+    # at most 42 partials merged in fp32 (a chain of up to 9 merges of 3 roundings, 2^-24 each): 1.6e-6 of a score.
+    (one, one_idx), (apart, apart_idx) = results
+    for b in range(p.B):
+        m, k = p.vis_len[b], fo.keep_count(p.vis_len[b], tau)
+        if k == 0:
+            continue
+        assert (np.abs(one[b, :m] - apart[b, :m]) <= 2e-6 * apart[b, :m]).all()
+        last = apart[b, apart_idx[b, :k]].min()
+        moved = np.setxor1d(one_idx[b, :k], apart_idx[b, :k])
+        assert (np.abs(apart[b, moved] - last) <= 4e-6 * last).all(), "the sets differ by more than ties at the threshold"
 
 
 def test_rows_that_are_not_16_byte_aligned_take_the_plain_kernels():

@@ -38,11 +38,15 @@ def test_static_scratch_entry_point_matches_the_workspace_one():
     big = TinyCase(seed=71, B=4, Hq=28, Hkv=4, d=128, n_vis=[3000, 1777, 2500, 64], pre=[32, 5, 0, 3],
                    post=[41, 130, 7, 0], dtype="bf16")
     small = TinyCase(seed=72, B=2, Hq=28, Hkv=4, d=128, n_vis=[500, 300], pre=[3, 9], post=[20, 1], dtype="bf16")
-    plain = TinyCase(seed=73, B=2, Hq=4, Hkv=2, d=64, n_vis=[150, 99], pre=[8, 3], post=[5, 7], dtype="f32")
+    f32 = TinyCase(seed=73, B=2, Hq=4, Hkv=2, d=64, n_vis=[150, 99], pre=[8, 3], post=[5, 7], dtype="f32")
+    cut = TinyCase(seed=74, B=2, Hq=4, Hkv=2, d=64, n_vis=[700, 420], pre=[8, 3], post=[5, 7], dtype="f32")
+    plain = TinyCase(seed=75, B=2, Hq=4, Hkv=2, d=96, n_vis=[350, 199], pre=[8, 3], post=[5, 7], dtype="f32")
     _both(problem_from_case(big), "first call")
     _both(problem_from_case(small), "second call, smaller input")
-    _both(problem_from_case(plain), "third call, fp32 plain-FMA kernels")
-    _both(problem_from_case(big), "fourth call, the large input again")
+    _both(problem_from_case(f32), "third call, fp32 on the matrix cores, a list that is not cut")
+    _both(problem_from_case(cut), "fourth call, fp32 on the matrix cores, ranges and their merge")
+    _both(problem_from_case(plain), "fifth call, fp32 plain-FMA kernels (head_dim 96) and their merge")
+    _both(problem_from_case(big), "sixth call, the large input again")
 
 
 def test_static_scratch_entry_point_refuses_what_does_not_fit():
