@@ -279,7 +279,7 @@ static int choose_splits(int op, const Shape &s, int max_positions, bool *partia
         const int streams = s.batch * (fast || s.fast32 ? s.kv.n_kv_heads : s.n_q_heads);
         // Measured on MI355X: the streaming kernels run best with about one workgroup per compute
         // unit (few, long, equally sized streams), the plain-FMA kernels with many small ones.
-        const int target_wg = fast ? kNumCU : 8 * kNumCU;
+        const int target_wg = 8 * kNumCU;
         if (fast && op == FASTOCR_OP_SPARSE_DECODE_ATTN && g_tune_attn_merge.load(std::memory_order_relaxed)) {
             // pruned attention is short: one launch whose eight-wave workgroups fill the chip once,
             // the ranges of a stream merged inside the launch.  Up to 14 tiles one workgroup has the whole list
@@ -322,6 +322,12 @@ static int choose_splits(int op, const Shape &s, int max_positions, bool *partia
             // a replay would gain half a microsecond from a cut, single launches lose two, so the line is theirs for both)
             if (op != FASTOCR_OP_FOCAL_SCORE && by_work <= (s.kv.head_dim == 64 ? 3 : 2)) nsplit = 1;
         }
+        // Dense attention of bf16 caches: rounded down, so that no compute unit holds two workgroups while others hold one (192 of
+        // 256 compute units already draw what the memory delivers; us with the range count rounded up / down, merge included:
+        // 28/4 heads, 12 x 1024 image tokens 12.5 / 11.0, 12 x 4096 26.3 / 21.6, 12 x 16384 81.6 / 64.7; 16/2 heads, 12 x 4096 17.5 / 14.4,
+        // 12 x 16384 47.1 / 35.4; head_dim 64, 32/8 heads, 12 x 4096 28.9 / 22.1; 64/8, 11 x 2048 27.2 / 21.5, where five ranges, 440
+        // workgroups, take 21.6).
+        else if (fast) nsplit = kNumCU / (streams > 0 ? streams : 1);
         else nsplit = (target_wg + streams - 1) / (streams > 0 ? streams : 1);
         // pruned attention is short: when eight waves get at most eight tiles each, or at least half
         // a chip of streams exists, one eight-wave workgroup per stream writes the final output

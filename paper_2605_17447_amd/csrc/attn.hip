@@ -149,10 +149,11 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
         pend = by_token ? u1 : min(L, u1 * kTile);
         nt = (pend - wp0 + kTile - 1) / kTile;
     } else {
+        // ranges of equal length to within one tile
         const int ntile = (L + kTile - 1) / kTile;
-        const int tps = (ntile + nsplit - 1) / nsplit;
-        const int t1 = min(ntile, split * tps + tps);
-        tfirst = split * tps + wave;
+        const int x = ntile / nsplit, rem = ntile - x * nsplit;
+        const int t1 = split * x + min(split, rem) + x + (split < rem ? 1 : 0);
+        tfirst = split * x + min(split, rem) + wave;
         nt = tfirst < t1 ? (t1 - 1 - tfirst) / kWaves + 1 : 0;
     }
     auto tile_pos = [&](int i) { return GATHER ? wp0 + i * kTile : (tfirst + i * kWaves) * kTile; };
