@@ -142,7 +142,9 @@ size_t fastocr_workspace_bytes(int op, const fastocr_kv_view *kv, const fastocr_
  * caches.  Every other shape (other head dimensions up to 256, larger groups, unaligned rows) runs on
  * plain-FMA kernels that accumulate in fp64, to the same error bars.
  * Concurrency: when the shape fits (bf16, head_dim 128 or 64, 1/2/4/8 kv heads with at most 8 query heads
- * each, batch <= 256 and <= the compute-unit count) this call and fastocr_focal_attn_score run as ONE kernel whose
+ * each, batch <= 256 and <= the compute-unit count) and is large (logits, batch x query heads x max_seq_len x 4 bytes, of more than 7 MiB;
+ * 9 MiB for a focal layer -- below that two launches that park the logits in the workspace are faster and
+ * wait for nothing) this call and fastocr_focal_attn_score run as ONE kernel whose
  * workgroups -- at most one per compute unit -- wait for each other's softmax statistics, so
  * all of them must be on the chip together.  Launched alone on the GPU (any number of calls in
  * order on one stream, HIP graphs included) that always holds.  If other kernels occupy compute
@@ -236,8 +238,9 @@ int fastocr_dense_decode_attn_static(const fastocr_kv_view *kv, const fastocr_ba
  * fastocr_focal_score for the same q, computed from a single pass over K and V where the
  * shape allows it: bf16, head_dim 128 or 64, group size <= 8, 1/2/4/8 KV heads, batch <= compute
  * units, at most 32 tiles of 32 image tokens per wave (one kernel that waits for itself, see
- * Concurrency above); fp32, head_dim 128 or 64, group size <= 16, 16-byte aligned rows (attention
- * partials and parked logits from one kernel, scores from a second, nothing waits).  Other shapes, and
+ * Concurrency above); bf16 of smaller sizes or other head counts, and fp32, head_dim 128 or 64, group size <= 16,
+ * 16-byte aligned rows (attention partials and parked logits from one kernel, scores and for bf16 the output's
+ * merge and the image mass from a second, nothing waits).  Other shapes, and
  * all of them with fastocr_set_tuning("focal_fused", 0), run the two separate calls' kernels one after the
  * other on the same stream, with identical results up to rounding order.
  * Arguments as in those two calls; out and scores are both required, lse and img_mass optional.
@@ -256,8 +259,8 @@ int fastocr_focal_attn_score(const fastocr_kv_view *kv, const fastocr_batch_view
  * buffer); prev_idx / sel_idx may alias.
  * Workspace: fastocr_workspace_bytes(FASTOCR_OP_FOCAL_SCORE_TOPK | FASTOCR_OP_FOCAL_ATTN_SCORE_TOPK, ..., kmax).
  * By default the two steps run as two launches one after the other on the stream.  With
- * fastocr_set_tuning("select_fused", 1), when scoring runs as its single register-resident kernel
- * and no image span exceeds 16384 tokens, the select runs INSIDE that launch: every range stores
+ * fastocr_set_tuning("select_fused", 1), when scoring runs as its single register-resident kernel or parks its
+ * logits by the size rule, and no image span exceeds 16384 tokens, the select runs INSIDE the launch that finishes the scores: every range stores
  * its scores at agent scope and counts itself out, and the sequence's last range to finish selects
  * over the whole sequence -- no second launch, nobody waits.  That form is measured slower on
  * MI355X (the select then runs on 8 waves instead of 16 and ends the launch alone), so it is not
@@ -316,7 +319,9 @@ typedef enum {
     FASTOCR_KERNEL_DENSE_ATTN = 4,
     FASTOCR_KERNEL_ATTN_COMBINE = 5,
     FASTOCR_KERNEL_FOCAL_FUSED = 6,    /* one pass over K and V: attention partials + scores */
-    FASTOCR_KERNEL_COUNT = 7
+    FASTOCR_KERNEL_PARKED_FINISH = 7,  /* scores from parked logits, where the library parks them by its size rule
+                                          (SCORE_FINALIZE: where it does because a single-kernel form is not to be had) */
+    FASTOCR_KERNEL_COUNT = 8
 } fastocr_kernel;
 
 int fastocr_kernel_timer_enable(int kernel, int capacity);
@@ -335,7 +340,7 @@ int fastocr_stream_probe(const void *src, void *dst, size_t bytes, void *sink, v
  *   "splits_score" | "splits_dense" | "splits_sparse"   ranges per stream; 0 = automatic
  *   "score_resident" | "focal_fused"   0 = always the separate kernels (score_resident 0 at head_dim 64: in
  *       the focal layer's call too); 1 = chosen by the library
- *       (default: the single-kernel form whenever the shape fits, the stream has an exchange slot
+ *       (default: by size, see fastocr_focal_score; the single-kernel form only if the stream has an exchange slot
  *       and no wave of such a form has ever given up waiting in this process); 2 = the
  *       single-kernel form whenever the shape fits and the stream has a slot
  *   "attn_waves"      4 | 8: waves per workgroup of attention launches that leave partials

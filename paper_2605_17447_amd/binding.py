@@ -23,7 +23,7 @@ F32, BF16 = 0, 1
 OP_FOCAL_SCORE, OP_TOPK_FIXATION, OP_SPARSE_DECODE_ATTN, OP_DENSE_DECODE_ATTN, OP_FOCAL_ATTN_SCORE = 0, 1, 2, 3, 4
 OP_FOCAL_SCORE_TOPK, OP_FOCAL_ATTN_SCORE_TOPK = 5, 6
 (KERNEL_SCORE_LOGITS, KERNEL_SCORE_FINALIZE, KERNEL_TOPK, KERNEL_SPARSE_ATTN, KERNEL_DENSE_ATTN,
- KERNEL_ATTN_COMBINE, KERNEL_FOCAL_FUSED) = range(7)
+ KERNEL_ATTN_COMBINE, KERNEL_FOCAL_FUSED, KERNEL_PARKED_FINISH) = range(8)
 
 EXPORTS = (
     "fastocr_keep_count", "fastocr_workspace_bytes", "fastocr_focal_score", "fastocr_topk_fixation",

@@ -327,7 +327,10 @@ static int choose_splits(int op, const Shape &s, int max_positions, bool *partia
         // 28/4 heads, 12 x 1024 image tokens 12.5 / 11.0, 12 x 4096 26.3 / 21.6, 12 x 16384 81.6 / 64.7; 16/2 heads, 12 x 4096 17.5 / 14.4,
         // 12 x 16384 47.1 / 35.4; head_dim 64, 32/8 heads, 12 x 4096 28.9 / 22.1; 64/8, 11 x 2048 27.2 / 21.5, where five ranges, 440
         // workgroups, take 21.6).
-        else if (fast) nsplit = kNumCU / (streams > 0 ? streams : 1);
+        // Scoring holds half the loads per workgroup (no V): two workgroups per compute unit where a stream gets only a few ranges
+        // (one / two per compute unit: head_dim 64, 96 streams of 4288 tokens 19.1 / 16.3, 144 of 1216 12.4 / 10.4; head_dim 128, 144 of 1192
+        // 16.0 / 14.6, 16 of 4288 9.3 / 9.6).
+        else if (fast) nsplit = (op == FASTOCR_OP_FOCAL_SCORE && 4 * streams > kNumCU ? 2 * kNumCU : kNumCU) / (streams > 0 ? streams : 1);
         else nsplit = (target_wg + streams - 1) / (streams > 0 ? streams : 1);
         // pruned attention is short: when eight waves get at most eight tiles each, or at least half
         // a chip of streams exists, one eight-wave workgroup per stream writes the final output
@@ -414,6 +417,14 @@ size_t fastocr_workspace_bytes(int op, const fastocr_kv_view *kv, const fastocr_
             const size_t one = round256(focal_f32_workspace_bytes(s, rows) + 256);
             need = need > one ? need : one;
         }
+        if (parks_by_head(s)) {
+            // the two-launch form, at the most rows of any batch up to this one (ranges fill the chip at most once)
+            const size_t streams = (size_t)s.batch * s.kv.n_kv_heads, G = s.n_q_heads / s.kv.n_kv_heads;
+            const size_t by_work = (size_t)std::min(256, std::max(1, (bv->max_seq_len + 127) / 128));
+            size_t rows = G * std::min(streams * by_work, std::max(streams, (size_t)plan_cu_count()));
+            rows = std::max(rows, G * streams * (size_t)choose_splits(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len));
+            need = std::max(need, round256(focal_parked_workspace_bytes(s, rows) + 256));
+        }
         const size_t fused = focal_fused_workspace_bytes(s, plan_cu_count());
         return fused > 0 ? std::max(need, round256(fused + 256)) : need;
     }
@@ -451,28 +462,40 @@ static int check_qo(const fastocr_kv_view *kv, const void *q, const void *out, f
     return FASTOCR_OK;
 }
 
-// The register-resident kernels (scoring alone, or fused with the dense output) pay a few
-// microseconds for their grid-wide exchange (statistics through memory, polled); the paths built
-// from separate kernels pay a second read of K or a round trip of the logits through memory, and
-// one or two more launches.  Measured on MI355X down to one image tile per wave (batch 1, N = 4096)
-// the single-kernel forms are never slower: scoring 13 us against 5 + 6 us in two launches, the
-// focal layer 16 + 5 us against 6 + 4 + 11 us, at batch 8 25 + 4 against 16 + 4 + 18 us.  So the
-// size rule (mode 1) takes them whenever the shape fits, like mode 2; mode 0 = never.  The
-// thresholds stay as the place to change that.
-constexpr int kResidentMinTiles = 1;
-constexpr int kFusedMinTiles = 1;
+// The register-resident kernels (scoring alone, or fused with the dense output) read K and V and write scores, but their
+// workgroups exchange statistics across the grid and finish in a chain of steps that nothing hides: 9 - 20 us whatever the size,
+// and more in a ragged batch, whose ranges every wave works out for itself.  Kernels that park the logits in memory
+// for a second launch have no such chain and pay for the logits' bytes, written into a read stream and read back.  So the library
+// parks up to this many bytes of logits (batch x query heads x longest sequence x 4; us, register-resident / parked; caches too
+// large for the last-level cache where there is room):
+//   scoring            28/4 heads: batch 1, 4096 image tokens 11.9 / 8.7, 4 x 4096 15.6 / 9.3, 12 x 4096 (5.8 MB) 17.7 / 15.7, 8 x 8192 (7.5) 19.9 / 19.9,
+//                      12 x 8192 (11.3) 24.4 / 27.2; 64/8 heads 12 x 2048 (6.9) 18.0 / 17.0, 8 x 4096 (8.8) 20.3 / 21.0
+//   layer and top-k    28/4: 1 x 4096 21.5 / 14.8, 12 x 4096 34.5 / 31.3, 8 x 8192 40.2 / 39.2, 12 x 8192 50.0 / 52.1; 64/8: 16 x 2048 (9.2) 43.5 / 42.2;
+//                      12/2: 24 x 8192 (9.7) 50.1 / 51.3
+//   layer alone        28/4: 1 x 4096 21.0 / 9.8, 12 x 4096 33.5 / 25.5, 12 x 8192 47.4 / 45.0, 16 x 8192 (15.0) 59.5 / 59.3;
+//                      64/8: 12 x 4096 (13.2) 48.6 / 49.4; head_dim 64, 64/8: 12 x 4096 32.2 / 32.7
+//   ragged and paged   28/4, 12 sequences of up to 5000: scoring 25.4 / 16.7, layer and top-k 42.4 / 32.0 (the host does not know
+//                      the lengths, only the longest: the same lines)
+constexpr int64_t kParkScore = 7 << 20, kParkLayer = 9 << 20;        // (a layer with and without its top-k: the same form, the same bits)
+
+static bool select_inside() { return g_tune_select_fused.load(std::memory_order_relaxed) != 0; }
+
+static bool parks(int mode, const Shape &s, int64_t limit)
+{
+    return mode == 1 && exchange_trusted() && parks_by_head(s) &&
+           (int64_t)s.batch * s.n_q_heads * s.bv.max_seq_len * (int64_t)sizeof(float) <= limit;
+}
 
 // mode: the tuning value (0 never, 1 the library's choice, 2 whenever the shape fits).  The
 // library's own choice also requires that no wave of a single-launch form has ever given up
 // waiting in this process: a launch that cannot have the chip to itself is not tried twice.
 // On success *slot is the call's exchange slot.
-static bool use_resident(int kind, int mode, const Shape &s, ResidentPlan *rp, int min_tiles, hipStream_t stream, int *slot,
-                         uint32_t **flag)
+static bool use_resident(int kind, int mode, const Shape &s, ResidentPlan *rp, hipStream_t stream, int *slot, uint32_t **flag)
 {
     const int cus = plan_cu_count();
     if (mode == 0 || !resident_plan(s, cus, rp)) return false;
     if (rp->nranges * s.batch > cus) return false;
-    if (mode != 2 && (rp->range_tokens / (32 * rp->wpk) < min_tiles || !exchange_trusted())) return false;
+    if (mode != 2 && !exchange_trusted()) return false;
     *slot = exchange_slot(kind, stream, flag);
     return *slot >= 0;
 }
@@ -514,12 +537,17 @@ static int focal_score_impl(const fastocr_kv_view *kv, const fastocr_batch_view 
     hipError_t e;
     int slot = -1;
     uint32_t *flag = nullptr;
-    if (use_resident(EX_SCORE, g_tune_score_resident.load(std::memory_order_relaxed), s, &rp, kResidentMinTiles, (hipStream_t)hip_stream, &slot, &flag)) {
-        const bool fuse = select && g_tune_select_fused.load(std::memory_order_relaxed) != 0 && resident_select_fits(s);
+    const int mode = g_tune_score_resident.load(std::memory_order_relaxed);
+    const bool fuse = select && select_inside() && resident_select_fits(s);
+    const bool park = parks(mode, s, kParkScore);
+    if (!park && use_resident(EX_SCORE, mode, s, &rp, (hipStream_t)hip_stream, &slot, &flag)) {
         e = launch_score_resident(s, rp, slot, flag, q, scale, scores, lse, img_mass, ws, (hipStream_t)hip_stream, fuse ? select : nullptr);
         if (fused) *fused = fuse;
     } else {
-        e = launch_score(s, q, scale, scores, lse, img_mass, ws, nsplit, (hipStream_t)hip_stream);
+        const bool selects = park && fuse;
+        e = launch_score(s, q, scale, scores, lse, img_mass, ws, nsplit, (hipStream_t)hip_stream,
+                         park ? K_PARKED_FINISH : K_SCORE_FINALIZE, selects ? select : nullptr);
+        if (fused) *fused = selects;
     }
     return e == hipSuccess ? FASTOCR_OK : FASTOCR_EHIP;
 }
@@ -666,8 +694,9 @@ static int focal_attn_score_impl(const fastocr_kv_view *kv, const fastocr_batch_
     // At head_dim 64 the layer has long been dense attention and then scoring: callers who overlap other work and keep its
     // scoring off the waiting grid ("score_resident" 0) have no such grid in this call either.
     const bool apart = kv->head_dim == 64 && g_tune_score_resident.load(std::memory_order_relaxed) == 0;
-    if (!apart && use_resident(EX_FUSED, g_tune_focal_fused.load(std::memory_order_relaxed), s, &rp, kFusedMinTiles, (hipStream_t)hip_stream, &slot, &flag)) {
-        const bool fuse = select && g_tune_select_fused.load(std::memory_order_relaxed) != 0 && resident_select_fits(s);
+    const int mode = g_tune_focal_fused.load(std::memory_order_relaxed);
+    const bool fuse = select && select_inside() && resident_select_fits(s);
+    if (!apart && !parks(mode, s, kParkLayer) && use_resident(EX_FUSED, mode, s, &rp, (hipStream_t)hip_stream, &slot, &flag)) {
         const bool hand_on = defer && deferred && !fuse && merge_shares_topk(s);
         hipError_t e = launch_focal_fused(s, rp, slot, flag, q, scale, out, scores, lse, img_mass, ws, (hipStream_t)hip_stream,
                                           fuse ? select : nullptr, hand_on ? defer : nullptr);
@@ -675,7 +704,16 @@ static int focal_attn_score_impl(const fastocr_kv_view *kv, const fastocr_batch_
         if (hand_on) *deferred = true;
         return e == hipSuccess ? FASTOCR_OK : FASTOCR_EHIP;
     }
-    if (s.fast32 && g_tune_focal_fused.load(std::memory_order_relaxed) != 0) {
+    if (parks_by_head(s) && !apart && mode != 0) {
+        const bool hand_on = defer && deferred && !fuse && merge_shares_topk(s);
+        const int nsplit = choose_splits(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len);
+        const hipError_t e = launch_focal_parked(s, q, scale, out, scores, lse, img_mass, ws, nsplit, (hipStream_t)hip_stream,
+                                                 fuse ? select : nullptr, hand_on ? defer : nullptr);
+        if (fused) *fused = fuse;
+        if (hand_on) *deferred = true;
+        return e == hipSuccess ? FASTOCR_OK : FASTOCR_EHIP;
+    }
+    if (s.fast32 && mode != 0) {
         const bool hand_on = defer && deferred && merge_shares_topk(s);
         const int nsplit = choose_splits(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len);
         const hipError_t e = launch_focal_f32(s, q, scale, out, scores, lse, img_mass, ws, nsplit, (hipStream_t)hip_stream,

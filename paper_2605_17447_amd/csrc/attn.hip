@@ -43,7 +43,10 @@ namespace fastocr {
 //             still publishes under its own call's tag, which no later call accepts.  A word's place
 //             depends on (stream number, range, element) only -- never on the call's shape -- so
 //             whatever a word still holds was written under an older number of the same counter.
-enum { kPartial = 0, kDirect = 1, kMerge = 2 };
+//   kParked : kPartial, and the logits of the image tokens stay behind in the workspace (fp32, log2 domain, [sequence][query
+//             head][token]): a focal layer's output and what its scores are formed from, from one read of K and V.
+//   kLogits : the logits and the ranges' statistics alone; V is not read (scoring).
+enum { kPartial = 0, kDirect = 1, kMerge = 2, kParked = 3, kLogits = 4 };
 constexpr int kMergeMaxSplits = 4;
 constexpr unsigned long long kTicketUnit = 12;                  // divisible by every range count 2 .. kMergeMaxSplits
 constexpr int kMergeMaxStreams = 128;
@@ -98,10 +101,13 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
     KvDev kv, BatchDev bv, const uint16_t *__restrict__ q, int Hq, int G, float scale_log2,
     const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt, int64_t kmax,
     float *__restrict__ part_o, float *__restrict__ part_ml, int nsplit, uint16_t *__restrict__ out,
-    float *__restrict__ lse, int merge_slot, long long spin_ticks, uint32_t *__restrict__ gave_up_flag)
+    float *__restrict__ lse, int merge_slot, long long spin_ticks, uint32_t *__restrict__ gave_up_flag,
+    float *__restrict__ logits, int64_t pitch, float *__restrict__ part_zi, uint32_t *__restrict__ zero)
 {
+    constexpr bool PARK = MODE == kParked || MODE == kLogits, PV = MODE != kLogits;
+    static_assert(!(GATHER && PARK), "scores are those of the whole cache");
     __shared__ __align__(16) unsigned char smem[kWaves][8192];
-    __shared__ float sm_m[kWaves][16], sm_z[kWaves][16];
+    __shared__ float sm_m[kWaves][16], sm_z[kWaves][16], sm_zi[PARK ? kWaves : 1][16];
     __shared__ uint32_t sm_tag;
 
     static_assert(D == 128 || D == 64, "head_dim 128 or 64");
@@ -113,6 +119,7 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
     const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
 
     const int stream_id = b * gridDim.y + kvh;
+    if (PARK && zero && split == 0 && kvh == 0 && threadIdx.x == 0) zero[b] = 0u;
     // this workgroup's ticket (see kMerge above), requested before anything else; the tag is only
     // needed after the tile loop and is put into LDS once the geometry (requested after it) is there
     unsigned long long ticket = 0;
@@ -200,7 +207,7 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
     const int vh = li >> 3, lc = lane & 7;
     // K first: its products and the exponentials run while V is still arriving
     // (off: what rowoff_of looked up for the pair of tiles that i belongs to, h: which of the two i is)
-    auto load_tile = [&](int i, int64_t off, int h, u32x4(&K)[NL], u32x4(&V)[NL]) {
+    auto load_tile = [&](int i, int64_t off, int h, u32x4(&K)[NL], u32x4(&V)[PV ? NL : 1]) {
         auto row = [&](int r) -> int64_t {
             if (GATHER || PAGED) return __shfl(off, 32 * h + r);
             return seq_base + (int64_t)min(tile_pos(i) + r, L - 1) * kv.stride_token;
@@ -209,25 +216,37 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
             int64_t ro[NL];
 #pragma unroll
             for (int e = 0; e < NL; ++e) { ro[e] = row(tile_row(lg, e)); K[e] = stream_load(kbase + ro[e] + 8 * li); }
+            if constexpr (PV) {
 #pragma unroll
-            for (int e = 0; e < NL; ++e) V[e] = stream_load(vbase + ro[e] + 8 * li);
+                for (int e = 0; e < NL; ++e) V[e] = stream_load(vbase + ro[e] + 8 * li);
+            }
         } else {
             // V: row 16 vh + 4 lg + e (the k-block's tokens); K: rows 8e .. 8e+7, one per 8 lanes
 #pragma unroll
             for (int e = 0; e < NL; ++e) K[e] = stream_load(kbase + row(8 * e + (lane >> 3)) + 8 * lc);
+            if constexpr (PV) {
 #pragma unroll
-            for (int e = 0; e < NL; ++e) V[e] = stream_load(vbase + row(16 * vh + 4 * lg + e) + 8 * lc);
+                for (int e = 0; e < NL; ++e) V[e] = stream_load(vbase + row(16 * vh + 4 * lg + e) + 8 * lc);
+            }
         }
         // nothing of the tile before may be moved in between: it would wait for that tile's rows
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    float m = -INFINITY, zl = 0.f;
-    f32x4 acc[NACC];
+    // (kParked, kLogits: a finite start, so that keys whose logits are all -inf leave weights of 0 behind)
+    float m = PARK ? kMinusHuge : -INFINITY, zl = 0.f, zi = 0.f;        // zi: the image tokens' part of zl
+    f32x4 acc[PV ? NACC : 1];
 #pragma unroll
-    for (int t = 0; t < NACC; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < (PV ? NACC : 1); ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // Parked logits: the group's G rows of `pitch` floats (whole tiles fit: a multiple of two of them) as a buffer, so that lanes
+    // without a head and tiles without image tokens are dropped by the buffer's range check.  In a branch the stores would
+    // leave the compiler without their number, and it would wait for them wherever it waits for the next tile's rows.
+    constexpr uint32_t kNowhere = 0x80000000u;
+    const uint32_t lane_park = 4u * ((uint32_t)li * (uint32_t)pitch + 4u * (uint32_t)lg);
+    const __amdgpu_buffer_rsrc_t lpark = __builtin_amdgcn_make_buffer_rsrc(
+        PARK ? logits + ((int64_t)b * Hq + (int64_t)kvh * G) * pitch : nullptr, 0, PARK ? (int)(4 * G * pitch) : 0, 0x00027000);
 
-    auto compute = [&](int i, u32x4(&K)[NL], u32x4(&V)[NL]) {
+    auto compute = [&](int i, u32x4(&K)[NL], u32x4(&V)[PV ? NL : 1]) {
         u32x4 ka[2 * KS];
         {
             unsigned char *sw = smem[wave];
@@ -268,6 +287,12 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
             s[r] = (pbase + r < pend) ? s0[r] * scale_log2 : -INFINITY;
             s[4 + r] = (pbase + 16 + r < pend) ? s1[r] * scale_log2 : -INFINITY;
         }
+        const bool some_image = PARK && tile_pos(i) < geo.v0 + geo.N && tile_pos(i) + kTile > geo.v0;      // wave-uniform
+        if constexpr (PARK) {
+            const uint32_t at = some_image && li < G ? lane_park + 4u * (uint32_t)tile_pos(i) : kNowhere;
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, (f32x4{s[0], s[1], s[2], s[3]})), lpark, at, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, (f32x4{s[4], s[5], s[6], s[7]})), lpark, at + 64u, 0, 0);
+        }
         float mx = s[0];
 #pragma unroll
         for (int e = 1; e < 8; ++e) mx = fmaxf(mx, s[e]);
@@ -279,6 +304,16 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
         for (int e = 0; e < 8; ++e) { p[e] = fast_exp2(s[e] - m_new); ps += p[e]; }
         zl = zl * alpha + ps;
         m = m_new;
+        if (PARK && part_zi) {
+            float pi = 0.f;
+            if (some_image) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    pi += (uint32_t)(pbase + (e < 4 ? e : 12 + e) - geo.v0) < (uint32_t)geo.N ? p[e] : 0.f;
+            }
+            zi = zi * alpha + pi;
+        }
+        if constexpr (PV) {
         bf16x8 pb;
 #pragma unroll
         for (int e = 0; e < 8; ++e) pb[e] = (__bf16)p[e];
@@ -318,6 +353,7 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
                 acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), pb, acc[t], 0, 0, 0);
             }
         }
+        }
     };
 
     if (nt > 0) {
@@ -328,7 +364,7 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
         // most of the first buffer's -- the tile just requested -- before it asks for the next
         // (32 streams of 8 / 15 / 27 tiles in one range each: 7.8 / 10.1 / 14.3 us, now 7.3 / 8.9 / 13.2; dense attention,
         // batch 4, 9216 tokens, 16/2 heads: 13.9 -> 12.3 us).
-        u32x4 KA[NL], VA[NL], KB[NL], VB[NL];
+        u32x4 KA[NL], VA[PV ? NL : 1], KB[NL], VB[PV ? NL : 1];
         constexpr bool kLookUp = GATHER || PAGED;
         // Row offsets that come from memory (selected indices, block table): each stage of a pair's look-up is sent
         // half a pair or more before it is used and BEFORE the rows of the tiles until then: loads return in
@@ -358,9 +394,35 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
 
     // ---- cross-wave merge through LDS -----------------------------------------------------
     zl = rows_sum(zl);
+    if constexpr (PARK) {
+        zi = rows_sum(zi);
+        if (lg == 0) sm_zi[wave][li] = zi;
+    }
+    // a range's statistics for head hh of the group: (max, sum-exp), and the image tokens' part of the sum
+    auto leave_stats = [&](int hh) {
+        float M = sm_m[0][hh], Z = 0.f, Zi = 0.f;
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) M = fmaxf(M, sm_m[w][hh]);
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const float f = fast_exp2(sm_m[w][hh] - M);
+            Z += f * sm_z[w][hh];
+            Zi += f * sm_zi[PARK ? w : 0][hh];
+        }
+        const int64_t ph = ((int64_t)b * Hq + (int64_t)kvh * G + hh) * nsplit + split;
+        part_ml[ph * 2] = M;
+        part_ml[ph * 2 + 1] = Z;
+        if (part_zi) part_zi[ph] = Zi;
+    };
+    if constexpr (!PV) {
+        if (lg == 0) { sm_m[wave][li] = m; sm_z[wave][li] = zl; }
+        __syncthreads();
+        if ((int)threadIdx.x < G) leave_stats(threadIdx.x);
+        return;
+    }
     float *buf = reinterpret_cast<float *>(smem[wave]);        // [16 heads][D dims], dims permuted per head (join_slot)
 #pragma unroll
-    for (int t = 0; t < NACC; ++t)
+    for (int t = 0; t < (PV ? NACC : 0); ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             // the operand row 4lg + r of block t: dim 8 row + t (D = 128), dim 8 (row & 7) + 2 t + (row >> 3) (D = 64)
@@ -470,6 +532,7 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
         }
         return;
     }
+    if (MODE == kParked && (int)threadIdx.x < G) leave_stats(threadIdx.x);
     for (int idx = threadIdx.x; idx < G * D; idx += 64 * kWaves) {
         const int hh = idx / D, c = idx % D;
         float o, M, Z;
@@ -488,7 +551,7 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
         } else {
             const int64_t ph = bh * nsplit + split;
             part_o[ph * D + c] = o;
-            if (c == 0) { part_ml[ph * 2] = M; part_ml[ph * 2 + 1] = Z; }
+            if (MODE == kPartial && c == 0) { part_ml[ph * 2] = M; part_ml[ph * 2 + 1] = Z; }
         }
     }
 }
@@ -671,7 +734,7 @@ static void launch_mfma(int kid, const Shape &s, const void *q, float scale_log2
     const long long spin_ticks = tune_spin_ticks();
 #define FASTOCR_ATTN(DD, W, MODE) FASTOCR_LAUNCH(kid, (attn_mfma_kernel<DD, GATHER, PAGED, W, MODE>), grid, dim3(64 * W), 0, stream, \
         s.kv, s.bv, (const uint16_t *)q, s.n_q_heads, G, scale_log2, sel_idx, sel_cnt, kmax, part_o, part_ml, nsplit, \
-        (uint16_t *)out, lse, slot, spin_ticks, flag)
+        (uint16_t *)out, lse, slot, spin_ticks, flag, nullptr, 0, nullptr, nullptr)
     if (s.kv.head_dim == 64) {
         if (nsplit == 1) FASTOCR_ATTN(64, 8, kDirect);
         else if (merge) FASTOCR_ATTN(64, 8, kMerge);
@@ -683,6 +746,23 @@ static void launch_mfma(int kid, const Shape &s, const void *q, float scale_log2
     else if (tune_attn_waves() == 8) FASTOCR_ATTN(128, 8, kPartial);
     else FASTOCR_ATTN(128, 4, kPartial);
 #undef FASTOCR_ATTN
+}
+
+hipError_t launch_attn_parked(int kid, const Shape &s, const void *q, float scale, float *part_o, float *part_ml, float *part_zi,
+                              int nsplit, float *logits, int64_t pitch, uint32_t *zero, hipStream_t stream)
+{
+    const int G = s.n_q_heads / s.kv.n_kv_heads;
+    dim3 grid(nsplit, s.kv.n_kv_heads, s.batch);
+    const float scale_log2 = scale * kLog2e;
+#define FASTOCR_PARK(DD, P, MODE) FASTOCR_LAUNCH(kid, (attn_mfma_kernel<DD, false, P, 4, MODE>), grid, dim3(256), 0, stream, \
+        s.kv, s.bv, (const uint16_t *)q, s.n_q_heads, G, scale_log2, nullptr, nullptr, 0, part_o, part_ml, nsplit, \
+        nullptr, nullptr, 0, 0, nullptr, logits, pitch, part_zi, zero)
+#define FASTOCR_PARK_D(DD, P) do { if (part_o) FASTOCR_PARK(DD, P, kParked); else FASTOCR_PARK(DD, P, kLogits); } while (0)
+    if (s.kv.head_dim == 64) { if (s.paged) FASTOCR_PARK_D(64, true); else FASTOCR_PARK_D(64, false); }
+    else                     { if (s.paged) FASTOCR_PARK_D(128, true); else FASTOCR_PARK_D(128, false); }
+#undef FASTOCR_PARK_D
+#undef FASTOCR_PARK
+    return hipGetLastError();
 }
 
 template <typename T, bool GATHER, bool PAGED>

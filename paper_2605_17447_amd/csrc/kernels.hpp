@@ -9,7 +9,7 @@ namespace fastocr {
 // Kernel ids mirror fastocr_kernel in fastocr.h (used by the per-kernel timers).
 enum KernelId {
     K_SCORE_LOGITS = 0, K_SCORE_FINALIZE = 1, K_TOPK = 2, K_SPARSE_ATTN = 3, K_DENSE_ATTN = 4,
-    K_ATTN_COMBINE = 5, K_FOCAL_FUSED = 6, K_COUNT = 7
+    K_ATTN_COMBINE = 5, K_FOCAL_FUSED = 6, K_PARKED_FINISH = 7, K_COUNT = 8
 };
 
 // Per-kernel timing (api.hip): when a timer is enabled for `kernel`, the next launch gets a pair of
@@ -81,6 +81,14 @@ struct MassArgs {
     int n_part;
 };
 
+// The top-k inside a launch that finishes scores (sel_idx == nullptr: none): the arguments of fastocr_topk_fixation.
+struct SelectArgs {
+    double tau;
+    const int32_t *prev_idx, *prev_cnt;
+    int32_t *sel_idx, *sel_cnt;
+    int64_t kmax;
+};
+
 // ---- attention (attn.hip) ---------------------------------------------------------------
 // Workspace: part_o fp32 [B][Hq][nsplit][d] followed by part_ml fp32 [B][Hq][nsplit][2].
 int attn_tile_tokens(const Shape &s);
@@ -94,6 +102,11 @@ bool attn_merges_in_kernel(const Shape &s, int nsplit);
 hipError_t launch_attn(const Shape &s, const void *q, float scale, const int32_t *sel_idx,
                        const int32_t *sel_cnt, int64_t kmax, void *out, float *lse, void *ws,
                        int nsplit, int merge_slot, uint32_t *gave_up_flag, hipStream_t stream);
+// Dense attention whose logits of the image tokens stay behind in `logits` (fp32, log2 domain, [sequence][query head][pitch]);
+// always partials.  part_o == nullptr: logits and statistics alone.  part_zi: the image tokens' part of every range's sum-exp,
+// [rows], or null.  zero: [batch] words the launch clears, or null.  Shapes with parks_by_head.
+hipError_t launch_attn_parked(int kid, const Shape &s, const void *q, float scale, float *part_o, float *part_ml, float *part_zi,
+                              int nsplit, float *logits, int64_t pitch, uint32_t *zero, hipStream_t stream);
 // merge of nsplit partials per (sequence, head) in the layout above into the final output.
 // With seq_meta (device int32 [B][2]: first workgroup, workgroup count) the partials are instead
 // those of the fused focal kernel, [workgroup][wpk][Hq][d] / [..][2], wpk per workgroup.
@@ -110,16 +123,24 @@ hipError_t launch_attn_f32(int kid, const Shape &s, const void *q, float scale, 
                            int64_t pitch, hipStream_t stream);
 
 // ---- focal scoring (score.hip) ----------------------------------------------------------
-// Workspace: logits fp32 [B][Hq][pitch], part_ml fp32 [B][Hq][nsplit][2], mass partials.
-int score_tile_tokens(const Shape &s);
+// Workspace: logits fp32 [B][Hq][pitch], part_ml fp32 [B][Hq][nsplit][2], image sums or mass partials.
 size_t score_workspace_bytes(const Shape &s, size_t rows);            // rows = B * Hq * nsplit
 hipError_t launch_score(const Shape &s, const void *q, float scale, float *scores, float *lse,
-                        float *img_mass, void *ws, int nsplit, hipStream_t stream);
+                        float *img_mass, void *ws, int nsplit, hipStream_t stream, int finish_kid = K_SCORE_FINALIZE,
+                        const SelectArgs *select = nullptr);
+
+struct CombineArgs;
+bool parks_by_head(const Shape &s);    // the matrix-core kernels of attn.hip park this shape's logits
+// A focal layer of a bf16 cache as two launches that wait for nothing (parks_by_head).  nsplit: that of dense attention.
+// select: the second launch does the top-k too (image spans of up to 16384 tokens, as in launch_score); defer (without
+// select): see launch_focal_fused; the image mass is not handed on.
+size_t focal_parked_workspace_bytes(const Shape &s, size_t rows);     // rows = B * Hq * nsplit
+hipError_t launch_focal_parked(const Shape &s, const void *q, float scale, void *out, float *scores, float *lse, float *img_mass,
+                               void *ws, int nsplit, hipStream_t stream, const SelectArgs *select = nullptr, CombineArgs *defer = nullptr);
 
 // A focal layer of an fp32 cache in one pass (s.fast32): attention partials and parked logits from one read of K
 // and V, then the scores.  nsplit: that of dense attention.  defer: see launch_focal_fused.
 size_t focal_f32_workspace_bytes(const Shape &s, size_t rows);        // rows = B * Hq * nsplit
-struct CombineArgs;
 hipError_t launch_focal_f32(const Shape &s, const void *q, float scale, void *out, float *scores, float *lse, float *img_mass,
                             void *ws, int nsplit, hipStream_t stream, CombineArgs *defer = nullptr);
 
@@ -129,14 +150,6 @@ hipError_t launch_focal_f32(const Shape &s, const void *q, float scale, void *ou
 // Workspace, W = nranges * batch: image-mass partials fp32 [W], per sequence its first workgroup
 // and range count int32 [B][2] (the ranges' softmax statistics travel through static device memory).
 struct ResidentPlan { int nranges, range_tokens, wpk; };
-// The top-k fused into a register-resident launch (sel_idx == nullptr: none): the arguments of
-// fastocr_topk_fixation.
-struct SelectArgs {
-    double tau;
-    const int32_t *prev_idx, *prev_cnt;
-    int32_t *sel_idx, *sel_cnt;
-    int64_t kmax;
-};
 // whether the fused select covers the shape (image spans of up to 16384 tokens)
 bool resident_select_fits(const Shape &s);
 bool resident_plan(const Shape &s, int num_cu, ResidentPlan *plan);

@@ -34,19 +34,6 @@ __device__ __forceinline__ uint32_t lds_address(const void *p)
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
 }
 
-// Data-parallel-primitive moves within a row of 16 lanes (full-rate VALU, no LDS traffic).
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float x)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
-}
-constexpr int kDppXor1 = 0xB1;          // quad_perm [1,0,3,2]
-constexpr int kDppXor2 = 0x4E;          // quad_perm [2,3,0,1]
-constexpr int kDppHalfMirror = 0x141;   // lane i <-> 7 - i within each 8 lanes
-constexpr int kDppRowMirror = 0x140;    // lane i <-> 15 - i within each 16 lanes
-constexpr int kDppRor8 = 0x128;         // lane i <- lane i ^ 8
-constexpr int kDppQuad0 = 0x00, kDppQuad1 = 0x55, kDppQuad2 = 0xAA, kDppQuad3 = 0xFF;      // quad_perm: lane k of each quad to its four lanes
-
 // ---- which (sequence, image-token range) a workgroup of a register-resident kernel works on ------
 // The grid has W workgroups (at most one per compute unit).  With sequences of equal length every
 // sequence gets W / batch ranges.  In a ragged batch an equal split would leave the chip waiting

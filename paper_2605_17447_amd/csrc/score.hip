@@ -2,231 +2,22 @@
 // cache, read at the image tokens (Eq. 1; text under Eq. 2).
 //
 // The average over heads is taken AFTER each head's softmax, so no score is final before
-// every head's normaliser over all S keys is known.  Two kernels:
-//   logits   : streams K once.  Per (sequence, kv head, token range) it computes the G query
-//              heads' logits, parks them (fp32, log2 domain) in the workspace and reduces a
-//              per-range (max, sum-exp) per head.
-//   finalize : merges the per-range statistics into each head's maximum M and sum Z and writes
-//              score_i = (1/Hq) sum_h 2^(logit_h,i - M_h) / Z_h for the image tokens.
-// The K stream uses the same MFMA tiling as the attention kernel (tokens x heads tiles of
-// v_mfma_f32_16x16x32_bf16) for bf16 caches of head_dim 128 and 64, the fp64 matrix-core kernel of attn_f32.hip for
-// fp32 caches of these, and a plain kernel otherwise.
+// every head's normaliser over all S keys is known.  Two launches:
+//   logits : streams K once (for a focal layer K and V).  Per (sequence, kv head, token range) it computes the query heads' logits, parks
+//            them (fp32, log2 domain) in the workspace and leaves a per-range (max, sum-exp) per head.  bf16 caches of head_dim 128 and
+//            64: attn.hip (kLogits, kParked); fp32 caches of these: attn_f32.hip; otherwise the plain kernel here.
+//   finish : merges the per-range statistics into each head's maximum M and sum Z and writes
+//            score_i = (1/Hq) sum_h 2^(logit_h,i - M_h) / Z_h for the image tokens; for bf16 also the image mass and the merge of
+//            the output's partials.
 #include "kernels.hpp"
+#include "combine.hpp"
+#include "topk_dev.hpp"
 
 namespace fastocr {
 
-constexpr int kTile = 32;          // tokens per wave tile
-
-// parked logits: fp32 [sequence][kv head][token (pitch)][Gp], Gp = G rounded up to 4 heads
+// Parked logits, fp32.  bf16 on the matrix cores (attn.hip, kLogits and kParked): [sequence][query head][token (pitch)].  Otherwise
+// [sequence][kv head][token (pitch)][Gp], Gp = G rounded up to 4 heads.
 __host__ __device__ inline int park_heads(int G) { return (G + 3) / 4 * 4; }
-
-// One workgroup per (token range, kv head, sequence); its four waves walk interleaved 32-token
-// tiles.  A tile is loaded with 1 KB-contiguous 16-byte loads (4 rows of 256 B per instruction),
-// re-laid through a wave-private XOR-swizzled LDS tile into the MFMA B layout, and multiplied
-//     C[head][token] = Q (16 heads x 32 dims) * K^T (32 dims x 16 tokens)   (v_mfma_f32_16x16x32_bf16)
-// so that a lane ends up with 4 consecutive heads of one token: the parked row [token][Gp] is
-// written with one 16-byte store per lane and no transposition.
-//   GR = 8 : the group's heads fill rows 0..7 for the tile's first 16 tokens and rows 8..15 for
-//            its second 16 tokens (the same accumulator, Q placed in the upper rows for the
-//            second product): all 64 lanes hold live logits, one 1 KB store per tile.
-//   GR = 16: heads fill all 16 rows; two accumulators per tile.
-// Each lane keeps a running (max, sum-exp) for its 4 heads; lanes, waves and ranges are merged
-// at the end.
-// D = 64 (rows of 128 bytes): a load instruction brings 8 rows, the LDS tile has a pitch of 128
-// bytes with chunk ^ ((row >> 1) & 7), and the product takes two k-steps per 16-token half.
-template <int D, bool PAGED, int GR, int kWaves, int NBUF>
-__global__ __launch_bounds__(64 * kWaves) void score_mfma_kernel(
-    KvDev kv, BatchDev bv, const uint16_t *__restrict__ q, int Hq, int G, float scale_log2,
-    float *__restrict__ logits, int64_t pitch, float *__restrict__ part_ml, int nsplit)
-{
-    __shared__ __align__(16) unsigned char smem[kWaves][8192];
-    __shared__ float sm_m[kWaves][16], sm_z[kWaves][16];
-
-    static_assert(D == 128 || D == 64, "head_dim 128 or 64");
-    constexpr int KS = D / 32;            // k-steps per product
-    constexpr int NL = D / 16;            // 1 KB load instructions per 32-token tile
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int li = lane & 15, lg = lane >> 4;
-    const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
-    const int Gp = park_heads(G);
-
-    const SeqGeom geo = seq_geom(bv, b);
-    const int L = geo.S;
-    const int ntile = (L + kTile - 1) / kTile;
-    const int tps = (ntile + nsplit - 1) / nsplit;
-    const int t0 = split * tps, t1 = min(ntile, t0 + tps);
-
-    // Q as the A operand: lane (row li, k-block lg) holds dims 32*kk + 8*lg .. +7 of step kk.
-    u32x4 qlo[KS], qhi[KS];
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-        qlo[kk] = u32x4{0u, 0u, 0u, 0u};
-        qhi[kk] = u32x4{0u, 0u, 0u, 0u};
-        const int hl = li, hh = li - 8;
-        if (hl < G && (GR == 16 || hl < 8)) {
-            const uint16_t *qp = q + ((int64_t)b * Hq + (int64_t)kvh * G + hl) * D + 8 * (4 * kk + lg);
-            qlo[kk] = *reinterpret_cast<const u32x4 *>(qp);
-        }
-        if (GR == 8 && hh >= 0 && hh < G) {
-            const uint16_t *qp = q + ((int64_t)b * Hq + (int64_t)kvh * G + hh) * D + 8 * (4 * kk + lg);
-            qhi[kk] = *reinterpret_cast<const u32x4 *>(qp);
-        }
-    }
-    const uint16_t *kbase = reinterpret_cast<const uint16_t *>(kv.k);
-    const int64_t seq_base = row_offset<false>(kv, b, 0, kvh);
-
-    auto rowoff_of = [&](int tile) -> int64_t {
-        int p = min(tile * kTile + (lane & 31), L - 1);
-        return row_offset<PAGED>(kv, b, p, kvh);
-    };
-
-    // load e covers rows 4e .. 4e+3 of the tile (D = 128: lane group lg takes row 4e+lg, lane li its 16-byte
-    // chunk) or rows 8e .. 8e+7 (D = 64: one row per 8 lanes)
-    constexpr int CH = D / 8;                      // 16-byte chunks per row
-    const int lrow = lane / CH, lchunk = lane % CH;
-    auto load_tile = [&](int tile, int64_t off, u32x4(&K)[NL]) {
-#pragma unroll
-        for (int e = 0; e < NL; ++e) {
-            const int r = (64 / CH) * e + lrow;
-            int64_t ro;
-            if (PAGED) ro = __shfl(off, r);
-            else ro = seq_base + (int64_t)min(tile * kTile + r, L - 1) * kv.stride_token;
-            K[e] = stream_load(kbase + ro + 8 * lchunk);
-        }
-    };
-    // byte offset of chunk c of row r in the wave's LDS tile
-    auto lds_at = [&](int r, int c) { return D == 128 ? r * 256 + (((c ^ r) & 15) << 4) : r * 128 + ((c ^ ((r >> 1) & 7)) << 4); };
-
-    // heads of this lane: hbase .. hbase+3 ; token of the tile: li (+16 in the upper lane groups for GR = 8)
-    const int hbase = (GR == 8) ? 4 * (lg & 1) : 4 * lg;
-    const int tok_in_tile = (GR == 8) ? li + 16 * (lg >> 1) : li;
-    const bool park = hbase < Gp;
-    float m[4], z[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) { m[r] = kMinusHuge; z[r] = 0.f; }
-    float *lpark = logits + ((int64_t)b * kv.n_kv_heads + kvh) * pitch * Gp + hbase;
-
-    auto compute = [&](int tile, u32x4(&K)[NL]) {
-        unsigned char *sw = smem[wave];
-#pragma unroll
-        for (int e = 0; e < NL; ++e) {
-            const int r = (64 / CH) * e + lrow;
-            *reinterpret_cast<u32x4 *>(sw + lds_at(r, lchunk)) = K[e];
-        }
-        wave_lds_fence();
-        u32x4 kb[2 * KS];
-#pragma unroll
-        for (int T = 0; T < 2; ++T)
-#pragma unroll
-            for (int kk = 0; kk < KS; ++kk)
-                kb[KS * T + kk] = *reinterpret_cast<const u32x4 *>(sw + lds_at(16 * T + li, 4 * kk + lg));
-        wave_lds_fence();
-        const int p0 = tile * kTile;
-        if (GR == 8) {
-            f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kk = 0; kk < KS; ++kk)
-                s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qlo[kk]),
-                                                            __builtin_bit_cast(bf16x8, kb[kk]), s, 0, 0, 0);
-#pragma unroll
-            for (int kk = 0; kk < KS; ++kk)
-                s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qhi[kk]),
-                                                            __builtin_bit_cast(bf16x8, kb[KS + kk]), s, 0, 0, 0);
-            const int p = p0 + tok_in_tile;
-            const bool valid = p < L;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) s[r] = valid ? s[r] * scale_log2 : -INFINITY;
-            if (park) *reinterpret_cast<f32x4 *>(lpark + (int64_t)p * Gp) = s;     // p < pitch
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float mn = fmaxf(m[r], s[r]);
-                z[r] = z[r] * fast_exp2(m[r] - mn) + fast_exp2(s[r] - mn);
-                m[r] = mn;
-            }
-        } else {
-            f32x4 s0 = f32x4{0.f, 0.f, 0.f, 0.f}, s1 = s0;
-#pragma unroll
-            for (int kk = 0; kk < KS; ++kk) {
-                s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qlo[kk]),
-                                                             __builtin_bit_cast(bf16x8, kb[kk]), s0, 0, 0, 0);
-                s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qlo[kk]),
-                                                             __builtin_bit_cast(bf16x8, kb[KS + kk]), s1, 0, 0, 0);
-            }
-            const int p = p0 + li;
-            const bool v0 = p < L, v1 = p + 16 < L;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                s0[r] = v0 ? s0[r] * scale_log2 : -INFINITY;
-                s1[r] = v1 ? s1[r] * scale_log2 : -INFINITY;
-            }
-            if (park) {
-                *reinterpret_cast<f32x4 *>(lpark + (int64_t)p * Gp) = s0;
-                *reinterpret_cast<f32x4 *>(lpark + (int64_t)(p + 16) * Gp) = s1;
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float mn = fmaxf(m[r], fmaxf(s0[r], s1[r]));
-                z[r] = z[r] * fast_exp2(m[r] - mn) + fast_exp2(s0[r] - mn) + fast_exp2(s1[r] - mn);
-                m[r] = mn;
-            }
-        }
-    };
-
-    if (t0 + wave < t1) {
-        // NBUF register buffers, software pipelined: a buffer is refilled (with the tile NBUF rounds
-        // ahead) right after it has been consumed, so NBUF-1 tiles are in flight during a compute.
-        // The refills are unconditional (past the end the last tile is loaded again) so that no
-        // branch separates a load from the wait that matches it -- a conditional prefetch makes the
-        // compiler drain every outstanding load at the join.
-        u32x4 KB[NBUF][NL];
-        int64_t off[NBUF];
-        int tile = t0 + wave;
-        const int last = tile + (t1 - 1 - tile) / kWaves * kWaves;
-#pragma unroll
-        for (int i = 0; i < NBUF; ++i) {
-            const int tl = min(tile + i * kWaves, last);
-            off[i] = PAGED ? rowoff_of(tl) : 0;
-            load_tile(tl, off[i], KB[i]);
-        }
-        for (;;) {
-#pragma unroll
-            for (int i = 0; i < NBUF; ++i) {
-                compute(tile, KB[i]);
-                const int tl = min(tile + NBUF * kWaves, last);
-                off[i] = PAGED ? rowoff_of(tl) : 0;
-                load_tile(tl, off[i], KB[i]);
-                tile += kWaves;
-                if (tile > last) goto stream_done;
-            }
-        }
-    }
-stream_done:
-
-    // ---- merge lanes that hold the same heads, then waves, then write the range's statistics ----
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) softmax_merge(m[r], z[r], __shfl_xor(m[r], o), __shfl_xor(z[r], o));
-        if (GR == 8) softmax_merge(m[r], z[r], __shfl_xor(m[r], 32), __shfl_xor(z[r], 32));
-    }
-    if (li == 0 && (GR == 16 || lg < 2)) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) { sm_m[wave][hbase + r] = m[r]; sm_z[wave][hbase + r] = z[r]; }
-    }
-    __syncthreads();
-    if (threadIdx.x < G) {
-        const int hh = threadIdx.x;
-        float M = sm_m[0][hh];
-#pragma unroll
-        for (int w = 1; w < kWaves; ++w) M = fmaxf(M, sm_m[w][hh]);
-        float Z = 0.f;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) Z += fast_exp2(sm_m[w][hh] - M) * sm_z[w][hh];
-        const int64_t ph = ((int64_t)b * Hq + (int64_t)kvh * G + hh) * nsplit + split;
-        part_ml[ph * 2] = M;
-        part_ml[ph * 2 + 1] = Z;
-    }
-}
 
 // Generic (fp32 caches of head_dim 128 and 64 take attn_f32.hip): one wave per (range, query head, sequence), lanes over tokens.  The q.k sums run in
 // fp64 (dot_row) and are scaled there; the logit is rounded to fp32 once, when it is parked.
@@ -352,9 +143,205 @@ __global__ void mass_reduce_kernel(const float *__restrict__ mass_part, int nblk
     if (threadIdx.x == 0) img_mass[b] = t;
 }
 
-// -----------------------------------------------------------------------------------------
-int score_tile_tokens(const Shape &s) { return mfma_path(s) ? kTile : 64; }
 
+// ---- bf16: what follows the kernels that park logits as [sequence][query head][token] ------------------------------------
+// One launch of up to three kinds of workgroup, none of which waits for another: the scores of 64 tokens each, the image mass of
+// a sequence, the merge of one query head's output partials.  Bound by latency (a few MB): every load a workgroup of the
+// first kind needs -- its logits and its heads' statistics, whose addresses do not depend on the sequence's geometry -- is
+// requested at once, one memory round trip; 16 lanes share a head and merge its ranges with lane moves, the heads of a token meet
+// by half swaps and one trip through LDS.
+constexpr int kFinTokens = 64;
+
+// (M, Z) of NU heads hg, hg + 16, .. over their nsplit ranges, and the image tokens' part of Z with MASS, in all 16 lanes of a row.
+// NS: ranges per lane requested at a time, 16 NS in all (1: up to 16 ranges in one round trip, 4: up to 64).
+template <int NU, int NS, bool MASS>
+__device__ __forceinline__ void parked_stats(const float *__restrict__ part_ml, const float *__restrict__ part_zi, int64_t bh0, int h0, int Hq,
+                                             int nsplit, float (&M)[NU], float (&Z)[NU], float (&Zi)[NU])
+{
+    const int tq = threadIdx.x & 15;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) { M[u] = kMinusHuge; Z[u] = 0.f; Zi[u] = 0.f; }
+    for (int s0 = 0; s0 < nsplit; s0 += 16 * NS) {
+        float mm[NU][NS], zz[NU][NS], ii[NU][NS];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int64_t row = (bh0 + min(h0 + 16 * u, Hq - 1)) * nsplit;
+#pragma unroll
+            for (int k = 0; k < NS; ++k) {
+                const int s = s0 + 16 * k + tq;
+                const int64_t at = row + min(s, nsplit - 1);
+                const float2 ml = *reinterpret_cast<const float2 *>(part_ml + 2 * at);
+                mm[u][k] = s < nsplit ? ml.x : kMinusHuge;
+                zz[u][k] = s < nsplit ? ml.y : 0.f;
+                ii[u][k] = MASS ? (s < nsplit ? part_zi[at] : 0.f) : 0.f;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            float mx = M[u];
+#pragma unroll
+            for (int k = 0; k < NS; ++k) mx = fmaxf(mx, mm[u][k]);
+            const float f0 = fast_exp2(M[u] - mx);
+            Z[u] *= f0;
+            if (MASS) Zi[u] *= f0;
+#pragma unroll
+            for (int k = 0; k < NS; ++k) {
+                const float f = fast_exp2(mm[u][k] - mx);
+                Z[u] += zz[u][k] * f;
+                if (MASS) Zi[u] += ii[u][k] * f;
+            }
+            M[u] = mx;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        float mx = M[u];
+        mx = fmaxf(mx, dpp_move<kDppXor1>(mx));
+        mx = fmaxf(mx, dpp_move<kDppXor2>(mx));
+        mx = fmaxf(mx, dpp_move<kDppHalfMirror>(mx));
+        mx = fmaxf(mx, dpp_move<kDppRowMirror>(mx));
+        const float f = fast_exp2(M[u] - mx);
+        float z = Z[u] * f, zi = MASS ? Zi[u] * f : 0.f;
+        z += dpp_move<kDppXor1>(z);
+        z += dpp_move<kDppXor2>(z);
+        z += dpp_move<kDppHalfMirror>(z);
+        z += dpp_move<kDppRowMirror>(z);
+        if (MASS) {
+            zi += dpp_move<kDppXor1>(zi);
+            zi += dpp_move<kDppXor2>(zi);
+            zi += dpp_move<kDppHalfMirror>(zi);
+            zi += dpp_move<kDppRowMirror>(zi);
+        }
+        M[u] = mx;
+        Z[u] = z;
+        Zi[u] = zi;
+    }
+}
+
+// Scores of the 64 tokens of block `blk` by 256 consecutive threads (all threads of the workgroup call: a barrier inside).
+// NU: sixteenths of the query heads a lane looks after at a time (1, 2, 4: up to 16, 32, 64 heads; more heads in rounds).
+// COHERENT: stored for a reader in the same launch.
+template <int NU, int NS, bool COHERENT>
+__device__ __forceinline__ void parked_scores(const BatchDev &bv, int b, int blk, int Hq, const float *__restrict__ logits, int64_t pitch,
+                                              const float *__restrict__ part_ml, int nsplit, float *__restrict__ scores,
+                                              float *__restrict__ lse, float *sm)
+{
+    const int t = threadIdx.x & 255, tq = t & 15, hg = t >> 4, wave = t >> 6;
+    const int64_t bh0 = (int64_t)b * Hq;
+    const int p0 = blk * kFinTokens + 4 * tq;                    // tokens of the sequence
+    const int at = min(p0, (int)pitch - 4);                      // inside the pitch
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int h0 = hg; h0 < Hq + hg; h0 += 16 * NU) {             // (every lane walks every round)
+        f32x4 l[NU];
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+            l[u] = *reinterpret_cast<const f32x4 *>(logits + (bh0 + min(h0 + 16 * u, Hq - 1)) * pitch + at);
+        float M[NU], Z[NU], unused[NU];
+        parked_stats<NU, NS, false>(part_ml, nullptr, bh0, h0, Hq, nsplit, M, Z, unused);
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const bool there = h0 + 16 * u < Hq;
+            const float inv = 1.0f / Z[u];
+            // relative to the head's maximum: the difference of two logits of like size is nearly exact
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] += there ? fast_exp2(l[u][e] - M[u]) * inv : 0.f;
+            if (lse && blk == 0 && tq == 0 && there) lse[bh0 + h0 + 16 * u] = (Z[u] > 0.f ? M[u] + log2f(Z[u]) : -INFINITY) * kLn2;
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] = rows_sum(acc[e]);       // the wave's four head groups
+    if ((t & 63) < 16) *reinterpret_cast<f32x4 *>(&sm[wave * kFinTokens + 4 * tq]) = acc;
+    const SeqGeom geo = seq_geom(bv, b);
+    __syncthreads();
+    if (t < kFinTokens) {
+        const int i = blk * kFinTokens + t - geo.v0;
+        const float sum = (sm[t] + sm[kFinTokens + t]) + (sm[2 * kFinTokens + t] + sm[3 * kFinTokens + t]);
+        if (i >= 0 && i < geo.N) {
+            float *to = &scores[(int64_t)b * bv.max_vis_len + i];
+            if (COHERENT) __hip_atomic_store(to, sum / (float)Hq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else *to = sum / (float)Hq;
+        }
+    }
+}
+
+// Image mass of sequence b by 256 threads of a workgroup all of which call.
+template <int NU, int NS>
+__device__ __forceinline__ void parked_mass(int b, int Hq, const float *__restrict__ part_ml, const float *__restrict__ part_zi, int nsplit,
+                                            float *__restrict__ img_mass, float *sm)
+{
+    const int t = threadIdx.x & 255, hg = t >> 4;
+    float sum = 0.f;
+    for (int h0 = hg; h0 < Hq + hg; h0 += 16 * NU) {
+        float M[NU], Z[NU], Zi[NU];
+        parked_stats<NU, NS, true>(part_ml, part_zi, (int64_t)b * Hq, h0, Hq, nsplit, M, Z, Zi);
+#pragma unroll
+        for (int u = 0; u < NU; ++u) sum += h0 + 16 * u < Hq && Z[u] > 0.f ? Zi[u] / Z[u] : 0.f;
+    }
+    sum = rows_sum(sum);
+    if (threadIdx.x < 256 && (t & 63) == 0) sm[t >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) img_mass[b] = ((sm[0] + sm[1]) + (sm[2] + sm[3])) / (float)Hq;
+}
+
+template <int NU, int NS>
+__global__ __launch_bounds__(kFinThreads) void parked_finish_kernel(
+    BatchDev bv, int Hq, const float *__restrict__ logits, int64_t pitch, const float *__restrict__ part_ml,
+    const float *__restrict__ part_zi, int nsplit, float *__restrict__ scores, float *__restrict__ lse, float *__restrict__ img_mass,
+    int nblk, const float *__restrict__ part_o, int d, uint16_t *__restrict__ out)
+{
+    __shared__ float sm_max[4];
+    __shared__ float sm_z[256];
+    __shared__ __align__(16) float sm_o[1024];
+    const int b = blockIdx.y, blk = blockIdx.x;
+    if (blk < nblk) parked_scores<NU, NS, false>(bv, b, blk, Hq, logits, pitch, part_ml, nsplit, scores, lse, sm_o);
+    else if (img_mass && blk == nblk) parked_mass<NU, NS>(b, Hq, part_ml, part_zi, nsplit, img_mass, sm_max);
+    else combine_wide_body<uint16_t>(part_o, part_ml, nsplit, d, out, nullptr, nullptr, 1, blk - nblk - (img_mass ? 1 : 0), b, Hq,
+                                     CombineShared<uint16_t>{sm_max, sm_z, sm_o});
+}
+
+// The same with the top-k of the scores in the launch ("select_fused" 1): workgroups of 1024 threads, 256 tokens each, count themselves out per
+// sequence (`done`, zeroed by the launch before) once their scores, stored at agent scope, have been performed; the
+// sequence's last one selects over all of them as topk_reg_kernel does, with the same bits.  Nobody waits for anybody.  Not the
+// default: the count and the scores' way back through memory cost more than a launch (a layer with its top-k, separate launches /
+// this one, us: 28/4 heads, batch 1, 4096 image tokens 14.8 / 16.1, 16384 22.0 / 28.7, 12 x 4096 31.3 / 33.4).
+constexpr int kFinSelThreads = 1024;
+constexpr int kFinSelBlocks = kFinSelThreads / 256;          // 64-token blocks per workgroup
+
+__global__ __launch_bounds__(kFinSelThreads) void parked_select_kernel(
+    BatchDev bv, int Hq, const float *__restrict__ logits, int64_t pitch, const float *__restrict__ part_ml,
+    const float *__restrict__ part_zi, int nsplit, float *__restrict__ scores, float *__restrict__ lse, float *__restrict__ img_mass,
+    int nwg, const float *__restrict__ part_o, int d, uint16_t *__restrict__ out, SelectArgs sel, uint32_t *__restrict__ done)
+{
+    __shared__ uint32_t hist[kWinBins];
+    __shared__ __align__(16) uint32_t list[kWinListWords];
+    __shared__ int s_pick[4];
+    __shared__ __align__(16) int w_ac[4 * (kFinSelThreads / 64)];
+    __shared__ float sm_max[4];
+    __shared__ float sm_z[256];
+    __shared__ __align__(16) float sm_o[1024];
+    __shared__ int s_last;
+    const int b = blockIdx.y, wg = blockIdx.x;
+    if (wg >= nwg) {
+        if (img_mass && wg == nwg) parked_mass<4, 4>(b, Hq, part_ml, part_zi, nsplit, img_mass, sm_max);
+        else combine_wide_body<uint16_t>(part_o, part_ml, nsplit, d, out, nullptr, nullptr, 1, wg - nwg - (img_mass ? 1 : 0), b, Hq,
+                                         CombineShared<uint16_t>{sm_max, sm_z, sm_o});
+        return;
+    }
+    const int sub = threadIdx.x >> 8;
+    parked_scores<4, 4, true>(bv, b, wg * kFinSelBlocks + sub, Hq, logits, pitch, part_ml, nsplit, scores, lse, sm_o + 256 * sub);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this thread's scores have been performed
+    __syncthreads();                                         // ... and every other thread's of the workgroup
+    if (threadIdx.x == 0)
+        s_last = __hip_atomic_fetch_add(&done[b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)nwg - 1u;
+    __syncthreads();
+    if (!s_last) return;
+    TopkRegShared sh;
+    sh.hist = hist; sh.list = list; sh.pick = s_pick; sh.w_ac = w_ac;
+    topk_reg_body<kFinSelThreads, 16, true, false>(scores, bv, b, sel.tau, sel.prev_idx, sel.prev_cnt, sel.sel_idx, sel.sel_cnt, sel.kmax, sh,
+                                                    [](int, int) {});
+}
+
+// -----------------------------------------------------------------------------------------
 static int fin_blocks(const Shape &s)
 {
     const int LP = fin_lanes_per_token(park_heads(s.n_q_heads / s.kv.n_kv_heads));
@@ -362,17 +349,25 @@ static int fin_blocks(const Shape &s)
     return max(1, (s.bv.max_vis_len + per - 1) / per);
 }
 
+bool parks_by_head(const Shape &s)
+{
+    // a group's rows are addressed with 32-bit byte offsets
+    return mfma_path(s) && (s.n_q_heads / s.kv.n_kv_heads) * logit_pitch(s.bv.max_seq_len) < ((int64_t)1 << 29);
+}
+
 static size_t parked_floats(const Shape &s)
 {
-    const int Gp = park_heads(s.n_q_heads / s.kv.n_kv_heads);
-    return (size_t)s.batch * s.kv.n_kv_heads * (size_t)logit_pitch(s.bv.max_seq_len) * Gp;
+    const size_t pitch = (size_t)logit_pitch(s.bv.max_seq_len);
+    if (parks_by_head(s)) return (size_t)s.batch * s.n_q_heads * pitch;
+    return (size_t)s.batch * s.kv.n_kv_heads * pitch * park_heads(s.n_q_heads / s.kv.n_kv_heads);
 }
 
 size_t score_workspace_bytes(const Shape &s, size_t rows)
 {
     size_t bytes = parked_floats(s) * sizeof(float);
-    bytes += rows * 2 * sizeof(float);
-    bytes += (size_t)s.batch * fin_blocks(s) * sizeof(float);
+    bytes += rows * (parks_by_head(s) ? 3 : 2) * sizeof(float);
+    if (parks_by_head(s)) bytes += (size_t)s.batch * sizeof(uint32_t);
+    if (!parks_by_head(s)) bytes += (size_t)s.batch * fin_blocks(s) * sizeof(float);
     return bytes;
 }
 
@@ -386,29 +381,50 @@ static hipError_t launch_finalize(const Shape &s, const float *logits, int64_t p
     return hipGetLastError();
 }
 
+// part_o, out: the merge of the output's partials as well (null: scores alone).  select: the top-k as well (parked_select_fits).
+static hipError_t launch_parked_finish(int kid, const Shape &s, const float *logits, int64_t pitch, const float *part_ml, const float *part_zi, int nsplit,
+                                       float *scores, float *lse, float *img_mass, const float *part_o, void *out,
+                                       const SelectArgs *select, uint32_t *done, hipStream_t stream)
+{
+    if (select) {
+        const int nwg = std::max(1, (s.bv.max_seq_len + kFinSelBlocks * kFinTokens - 1) / (kFinSelBlocks * kFinTokens));
+        const dim3 grid(nwg + (img_mass ? 1 : 0) + (out ? s.n_q_heads : 0), s.batch), block(kFinSelThreads);
+        FASTOCR_LAUNCH(kid, parked_select_kernel, grid, block, 0, stream, s.bv, s.n_q_heads, logits, pitch, part_ml, part_zi, nsplit, scores, lse,
+                       img_mass, nwg, part_o, s.kv.head_dim, (uint16_t *)out, *select, done);
+        return hipGetLastError();
+    }
+    // over the sequence's tokens, so that nothing waits for where its image starts; blocks without image tokens end at once
+    const int nblk = std::max(1, (s.bv.max_seq_len + kFinTokens - 1) / kFinTokens);
+    const dim3 grid(nblk + (img_mass ? 1 : 0) + (out ? s.n_q_heads : 0), s.batch), block(kFinThreads);
+#define FASTOCR_FINISH_N(NU, NS) FASTOCR_LAUNCH(kid, (parked_finish_kernel<NU, NS>), grid, block, 0, stream, s.bv, s.n_q_heads, logits, pitch, \
+        part_ml, part_zi, nsplit, scores, lse, img_mass, nblk, part_o, s.kv.head_dim, (uint16_t *)out)
+#define FASTOCR_FINISH(NU) do { if (nsplit <= 16) FASTOCR_FINISH_N(NU, 1); else FASTOCR_FINISH_N(NU, 4); } while (0)
+    if (s.n_q_heads <= 16) FASTOCR_FINISH(1);
+    else if (s.n_q_heads <= 32) FASTOCR_FINISH(2);
+    else FASTOCR_FINISH(4);
+#undef FASTOCR_FINISH
+#undef FASTOCR_FINISH_N
+    return hipGetLastError();
+}
+
 hipError_t launch_score(const Shape &s, const void *q, float scale, float *scores, float *lse,
-                        float *img_mass, void *ws, int nsplit, hipStream_t stream)
+                        float *img_mass, void *ws, int nsplit, hipStream_t stream, int finish_kid, const SelectArgs *select)
 {
     const int64_t pitch = logit_pitch(s.bv.max_seq_len);
     const size_t rows = (size_t)s.batch * s.n_q_heads;
     float *logits = reinterpret_cast<float *>(ws);
     float *part_ml = logits + parked_floats(s);
+    if (parks_by_head(s)) {
+        float *part_zi = img_mass ? part_ml + rows * nsplit * 2 : nullptr;
+        uint32_t *done = select ? reinterpret_cast<uint32_t *>(part_ml + rows * nsplit * 3) : nullptr;
+        const hipError_t e = launch_attn_parked(K_SCORE_LOGITS, s, q, scale, nullptr, part_ml, part_zi, nsplit, logits, pitch, done, stream);
+        if (e != hipSuccess) return e;
+        return launch_parked_finish(finish_kid, s, logits, pitch, part_ml, part_zi, nsplit, scores, lse, img_mass, nullptr, nullptr,
+                                    select, done, stream);
+    }
     float *mass_part = part_ml + rows * nsplit * 2;
-    const float scale_log2 = scale * kLog2e;
     const int G = s.n_q_heads / s.kv.n_kv_heads;
-
-    if (mfma_path(s)) {
-        dim3 grid(nsplit, s.kv.n_kv_heads, s.batch);
-#define FASTOCR_SCORE(DD, P, GR) FASTOCR_LAUNCH(K_SCORE_LOGITS, (score_mfma_kernel<DD, P, GR, 4, 2>), grid, dim3(256), 0, stream, \
-        s.kv, s.bv, (const uint16_t *)q, s.n_q_heads, G, scale_log2, logits, pitch, part_ml, nsplit)
-        if (s.kv.head_dim == 64) {
-            if (s.paged) { if (G <= 8) FASTOCR_SCORE(64, true, 8); else FASTOCR_SCORE(64, true, 16); }
-            else         { if (G <= 8) FASTOCR_SCORE(64, false, 8); else FASTOCR_SCORE(64, false, 16); }
-        }
-        else if (s.paged) { if (G <= 8) FASTOCR_SCORE(128, true, 8); else FASTOCR_SCORE(128, true, 16); }
-        else              { if (G <= 8) FASTOCR_SCORE(128, false, 8); else FASTOCR_SCORE(128, false, 16); }
-#undef FASTOCR_SCORE
-    } else if (f32_mfma_path(s)) {
+    if (f32_mfma_path(s)) {
         const hipError_t e = launch_attn_f32(K_SCORE_LOGITS, s, q, scale, nullptr, nullptr, 0, nullptr, part_ml, nsplit, nullptr, nullptr,
                                              logits, pitch, stream);
         if (e != hipSuccess) return e;
@@ -427,6 +443,32 @@ hipError_t launch_score(const Shape &s, const void *q, float scale, float *score
     if (e != hipSuccess || !img_mass) return e;
     mass_reduce_kernel<<<s.batch, 64, 0, stream>>>(mass_part, fin_blocks(s), img_mass);
     return hipGetLastError();
+}
+
+// A focal layer of a bf16 cache as two launches: attention partials and parked logits, then scores, image mass and (unless it is
+// handed on to the top-k's launch) the output's merge at once.
+// Workspace: logits, the attention partials fp32 [rows][d], the ranges' statistics [rows][2] and image sums [rows], a count per sequence.
+size_t focal_parked_workspace_bytes(const Shape &s, size_t rows)
+{
+    return (parked_floats(s) + rows * (3 + s.kv.head_dim) + s.batch) * sizeof(float);
+}
+
+hipError_t launch_focal_parked(const Shape &s, const void *q, float scale, void *out, float *scores, float *lse, float *img_mass,
+                               void *ws, int nsplit, hipStream_t stream, const SelectArgs *select, CombineArgs *defer)
+{
+    const int64_t pitch = logit_pitch(s.bv.max_seq_len);
+    const size_t rows = (size_t)s.batch * s.n_q_heads * nsplit;
+    float *logits = reinterpret_cast<float *>(ws);
+    float *part_o = logits + parked_floats(s);                       // 16-byte aligned: the pitch is a multiple of 64
+    float *part_ml = part_o + rows * s.kv.head_dim;
+    float *part_zi = img_mass ? part_ml + rows * 2 : nullptr;
+    uint32_t *done = select ? reinterpret_cast<uint32_t *>(part_ml + rows * 3) : nullptr;
+    const hipError_t e = launch_attn_parked(K_FOCAL_FUSED, s, q, scale, part_o, part_ml, part_zi, nsplit, logits, pitch, done, stream);
+    if (e != hipSuccess) return e;
+    const bool hand_on = defer && !select;
+    if (hand_on) *defer = CombineArgs{part_o, part_ml, nsplit, s.kv.head_dim, s.n_q_heads, 1, nullptr, out, false, MassArgs{nullptr, nullptr, 0}};
+    return launch_parked_finish(hand_on || select ? K_PARKED_FINISH : K_ATTN_COMBINE, s, logits, pitch, part_ml, part_zi, nsplit, scores, lse, img_mass,
+                                hand_on ? nullptr : part_o, hand_on ? nullptr : out, select, done, stream);
 }
 
 // Workspace: as launch_score's, then the attention partials fp32 [B][Hq][nsplit][d] (the softmax statistics serve both).

@@ -1,0 +1,130 @@
+"""The forms that park a bf16 cache's logits for a second launch (scoring, a focal layer, with and without the top-k) against the
+oracle: tile, block and range edges, every way the heads are dealt, spans that start anywhere, dead keys, replays."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_17447_amd as fo
+from paper_2605_17447_amd import binding as fb
+from util import TinyCase, as_f64, f32_to_bf16_bits
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from gpu_util import DEV, check_out, check_scores, paged_twin, problem_from_case, to_np
+
+
+@pytest.fixture
+def finish_launches():
+    for k in (fb.KERNEL_PARKED_FINISH, fb.KERNEL_ATTN_COMBINE):
+        fb.kernel_timer_enable(k, 64)
+    yield lambda k: len(fb.kernel_timer_read(k))
+    for k in (fb.KERNEL_PARKED_FINISH, fb.KERNEL_ATTN_COMBINE):
+        fb.kernel_timer_enable(k, 0)
+
+
+def _check(p, launches, what, ref=None, tau=0.07):
+    """ref: (scores, lse, image mass, output) instead of the oracle's."""
+    if ref is None:
+        oc = p.oracle_args()
+        ref = (*oracle.focal_score(*oc), oracle.decode_attn(*oc)[0])
+    ref_sc, ref_lse, ref_mass, ref_out = ref
+    sc, lse, mass = p.scores(want_lse=True, want_mass=True)
+    assert launches(fb.KERNEL_PARKED_FINISH) == 1, what
+    check_scores(sc, ref_sc, p.vis_len, what + " scores")
+    assert np.allclose(lse.cpu().numpy(), ref_lse, rtol=2e-5, atol=2e-5) and np.allclose(mass.cpu().numpy(), ref_mass, atol=2e-5), what
+    for b, n in enumerate(p.vis_len):
+        assert (sc[b, n:] == -7.0).all(), f"{what}: scores past sequence {b}'s image were written"
+    out, sc, lse, mass = p.focal_attn(want_lse=True, want_mass=True)
+    assert launches(fb.KERNEL_ATTN_COMBINE) == 1 and launches(fb.KERNEL_PARKED_FINISH) == 0, what      # one launch for all of it
+    check_out(out, ref_out, what + " output")
+    check_scores(sc, ref_sc, p.vis_len, what + " layer's scores")
+    assert np.allclose(lse.cpu().numpy(), ref_lse, rtol=2e-5, atol=2e-5) and np.allclose(mass.cpu().numpy(), ref_mass, atol=2e-5), what
+    # with the top-k, in launches of its own and inside: the same bits, the exact set of these scores
+    kmax = max(1, fo.keep_count(p.batch.max_vis_len, tau))
+    for inside in (0, 1):
+        fb.set_tuning("select_fused", inside)
+        try:
+            out2, sc2, mass2 = torch.full_like(p.q, 3.0), torch.full_like(sc, -7.0), torch.zeros_like(mass)
+            idx, cnt = torch.zeros((p.B, kmax), dtype=torch.int32, device=DEV), torch.zeros((p.B,), dtype=torch.int32, device=DEV)
+            fo.focal_attn_score_topk(p.cache, p.batch, p.q, p.scale, tau, out2, sc2, idx, cnt, p.ws(fb.OP_FOCAL_ATTN_SCORE_TOPK, kmax), img_mass=mass2)
+        finally:
+            fb.set_tuning("select_fused", 0)
+        assert torch.equal(out, out2) and torch.equal(sc, sc2) and torch.equal(mass, mass2), f"{what} select_fused {inside}"
+        for b, n in enumerate(p.vis_len):
+            k = fo.keep_count(n, tau)
+            assert int(cnt[b]) == k and np.array_equal(idx[b, :k].cpu().numpy(), oracle.topk(to_np(sc)[b, :n], k)), f"{what} set {b}"
+    launches(fb.KERNEL_PARKED_FINISH), launches(fb.KERNEL_ATTN_COMBINE)
+
+
+# 1, 2, 4 sixteenths of the heads per lane and rounds of them; groups of 1 .. 16; 1 .. 10 kv heads (10, 3 and groups above 8 have no other one-pass form)
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("Hq,Hkv", [(28, 4), (5, 1), (16, 16), (40, 10), (64, 8), (32, 2), (96, 6), (9, 3)])
+def test_edges(Hq, Hkv, d, finish_launches):
+    # images of one token less, exactly and one more than a tile, a 64-token block and two; starts that are no multiple of anything
+    n = [0, 1, 31, 32, 33, 63, 64, 65, 129, 700, 191]
+    case = TinyCase(seed=Hq + d, B=len(n), Hq=Hq, Hkv=Hkv, d=d, n_vis=n, pre=[3, 0, 1, 32, 5, 64, 63, 7, 30, 127, 600],
+                    post=[40, 1, 0, 2, 33, 1, 31, 66, 5, 9, 450], dtype="bf16")
+    p = problem_from_case(case)
+    _check(p, finish_launches, f"{Hq}/{Hkv} d{d}")
+    _check(problem_from_case(case, "bshd"), finish_launches, f"{Hq}/{Hkv} d{d} bshd")
+    _check(paged_twin(p, 48, 5), finish_launches, f"{Hq}/{Hkv} d{d} paged")
+
+
+@pytest.mark.parametrize("Hq,Hkv,B,n", [(8, 1, 1, 9000), (4, 1, 1, 2100), (8, 2, 1, 8400), (28, 4, 3, 4097)])      # 72, 18, 67, 21 ranges
+def test_many_ranges(Hq, Hkv, B, n, finish_launches):
+    case = TinyCase(seed=n, B=B, Hq=Hq, Hkv=Hkv, d=128, n_vis=n, pre=17, post=50, dtype="bf16", spread=1.5)
+    _check(problem_from_case(case), finish_launches, f"{Hq}/{Hkv} {n}")
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_dead_keys(d, finish_launches):
+    """Keys of logit -inf (whole tiles, a whole range, single ones): weight 0, nothing else touched."""
+    n, pre, post = [300, 1500], [9, 40], [70, 3]
+    case = TinyCase(seed=d, B=2, Hq=16, Hkv=2, d=d, n_vis=n, pre=pre, post=post, dtype="bf16")
+    case.q = f32_to_bf16_bits(np.abs(as_f64(case.q)).astype(np.float32) + np.float32(0.25))
+    ninf = f32_to_bf16_bits(np.array([-np.inf], np.float32))[0]
+    live = [np.ones(s, bool) for s in case.seq_len]
+    for b, (lo, hi) in ((0, (0, 64)), (0, (200, 201)), (0, (340, 379)), (1, (64, 224)), (1, (700, 733)), (1, (1542, 1543))):
+        live[b][lo:hi] = False
+        case.k[b, :, lo:hi, 3] = ninf
+    k, v, q = as_f64(case.k), as_f64(case.v), as_f64(case.q)
+    sc, lse, out = np.zeros((2, max(n))), np.zeros((2, 16)), np.zeros((2, 16, d))
+    for b in range(2):
+        for h in range(16):
+            lg = k[b, h // 8, : case.seq_len[b]][live[b]] @ q[b, h] * case.scale
+            w = np.exp(lg - lg.max())
+            lse[b, h] = lg.max() + np.log(w.sum())
+            full = np.zeros(case.seq_len[b])
+            full[live[b]] = w / w.sum()
+            out[b, h] = full @ v[b, h // 8, : case.seq_len[b]]
+            sc[b, : n[b]] += full[pre[b]: pre[b] + n[b]] / 16
+    _check(problem_from_case(case), finish_launches, f"dead keys d{d}", ref=(sc, lse, sc.sum(1), out))
+
+
+def test_replayed_from_a_graph_next_to_eager_calls():
+    case = TinyCase(seed=3, B=3, Hq=28, Hkv=4, d=128, n_vis=[900, 333, 1200], pre=[5, 0, 64], post=[30, 9, 100], dtype="bf16")
+    p = problem_from_case(case)
+    kmax = fo.keep_count(1200, 0.05)
+    mk = lambda: (torch.zeros_like(p.q), torch.zeros((3, 1200), device=DEV), torch.zeros((3, kmax), dtype=torch.int32, device=DEV),
+                  torch.zeros((3,), dtype=torch.int32, device=DEV), torch.empty_like(p.ws(fb.OP_FOCAL_ATTN_SCORE_TOPK, kmax)))
+    run = lambda o, s, i, c, ws: fo.focal_attn_score_topk(p.cache, p.batch, p.q, p.scale, 0.05, o, s, i, c, ws)
+    for inside in (0, 1):
+        fb.set_tuning("select_fused", inside)
+        try:
+            a, e = mk(), mk()
+            run(*a)
+            torch.cuda.synchronize()
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g):
+                run(*a)
+            rng = np.random.default_rng(2)
+            for _ in range(4):
+                p.q.copy_(torch.from_numpy(rng.standard_normal(p.q.shape).astype(np.float32)).to(DEV).to(torch.bfloat16))
+                g.replay()
+                run(*e)
+                torch.cuda.synchronize()
+                assert all(torch.equal(x, y) for x, y in zip(a[:4], e[:4]))
+        finally:
+            fb.set_tuning("select_fused", 0)
