@@ -25,6 +25,21 @@ HOST_SANITIZE = ["-g", "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsa
 LIB_HOSTSAN = os.path.join(HERE, "libfastocr_hostsan.so")
 
 
+# The binding's hot path (csrc/pycall.cpp), a Python extension over torch's own tensor headers; host code only.
+CALL_LIB = os.path.join(HERE, "_fastocr_call.so")
+
+
+def _call_command(out: str):
+    import sysconfig
+    import torch
+    home = os.path.dirname(torch.__file__)
+    inc = os.path.join(home, "include")
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-I", INCLUDE, "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+            "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "pycall.cpp"), "-o", out,
+            "-L", os.path.join(home, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
 def build(verbose: bool = False, host_sanitize: bool = False) -> str:
     """Compile every source and link the shared library; returns its path."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -39,6 +54,9 @@ def build(verbose: bool = False, host_sanitize: bool = False) -> str:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
+    call_tmp = CALL_LIB + f".tmp{os.getpid()}"
+    if not host_sanitize:
+        procs.append(("pycall.cpp", subprocess.Popen(_call_command(call_tmp), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     failed = False
     for src, p in procs:
         out, _ = p.communicate()
@@ -56,6 +74,8 @@ def build(verbose: bool = False, host_sanitize: bool = False) -> str:
         link += ["-fsanitize=address", "-fsanitize=undefined", "-shared-libsan"]
     subprocess.check_call(link)
     os.replace(tmp, lib)
+    if not host_sanitize:
+        os.replace(call_tmp, CALL_LIB)
     return lib
 
 

@@ -57,6 +57,7 @@ class FastOcrError(RuntimeError):
 
 
 _lib = None
+_call = None          # csrc/pycall.cpp bound to the loaded library (None: no library loaded yet, or the extension is not built)
 
 
 def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
@@ -102,7 +103,25 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib.fastocr_strerror.restype, lib.fastocr_strerror.argtypes = ctypes.c_char_p, [I]
     lib.fastocr_version.restype, lib.fastocr_version.argtypes = ctypes.c_char_p, []
     _lib = lib
+    _bind_call(lib)
     return lib
+
+
+def _bind_call(lib) -> None:
+    """Step calls go through the native extension where it is built: it returns the status, or None for whatever it leaves
+    to the functions below."""
+    global _call
+    if _raw_stream is None or _current_device is None:
+        return
+    try:
+        from . import _fastocr_call as call
+    except ImportError:
+        return
+    names = ("focal_score", "topk_fixation", "sparse_decode_attn", "dense_decode_attn", "focal_attn_score", "focal_score_topk",
+             "focal_attn_score_topk")
+    call.bind(KvCache, SeqBatch, _current_device, _raw_stream, torch.cuda.is_initialized,
+              *(ctypes.cast(getattr(lib, "fastocr_" + n), ctypes.c_void_p).value for n in names))
+    _call = call
 
 
 def strerror(status: int) -> str:
@@ -254,6 +273,10 @@ def focal_score(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scale: float, 
                 ws: torch.Tensor, lse: Optional[torch.Tensor] = None,
                 img_mass: Optional[torch.Tensor] = None, stream=None) -> None:
     """fastocr_focal_score: q [B,Hq,d]; scores fp32 [B, max_vis_len] (written in place)."""
+    if _call is not None:
+        rc = _call.focal_score(cache, batch, q, scale, scores, ws, lse, img_mass, stream)
+        if rc is not None:
+            return _check(rc, "fastocr_focal_score")
     lib = _lib or load_library()
     kv, bv = cache.view(), batch.view()
     assert q.is_contiguous() and scores.is_contiguous() and scores.dtype == torch.float32
@@ -268,6 +291,10 @@ def topk_fixation(scores: torch.Tensor, batch: SeqBatch, tau: float, sel_idx: to
                   prev_idx: Optional[torch.Tensor] = None, prev_cnt: Optional[torch.Tensor] = None,
                   stream=None) -> None:
     """fastocr_topk_fixation: sel_idx int32 [B,kmax], sel_cnt int32 [B] (written in place)."""
+    if _call is not None:
+        rc = _call.topk(scores, batch, tau, sel_idx, sel_cnt, ws, prev_idx, prev_cnt, stream)
+        if rc is not None:
+            return _check(rc, "fastocr_topk_fixation")
     lib = _lib or load_library()
     bv = batch.view()
     assert sel_idx.dtype == torch.int32 and sel_idx.is_contiguous() and sel_cnt.dtype == torch.int32
@@ -285,6 +312,10 @@ def sparse_decode_attn(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scale: 
                        sel_idx: torch.Tensor, sel_cnt: torch.Tensor, out: torch.Tensor,
                        ws: torch.Tensor, stream=None) -> None:
     """fastocr_sparse_decode_attn: out [B,Hq,d] in the cache dtype (written in place)."""
+    if _call is not None:
+        rc = _call.sparse(cache, batch, q, scale, sel_idx, sel_cnt, out, ws, stream)
+        if rc is not None:
+            return _check(rc, "fastocr_sparse_decode_attn")
     lib = _lib or load_library()
     kv, bv = cache.view(), batch.view()
     assert q.is_contiguous() and out.is_contiguous() and out.shape == q.shape and out.dtype == q.dtype
@@ -298,6 +329,10 @@ def sparse_decode_attn(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scale: 
 def dense_decode_attn(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scale: float, out: torch.Tensor,
                       ws: torch.Tensor, lse: Optional[torch.Tensor] = None, stream=None) -> None:
     """fastocr_dense_decode_attn: out [B,Hq,d] in the cache dtype (written in place)."""
+    if _call is not None:
+        rc = _call.dense(cache, batch, q, scale, out, ws, lse, stream)
+        if rc is not None:
+            return _check(rc, "fastocr_dense_decode_attn")
     lib = _lib or load_library()
     kv, bv = cache.view(), batch.view()
     assert q.is_contiguous() and out.is_contiguous() and out.shape == q.shape and out.dtype == q.dtype
@@ -321,6 +356,10 @@ def focal_attn_score(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scale: fl
                      scores: torch.Tensor, ws: torch.Tensor, lse: Optional[torch.Tensor] = None,
                      img_mass: Optional[torch.Tensor] = None, stream=None) -> None:
     """fastocr_focal_attn_score: dense output [B,Hq,d] and scores fp32 [B, max_vis_len] in one call."""
+    if _call is not None:
+        rc = _call.layer(cache, batch, q, scale, out, scores, ws, lse, img_mass, stream)
+        if rc is not None:
+            return _check(rc, "fastocr_focal_attn_score")
     lib = _lib or load_library()
     kv, bv = cache.view(), batch.view()
     assert q.is_contiguous() and out.is_contiguous() and out.shape == q.shape and out.dtype == q.dtype
@@ -336,6 +375,10 @@ def focal_score_topk(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scale: fl
                      prev_idx: Optional[torch.Tensor] = None, prev_cnt: Optional[torch.Tensor] = None,
                      lse: Optional[torch.Tensor] = None, img_mass: Optional[torch.Tensor] = None, stream=None) -> None:
     """fastocr_focal_score_topk: scores and the selected set from one call."""
+    if _call is not None:
+        rc = _call.score_topk(cache, batch, q, scale, tau, scores, sel_idx, sel_cnt, ws, prev_idx, prev_cnt, lse, img_mass, stream)
+        if rc is not None:
+            return _check(rc, "fastocr_focal_score_topk")
     lib = _lib or load_library()
     kv, bv = cache.view(), batch.view()
     assert q.is_contiguous() and scores.is_contiguous() and scores.dtype == torch.float32
@@ -354,6 +397,10 @@ def focal_attn_score_topk(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scal
                           prev_idx: Optional[torch.Tensor] = None, prev_cnt: Optional[torch.Tensor] = None,
                           lse: Optional[torch.Tensor] = None, img_mass: Optional[torch.Tensor] = None, stream=None) -> None:
     """fastocr_focal_attn_score_topk: a focal layer's dense output, its scores and the selected set from one call."""
+    if _call is not None:
+        rc = _call.layer_topk(cache, batch, q, scale, tau, out, scores, sel_idx, sel_cnt, ws, prev_idx, prev_cnt, lse, img_mass, stream)
+        if rc is not None:
+            return _check(rc, "fastocr_focal_attn_score_topk")
     lib = _lib or load_library()
     kv, bv = cache.view(), batch.view()
     assert q.is_contiguous() and out.is_contiguous() and out.shape == q.shape and out.dtype == q.dtype
