@@ -143,7 +143,7 @@ size_t fastocr_workspace_bytes(int op, const fastocr_kv_view *kv, const fastocr_
  * plain-FMA kernels that accumulate in fp64, to the same error bars.
  * Concurrency: when the shape fits (bf16, head_dim 128 or 64, 1/2/4/8 kv heads with at most 8 query heads
  * each, batch <= 256 and <= the compute-unit count) and is large (logits, batch x query heads x max_seq_len x 4 bytes, of more than 7 MiB;
- * 9 MiB for a focal layer -- below that two launches that park the logits in the workspace are faster and
+ * 8 MiB for a focal layer -- below that two launches that park the logits in the workspace are faster and
  * wait for nothing) this call and fastocr_focal_attn_score run as ONE kernel whose
  * workgroups -- at most one per compute unit -- wait for each other's softmax statistics, so
  * all of them must be on the chip together.  Launched alone on the GPU (any number of calls in

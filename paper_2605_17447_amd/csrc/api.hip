@@ -476,7 +476,7 @@ static int check_qo(const fastocr_kv_view *kv, const void *q, const void *out, f
 //                      64/8: 12 x 4096 (13.2) 48.6 / 49.4; head_dim 64, 64/8: 12 x 4096 32.2 / 32.7
 //   ragged and paged   28/4, 12 sequences of up to 5000: scoring 25.4 / 16.7, layer and top-k 42.4 / 32.0 (the host does not know
 //                      the lengths, only the longest: the same lines)
-constexpr int64_t kParkScore = 7 << 20, kParkLayer = 9 << 20;        // (a layer with and without its top-k: the same form, the same bits)
+constexpr int64_t kParkScore = 7 << 20, kParkLayer = 8 << 20;        // (a layer with and without its top-k: the same form, the same bits)
 
 static bool select_inside() { return g_tune_select_fused.load(std::memory_order_relaxed) != 0; }
 
