@@ -259,9 +259,23 @@ static int f32_ranges(int op, const Shape &s, int num_cu, int blocks)
     return uneven && 2 * blocks >= (op == FASTOCR_OP_FOCAL_SCORE ? 3 : 4) * finer ? finer : n;
 }
 
+// Dense attention of bf16 caches over a list so short that one eight-wave workgroup per stream, which writes the output itself, is
+// done before partials and their merge would be: a launch less against one compute unit's load path (us, ranges and merge / one:
+// head_dim 128, 4 streams of 8 / 12 / 16 tiles 7.0 / 5.0, 7.0 / 5.9, 7.2 / 7.7; 32 streams 7.7 / 6.0, 7.7 / 7.2, 7.8 / 8.5; 64 of
+// 12 / 16 / 20 8.3 / 7.5, 8.9 / 8.9, 9.7 / 10.2; 96 of 16 / 24 / 32 10.5 / 9.3, 12.0 / 11.9, 14.0 / 14.9; 128 of 16 / 32 / 40
+// 12.1 / 9.6, 17.3 / 16.4, 19.0 / 18.3, but lists of 5 .. 40 14.8 / 15.1; head_dim 64, 8 and 32 streams of 8 / 12 7.8 / 7.2,
+// 7.9 / 8.0 and 8.1 / 7.6, 8.0 / 8.3; 128 of 16 / 24 9.9 / 9.3, 10.6 / 10.6).
+static bool dense_in_one(const Shape &s, int ntile, int num_cu)
+{
+    const int streams = s.batch * s.kv.n_kv_heads;
+    if (s.kv.head_dim == 64) return ntile <= (2 * streams >= num_cu ? 24 : 8);
+    return ntile <= (2 * streams >= num_cu ? 32 : (8 * streams >= 3 * num_cu ? 24 : (4 * streams >= num_cu ? 16 : 12)));
+}
+
 // replay: 0 / 1 = as if "graph_replay" were that, -1 = the tuning's value.  *partials (if given) is set
-// when the choice only holds as partials in the workspace followed by the merge kernel.
-static int choose_splits(int op, const Shape &s, int max_positions, bool *partials = nullptr, int replay = -1)
+// when the choice only holds as partials in the workspace followed by the merge kernel.  parks: ranges of the kernel that parks its
+// logits, which a second launch follows anyway.
+static int choose_splits(int op, const Shape &s, int max_positions, bool *partials = nullptr, int replay = -1, bool parks = false)
 {
     if (partials) *partials = false;
     if (replay < 0) replay = g_tune_graph_replay.load(std::memory_order_relaxed);
@@ -336,6 +350,7 @@ static int choose_splits(int op, const Shape &s, int max_positions, bool *partia
         // a chip of streams exists, one eight-wave workgroup per stream writes the final output
         // itself (no partials, no merge kernel -- a second launch costs more than it saves here)
         if (fast && op == FASTOCR_OP_SPARSE_DECODE_ATTN && (2 * streams >= kNumCU || ntile <= 64)) nsplit = 1;
+        if (fast && op == FASTOCR_OP_DENSE_DECODE_ATTN && !parks && dense_in_one(s, ntile, kNumCU)) nsplit = 1;
     }
     if (nsplit > by_work) nsplit = by_work;
     if (nsplit > 256) nsplit = 256;
@@ -422,7 +437,7 @@ size_t fastocr_workspace_bytes(int op, const fastocr_kv_view *kv, const fastocr_
             const size_t streams = (size_t)s.batch * s.kv.n_kv_heads, G = s.n_q_heads / s.kv.n_kv_heads;
             const size_t by_work = (size_t)std::min(256, std::max(1, (bv->max_seq_len + 127) / 128));
             size_t rows = G * std::min(streams * by_work, std::max(streams, (size_t)plan_cu_count()));
-            rows = std::max(rows, G * streams * (size_t)choose_splits(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len));
+            rows = std::max(rows, G * streams * (size_t)choose_splits(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len, nullptr, -1, true));
             need = std::max(need, round256(focal_parked_workspace_bytes(s, rows) + 256));
         }
         const size_t fused = focal_fused_workspace_bytes(s, plan_cu_count());
@@ -706,7 +721,7 @@ static int focal_attn_score_impl(const fastocr_kv_view *kv, const fastocr_batch_
     }
     if (parks_by_head(s) && !apart && mode != 0) {
         const bool hand_on = defer && deferred && !fuse && merge_shares_topk(s);
-        const int nsplit = choose_splits(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len);
+        const int nsplit = choose_splits(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len, nullptr, -1, true);
         const hipError_t e = launch_focal_parked(s, q, scale, out, scores, lse, img_mass, ws, nsplit, (hipStream_t)hip_stream,
                                                  fuse ? select : nullptr, hand_on ? defer : nullptr);
         if (fused) *fused = fuse;
