@@ -129,6 +129,10 @@ hipError_t launch_score(const Shape &s, const void *q, float scale, float *score
                         float *img_mass, void *ws, int nsplit, hipStream_t stream, int finish_kid = K_SCORE_FINALIZE,
                         const SelectArgs *select = nullptr);
 
+// Where a row's parked logits are read for the tokens p .. p + 3 (p a multiple of 4): past the pitch its last four, which nobody uses.
+// A batch of empty sequences alone has a pitch of 0: its reads meet the statistics, which follow the logits and are at least as large.
+__host__ __device__ inline int parked_token(int p, int64_t pitch) { return max(0, min(p, (int)pitch - 4)); }
+
 struct CombineArgs;
 bool parks_by_head(const Shape &s);    // the matrix-core kernels of attn.hip park this shape's logits
 // A focal layer of a bf16 cache as two launches that wait for nothing (parks_by_head).  nsplit: that of dense attention.

@@ -229,7 +229,7 @@ __device__ __forceinline__ void parked_scores(const BatchDev &bv, int b, int blk
     const int t = threadIdx.x & 255, tq = t & 15, hg = t >> 4, wave = t >> 6;
     const int64_t bh0 = (int64_t)b * Hq;
     const int p0 = blk * kFinTokens + 4 * tq;                    // tokens of the sequence
-    const int at = min(p0, (int)pitch - 4);                      // inside the pitch
+    const int at = parked_token(p0, pitch);
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int h0 = hg; h0 < Hq + hg; h0 += 16 * NU) {             // (every lane walks every round)
         f32x4 l[NU];

@@ -12,7 +12,7 @@ from util import TinyCase, as_f64, f32_to_bf16_bits
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
-    from gpu_util import DEV, check_out, check_scores, paged_twin, problem_from_case, to_np
+    from gpu_util import DEV, GpuProblem, check_out, check_scores, paged_twin, problem_from_case, to_np
 
 
 @pytest.fixture
@@ -128,3 +128,27 @@ def test_replayed_from_a_graph_next_to_eager_calls():
                 assert all(torch.equal(x, y) for x, y in zip(a[:4], e[:4]))
         finally:
             fb.set_tuning("select_fused", 0)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d", [(28, 4, 128), (64, 8, 64), (5, 1, 128)])
+def test_a_batch_of_empty_sequences_alone(Hq, Hkv, d, finish_launches):
+    B = 3
+    k, v = (torch.randn((B, Hkv, 8, d), device=DEV).to(torch.bfloat16) for _ in range(2))
+    p = GpuProblem(k, v, torch.randn((B, Hq, d), device=DEV).to(torch.bfloat16), [0] * B, [0] * B, [0] * B, d ** -0.5)
+    assert p.batch.max_seq_len == 0
+    for q in (p, paged_twin(p, 4, 1)):
+        _, lse, mass = q.scores(want_lse=True, want_mass=True)
+        assert (lse == -float("inf")).all() and (mass == 0).all()
+        out, _, lse, mass = q.focal_attn(want_lse=True, want_mass=True)
+        assert (lse == -float("inf")).all() and (mass == 0).all() and (out == 0).all()
+        for inside in (0, 1):
+            fb.set_tuning("select_fused", inside)
+            try:
+                out, mass = torch.full_like(q.q, 3.0), torch.full((B,), 3.0, device=DEV)
+                idx, cnt = torch.zeros((B, 1), dtype=torch.int32, device=DEV), torch.full((B,), 3, dtype=torch.int32, device=DEV)
+                ws = q.ws(fb.OP_FOCAL_ATTN_SCORE_TOPK, 1)
+                fo.focal_attn_score_topk(q.cache, q.batch, q.q, q.scale, 0.1, out, torch.zeros((B, 0), device=DEV), idx, cnt, ws, img_mass=mass)
+            finally:
+                fb.set_tuning("select_fused", 0)
+            assert (cnt == 0).all() and (mass == 0).all() and (out == 0).all()
+        assert finish_launches(fb.KERNEL_PARKED_FINISH) > 0
