@@ -228,8 +228,7 @@ static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 
 // that the workspace query and the launch agree.
 // Pruned attention as partials over four-wave workgroups of one tile per wave: the finest cut
 // choose_splits ever makes of a short list.  *fits: such a cut leaves at most one workgroup per compute
-// unit (only then is it taken).  The value is capped at that and so monotone in the list's length:
-// it is what the workspace is sized for, whatever length the calls then have.
+// unit (only then is it taken).
 static int finest_splits(const Shape &s, int max_positions, bool *fits = nullptr)
 {
     const int streams = s.batch * s.kv.n_kv_heads;
@@ -358,18 +357,25 @@ static int choose_splits(int op, const Shape &s, int max_positions, bool *partia
     return nsplit;
 }
 
-// Partial rows (sequence, query head, range) to size a workspace for.  For fp32 caches on the matrix cores the most that
-// a call with this many sequences or fewer leaves (a call's own count goes up and down with the batch, by the rounding
-// of its range count, see f32_ranges): at most 2 CU workgroups with a row per query head of their group, or with one
+// Partial rows (sequence, query head, range) to size a workspace for: the most that a call with this many sequences or fewer, as long or
+// shorter, leaves (a call's own count goes up and down with both, by the rounding of its range count).
+// bf16 on the matrix cores: ranges of at least four tiles that fill the chip at most once (scoring, from a quarter of a chip of streams on:
+// twice), or one range per stream.
+// fp32 on the matrix cores (see f32_ranges): at most 2 CU workgroups with a row per query head of their group, or with one
 // head per group 3.4 CU of them, or three ranges of up to 1.7 CU streams, or one range per sequence.  That is at most 8192
 // rows of 256 CUs and 16 heads, 4.3 MB at head_dim 128, unless the batch itself has more, so every shape whose single
 // ranges fit the static scratch is served from it.
 static size_t partial_rows(int op, const Shape &s, int max_positions, int nsplit)
 {
     const size_t heads = (size_t)s.batch * s.n_q_heads;
-    if (!s.fast32 || g_tune_splits[op].load(std::memory_order_relaxed) > 0) return heads * nsplit;
-    const size_t by_work = (size_t)std::min(256, std::max(1, (max_positions + 63) / 64));
+    if (!(s.fast || s.fast32) || g_tune_splits[op].load(std::memory_order_relaxed) > 0) return heads * nsplit;
     const size_t cus = (size_t)plan_cu_count(), Hkv = (size_t)s.kv.n_kv_heads;
+    if (s.fast) {
+        const size_t streams = s.batch * Hkv, by_work = (size_t)std::min(256, std::max(1, (max_positions + 127) / 128));
+        const size_t filled = op == FASTOCR_OP_FOCAL_SCORE && 4 * streams > cus ? 2 * cus : cus;
+        return s.n_q_heads / Hkv * std::min(streams * by_work, std::max(streams, filled));
+    }
+    const size_t by_work = (size_t)std::min(256, std::max(1, (max_positions + 63) / 64));
     size_t filled = 2 * cus / Hkv;                                        // sequences times ranges
     if ((size_t)s.n_q_heads == Hkv) {
         filled = 34 * cus / 10 / Hkv;
@@ -433,25 +439,16 @@ size_t fastocr_workspace_bytes(int op, const fastocr_kv_view *kv, const fastocr_
             need = need > one ? need : one;
         }
         if (parks_by_head(s)) {
-            // the two-launch form, at the most rows of any batch up to this one (ranges fill the chip at most once)
-            const size_t streams = (size_t)s.batch * s.kv.n_kv_heads, G = s.n_q_heads / s.kv.n_kv_heads;
-            const size_t by_work = (size_t)std::min(256, std::max(1, (bv->max_seq_len + 127) / 128));
-            size_t rows = G * std::min(streams * by_work, std::max(streams, (size_t)plan_cu_count()));
-            rows = std::max(rows, G * streams * (size_t)choose_splits(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len, nullptr, -1, true));
+            const int nsplit = choose_splits(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len, nullptr, -1, true);
+            const size_t rows = partial_rows(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len, nsplit);
             need = std::max(need, round256(focal_parked_workspace_bytes(s, rows) + 256));
         }
         const size_t fused = focal_fused_workspace_bytes(s, plan_cu_count());
         return fused > 0 ? std::max(need, round256(fused + 256)) : need;
     }
-    // Pruned attention (bf16): sized for the finest cut as well, whether or not "graph_replay" asks for it.  That cut is
-    // monotone in the list's length and as fine as any that is merged inside the launch (whose own count falls from four
-    // ranges to three after 32 tiles), so a size taken with a larger kmax (or none) also covers.
+    // (pruned attention: whatever "graph_replay" asks for, and a size taken with a larger kmax, or none, also covers)
     const int positions = op == FASTOCR_OP_SPARSE_DECODE_ATTN ? sparse_positions(bv, kmax) : bv->max_seq_len;
-    int nsplit = choose_splits(op, s, positions, nullptr, 0);
-    if (op == FASTOCR_OP_SPARSE_DECODE_ATTN && s.fast && g_tune_splits[op].load(std::memory_order_relaxed) <= 0) {
-        const int finest = finest_splits(s, positions);
-        nsplit = nsplit > finest ? nsplit : finest;
-    }
+    const int nsplit = choose_splits(op, s, positions, nullptr, 0);
     if (op == FASTOCR_OP_FOCAL_SCORE) {
         // sized for either scoring path, so that the choice can be made at launch
         size_t need = score_workspace_bytes(s, partial_rows(op, s, positions, nsplit));

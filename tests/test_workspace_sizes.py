@@ -61,9 +61,32 @@ def test_a_size_for_a_batch_covers_fewer_sequences(need):
                     _never_shrinks((f"{op} fp32 {heads} d={d} batch {B}, {n} image tokens", need(op, fb.F32, d, heads, B, n + 60, n, 500))
                                    for B in range(1, 700, 3))
                 if heads != (5, 5):
-                    # (the scoring statistics alone, at most a few KB, are not monotone: sizes from 64 sequences on)
                     _never_shrinks((f"focal bf16 {heads} d={d} batch {B}, {n} image tokens", need("focal", fb.BF16, d, heads, B, n + 60, n))
                                    for B in range(1, 256, 5))
+
+
+@pytest.mark.parametrize("op", list(OPS))
+def test_a_bf16_size_for_a_batch_covers_fewer_sequences(need, op):
+    batches = list(range(1, 140)) + [160, 192, 255, 256, 257, 300, 511, 512, 513, 900]
+    for heads in HEADS:
+        for d in (128, 64):
+            for n in (33, 150, 300, 1000, 5000, 17000):
+                _never_shrinks((f"{op} {heads} d={d} batch {B}, {n} tokens", need(op, fb.BF16, d, heads, B, n, n - 20, 500)) for B in batches)
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_the_static_scratch_serves_every_bf16_group_size(d):
+    # dense attention of up to a chip of streams (256 compute units, 16 heads a group), or more of single ranges that fit
+    lib = fb.load_library()
+    for G in (1, 2, 5, 7, 8, 16):
+        for Hkv in (1, 2, 4, 8, 16):
+            for B in (1, 2, 3, 7, 16, 17, 23, 40, 100, 250):
+                if G * Hkv > 256 or B * G * Hkv > 16000:
+                    continue
+                for S in (64, 500, 1000, 4000, 20000):
+                    kv, bv = _kv(fb.BF16, Hkv=Hkv, d=d, S=S), _bv(B, S, S // 2)
+                    n = lib.fastocr_workspace_bytes(fb.OP_DENSE_DECODE_ATTN, ctypes.byref(kv), ctypes.byref(bv), G * Hkv, 0)
+                    assert 0 < n <= fb.STATIC_SCRATCH_BYTES, (G, Hkv, B, S, n)
 
 
 def test_the_static_scratch_serves_every_fp32_group_size():
