@@ -233,8 +233,8 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    // (kParked, kLogits: a finite start, so that keys whose logits are all -inf leave weights of 0 behind)
-    float m = PARK ? kMinusHuge : -INFINITY, zl = 0.f, zi = 0.f;        // zi: the image tokens' part of zl
+    // (the lowest finite start: keys whose logits are all -inf leave weights of 0 behind, not the -inf - -inf of a first such tile)
+    float m = kLowest, zl = 0.f, zi = 0.f;        // zi: the image tokens' part of zl
     f32x4 acc[PV ? NACC : 1];
 #pragma unroll
     for (int t = 0; t < (PV ? NACC : 1); ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -297,7 +297,7 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
 #pragma unroll
         for (int e = 1; e < 8; ++e) mx = fmaxf(mx, s[e]);
         mx = rows_max(mx);
-        const float m_new = fmaxf(m, mx);          // finite: every tile holds a valid position
+        const float m_new = fmaxf(m, mx);
         const float alpha = fast_exp2(m - m_new);
         float p[8], ps = 0.f;
 #pragma unroll

@@ -32,7 +32,6 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kF32Tile = 16;       // tokens per wave tile
 constexpr int kF32Waves = 4;
-constexpr float kLowest = -3.402823466e+38f;
 constexpr double kRound = 6755399441055744.0;      // 1.5 * 2^52
 
 __device__ __forceinline__ f32x4 stream_load_f32(const float *p)

@@ -222,6 +222,8 @@ __device__ __forceinline__ u32x4 stream_load(const uint16_t *p)
 
 // Finite stand-in for "no logit yet": keeps 2^(m - m') free of inf - inf.
 constexpr float kMinusHuge = -1.0e30f;
+// The same where every finite logit has to keep its weight.
+constexpr float kLowest = -3.402823466e38f;
 
 // (max, sum-exp) of two disjoint sets of base-2 logits -> of their union
 __device__ __forceinline__ void softmax_merge(float &m, float &z, float mo, float zo)

@@ -160,7 +160,7 @@ __device__ __forceinline__ void parked_stats(const float *__restrict__ part_ml, 
 {
     const int tq = threadIdx.x & 15;
 #pragma unroll
-    for (int u = 0; u < NU; ++u) { M[u] = kMinusHuge; Z[u] = 0.f; Zi[u] = 0.f; }
+    for (int u = 0; u < NU; ++u) { M[u] = kLowest; Z[u] = 0.f; Zi[u] = 0.f; }
     for (int s0 = 0; s0 < nsplit; s0 += 16 * NS) {
         float mm[NU][NS], zz[NU][NS], ii[NU][NS];
 #pragma unroll
@@ -171,7 +171,7 @@ __device__ __forceinline__ void parked_stats(const float *__restrict__ part_ml, 
                 const int s = s0 + 16 * k + tq;
                 const int64_t at = row + min(s, nsplit - 1);
                 const float2 ml = *reinterpret_cast<const float2 *>(part_ml + 2 * at);
-                mm[u][k] = s < nsplit ? ml.x : kMinusHuge;
+                mm[u][k] = s < nsplit ? ml.x : kLowest;
                 zz[u][k] = s < nsplit ? ml.y : 0.f;
                 ii[u][k] = MASS ? (s < nsplit ? part_zi[at] : 0.f) : 0.f;
             }
