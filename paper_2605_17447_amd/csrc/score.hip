@@ -264,9 +264,9 @@ __device__ __forceinline__ void parked_scores(const BatchDev &bv, int b, int blk
     }
 }
 
-// Image mass of sequence b by 256 threads of a workgroup all of which call.
+// Image mass of sequence b by 256 threads of a workgroup all of which call: the sum of its scores, no number where they are none.
 template <int NU, int NS>
-__device__ __forceinline__ void parked_mass(int b, int Hq, const float *__restrict__ part_ml, const float *__restrict__ part_zi, int nsplit,
+__device__ __forceinline__ void parked_mass(const BatchDev &bv, int b, int Hq, const float *__restrict__ part_ml, const float *__restrict__ part_zi, int nsplit,
                                             float *__restrict__ img_mass, float *sm)
 {
     const int t = threadIdx.x & 255, hg = t >> 4;
@@ -275,12 +275,12 @@ __device__ __forceinline__ void parked_mass(int b, int Hq, const float *__restri
         float M[NU], Z[NU], Zi[NU];
         parked_stats<NU, NS, true>(part_ml, part_zi, (int64_t)b * Hq, h0, Hq, nsplit, M, Z, Zi);
 #pragma unroll
-        for (int u = 0; u < NU; ++u) sum += h0 + 16 * u < Hq && Z[u] > 0.f ? Zi[u] / Z[u] : 0.f;
+        for (int u = 0; u < NU; ++u) sum += h0 + 16 * u < Hq ? Zi[u] / Z[u] : 0.f;
     }
     sum = rows_sum(sum);
     if (threadIdx.x < 256 && (t & 63) == 0) sm[t >> 6] = sum;
     __syncthreads();
-    if (threadIdx.x == 0) img_mass[b] = ((sm[0] + sm[1]) + (sm[2] + sm[3])) / (float)Hq;
+    if (threadIdx.x == 0) img_mass[b] = seq_geom(bv, b).N > 0 ? ((sm[0] + sm[1]) + (sm[2] + sm[3])) / (float)Hq : 0.f;
 }
 
 template <int NU, int NS>
@@ -294,7 +294,7 @@ __global__ __launch_bounds__(kFinThreads) void parked_finish_kernel(
     __shared__ __align__(16) float sm_o[1024];
     const int b = blockIdx.y, blk = blockIdx.x;
     if (blk < nblk) parked_scores<NU, NS, false>(bv, b, blk, Hq, logits, pitch, part_ml, nsplit, scores, lse, sm_o);
-    else if (img_mass && blk == nblk) parked_mass<NU, NS>(b, Hq, part_ml, part_zi, nsplit, img_mass, sm_max);
+    else if (img_mass && blk == nblk) parked_mass<NU, NS>(bv, b, Hq, part_ml, part_zi, nsplit, img_mass, sm_max);
     else combine_wide_body<uint16_t>(part_o, part_ml, nsplit, d, out, nullptr, nullptr, 1, blk - nblk - (img_mass ? 1 : 0), b, Hq,
                                      CombineShared<uint16_t>{sm_max, sm_z, sm_o});
 }
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(kFinSelThreads) void parked_select_kernel(
     __shared__ int s_last;
     const int b = blockIdx.y, wg = blockIdx.x;
     if (wg >= nwg) {
-        if (img_mass && wg == nwg) parked_mass<4, 4>(b, Hq, part_ml, part_zi, nsplit, img_mass, sm_max);
+        if (img_mass && wg == nwg) parked_mass<4, 4>(bv, b, Hq, part_ml, part_zi, nsplit, img_mass, sm_max);
         else combine_wide_body<uint16_t>(part_o, part_ml, nsplit, d, out, nullptr, nullptr, 1, wg - nwg - (img_mass ? 1 : 0), b, Hq,
                                          CombineShared<uint16_t>{sm_max, sm_z, sm_o});
         return;

@@ -152,3 +152,19 @@ def test_a_batch_of_empty_sequences_alone(Hq, Hkv, d, finish_launches):
                 fb.set_tuning("select_fused", 0)
             assert (cnt == 0).all() and (mass == 0).all() and (out == 0).all()
         assert finish_launches(fb.KERNEL_PARKED_FINISH) > 0
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_a_nan_reaches_the_image_mass_of_its_sequence(d):
+    """A key that is no number, of the image or of the text: the scores of its sequence are none and so is their sum, the other sequences' stay."""
+    case = TinyCase(seed=d, B=4, Hq=16, Hkv=2, d=d, n_vis=[300, 300, 0, 300], pre=[9, 9, 3, 9], post=[70, 70, 50, 70], dtype="bf16")
+    clean = problem_from_case(case)
+    want_sc, _, want = clean.scores(want_mass=True)
+    nan = f32_to_bf16_bits(np.array([np.nan], np.float32))[0]
+    case.k[0, 1, 100, 3] = nan                                # image
+    case.k[1, 0, 350, 3] = nan                                # text
+    case.k[2, 0, 20, 3] = nan                                 # a sequence without an image: a sum of nothing
+    p = problem_from_case(case)
+    for sc, mass in ((p.scores(want_mass=True)[::2]), (p.focal_attn(want_mass=True)[1::2])):
+        assert torch.isnan(sc[:2, :300]).all() and torch.isnan(mass[:2]).all()
+        assert mass[2] == 0 and torch.equal(mass[3], want[3]) and torch.equal(sc[3], want_sc[3])
