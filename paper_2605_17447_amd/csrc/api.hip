@@ -271,6 +271,32 @@ static bool dense_in_one(const Shape &s, int ntile, int num_cu)
     return ntile <= (2 * streams >= num_cu ? 32 : (8 * streams >= 3 * num_cu ? 24 : (4 * streams >= num_cu ? 16 : 12)));
 }
 
+// Ranges per stream of the bf16 streaming kernels (dense attention, scoring, kernels that park their logits): about one workgroup of four waves per
+// compute unit, rounded down (see choose_splits), except where streams of unlike lengths -- the host knows the longest only -- or an uneven
+// last round would leave compute units idle.  Measured in us, "equal": all sequences as long as the longest, "unlike": an eighth to all of that,
+// the mean of three to five batches.
+static int even_ranges(int op, const Shape &s, int ntile, int num_cu, bool parks)
+{
+    const int streams = s.batch * s.kv.n_kv_heads;
+    if (streams < 1) return 1;
+    int n = std::max(1, num_cu / streams);
+    if (op == FASTOCR_OP_FOCAL_SCORE) {
+        // Scoring holds half the loads per workgroup (no V): two workgroups per compute unit where a stream gets only a few ranges
+        // (one / two per compute unit: head_dim 64, 96 streams of 4288 tokens 19.1 / 16.3, 144 of 1216 12.4 / 10.4; head_dim 128, 144 of 1192
+        // 16.0 / 14.6, 16 of 4288 9.3 / 9.6), doubled while a range has more than 1024 tokens
+        // (scoring in two launches, without / with the doubling, equal then unlike: 64/8 heads, 22 x 12000 141.8 / 120.5, 108.7 / 86.0; 28/4, 36 x 6000 54.8 / 53.7, 42.5 / 36.8;
+        // head_dim 64, 64/8, 36 x 8000 104.5 / 80.6, 85.5 / 65.1; 8/1, 176 x 12000 158.4 / 136.6, 124.2 / 97.5)
+        if (4 * streams > num_cu) n = std::max(1, 2 * num_cu / streams);
+        while (ntile > 32 * n) n *= 2;
+    }
+    // A little more than a chip of streams, in kernels that leave partials anyway, in halves (one range / two, equal then unlike: 28/4 heads, 72 x 1000,
+    // scoring 26.0 / 23.0, 20.3 / 18.4, focal layer 43.2 / 38.4, 34.2 / 26.7; 96 x 500, 17.0 / 15.9, 14.0 / 12.7, 28.5 / 28.3, 23.2 / 22.2;
+    // short lists the other way: 72 x 200, layer 16.7 / 16.7, 14.7 / 15.4; and so do streams near two chips: head_dim 64, 32/8, 60 x 600, layer
+    // 23.8 / 27.4)
+    if ((parks || op == FASTOCR_OP_FOCAL_SCORE) && streams > num_cu && 2 * streams <= 3 * num_cu && ntile >= 16) n = std::max(n, 2);
+    return n;
+}
+
 // replay: 0 / 1 = as if "graph_replay" were that, -1 = the tuning's value.  *partials (if given) is set
 // when the choice only holds as partials in the workspace followed by the merge kernel.  parks: ranges of the kernel that parks its
 // logits, which a second launch follows anyway.
@@ -340,10 +366,7 @@ static int choose_splits(int op, const Shape &s, int max_positions, bool *partia
         // 28/4 heads, 12 x 1024 image tokens 12.5 / 11.0, 12 x 4096 26.3 / 21.6, 12 x 16384 81.6 / 64.7; 16/2 heads, 12 x 4096 17.5 / 14.4,
         // 12 x 16384 47.1 / 35.4; head_dim 64, 32/8 heads, 12 x 4096 28.9 / 22.1; 64/8, 11 x 2048 27.2 / 21.5, where five ranges, 440
         // workgroups, take 21.6).
-        // Scoring holds half the loads per workgroup (no V): two workgroups per compute unit where a stream gets only a few ranges
-        // (one / two per compute unit: head_dim 64, 96 streams of 4288 tokens 19.1 / 16.3, 144 of 1216 12.4 / 10.4; head_dim 128, 144 of 1192
-        // 16.0 / 14.6, 16 of 4288 9.3 / 9.6).
-        else if (fast) nsplit = (op == FASTOCR_OP_FOCAL_SCORE && 4 * streams > kNumCU ? 2 * kNumCU : kNumCU) / (streams > 0 ? streams : 1);
+        else if (fast) nsplit = even_ranges(op, s, ntile, kNumCU, parks);
         else nsplit = (target_wg + streams - 1) / (streams > 0 ? streams : 1);
         // pruned attention is short: when eight waves get at most eight tiles each, or at least half
         // a chip of streams exists, one eight-wave workgroup per stream writes the final output
@@ -365,15 +388,17 @@ static int choose_splits(int op, const Shape &s, int max_positions, bool *partia
 // head per group 3.4 CU of them, or three ranges of up to 1.7 CU streams, or one range per sequence.  That is at most 8192
 // rows of 256 CUs and 16 heads, 4.3 MB at head_dim 128, unless the batch itself has more, so every shape whose single
 // ranges fit the static scratch is served from it.
-static size_t partial_rows(int op, const Shape &s, int max_positions, int nsplit)
+static size_t partial_rows(int op, const Shape &s, int max_positions, int nsplit, bool parks = false)
 {
     const size_t heads = (size_t)s.batch * s.n_q_heads;
     if (!(s.fast || s.fast32) || g_tune_splits[op].load(std::memory_order_relaxed) > 0) return heads * nsplit;
     const size_t cus = (size_t)plan_cu_count(), Hkv = (size_t)s.kv.n_kv_heads;
     if (s.fast) {
-        const size_t streams = s.batch * Hkv, by_work = (size_t)std::min(256, std::max(1, (max_positions + 127) / 128));
-        const size_t filled = op == FASTOCR_OP_FOCAL_SCORE && 4 * streams > cus ? 2 * cus : cus;
-        return s.n_q_heads / Hkv * std::min(streams * by_work, std::max(streams, filled));
+        const size_t streams = s.batch * Hkv, tiles = (size_t)(max_positions + 31) / 32, by_work = std::min<size_t>(256, std::max<size_t>(1, (tiles + 3) / 4));
+        size_t filled = std::max(streams, cus);                           // see even_ranges
+        if (op == FASTOCR_OP_FOCAL_SCORE) filled = std::max({filled, 4 * streams > cus ? 2 * cus : 0, streams * (tiles / 16)});
+        if (op == FASTOCR_OP_FOCAL_SCORE || parks) { if (streams > cus) filled = std::max(filled, std::min(2 * streams, 3 * cus)); }
+        return s.n_q_heads / Hkv * std::min(streams * by_work, filled);
     }
     const size_t by_work = (size_t)std::min(256, std::max(1, (max_positions + 63) / 64));
     size_t filled = 2 * cus / Hkv;                                        // sequences times ranges
@@ -440,7 +465,7 @@ size_t fastocr_workspace_bytes(int op, const fastocr_kv_view *kv, const fastocr_
         }
         if (parks_by_head(s)) {
             const int nsplit = choose_splits(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len, nullptr, -1, true);
-            const size_t rows = partial_rows(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len, nsplit);
+            const size_t rows = partial_rows(FASTOCR_OP_DENSE_DECODE_ATTN, s, bv->max_seq_len, nsplit, true);
             need = std::max(need, round256(focal_parked_workspace_bytes(s, rows) + 256));
         }
         const size_t fused = focal_fused_workspace_bytes(s, plan_cu_count());

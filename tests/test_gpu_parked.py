@@ -78,6 +78,28 @@ def test_many_ranges(Hq, Hkv, B, n, finish_launches):
     _check(problem_from_case(case), finish_launches, f"{Hq}/{Hkv} {n}")
 
 
+# around the list lengths where a little more than a chip of streams is halved (481, 512 and 513 tokens) and where scoring doubles its ranges
+# (7 and 14 of 72 streams, 1 and 2 of 400)
+@pytest.mark.parametrize("Hq,Hkv,B,lengths", [(10, 10, 26, (480, 481, 512, 513)), (16, 8, 48, (512, 513)), (8, 8, 9, (7168, 7169)), (10, 10, 40, (1024, 1025))])
+def test_ranges_by_size(Hq, Hkv, B, lengths, finish_launches):
+    for S in lengths:
+        n = [S - 20] + [(S * (b % 7)) // 9 for b in range(1, B)]
+        case = TinyCase(seed=S, B=B, Hq=Hq, Hkv=Hkv, d=64 if B > 40 else 128, n_vis=n, pre=11, post=9, dtype="bf16")
+        p = problem_from_case(case)
+        ref_sc, ref_lse, ref_mass = oracle.focal_score(*p.oracle_args())
+        for mode in (1, 0):                                   # parked by its size or not, and always
+            fb.set_tuning("score_resident", mode)
+            try:
+                sc, lse, mass = p.scores(want_lse=True, want_mass=True)
+            finally:
+                fb.set_tuning("score_resident", 1)
+            check_scores(sc, ref_sc, p.vis_len, f"{S} scores")
+            assert np.allclose(lse.cpu().numpy(), ref_lse, rtol=2e-5, atol=2e-5) and np.allclose(mass.cpu().numpy(), ref_mass, atol=2e-5)
+        out, sc, _, _ = p.focal_attn()
+        check_out(out, oracle.decode_attn(*p.oracle_args())[0], f"{S} layer")
+        check_scores(sc, ref_sc, p.vis_len, f"{S} layer's scores")
+
+
 @pytest.mark.parametrize("d", [128, 64])
 def test_dead_keys(d, finish_launches):
     """Keys of logit -inf (whole tiles, a whole range, single ones): weight 0, nothing else touched."""
