@@ -294,6 +294,19 @@ static int even_ranges(int op, const Shape &s, int ntile, int num_cu, bool parks
     // short lists the other way: 72 x 200, layer 16.7 / 16.7, 14.7 / 15.4; and so do streams near two chips: head_dim 64, 32/8, 60 x 600, layer
     // 23.8 / 27.4)
     if ((parks || op == FASTOCR_OP_FOCAL_SCORE) && streams > num_cu && 2 * streams <= 3 * num_cu && ntile >= 16) n = std::max(n, 2);
+    // Dense attention of half a chip of streams to a whole one: one range each leaves up to half of the compute units idle and lasts as long as the
+    // longest sequence, two fill the chip unevenly.  Three or four, which fill two or three rounds, from the length on where unlike lists gain more
+    // than equal ones lose (one / two / three or four ranges, equal then unlike; 64/8 heads: 17 x 2700 35.1 / 44.5 / 35.2, 31.1 / 30.0 / 27.9;
+    // 17 x 12000 139 / 172 / 131, 120 / 92 / 94; 21 x 2700 38.1 / 46.3 / 42.1, 32.5 / 31.6 / 30.2; 21 x 6000 79.9 / 94.0 / 83.6, 66.0 / 63.4 / 57.0;
+    // 22 x 6000 82.8 / 94.2 / 86.2, 66.4 / 66.6 / 57.1; 22 x 16900 226 / 249 / 227, 185 / 164 / 152; 28 x 12000 200 / 210 / 211, 147 / 150 / 148;
+    // head_dim 64: 17 x 3300 25.1 / 33.0 / 26.5, 23.1 / 21.6 / 22.1; 17 x 6000 40.9 / 51.8 / 39.9, 37.4 / 35.0 / 33.0; and beyond three quarters of a
+    // chip 31 x 16900 165.5 / 160.1, 118.4 / 110.8, where head_dim 128 takes 260 / 267, 199 / 192 at 26 x 16900)
+    if (op == FASTOCR_OP_DENSE_DECODE_ATTN && !parks && 2 * streams > num_cu && streams <= num_cu) {
+        if (4 * streams > 3 * num_cu) n = s.kv.head_dim == 64 && ntile >= 512 ? 2 : 1;
+        else if (3 * streams > 2 * num_cu) n = ntile >= 384 ? 4 : 1;
+        else if (5 * streams > 3 * num_cu) n = ntile >= 192 ? 3 : 1;
+        else n = ntile >= (s.kv.head_dim == 64 ? 160 : 80) ? 3 : 1;
+    }
     return n;
 }
 
@@ -398,6 +411,7 @@ static size_t partial_rows(int op, const Shape &s, int max_positions, int nsplit
         size_t filled = std::max(streams, cus);                           // see even_ranges
         if (op == FASTOCR_OP_FOCAL_SCORE) filled = std::max({filled, 4 * streams > cus ? 2 * cus : 0, streams * (tiles / 16)});
         if (op == FASTOCR_OP_FOCAL_SCORE || parks) { if (streams > cus) filled = std::max(filled, std::min(2 * streams, 3 * cus)); }
+        else if (op == FASTOCR_OP_DENSE_DECODE_ATTN && 2 * streams > cus) filled = std::max(filled, 3 * cus);
         return s.n_q_heads / Hkv * std::min(streams * by_work, filled);
     }
     const size_t by_work = (size_t)std::min(256, std::max(1, (max_positions + 63) / 64));

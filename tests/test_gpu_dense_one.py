@@ -1,5 +1,5 @@
 """Dense attention of lists short enough for one workgroup per stream, and the ranges and merge just above: both sides of each
-limit against the oracle, ragged lists among them, the paged cache."""
+limit against the oracle, ragged lists among them, the paged cache.  Then the lengths from which half a chip of streams and more is cut."""
 import pytest
 import torch
 
@@ -35,3 +35,22 @@ def test_both_sides_of_the_limit(Hq, Hkv, d, B, tiles):
                 fb.kernel_timer_enable(fb.KERNEL_ATTN_COMBINE, 0)
             check_out(out, ref, f"{Hq}/{Hkv} d{d} x{B} {T} {what}")
             assert torch.cuda.get_device_properties(0).multi_processor_count != 256 or merges == int(extra > 0), (T, what, merges)
+
+
+# streams of 256 compute units, tiles of 32 tokens from which they are cut into three, four or (the last) two ranges
+@pytest.mark.parametrize("Hkv,d,B,tiles", [(8, 128, 17, 80), (8, 64, 18, 160), (10, 128, 16, 192), (16, 64, 12, 384), (10, 64, 24, 512)])
+def test_streams_that_do_not_fill_the_chip(Hkv, d, B, tiles):
+    for T in (32 * tiles - 32, 32 * tiles - 31):
+        n = [T - 50] + [(T * (b % 5)) // 16 for b in range(1, B)]
+        case = TinyCase(seed=tiles + B, B=B, Hq=Hkv, Hkv=Hkv, d=d, n_vis=n, pre=10, post=40, dtype="bf16")
+        p = problem_from_case(case)
+        ref, ref_lse = oracle.decode_attn(*p.oracle_args())
+        fb.kernel_timer_enable(fb.KERNEL_ATTN_COMBINE, 16)
+        try:
+            out, lse = p.dense(want_lse=True)
+            merges = len(fb.kernel_timer_read(fb.KERNEL_ATTN_COMBINE))
+        finally:
+            fb.kernel_timer_enable(fb.KERNEL_ATTN_COMBINE, 0)
+        check_out(out, ref, f"{Hkv} d{d} x{B} {T}")
+        assert torch.allclose(lse.double().cpu(), torch.from_numpy(ref_lse), rtol=2e-5, atol=2e-5)
+        assert torch.cuda.get_device_properties(0).multi_processor_count != 256 or merges == int(T > 32 * tiles - 32), (T, merges)
