@@ -533,7 +533,7 @@ static bool select_inside() { return g_tune_select_fused.load(std::memory_order_
 
 static bool parks(int mode, const Shape &s, int64_t limit)
 {
-    return mode == 1 && exchange_trusted() && parks_by_head(s) &&
+    return mode == 1 && parks_by_head(s) &&
            (int64_t)s.batch * s.n_q_heads * s.bv.max_seq_len * (int64_t)sizeof(float) <= limit;
 }
 

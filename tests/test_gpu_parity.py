@@ -636,19 +636,25 @@ def test_a_barrier_that_gives_up_poisons_the_result_and_leaves_the_library_usabl
         check_scores(sc, ref_sc, p.vis_len, "scores after a timed-out call")
         check_scores(sc2, ref_sc, p.vis_len, "one-pass scores after a timed-out call")
         check_out(out, ref_dense, "one-pass output after a timed-out call")
-        # left to itself (mode 1) the library no longer takes the single-kernel forms in this process:
-        # scoring runs as its two kernels (the finalize kernel is launched) until it is re-armed
+        # left to itself (mode 1) the library no longer takes the single-kernel forms in this process: scoring of a size that
+        # takes one (logits of more than 7 MiB) runs in two launches until it is re-armed
+        case = TinyCase(seed=501, B=2, Hq=28, Hkv=4, d=128, n_vis=[34000, 9000], pre=[12, 0], post=[30, 9], dtype="bf16")
+        p = problem_from_case(case)
+        ref_sc, _, _ = oracle.focal_score(*p.oracle_args())
+        finishing = (fb.KERNEL_SCORE_FINALIZE, fb.KERNEL_PARKED_FINISH)
         fb.set_tuning("score_resident", 1)
-        fb.kernel_timer_enable(fb.KERNEL_SCORE_FINALIZE, 4)
+        for k in finishing:
+            fb.kernel_timer_enable(k, 4)
         sc, _, _ = p.scores()
         check_scores(sc, ref_sc, p.vis_len, "scores by the separate kernels after a timed-out call")
-        assert len(fb.kernel_timer_read(fb.KERNEL_SCORE_FINALIZE)) == 1
+        assert sum(len(fb.kernel_timer_read(k)) for k in finishing) == 1
         fb.set_tuning("exchange_fallback", 0)
         sc, _, _ = p.scores()
         check_scores(sc, ref_sc, p.vis_len, "scores after re-arming")
-        assert len(fb.kernel_timer_read(fb.KERNEL_SCORE_FINALIZE)) == 0
+        assert sum(len(fb.kernel_timer_read(k)) for k in finishing) == 0
     finally:
         fb.kernel_timer_enable(fb.KERNEL_SCORE_FINALIZE, 0)
+        fb.kernel_timer_enable(fb.KERNEL_PARKED_FINISH, 0)
         fb.set_tuning("barrier_spin_us", 0)
         fb.set_tuning("score_resident", 1)
         fb.set_tuning("focal_fused", 1)

@@ -190,3 +190,26 @@ def test_a_nan_reaches_the_image_mass_of_its_sequence(d):
     for sc, mass in ((p.scores(want_mass=True)[::2]), (p.focal_attn(want_mass=True)[1::2])):
         assert torch.isnan(sc[:2, :300]).all() and torch.isnan(mass[:2]).all()
         assert mass[2] == 0 and torch.equal(mass[3], want[3]) and torch.equal(sc[3], want_sc[3])
+
+
+def test_a_process_that_no_longer_trusts_the_exchange_parks_as_before(finish_launches):
+    """The parked forms wait for nobody: a call of their size is the same launches after a wave of another form has given up waiting."""
+    case = TinyCase(seed=8, B=2, Hq=28, Hkv=4, d=128, n_vis=[900, 400], pre=[5, 0], post=[30, 9], dtype="bf16")
+    p = problem_from_case(case)
+    kmax = fo.keep_count(900, 0.05)
+    results = []
+    fb.kernel_timer_enable(fb.KERNEL_TOPK, 8)
+    fb.set_tuning("select_fused", 1)
+    try:
+        for distrust in (0, 1):
+            fb.set_tuning("exchange_fallback", distrust)
+            sc, idx = torch.zeros((2, 900), device=DEV), torch.zeros((2, kmax), dtype=torch.int32, device=DEV)
+            cnt = torch.zeros((2,), dtype=torch.int32, device=DEV)
+            fo.focal_score_topk(p.cache, p.batch, p.q, p.scale, 0.05, sc, idx, cnt, p.ws(fb.OP_FOCAL_SCORE_TOPK, kmax))
+            assert finish_launches(fb.KERNEL_PARKED_FINISH) == 1 and len(fb.kernel_timer_read(fb.KERNEL_TOPK)) == 0, distrust
+            results.append((sc, idx, cnt))
+        assert all(torch.equal(a, b) for a, b in zip(*results))
+    finally:
+        fb.set_tuning("exchange_fallback", 0)
+        fb.set_tuning("select_fused", 0)
+        fb.kernel_timer_enable(fb.KERNEL_TOPK, 0)
