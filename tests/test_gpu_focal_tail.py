@@ -21,9 +21,17 @@ def _layer(p, tau, mass):
     return out, sc, idx, cnt
 
 
+@pytest.fixture(params=[1, 2], ids=["by size", "single kernel"])
+def fused(request):
+    """The library's choice, which parks the logits at these sizes, and the one-pass kernel (fp32 caches: the same form twice)."""
+    fb.set_tuning("focal_fused", request.param)
+    yield request.param
+    fb.set_tuning("focal_fused", 1)
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64)])
 @pytest.mark.parametrize("B,apart", [(20, 0), (21, 1)])          # 1280 and 1344 merges of 64 heads, 256 compute units
-def test_many_merges_keep_their_own_launch(dtype, d, B, apart):
+def test_many_merges_keep_their_own_launch(dtype, d, B, apart, fused):
     n = [40 + 7 * (b % 9) for b in range(B)]
     case = TinyCase(seed=700 + d + B, B=B, Hq=64, Hkv=8, d=d, n_vis=n, pre=[b % 5 for b in range(B)], post=[b % 11 for b in range(B)], dtype=dtype)
     p = problem_from_case(case)
@@ -46,7 +54,7 @@ def test_many_merges_keep_their_own_launch(dtype, d, B, apart):
 
 @pytest.mark.parametrize("dtype,d,Hq,Hkv,B", [("bf16", 128, 28, 4, 3), ("bf16", 64, 64, 8, 5), ("bf16", 128, 8, 1, 40),
                                               ("f32", 128, 28, 4, 3), ("f32", 64, 4, 1, 7)])
-def test_the_image_mass_is_summed_by_the_shared_launch(dtype, d, Hq, Hkv, B):
+def test_the_image_mass_is_summed_by_the_shared_launch(dtype, d, Hq, Hkv, B, fused):
     # ragged, one sequence without an image, one of a single image token; up to several partials of mass per sequence
     n = [(997 * (b + 1)) % 2300 + 3 for b in range(B)]
     n[1], n[2] = 0, 1

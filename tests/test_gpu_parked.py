@@ -213,3 +213,31 @@ def test_a_process_that_no_longer_trusts_the_exchange_parks_as_before(finish_lau
         fb.set_tuning("exchange_fallback", 0)
         fb.set_tuning("select_fused", 0)
         fb.kernel_timer_enable(fb.KERNEL_TOPK, 0)
+
+
+# 7 MiB of logits of 4 x 64 heads are 7168 tokens, 8 MiB 8192
+@pytest.mark.parametrize("call,S,parked", [("score", 7168, True), ("score", 7169, False), ("layer", 8192, True), ("layer", 8193, False)])
+def test_both_sides_of_the_size_rule(call, S, parked):
+    case = TinyCase(seed=S, B=4, Hq=64, Hkv=8, d=64, n_vis=[S - 40, S - 900, 33, 5000], pre=[10, 3, 5, 0], post=[30, 7, 9, 50], dtype="bf16")
+    p = problem_from_case(case)
+    assert p.batch.max_seq_len == S
+    ref_sc, ref_lse, ref_mass = oracle.focal_score(*p.oracle_args())
+    kinds = (fb.KERNEL_SCORE_LOGITS, fb.KERNEL_FOCAL_FUSED, fb.KERNEL_PARKED_FINISH, fb.KERNEL_ATTN_COMBINE)
+    for k in kinds:
+        fb.kernel_timer_enable(k, 16)
+    try:
+        if call == "score":
+            sc, lse, mass = p.scores(want_lse=True, want_mass=True)
+            want = (1, 0, int(parked), 0)
+        else:
+            out, sc, lse, mass = p.focal_attn(want_lse=True, want_mass=True)
+            want = (0, 1, 0, 1)
+        got = tuple(len(fb.kernel_timer_read(k)) for k in kinds)
+    finally:
+        for k in kinds:
+            fb.kernel_timer_enable(k, 0)
+    assert got == want or torch.cuda.get_device_properties(0).multi_processor_count != 256, got
+    check_scores(sc, ref_sc, p.vis_len, call)
+    assert np.allclose(lse.cpu().numpy(), ref_lse, rtol=2e-5, atol=2e-5) and np.allclose(mass.cpu().numpy(), ref_mass, atol=2e-5)
+    if call == "layer":
+        check_out(out, oracle.decode_attn(*p.oracle_args())[0], "output")

@@ -16,11 +16,17 @@ from util import TinyCase
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture(autouse=True)
-def _select_inside_the_launch():
+@pytest.fixture(autouse=True, params=[1, 2], ids=["by size", "single kernel"])
+def mode(request):
+    """Both launches the select runs inside: the one that finishes parked logits (1: the library's choice at these sizes) and the register-resident
+    kernels (2)."""
     fb.set_tuning("select_fused", 1)
-    yield
+    fb.set_tuning("score_resident", request.param)
+    fb.set_tuning("focal_fused", request.param)
+    yield request.param
     fb.set_tuning("select_fused", 0)
+    fb.set_tuning("score_resident", 1)
+    fb.set_tuning("focal_fused", 1)
 
 if torch.cuda.is_available():
     from gpu_util import DEV, GpuProblem, check_out, check_scores, problem_from_case
@@ -104,16 +110,14 @@ def test_select_inside_the_launch_paged_ragged_and_constant_scores():
 def test_the_separate_select_is_taken_when_it_must_be():
     case = TinyCase(seed=31, B=2, Hq=28, Hkv=4, d=128, n_vis=[1500, 900], pre=[4, 0], post=[30, 9], dtype="bf16")
     p = problem_from_case(case)
-    try:
-        fb.set_tuning("select_fused", 0)
-        _one_call_vs_separate(p, 0.05, "select_fused 0", expect_fused=False, rounds=2)
-        fb.set_tuning("select_fused", 1)
-        fb.set_tuning("score_resident", 0)
-        fb.set_tuning("focal_fused", 0)
-        _one_call_vs_separate(p, 0.05, "separate kernels", expect_fused=False, rounds=2)
-    finally:
-        fb.set_tuning("score_resident", 1)
-        fb.set_tuning("focal_fused", 1)
+    fb.set_tuning("select_fused", 0)
+    _one_call_vs_separate(p, 0.05, "select_fused 0", expect_fused=False, rounds=2)
+    fb.set_tuning("select_fused", 1)
+    fb.set_tuning("score_resident", 0)
+    fb.set_tuning("focal_fused", 0)
+    _one_call_vs_separate(p, 0.05, "separate kernels", expect_fused=False, rounds=2)
+    fb.set_tuning("score_resident", 1)
+    fb.set_tuning("focal_fused", 1)
     # fp32 cache: the plain kernels, then the stand-alone select
     case = TinyCase(seed=32, B=2, Hq=4, Hkv=2, d=64, n_vis=[300, 200], pre=[4, 0], post=[30, 9], dtype="f32")
     _one_call_vs_separate(problem_from_case(case), 0.05, "fp32", expect_fused=False, rounds=2)
@@ -144,7 +148,7 @@ def test_select_inside_the_launch_at_config4_size_is_repeatable():
 
 
 def test_select_inside_the_launch_replays_in_a_graph():
-    """A captured one-call focal layer (select inside the launch) keeps its exchange slot; every replay, with a new
+    """A captured one-call focal layer (select inside the launch; the single kernel keeps its exchange slot); every replay, with a new
     query and the previous replay's set as the warm start in place, must match the eager separate calls."""
     case = TinyCase(seed=820, B=3, Hq=28, Hkv=4, d=128, n_vis=[2100, 1700, 2500], pre=[10, 3, 0], post=[50, 30, 9], dtype="bf16")
     p = problem_from_case(case)

@@ -19,6 +19,16 @@ if torch.cuda.is_available():
     from gpu_util import DEV, check_out, check_scores, problem_from_case
 
 
+@pytest.fixture(autouse=True)
+def _single_kernel_forms():
+    """At these sizes the library's own choice waits for nobody; the slots are those of the forms that do."""
+    fb.set_tuning("score_resident", 2)
+    fb.set_tuning("focal_fused", 2)
+    yield
+    fb.set_tuning("score_resident", 1)
+    fb.set_tuning("focal_fused", 1)
+
+
 class _Run:
     """One problem's buffers and the three single-launch calls (+ top-k) on a given stream."""
 
@@ -68,8 +78,6 @@ def test_graph_replays_on_one_stream_next_to_eager_calls_on_another():
     b = _Run(TinyCase(seed=602, B=2, Hq=64, Hkv=8, d=128, n_vis=[1100, 1300], pre=[5, 0], post=[70, 20], dtype="bf16"), 0.1)
     timeouts_before = fb.exchange_timeouts()
     fb.set_tuning("splits_sparse", 3)                 # several ranges per stream: merged inside the launch
-    fb.set_tuning("score_resident", 2)
-    fb.set_tuning("focal_fused", 2)
     try:
         # each problem alone: the reference bits
         a.enqueue(); torch.cuda.synchronize(); want_a = a.results(); a.check_against_oracle("problem A alone")
@@ -96,8 +104,6 @@ def test_graph_replays_on_one_stream_next_to_eager_calls_on_another():
         assert fb.exchange_timeouts() == timeouts_before
     finally:
         fb.set_tuning("splits_sparse", 0)
-        fb.set_tuning("score_resident", 1)
-        fb.set_tuning("focal_fused", 1)
 
 
 def test_more_streams_than_exchange_slots_fall_back_to_the_separate_kernels():
@@ -106,9 +112,14 @@ def test_more_streams_than_exchange_slots_fall_back_to_the_separate_kernels():
     runs = [_Run(TinyCase(seed=700 + i, B=2, Hq=28, Hkv=4, d=128, n_vis=[700 + 13 * i, 500], pre=[4, 1], post=[30 + i, 9],
                           dtype="bf16"), 0.1) for i in range(4)]
     fb.set_tuning("splits_sparse", 2)
+    finishing = (fb.KERNEL_SCORE_FINALIZE, fb.KERNEL_PARKED_FINISH)         # launched by calls without a slot alone
+    for k in finishing:
+        fb.kernel_timer_enable(k, 256)
     try:
         streams = [torch.cuda.Stream() for _ in range(40)]
         torch.cuda.synchronize()
+        for st in streams:
+            fb.stream_release(st)                       # whatever earlier tests left on the pool's handles
         for rnd in range(10):
             for i, r in enumerate(runs):
                 r.clear()
@@ -118,7 +129,12 @@ def test_more_streams_than_exchange_slots_fall_back_to_the_separate_kernels():
             torch.cuda.synchronize()
             for i, r in enumerate(runs):
                 r.check_against_oracle(f"round {rnd}, stream {4 * rnd + i}")
+        assert 0 < sum(len(fb.kernel_timer_read(k)) for k in finishing) < 40
     finally:
+        for k in finishing:
+            fb.kernel_timer_enable(k, 0)
+        for st in streams:
+            fb.stream_release(st)
         fb.set_tuning("splits_sparse", 0)
 
 
