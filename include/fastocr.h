@@ -313,14 +313,14 @@ int fastocr_select_focal_layers(const float *ratio, int steps, int layers, int b
  */
 typedef enum {
     FASTOCR_KERNEL_SCORE_LOGITS = 0,   /* streams K: logits + per-split softmax statistics */
-    FASTOCR_KERNEL_SCORE_FINALIZE = 1,
+    FASTOCR_KERNEL_SCORE_FINALIZE = 1, /* scores from parked logits: fp32 caches, and bf16 shapes on the plain kernels */
     FASTOCR_KERNEL_TOPK = 2,
     FASTOCR_KERNEL_SPARSE_ATTN = 3,
     FASTOCR_KERNEL_DENSE_ATTN = 4,
     FASTOCR_KERNEL_ATTN_COMBINE = 5,
     FASTOCR_KERNEL_FOCAL_FUSED = 6,    /* one pass over K and V: attention partials + scores */
-    FASTOCR_KERNEL_PARKED_FINISH = 7,  /* scores from parked logits, where the library parks them by its size rule
-                                          (SCORE_FINALIZE: where it does because a single-kernel form is not to be had) */
+    FASTOCR_KERNEL_PARKED_FINISH = 7,  /* scores from logits that a matrix-core kernel parked (bf16), with the image mass, and for
+                                          a focal layer the merge of its output unless the top-k's launch does that */
     FASTOCR_KERNEL_COUNT = 8
 } fastocr_kernel;
 

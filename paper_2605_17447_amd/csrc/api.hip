@@ -596,8 +596,7 @@ static int focal_score_impl(const fastocr_kv_view *kv, const fastocr_batch_view 
         if (fused) *fused = fuse;
     } else {
         const bool selects = park && fuse;
-        e = launch_score(s, q, scale, scores, lse, img_mass, ws, nsplit, (hipStream_t)hip_stream,
-                         park ? K_PARKED_FINISH : K_SCORE_FINALIZE, selects ? select : nullptr);
+        e = launch_score(s, q, scale, scores, lse, img_mass, ws, nsplit, (hipStream_t)hip_stream, selects ? select : nullptr);
         if (fused) *fused = selects;
     }
     return e == hipSuccess ? FASTOCR_OK : FASTOCR_EHIP;

@@ -126,8 +126,7 @@ hipError_t launch_attn_f32(int kid, const Shape &s, const void *q, float scale, 
 // Workspace: logits fp32 [B][Hq][pitch], part_ml fp32 [B][Hq][nsplit][2], image sums or mass partials.
 size_t score_workspace_bytes(const Shape &s, size_t rows);            // rows = B * Hq * nsplit
 hipError_t launch_score(const Shape &s, const void *q, float scale, float *scores, float *lse,
-                        float *img_mass, void *ws, int nsplit, hipStream_t stream, int finish_kid = K_SCORE_FINALIZE,
-                        const SelectArgs *select = nullptr);
+                        float *img_mass, void *ws, int nsplit, hipStream_t stream, const SelectArgs *select = nullptr);
 
 // Where a row's parked logits are read for the tokens p .. p + 3 (p a multiple of 4): past the pitch its last four, which nobody uses.
 // A batch of empty sequences alone has a pitch of 0: its reads meet the statistics, which follow the logits and are at least as large.

@@ -382,21 +382,21 @@ static hipError_t launch_finalize(const Shape &s, const float *logits, int64_t p
 }
 
 // part_o, out: the merge of the output's partials as well (null: scores alone).  select: the top-k as well (parked_select_fits).
-static hipError_t launch_parked_finish(int kid, const Shape &s, const float *logits, int64_t pitch, const float *part_ml, const float *part_zi, int nsplit,
+static hipError_t launch_parked_finish(const Shape &s, const float *logits, int64_t pitch, const float *part_ml, const float *part_zi, int nsplit,
                                        float *scores, float *lse, float *img_mass, const float *part_o, void *out,
                                        const SelectArgs *select, uint32_t *done, hipStream_t stream)
 {
     if (select) {
         const int nwg = std::max(1, (s.bv.max_seq_len + kFinSelBlocks * kFinTokens - 1) / (kFinSelBlocks * kFinTokens));
         const dim3 grid(nwg + (img_mass ? 1 : 0) + (out ? s.n_q_heads : 0), s.batch), block(kFinSelThreads);
-        FASTOCR_LAUNCH(kid, parked_select_kernel, grid, block, 0, stream, s.bv, s.n_q_heads, logits, pitch, part_ml, part_zi, nsplit, scores, lse,
+        FASTOCR_LAUNCH(K_PARKED_FINISH, parked_select_kernel, grid, block, 0, stream, s.bv, s.n_q_heads, logits, pitch, part_ml, part_zi, nsplit, scores, lse,
                        img_mass, nwg, part_o, s.kv.head_dim, (uint16_t *)out, *select, done);
         return hipGetLastError();
     }
     // over the sequence's tokens, so that nothing waits for where its image starts; blocks without image tokens end at once
     const int nblk = std::max(1, (s.bv.max_seq_len + kFinTokens - 1) / kFinTokens);
     const dim3 grid(nblk + (img_mass ? 1 : 0) + (out ? s.n_q_heads : 0), s.batch), block(kFinThreads);
-#define FASTOCR_FINISH_N(NU, NS) FASTOCR_LAUNCH(kid, (parked_finish_kernel<NU, NS>), grid, block, 0, stream, s.bv, s.n_q_heads, logits, pitch, \
+#define FASTOCR_FINISH_N(NU, NS) FASTOCR_LAUNCH(K_PARKED_FINISH, (parked_finish_kernel<NU, NS>), grid, block, 0, stream, s.bv, s.n_q_heads, logits, pitch, \
         part_ml, part_zi, nsplit, scores, lse, img_mass, nblk, part_o, s.kv.head_dim, (uint16_t *)out)
 #define FASTOCR_FINISH(NU) do { if (nsplit <= 16) FASTOCR_FINISH_N(NU, 1); else FASTOCR_FINISH_N(NU, 4); } while (0)
     if (s.n_q_heads <= 16) FASTOCR_FINISH(1);
@@ -408,7 +408,7 @@ static hipError_t launch_parked_finish(int kid, const Shape &s, const float *log
 }
 
 hipError_t launch_score(const Shape &s, const void *q, float scale, float *scores, float *lse,
-                        float *img_mass, void *ws, int nsplit, hipStream_t stream, int finish_kid, const SelectArgs *select)
+                        float *img_mass, void *ws, int nsplit, hipStream_t stream, const SelectArgs *select)
 {
     const int64_t pitch = logit_pitch(s.bv.max_seq_len);
     const size_t rows = (size_t)s.batch * s.n_q_heads;
@@ -419,7 +419,7 @@ hipError_t launch_score(const Shape &s, const void *q, float scale, float *score
         uint32_t *done = select ? reinterpret_cast<uint32_t *>(part_ml + rows * nsplit * 3) : nullptr;
         const hipError_t e = launch_attn_parked(K_SCORE_LOGITS, s, q, scale, nullptr, part_ml, part_zi, nsplit, logits, pitch, done, stream);
         if (e != hipSuccess) return e;
-        return launch_parked_finish(finish_kid, s, logits, pitch, part_ml, part_zi, nsplit, scores, lse, img_mass, nullptr, nullptr,
+        return launch_parked_finish(s, logits, pitch, part_ml, part_zi, nsplit, scores, lse, img_mass, nullptr, nullptr,
                                     select, done, stream);
     }
     float *mass_part = part_ml + rows * nsplit * 2;
@@ -467,7 +467,7 @@ hipError_t launch_focal_parked(const Shape &s, const void *q, float scale, void 
     if (e != hipSuccess) return e;
     const bool hand_on = defer && !select;
     if (hand_on) *defer = CombineArgs{part_o, part_ml, nsplit, s.kv.head_dim, s.n_q_heads, 1, nullptr, out, false, MassArgs{nullptr, nullptr, 0}};
-    return launch_parked_finish(hand_on || select ? K_PARKED_FINISH : K_ATTN_COMBINE, s, logits, pitch, part_ml, part_zi, nsplit, scores, lse, img_mass,
+    return launch_parked_finish(s, logits, pitch, part_ml, part_zi, nsplit, scores, lse, img_mass,
                                 hand_on ? nullptr : part_o, hand_on ? nullptr : out, select, done, stream);
 }
 

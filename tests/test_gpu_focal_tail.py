@@ -43,7 +43,9 @@ def test_many_merges_keep_their_own_launch(dtype, d, B, apart, fused):
     try:
         for mass in (None, torch.full((B,), -3.0, dtype=torch.float32, device=DEV)):
             out, sc, idx, cnt = _layer(p, tau, mass)
-            assert len(fb.kernel_timer_read(fb.KERNEL_ATTN_COMBINE)) == (apart if cus == 256 else int(64 * B > 5 * cus))
+            # (parked logits: the launch that finishes the scores merges the output where the select's does not)
+            own = 0 if dtype == "bf16" and fused == 1 else apart if cus == 256 else int(64 * B > 5 * cus)
+            assert len(fb.kernel_timer_read(fb.KERNEL_ATTN_COMBINE)) == own
             assert torch.equal(out, want_out) and torch.equal(cnt, want_cnt) and (mass is None or torch.equal(mass, want_mass))
             for b in range(B):
                 assert torch.equal(sc[b, : n[b]], want_sc[b, : n[b]])

@@ -514,10 +514,10 @@ def test_scoring_paths_paged(resident):
 @pytest.mark.parametrize("Hq,Hkv", [(32, 8), (16, 2), (7, 1), (12, 4)])
 def test_scoring_paths_head_dim_64(resident, Hq, Hkv):
     """head_dim 64 through the register-resident kernel (128-byte rows: eight rows per load, two k-steps
-    per product) and through the two kernels; which of them ran is read off the finalize kernel's
+    per product) and through the two kernels; which of them ran is read off the finishing kernel's
     launch count.  Contiguous ragged batch in both layouts, then a paged one."""
     fb.set_tuning("score_resident", resident)
-    fb.kernel_timer_enable(fb.KERNEL_SCORE_FINALIZE, 8)
+    fb.kernel_timer_enable(fb.KERNEL_PARKED_FINISH, 8)
     try:
         case = TinyCase(seed=264 + Hq, B=40, Hq=Hq, Hkv=Hkv, d=64, n_vis=[1500 + 37 * i for i in range(40)],
                         pre=[i % 7 * 5 for i in range(40)], post=[(i * 13) % 90 for i in range(40)], dtype="bf16")
@@ -528,7 +528,7 @@ def test_scoring_paths_head_dim_64(resident, Hq, Hkv):
             check_scores(sc, ref_sc, p.vis_len, f"d64 {layout} resident={resident} scores")
             assert np.allclose(lse.cpu().numpy(), ref_lse, rtol=2e-5, atol=2e-5)
             assert np.allclose(mass.cpu().numpy(), ref_mass, atol=2e-5)
-            assert len(fb.kernel_timer_read(fb.KERNEL_SCORE_FINALIZE)) == (0 if resident else 1)
+            assert len(fb.kernel_timer_read(fb.KERNEL_PARKED_FINISH)) == (0 if resident else 1)
         wl = fs.config(5, batch=24, steps=4, n_visual=(600, 3000), grid_w=(20, 60), text_prefix=(3, 300), page_tokens=64,
                        head_dim=64, n_q_heads=Hq, n_kv_heads=Hkv)
         bt = fs.make_batch(wl, device=DEV)
@@ -539,9 +539,9 @@ def test_scoring_paths_head_dim_64(resident, Hq, Hkv):
         sc, lse, _ = p.scores(want_lse=True)
         check_scores(sc, ref_sc, p.vis_len, f"d64 paged resident={resident}")
         assert np.allclose(lse.cpu().numpy(), ref_lse, rtol=2e-5, atol=2e-5)
-        assert len(fb.kernel_timer_read(fb.KERNEL_SCORE_FINALIZE)) == (0 if resident else 1)
+        assert len(fb.kernel_timer_read(fb.KERNEL_PARKED_FINISH)) == (0 if resident else 1)
     finally:
-        fb.kernel_timer_enable(fb.KERNEL_SCORE_FINALIZE, 0)
+        fb.kernel_timer_enable(fb.KERNEL_PARKED_FINISH, 0)
         fb.set_tuning("score_resident", 1)
 
 
@@ -641,19 +641,16 @@ def test_a_barrier_that_gives_up_poisons_the_result_and_leaves_the_library_usabl
         case = TinyCase(seed=501, B=2, Hq=28, Hkv=4, d=128, n_vis=[34000, 9000], pre=[12, 0], post=[30, 9], dtype="bf16")
         p = problem_from_case(case)
         ref_sc, _, _ = oracle.focal_score(*p.oracle_args())
-        finishing = (fb.KERNEL_SCORE_FINALIZE, fb.KERNEL_PARKED_FINISH)
         fb.set_tuning("score_resident", 1)
-        for k in finishing:
-            fb.kernel_timer_enable(k, 4)
+        fb.kernel_timer_enable(fb.KERNEL_PARKED_FINISH, 4)
         sc, _, _ = p.scores()
         check_scores(sc, ref_sc, p.vis_len, "scores by the separate kernels after a timed-out call")
-        assert sum(len(fb.kernel_timer_read(k)) for k in finishing) == 1
+        assert len(fb.kernel_timer_read(fb.KERNEL_PARKED_FINISH)) == 1
         fb.set_tuning("exchange_fallback", 0)
         sc, _, _ = p.scores()
         check_scores(sc, ref_sc, p.vis_len, "scores after re-arming")
-        assert sum(len(fb.kernel_timer_read(k)) for k in finishing) == 0
+        assert len(fb.kernel_timer_read(fb.KERNEL_PARKED_FINISH)) == 0
     finally:
-        fb.kernel_timer_enable(fb.KERNEL_SCORE_FINALIZE, 0)
         fb.kernel_timer_enable(fb.KERNEL_PARKED_FINISH, 0)
         fb.set_tuning("barrier_spin_us", 0)
         fb.set_tuning("score_resident", 1)

@@ -37,7 +37,7 @@ def _check(p, launches, what, ref=None, tau=0.07):
     for b, n in enumerate(p.vis_len):
         assert (sc[b, n:] == -7.0).all(), f"{what}: scores past sequence {b}'s image were written"
     out, sc, lse, mass = p.focal_attn(want_lse=True, want_mass=True)
-    assert launches(fb.KERNEL_ATTN_COMBINE) == 1 and launches(fb.KERNEL_PARKED_FINISH) == 0, what      # one launch for all of it
+    assert launches(fb.KERNEL_ATTN_COMBINE) == 0 and launches(fb.KERNEL_PARKED_FINISH) == 1, what      # one launch for all of it
     check_out(out, ref_out, what + " output")
     check_scores(sc, ref_sc, p.vis_len, what + " layer's scores")
     assert np.allclose(lse.cpu().numpy(), ref_lse, rtol=2e-5, atol=2e-5) and np.allclose(mass.cpu().numpy(), ref_mass, atol=2e-5), what
@@ -231,7 +231,7 @@ def test_both_sides_of_the_size_rule(call, S, parked):
             want = (1, 0, int(parked), 0)
         else:
             out, sc, lse, mass = p.focal_attn(want_lse=True, want_mass=True)
-            want = (0, 1, 0, 1)
+            want = (0, 1, int(parked), int(not parked))
         got = tuple(len(fb.kernel_timer_read(k)) for k in kinds)
     finally:
         for k in kinds:
