@@ -25,16 +25,24 @@ HOST_SANITIZE = ["-g", "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsa
 LIB_HOSTSAN = os.path.join(HERE, "libfastocr_hostsan.so")
 
 
-# The binding's hot path (csrc/pycall.cpp), a Python extension over torch's own tensor headers; host code only.
+# The binding's hot path (csrc/pycall.cpp), a Python extension over torch's own tensor headers; host code only.  The binding does without it
+# where it is not there, so the library is built also where it cannot be.
 CALL_LIB = os.path.join(HERE, "_fastocr_call.so")
+CALL_LIB_HOSTSAN = os.path.join(HERE, "_fastocr_call_hostsan.so")
 
 
-def _call_command(out: str):
+def _call_command(out: str, hipcc: str, host_sanitize: bool):
     import sysconfig
     import torch
     home = os.path.dirname(torch.__file__)
     inc = os.path.join(home, "include")
-    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+    # (the checking build with the compiler whose sanitizer runtime the library's own checking build needs)
+    compiler = ["g++", "-O2"]
+    if host_sanitize:
+        clang = os.path.join(os.path.dirname(os.path.dirname(hipcc)), "lib", "llvm", "bin", "clang++")
+        compiler = [clang, "-O1", "-g", "-fsanitize=address", "-fsanitize=undefined", "-fno-sanitize-recover=undefined",
+                    "-fno-sanitize=vptr,function", "-fno-omit-frame-pointer", "-shared-libsan"]
+    return [*compiler, "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
             "-I", INCLUDE, "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
             "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "pycall.cpp"), "-o", out,
             "-L", os.path.join(home, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
@@ -54,9 +62,13 @@ def build(verbose: bool = False, host_sanitize: bool = False) -> str:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
-    call_tmp = CALL_LIB + f".tmp{os.getpid()}"
-    if not host_sanitize:
-        procs.append(("pycall.cpp", subprocess.Popen(_call_command(call_tmp), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    call_lib = CALL_LIB_HOSTSAN if host_sanitize else CALL_LIB
+    call_tmp = call_lib + f".tmp{os.getpid()}"
+    try:
+        call = subprocess.Popen(_call_command(call_tmp, hipcc, host_sanitize), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        call_why = ""
+    except Exception as e:                                       # no torch, no compiler
+        call, call_why = None, str(e)
     failed = False
     for src, p in procs:
         out, _ = p.communicate()
@@ -66,16 +78,26 @@ def build(verbose: bool = False, host_sanitize: bool = False) -> str:
             sys.stderr.write(f"--- {src} failed ---\n{out}\n")
         elif verbose and out.strip():
             print(out)
+    if call is not None:
+        call_why, _ = call.communicate()
+    # the extension belongs to the library of the same sources: an older one goes, whatever came of the new one
+    built = call is not None and call.returncode == 0
+    if not built or failed:
+        for f in (call_tmp,) if failed else (call_tmp, call_lib):
+            if os.path.exists(f):
+                os.remove(f)
     if failed:
         raise RuntimeError("hipcc failed")
+    if not built:
+        sys.stderr.write(f"--- pycall.cpp was not built: calls go through ctypes, about 3 us slower ---\n{call_why}\n")
     tmp = lib + f".tmp{os.getpid()}"
     link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     if host_sanitize:
         link += ["-fsanitize=address", "-fsanitize=undefined", "-shared-libsan"]
     subprocess.check_call(link)
     os.replace(tmp, lib)
-    if not host_sanitize:
-        os.replace(call_tmp, CALL_LIB)
+    if built:
+        os.replace(call_tmp, call_lib)
     return lib
 
 

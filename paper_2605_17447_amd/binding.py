@@ -114,7 +114,13 @@ def _bind_call(lib) -> None:
     if _raw_stream is None or _current_device is None:
         return
     try:
-        from . import _fastocr_call as call
+        if os.environ.get("FASTOCR_CALL"):                       # another build of the extension, as FASTOCR_LIB names one of the library
+            import importlib.util
+            spec = importlib.util.spec_from_file_location("_fastocr_call", os.environ["FASTOCR_CALL"])
+            call = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(call)
+        else:
+            from . import _fastocr_call as call
     except ImportError:
         return
     names = ("focal_score", "topk_fixation", "sparse_decode_attn", "dense_decode_attn", "focal_attn_score", "focal_score_topk",

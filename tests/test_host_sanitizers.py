@@ -1,7 +1,7 @@
 """Host code under AddressSanitizer + UndefinedBehaviorSanitizer (CPU only, no GPU code runs):
-the C oracle while its pins run, and the C-ABI library's argument validation and host routines
-while the host ABI tests run.  Each runs in a child process with the sanitizer runtime preloaded;
-any report aborts the child."""
+the C oracle while its pins run, the C-ABI library's argument validation and host routines and the
+binding's native call path while the tests of either run.  Each runs in a child process with the
+sanitizer runtime preloaded; any report aborts the child."""
 import glob
 import os
 import subprocess
@@ -31,8 +31,9 @@ def test_oracle_pins_under_address_and_undefined_behaviour_sanitizers():
 
 
 def test_abi_validation_under_address_and_undefined_behaviour_sanitizers():
-    from paper_2605_17447_amd._build import build
+    from paper_2605_17447_amd._build import CALL_LIB_HOSTSAN, build
     lib = build(host_sanitize=True)
+    assert os.path.exists(CALL_LIB_HOSTSAN)
     found = glob.glob("/opt/rocm/lib/llvm/lib/clang/*/lib/linux/libclang_rt.asan-x86_64.so")
     assert found, "clang's AddressSanitizer runtime not found"
-    _run(["tests/test_abi_host.py"], {"FASTOCR_LIB": lib}, found[0])
+    _run(["tests/test_abi_host.py", "tests/test_native_call.py"], {"FASTOCR_LIB": lib, "FASTOCR_CALL": CALL_LIB_HOSTSAN}, found[0])
