@@ -142,9 +142,9 @@ size_t fastocr_workspace_bytes(int op, const fastocr_kv_view *kv, const fastocr_
  * caches.  Every other shape (other head dimensions up to 256, larger groups, unaligned rows) runs on
  * plain-FMA kernels that accumulate in fp64, to the same error bars.
  * Concurrency: when the shape fits (bf16, head_dim 128 or 64, 1/2/4/8 kv heads with at most 8 query heads
- * each, batch <= 256 and <= the compute-unit count) and is large (logits, batch x query heads x max_seq_len x 4 bytes, of more than 7 MiB;
- * 8 MiB for a focal layer -- below that two launches that park the logits in the workspace are faster and
- * wait for nothing) this call and fastocr_focal_attn_score run as ONE kernel whose
+ * each, batch <= 256 and <= the compute-unit count) and is large (logits, batch x query heads x max_seq_len x 4 bytes,
+ * of more than 7 MiB; 8 MiB for a focal layer -- up to that two launches that park the logits in the workspace
+ * run instead, which wait for nothing) this call and fastocr_focal_attn_score run as ONE kernel whose
  * workgroups -- at most one per compute unit -- wait for each other's softmax statistics, so
  * all of them must be on the chip together.  Launched alone on the GPU (any number of calls in
  * order on one stream, HIP graphs included) that always holds.  If other kernels occupy compute
@@ -263,13 +263,12 @@ int fastocr_focal_attn_score(const fastocr_kv_view *kv, const fastocr_batch_view
  * logits by the size rule, and no image span exceeds 16384 tokens, the select runs INSIDE the launch that finishes the scores: every range stores
  * its scores at agent scope and counts itself out, and the sequence's last range to finish selects
  * over the whole sequence -- no second launch, nobody waits.  That form is measured slower on
- * MI355X (the select then runs on 8 waves instead of 16 and ends the launch alone), so it is not
- * the default.
- * fastocr_focal_attn_score_topk by default: when the layer runs as its one-pass kernel and no image span
- * exceeds 16384 tokens, the merge of the dense output's partials (and the sum of the image mass) is done by
- * extra workgroups of the select's launch (both depend on the one-pass kernel only): two launches instead of
- * three, same bits.  With many sequences and heads (more than five merges per compute unit) the merge keeps
- * a launch of its own.
+ * MI355X (the scores come back through memory, in the register-resident kernels to 8 waves instead of 16, and the
+ * select ends the launch alone), so it is not the default.
+ * fastocr_focal_attn_score_topk by default: when the layer runs from one pass over K and V and no image span
+ * exceeds 16384 tokens, the merge of the dense output's partials (and, of the single kernel, the sum of the image
+ * mass) is done by extra workgroups of the select's launch: a launch less, same bits.  With many sequences and
+ * heads (more than five merges per compute unit) the merge stays out of that launch.
  */
 int fastocr_focal_score_topk(const fastocr_kv_view *kv, const fastocr_batch_view *bv, const void *q,
                              int n_q_heads, float scale, double tau, const int32_t *prev_idx,
@@ -353,7 +352,7 @@ int fastocr_stream_probe(const void *src, void *dst, size_t bytes, void *sink, v
  *       a second kernel; 0 (default) = calls are launched one by one, such lists stay one launch.  The
  *       workspace size covers both, results agree to rounding.
  *   "select_fused"    fastocr_focal_score_topk / fastocr_focal_attn_score_topk: 0 = the select is a launch of
- *       its own (default), 1 = it runs inside the scoring launch when it can
+ *       its own (default), 1 = it runs inside the launch that finishes the scores when it can
  *   "timer_every"     n >= 1: see the kernel timers above
  *   "barrier_spin_us" how long a workgroup of a single-launch form waits for the others; 0 restores
  *       the default of 250000; 1 makes waiting workgroups give up at once (tests use it to exercise

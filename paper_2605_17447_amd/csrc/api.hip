@@ -520,14 +520,21 @@ static int check_qo(const fastocr_kv_view *kv, const void *q, const void *out, f
 // parks up to this many bytes of logits (batch x query heads x longest sequence x 4; us, register-resident / parked; caches too
 // large for the last-level cache where there is room):
 //   scoring            28/4 heads: batch 1, 4096 image tokens 11.9 / 8.7, 4 x 4096 15.6 / 9.3, 12 x 4096 (5.8 MB) 17.7 / 15.7, 8 x 8192 (7.5) 19.9 / 19.9,
-//                      12 x 8192 (11.3) 24.4 / 27.2; 64/8 heads 12 x 2048 (6.9) 18.0 / 17.0, 8 x 4096 (8.8) 20.3 / 21.0
-//   layer and top-k    28/4: 1 x 4096 21.5 / 14.8, 12 x 4096 34.5 / 31.3, 8 x 8192 40.2 / 39.2, 12 x 8192 50.0 / 52.1; 64/8: 16 x 2048 (9.2) 43.5 / 42.2;
-//                      12/2: 24 x 8192 (9.7) 50.1 / 51.3
-//   layer alone        28/4: 1 x 4096 21.0 / 9.8, 12 x 4096 33.5 / 25.5, 12 x 8192 47.4 / 45.0, 16 x 8192 (15.0) 59.5 / 59.3;
-//                      64/8: 12 x 4096 (13.2) 48.6 / 49.4; head_dim 64, 64/8: 12 x 4096 32.2 / 32.7
-//   ragged and paged   28/4, 12 sequences of up to 5000: scoring 25.4 / 16.7, layer and top-k 42.4 / 32.0 (the host does not know
-//                      the lengths, only the longest: the same lines)
-constexpr int64_t kParkScore = 7 << 20, kParkLayer = 8 << 20;        // (a layer with and without its top-k: the same form, the same bits)
+//                      12 x 8192 (11.3) 24.4 / 27.2; 64/8 heads 12 x 2048 (6.9) 18.0 / 17.0, 8 x 4096 (8.8) 20.3 / 21.0.  Sequences of equal length
+//                      lose from about 5.5 MiB on, most with many short ones (64/8, 17 x 1500 18.4 / 19.7; 32/8, 36 x 1500 24.2 / 27.9; of 503 shapes
+//                      below the limit 17 by more than 3 %, at most 16 %); lengths from an eighth of the longest to all of it gain up to
+//                      the limit and beyond (28/4, 16 x 4000 22.0 / 16.5; 64/8, 22 x 1000 19.4 / 13.8; of 468 none loses, on the mean -25 % at
+//                      5.5 - 7 MiB).  The host knows the longest sequence only; a decode batch seldom has equal ones
+//   layer and top-k    28/4: 1 x 4096 21.5 / 14.8, 12 x 4096 34.5 / 31.3, 8 x 8192 40.2 / 39.2, 12 x 6200 (8.03 MiB) 43.6 / 42.3, 12 x 8192 50.0 / 52.1;
+//                      64/8: 16 x 2048 (8.25) 44.2 / 41.2; 12/2: 24 x 7300 (8.09) 45.7 / 47.1, 24 x 8192 51.6 / 52.4; head_dim 64, 64/8: 16 x 2100 (8.45)
+//                      31.7 / 32.5: these last rows set the limit
+//   layer alone        gains further up (28/4: 12 x 6200 40.9 / 35.4, 12 x 8192 47.4 / 45.0, 16 x 8192 (15.0) 59.5 / 59.3; 64/8: 16 x 2048 39.2 / 34.1,
+//                      12 x 4096 (13.2) 48.6 / 49.4; head_dim 64, 64/8: 12 x 4096 32.2 / 32.7), but has the form, and so the bits, of the call with its top-k
+//   ragged and paged   28/4, 12 sequences of up to 5000: scoring 25.4 / 16.7, layer and top-k 42.4 / 32.0
+//   mostly text        28/4, 12 x 200 image tokens and 5000 of text: scoring 33.3 / 16.7, layer 63.4 / 27.7; 1 x 64 and 16000: 280 / 9.5, 559 / 13.3
+// Where the single kernel is not to be had (head counts, a stream without a slot, a process that distrusts the exchange) a layer parks at every
+// size, instead of dense attention and then scoring: 28/4, 12 x 8192 80.5 / 46.2; 64/8, 16 x 16384 283 / 231; 96/8, 16 x 16384 312 / 251.
+constexpr int64_t kParkScore = 7 << 20, kParkLayer = 8 << 20;
 
 static bool select_inside() { return g_tune_select_fused.load(std::memory_order_relaxed) != 0; }
 

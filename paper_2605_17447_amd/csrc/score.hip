@@ -393,7 +393,8 @@ static hipError_t launch_parked_finish(const Shape &s, const float *logits, int6
                        img_mass, nwg, part_o, s.kv.head_dim, (uint16_t *)out, *select, done);
         return hipGetLastError();
     }
-    // over the sequence's tokens, so that nothing waits for where its image starts; blocks without image tokens end at once
+    // Over the longest sequence's tokens, so that no load waits for where an image starts or a sequence ends: workgroups without image tokens read
+    // words that nobody wrote and drop what they make of them.
     const int nblk = std::max(1, (s.bv.max_seq_len + kFinTokens - 1) / kFinTokens);
     const dim3 grid(nblk + (img_mass ? 1 : 0) + (out ? s.n_q_heads : 0), s.batch), block(kFinThreads);
 #define FASTOCR_FINISH_N(NU, NS) FASTOCR_LAUNCH(K_PARKED_FINISH, (parked_finish_kernel<NU, NS>), grid, block, 0, stream, s.bv, s.n_q_heads, logits, pitch, \

@@ -1,8 +1,8 @@
 // Focal-layer scoring with the softmax weights kept on chip (Eq. 1; text under Eq. 2).
 //
 // The head average is taken after each head's softmax, so a score needs every head's
-// normaliser over the whole cache.  The two-kernel path parks all fp32 logits in HBM; mixing
-// those writes into the K stream costs far more than their bytes on this chip.  This kernel
+// normaliser over the whole cache.  The form in two launches (score.hip) parks the fp32 logits in HBM; from some
+// megabytes of them on, mixing those writes into the K stream costs far more than their bytes on this chip.  This kernel
 // keeps what it needs of them in registers instead:
 //   - one 512-thread workgroup per (image-token range, sequence), at most one per compute unit,
 //     so the whole grid is resident at once; a ragged batch's sequences get ranges in proportion
@@ -25,7 +25,7 @@
 //     are summed through LDS and the finished scores are written -- the only HBM writes.
 // head_dim 128 or 64 (a template parameter: rows of 256 or 128 bytes, 4 or 2 k-steps per logit).
 // Shapes that do not fit (group size > 8, Hkv not dividing 8, more sequences than compute
-// units, more than 32 tiles per wave, pages shorter than a tile) take the two-kernel path.
+// units, more than 32 tiles per wave, pages shorter than a tile), and by default sizes below api.hip's limit, park.
 #include <algorithm>
 
 #include "kernels.hpp"
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(kResThreads) void score_resident_kernel(
     // exponents near 0, relative to a far reference they do not, and the weight's relative error is
     // that rounding times ln 2.  So a logit more than kRefSlack above the reference moves the reference
     // there and rescales what the lane holds: exponents stay below 16 (error <= 3.3e-7 of the weight,
-    // what the two-kernel path reaches; with a slack of 64 a score of 0.3 was off by 1.3e-6), and a
+    // what the form in two launches reaches; with a slack of 64 a score of 0.3 was off by 1.3e-6), and a
     // lane moves once per 11 nats its logits rise above its first one -- rarely.
     float ref[4], z[4];
 #pragma unroll
