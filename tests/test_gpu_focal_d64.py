@@ -21,8 +21,11 @@ def _check(p, what, tau=0.05):
     ref_sc, ref_lse, ref_mass = oracle.focal_score(*oc)
     ref_dense, _ = oracle.decode_attn(*oc)
     fb.kernel_timer_read(fb.KERNEL_FOCAL_FUSED)
+    fb.kernel_timer_enable(fb.KERNEL_PARKED_FINISH, 8)
     out, sc, lse, mass = p.focal_attn(want_lse=True, want_mass=True)
     assert len(fb.kernel_timer_read(fb.KERNEL_FOCAL_FUSED)) == 1, "the one-pass kernel did not run"
+    assert len(fb.kernel_timer_read(fb.KERNEL_PARKED_FINISH)) == 0, "the logits were parked"
+    fb.kernel_timer_enable(fb.KERNEL_PARKED_FINISH, 0)
     check_out(out, ref_dense, what)
     check_scores(sc, ref_sc, p.vis_len, what)
     assert np.allclose(lse.cpu().numpy(), ref_lse, rtol=2e-5, atol=2e-5)
@@ -80,6 +83,7 @@ def test_scoring_kept_off_the_waiting_grid_keeps_the_head_dim_64_layer_off_it(d)
     want, _ = oracle.decode_attn(*p.oracle_args())
     ref_sc, _, _ = oracle.focal_score(*p.oracle_args())
     fb.kernel_timer_enable(fb.KERNEL_FOCAL_FUSED, 8)
+    fb.set_tuning("focal_fused", 2)                              # (left to its size the layer would wait for nobody)
     try:
         for scoring, launches in ((1, 1), (0, 0 if d == 64 else 1)):
             fb.set_tuning("score_resident", scoring)
@@ -89,4 +93,5 @@ def test_scoring_kept_off_the_waiting_grid_keeps_the_head_dim_64_layer_off_it(d)
             check_scores(sc, ref_sc, p.vis_len, f"score_resident {scoring}")
     finally:
         fb.kernel_timer_enable(fb.KERNEL_FOCAL_FUSED, 0)
+        fb.set_tuning("focal_fused", 1)
         fb.set_tuning("score_resident", 1)

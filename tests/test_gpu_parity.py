@@ -19,9 +19,11 @@ if torch.cuda.is_available():
 
 
 def full_check(p: "GpuProblem", tau: float, what: str, exact_topk=True):
-    """All calls of one problem against the oracle.  Scoring and the one-call focal layer run in
-    both of their forms: the single register-resident kernel wherever the shape fits it (mode 2)
-    and the separate kernels (mode 0); the size rule in between only picks one of the two."""
+    """All calls of one problem against the oracle.  Scoring runs in both of its forms: the single
+    register-resident kernel wherever the shape fits it (mode 2) and two launches (mode 0); the size
+    rule in between picks one of these.  The one-call focal layer runs as the single kernel (mode 2),
+    as dense attention and then scoring (mode 0), and as the size rule has it (mode 1: small sizes of
+    bf16 caches in one pass with parked logits)."""
     oc = p.oracle_args()
     ref_sc, ref_lse, ref_mass = oracle.focal_score(*oc)
     nz = [b for b in range(p.B) if p.seq_len[b] > 0]
@@ -60,7 +62,7 @@ def full_check(p: "GpuProblem", tau: float, what: str, exact_topk=True):
 
     # the focal layer in one call: the dense output and the scores together
     try:
-        for mode in (0, 2):
+        for mode in (0, 1, 2):
             fb.set_tuning("focal_fused", mode)
             out, sc, lse, mass = p.focal_attn(want_lse=True, want_mass=True)
             check_out(out, ref_dense, f"{what} focal-layer output (mode {mode})")
