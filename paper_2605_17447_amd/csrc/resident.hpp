@@ -328,10 +328,10 @@ __device__ __forceinline__ void resident_select_tail(const float *scores, int b,
     sh.hist = reinterpret_cast<uint32_t *>(lds);
     sh.list = reinterpret_cast<uint32_t *>(lds + 4 * kWinBins);
     int *misc = reinterpret_cast<int *>(lds + 4 * kWinBins + 4 * kWinListWords);
-    sh.w_ac = misc;                                          // 4 * 8 wave values, 16-byte aligned
-    sh.pick = misc + 32;
+    sh.w_ac = misc;                                          // 6 * 8 wave values
+    sh.pick = misc + 48;
     topk_reg_body<kResThreads, kSelPer, true, false>(scores, bv, b, sa.tau, sa.prev_idx, sa.prev_cnt, sa.sel_idx, sa.sel_cnt,
-                                              sa.kmax, sh, [](int, int) {});
+                                              sa.kmax, sh);
     if (threadIdx.x == 0) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 

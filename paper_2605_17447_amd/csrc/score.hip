@@ -315,7 +315,7 @@ __global__ __launch_bounds__(kFinSelThreads) void parked_select_kernel(
     __shared__ uint32_t hist[kWinBins];
     __shared__ __align__(16) uint32_t list[kWinListWords];
     __shared__ int s_pick[4];
-    __shared__ __align__(16) int w_ac[4 * (kFinSelThreads / 64)];
+    __shared__ __align__(16) int w_ac[6 * (kFinSelThreads / 64)];
     __shared__ float sm_max[4];
     __shared__ float sm_z[256];
     __shared__ __align__(16) float sm_o[1024];
@@ -337,8 +337,7 @@ __global__ __launch_bounds__(kFinSelThreads) void parked_select_kernel(
     if (!s_last) return;
     TopkRegShared sh;
     sh.hist = hist; sh.list = list; sh.pick = s_pick; sh.w_ac = w_ac;
-    topk_reg_body<kFinSelThreads, 16, true, false>(scores, bv, b, sel.tau, sel.prev_idx, sel.prev_cnt, sel.sel_idx, sel.sel_cnt, sel.kmax, sh,
-                                                    [](int, int) {});
+    topk_reg_body<kFinSelThreads, 16, true, false>(scores, bv, b, sel.tau, sel.prev_idx, sel.prev_cnt, sel.sel_idx, sel.sel_cnt, sel.kmax, sh);
 }
 
 // -----------------------------------------------------------------------------------------

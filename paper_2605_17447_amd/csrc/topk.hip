@@ -217,12 +217,11 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(
     __shared__ uint32_t hist[kWinBins];
     __shared__ __align__(16) uint32_t list[kWinListWords];
     __shared__ int s_pick[4];
-    __shared__ __align__(16) int w_ac[4 * kTopkWaves];
+    __shared__ __align__(16) int w_ac[6 * kTopkWaves];
 
     TopkRegShared sh;
     sh.hist = hist; sh.list = list; sh.pick = s_pick; sh.w_ac = w_ac;
-    topk_reg_body<kTopkThreads, PER, false, VEC>(scores, bv, blockIdx.x, tau, prev_idx, prev_cnt, sel_idx, sel_cnt, kmax, sh,
-                                          [](int, int) {});
+    topk_reg_body<kTopkThreads, PER, false, VEC>(scores, bv, blockIdx.x, tau, prev_idx, prev_cnt, sel_idx, sel_cnt, kmax, sh);
 }
 
 // The same, with batch * Hq more workgroups behind the selecting ones: each merges the attention
@@ -237,7 +236,7 @@ __global__ __launch_bounds__(kTopkThreads) void focal_tail_kernel(
     __shared__ uint32_t hist[kWinBins];
     __shared__ __align__(16) uint32_t list[kWinListWords];
     __shared__ int s_pick[4];
-    __shared__ __align__(16) int w_ac[4 * kTopkWaves];
+    __shared__ __align__(16) int w_ac[6 * kTopkWaves];
     __shared__ float sm_max[4];
     __shared__ typename CombineAcc<T>::type sm_z[256];
     __shared__ __align__(32) typename CombineAcc<T>::type sm_o[1024];
@@ -245,8 +244,7 @@ __global__ __launch_bounds__(kTopkThreads) void focal_tail_kernel(
     if ((int)blockIdx.x < batch) {
         TopkRegShared sh;
         sh.hist = hist; sh.list = list; sh.pick = s_pick; sh.w_ac = w_ac;
-        topk_reg_body<kTopkThreads, PER, false, VEC>(scores, bv, blockIdx.x, tau, prev_idx, prev_cnt, sel_idx, sel_cnt, kmax, sh,
-                                              [](int, int) {});
+        topk_reg_body<kTopkThreads, PER, false, VEC>(scores, bv, blockIdx.x, tau, prev_idx, prev_cnt, sel_idx, sel_cnt, kmax, sh);
     } else if (MASS && (int)blockIdx.x < 2 * batch) {
         image_mass_sum(c.mass, c.seq_meta, (int)blockIdx.x - batch);
     } else {

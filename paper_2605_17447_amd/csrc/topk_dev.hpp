@@ -1,5 +1,5 @@
 // Device code of the exact top-k select as templates (workgroup size and keys per thread are
-// parameters, a hook is called for every selected entry); topk.hip instantiates it.
+// parameters); topk.hip instantiates it.
 #pragma once
 #include "kernels.hpp"
 
@@ -100,44 +100,61 @@ __device__ uint32_t radix_select(const uint32_t *keys, int n, int k, uint32_t (*
 // below), the result is written in index order through a block-wide prefix sum: no candidate list,
 // no atomics on memory, no index arrays.
 
-// max / min over the 64 lanes of a wave with data-parallel-primitive moves (see wave_scan_incl);
-// the result is the same in every lane
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x)
-{
-#define FASTOCR_DPP_STEP(CTRL, ROWS) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, ROWS, 0xf, false))
-    FASTOCR_DPP_STEP(0x111, 0xf); FASTOCR_DPP_STEP(0x112, 0xf); FASTOCR_DPP_STEP(0x114, 0xf); FASTOCR_DPP_STEP(0x118, 0xf);
-    FASTOCR_DPP_STEP(0x142, 0xa); FASTOCR_DPP_STEP(0x143, 0xc);
-#undef FASTOCR_DPP_STEP
-    return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
-}
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) { return ~wave_max_u32(~x); }
+// What bounds it: one workgroup per sequence works on one compute unit, whose sixteen waves pass every VALU instruction through four
+// SIMDs, 7.6 ns each; exchanges between the waves, which every wave needs the result of, cost their instruction count rather than
+// their latency.  So the four bounds are reduced together (row and half swaps bring them into one register, ten instructions instead of
+// 28), each wave combines the sixteen waves' values with lane moves instead of walking them (stamped in the kernel: 1.3 -> 0.6 us),
+// the two counts of the prefix sum share a word and the second one is seldom needed (1.7 -> 0.8 us), and keys of scores without a
+// sign bit take one instruction each.
 
-// exclusive prefix sums of (a, c) over the workgroup's THREADS threads; totals through *ta, *tc.  All threads call.
-// w_ac: at least 2 x THREADS/64 wave totals, 16-byte aligned.
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-template <int THREADS>
-__device__ __forceinline__ void block_scan2(int a, int c, int *w_ac, int &a_excl, int &c_excl, int *ta, int *tc)
+#define FASTOCR_ROW_STEP(OP, X, CTRL) X = OP(X, (uint32_t)__builtin_amdgcn_update_dpp((int)(X), (int)(X), CTRL, 0xf, 0xf, false))
+// the maximum over each row of 16 lanes, in all of them
+__device__ __forceinline__ uint32_t row_max_u32(uint32_t x)
 {
+    FASTOCR_ROW_STEP(max, x, kDppXor1);
+    FASTOCR_ROW_STEP(max, x, kDppXor2);
+    FASTOCR_ROW_STEP(max, x, kDppHalfMirror);
+    FASTOCR_ROW_STEP(max, x, kDppRowMirror);
+    return x;
+}
+#undef FASTOCR_ROW_STEP
+
+// Maxima over the workgroup of four values per thread, the same in every thread.  All threads call.  w: 4 * THREADS / 64 words.
+template <int THREADS>
+__device__ __forceinline__ void block_max4(uint32_t &a, uint32_t &b, uint32_t &c, uint32_t &d, int *w)
+{
+    constexpr int W = THREADS / 64;
+    static_assert(W == 8 || W == 16, "a row of 16 lanes holds the waves' values");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int ai = wave_scan_incl(a), ci = wave_scan_incl(c);
-    if (lane == 63) { w_ac[wave] = ai; w_ac[(THREADS / 64) + wave] = ci; }
+    const auto ab = __builtin_amdgcn_permlane32_swap(a, b, false, false), cd = __builtin_amdgcn_permlane32_swap(c, d, false, false);
+    const uint32_t mab = max((uint32_t)ab[0], (uint32_t)ab[1]), mcd = max((uint32_t)cd[0], (uint32_t)cd[1]);       // halves: a b, c d
+    const auto m = __builtin_amdgcn_permlane16_swap(mab, mcd, false, false);
+    const uint32_t x = row_max_u32(max((uint32_t)m[0], (uint32_t)m[1]));                                            // rows: a c b d
+    if ((lane & 15) == 0) w[(lane >> 4) * W + wave] = (int)x;
     __syncthreads();
-    int ab = 0, cb = 0, at = 0, ct = 0;
-#pragma unroll
-    for (int v = 0; v < (THREADS / 64) / 4; ++v) {
-        const i32x4 x = reinterpret_cast<const i32x4 *>(w_ac)[v], y = reinterpret_cast<const i32x4 *>(w_ac)[(THREADS / 64) / 4 + v];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (4 * v + e < wave) { ab += x[e]; cb += y[e]; }
-            at += x[e];
-            ct += y[e];
-        }
-    }
-    a_excl = ab + ai - a;
-    c_excl = cb + ci - c;
-    *ta = at;
-    *tc = ct;
+    const uint32_t y = row_max_u32((uint32_t)w[(lane >> 4) * W + (lane & (W - 1))]);
+    a = (uint32_t)__builtin_amdgcn_readlane((int)y, 0);
+    c = (uint32_t)__builtin_amdgcn_readlane((int)y, 16);
+    b = (uint32_t)__builtin_amdgcn_readlane((int)y, 32);
+    d = (uint32_t)__builtin_amdgcn_readlane((int)y, 48);
+}
+
+// exclusive prefix sum of x over the workgroup's threads; all threads call, a barrier inside.  w: THREADS / 64 words.
+template <int THREADS>
+__device__ __forceinline__ uint32_t block_scan(uint32_t x, int *w)
+{
+    constexpr int W = THREADS / 64;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int incl = wave_scan_incl((int)x);
+    if (lane == 63) w[wave] = incl;
     __syncthreads();
+    const int own = w[lane & (W - 1)];
+    int t = own;                                                  // inclusive sums within the row
+    t += __builtin_amdgcn_update_dpp(0, t, 0x111, 0xf, 0xf, false);
+    t += __builtin_amdgcn_update_dpp(0, t, 0x112, 0xf, 0xf, false);
+    t += __builtin_amdgcn_update_dpp(0, t, 0x114, 0xf, 0xf, false);
+    t += __builtin_amdgcn_update_dpp(0, t, 0x118, 0xf, 0xf, false);
+    return (uint32_t)(__builtin_amdgcn_readlane(t - own, wave) + incl) - x;
 }
 
 // Shared memory of topk_reg_body, provided by the calling kernel.
@@ -147,8 +164,9 @@ constexpr int kWinListWords = 3 * kWinRank; // the bin's keys, then how many key
 struct TopkRegShared {
     uint32_t *hist;             // [kWinBins]
     uint32_t *list;             // [kWinListWords], 16-byte aligned
-    int *pick;                  // [4]: bin, rank within it, keys copied so far
-    int *w_ac;                  // [4 * THREADS / 64], 16-byte aligned
+    int *pick;                  // [4]: bin, rank within it, keys copied so far, whether every key equal to the threshold is wanted
+    int *w_ac;                  // [6 * THREADS / 64]: the bounds of the waves, then the totals of the two prefix sums (no barrier
+                                // stands between the three where all keys are equal)
 };
 
 // The k-th largest of the workgroup's keys, all of them in the threads' registers, given a window lo <= key <= key_max that holds at least the k
@@ -160,10 +178,11 @@ struct TopkRegShared {
 // over all threads, and the key with above < rank <= above + equal is the threshold.  A window of
 // single key values (shift 0) names the threshold by its bin.  One pass and the ranking is the usual
 // case.  hist and the list's counters must be zero and pick[2] = 0 on entry (the caller clears them
-// before a barrier of its own).  *ties = how many keys equal to the threshold belong to the k largest.
+// before a barrier of its own).  *ties = how many keys equal to the threshold belong to the k largest, *all: those are known to be
+// all of them.
 template <int THREADS, int PER>
 __device__ __forceinline__ uint32_t window_select(const uint32_t (&key)[PER], uint32_t lo, uint32_t key_max,
-                                                  int k, const TopkRegShared &sh, int *ties)
+                                                  int k, const TopkRegShared &sh, int *ties, bool *all)
 {
     static_assert(THREADS >= kWinBins && THREADS % 256 == 0, "one thread clears one bin; whole vectors of wave totals");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -171,6 +190,7 @@ __device__ __forceinline__ uint32_t window_select(const uint32_t (&key)[PER], ui
     uint32_t span = key_max - lo;                    // the window: lo <= key <= lo + span
     int shift = max(0, 23 - (int)__builtin_clz(span | 1u));                     // span >> shift < 512
     int rank = k, nb = 0;
+    *all = false;
     if (span == 0u) {                                // every key of the window is the same
         *ties = k;
         return lo;
@@ -213,6 +233,7 @@ __device__ __forceinline__ uint32_t window_select(const uint32_t (&key)[PER], ui
         lo += (uint32_t)bin << shift;
         if (shift == 0) {                            // the window's bins were single key values
             *ties = rank;
+            *all = rank == nb;
             return lo;
         }
         span = (1u << shift) - 1u;                   // the bin is the next window
@@ -292,15 +313,15 @@ __device__ __forceinline__ uint32_t window_select(const uint32_t (&key)[PER], ui
     __syncthreads();
     if (tid < nb) {
         const int gt = (int)sh.list[kWinRank + tid], eq = (int)sh.list[2 * kWinRank + tid];
-        if (gt < rank && rank <= gt + eq) { sh.pick[0] = (int)sh.list[tid]; sh.pick[1] = rank - gt; }     // equal keys write the same
+        if (gt < rank && rank <= gt + eq) { sh.pick[0] = (int)sh.list[tid]; sh.pick[1] = rank - gt; sh.pick[3] = rank == gt + eq; }     // equal keys write the same
     }
     __syncthreads();
     *ties = sh.pick[1];
+    *all = sh.pick[3] != 0;
     return (uint32_t)sh.pick[0];
 }
 
-// One workgroup of THREADS threads selects sequence b's set.  publish(position, index) is called by
-// the thread that writes sel_idx[position] = index, for every entry of the result.
+// One workgroup of THREADS threads selects sequence b's set.
 // The first window runs from a lower bound of the threshold to the largest key.  The bound is the
 // smallest key of all, or -- the warm start -- the smallest CURRENT key among the previous set's k
 // tokens when that set is k distinct valid tokens: k keys reach it, so the threshold cannot lie
@@ -316,15 +337,15 @@ __device__ __forceinline__ float score_at(const float *p)
     return *p;
 }
 
-template <int THREADS, int PER, bool COHERENT, bool VEC, typename Publish>
+template <int THREADS, int PER, bool COHERENT, bool VEC>
 __device__ __forceinline__ void topk_reg_body(
     const float *__restrict__ scores, const BatchDev &bv, int b, double tau, const int32_t *prev_idx,
-    const int32_t *prev_cnt, int32_t *sel_idx, int32_t *sel_cnt, int64_t kmax, const TopkRegShared &sh,
-    Publish publish)
+    const int32_t *prev_cnt, int32_t *sel_idx, int32_t *sel_cnt, int64_t kmax, const TopkRegShared &sh)
 {
     static_assert(PER <= 32 && PER % 4 == 0, "a thread's keys are tracked in 32-bit masks and loaded 16 bytes at a time");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x;
     constexpr int W = THREADS / 64;
+    static_assert(THREADS * PER < 1 << 16, "two counts share a word");
     int32_t *out = sel_idx + (int64_t)b * kmax;
     const float *srow = scores + (int64_t)b * bv.max_vis_len;
 
@@ -384,7 +405,7 @@ __device__ __forceinline__ void topk_reg_body(
 
     if (k <= 0 || k >= N) {
         if (k >= N && k > 0)
-            for (int i = tid; i < N; i += THREADS) { out[i] = i; publish(i, i); }
+            for (int i = tid; i < N; i += THREADS) out[i] = i;
         if (tid == 0) sel_cnt[b] = k <= 0 ? 0 : N;
         return;
     }
@@ -395,9 +416,20 @@ __device__ __forceinline__ void topk_reg_body(
     // scalar registers, as `j < nvalid` would have it, take most of the scalar file)
     const uint32_t vmask = nvalid >= 32 ? 0xffffffffu : ((1u << nvalid) - 1u);
     auto real = [&](int j) { return ((vmask >> j) & 1u) != 0u; };
-    uint32_t key[PER];
+    uint32_t key[PER], signs = 0u;
 #pragma unroll
-    for (int j = 0; j < PER; ++j) key[j] = real(j) ? order_key(raw[j]) : 0u;
+    for (int j = 0; j < PER; ++j) { key[j] = __float_as_uint(raw[j]); signs |= key[j]; }
+    if (__builtin_amdgcn_ballot_w64((int)signs < 0) == 0ull) {     // no sign bit in the wave (weights never have one): order_key sets it
+#pragma unroll
+        for (int j = 0; j < PER; ++j) key[j] |= 0x80000000u;
+    } else {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) key[j] = order_key(raw[j]);
+    }
+    if (__builtin_amdgcn_ballot_w64(nvalid < PER) != 0ull) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) key[j] = real(j) ? key[j] : 0u;
+    }
     // the previous set's entries beyond the first THREADS (keep ratios above 1/PER)
     if (have_prev) {
         for (int r = tid + THREADS; r < k; r += THREADS) {
@@ -425,62 +457,46 @@ __device__ __forceinline__ void topk_reg_body(
     // reach that value (scores without structure: about a third of the keys, which spares the
     // histogram pass the other two thirds of its LDS atomics).
     uint32_t lo_own = (nvalid > 0 && k <= (N + PER - 1) / PER) ? kmx : (nvalid > 0 ? 0u : 0xffffffffu);
-    kmx = wave_max_u32(kmx);
-    kmn = wave_min_u32(kmn);
-    lo_prev = wave_min_u32(lo_prev);
-    lo_own = wave_min_u32(lo_own);
-    if (lane == 0) {
-        sh.w_ac[wave] = (int)kmx;
-        sh.w_ac[W + wave] = (int)~kmn;
-        sh.w_ac[2 * W + wave] = (int)~lo_prev;
-        sh.w_ac[3 * W + wave] = (int)~lo_own;
-    }
-    __syncthreads();
-    uint32_t nmn = 0u, nlo = 0u, now = 0u;                        // complements: everything is a maximum
-#pragma unroll
-    for (int v = 0; v < W / 4; ++v) {
-        const i32x4 *wv = reinterpret_cast<const i32x4 *>(sh.w_ac);
-        const i32x4 x = wv[v], y = wv[W / 4 + v], z = wv[2 * (W / 4) + v], u = wv[3 * (W / 4) + v];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            kmx = max(kmx, (uint32_t)x[e]);
-            nmn = max(nmn, (uint32_t)y[e]);
-            nlo = max(nlo, (uint32_t)z[e]);
-            now = max(now, (uint32_t)u[e]);
-        }
-    }
-    // (a sequence whose threads past its end vote 0xffffffff alone cannot happen: N >= 1 here)
-    const uint32_t lo = max(max(~nmn, ~nlo), ~now);               // (w_ac is next written two barriers further on)
+    // (complements: everything is a maximum.  A sequence whose threads past its end vote 0xffffffff alone cannot happen: N >= 1 here)
+    kmn = ~kmn;
+    lo_prev = ~lo_prev;
+    lo_own = ~lo_own;
+    block_max4<THREADS>(kmx, kmn, lo_prev, lo_own, sh.w_ac);
+    const uint32_t lo = max(max(~kmn, ~lo_prev), ~lo_own);
 
     // ---- the threshold ---------------------------------------------------------------------------------
     int ties;
-    const uint32_t theta = window_select<THREADS, PER>(key, lo, kmx, k, sh, &ties);
+    bool all;
+    const uint32_t theta = window_select<THREADS, PER>(key, lo, kmx, k, sh, &ties, &all);
 
     // ---- the result in ascending index order; ties go to the lowest indices ------------------------
-    // bit j of the masks: key j of this thread lies above / on the threshold
+    // bit j of the masks: key j of this thread reaches / lies above the threshold
     // (shifted in from the top key down: a compare and an add-with-carry per key and mask; a padding key,
     // 0, is never above a threshold and is taken off the ties by the validity mask)
-    uint32_t m_gt = 0u, m_eq = 0u;
+    uint32_t take = 0u;
 #pragma unroll
-    for (int j = PER - 1; j >= 0; --j) {
-        m_gt = m_gt + m_gt + ((key[j] > theta) ? 1u : 0u);
-        m_eq = m_eq + m_eq + ((key[j] == theta) ? 1u : 0u);
-    }
-    m_eq &= vmask;
-    int gt_excl, eq_excl, gt_tot, eq_tot;
-    block_scan2<THREADS>(__popc(m_gt), __popc(m_eq), sh.w_ac, gt_excl, eq_excl, &gt_tot, &eq_tot);
-    // of this thread's keys on the threshold, the first (ties - eq_excl) are still wanted
-    uint32_t take = m_gt;
-    {
+    for (int j = PER - 1; j >= 0; --j) take = take + take + ((key[j] >= theta) ? 1u : 0u);
+    take &= vmask;
+    int opos;
+    if (all) {                                   // the usual case: as many keys reach the threshold as are wanted
+        opos = (int)block_scan<THREADS>((uint32_t)__popc(take), sh.w_ac + 4 * W);
+    } else {
+        uint32_t m_gt = 0u;
+#pragma unroll
+        for (int j = PER - 1; j >= 0; --j) m_gt = m_gt + m_gt + ((key[j] > theta) ? 1u : 0u);
+        const uint32_t m_eq = take & ~m_gt;
+        const uint32_t upto = block_scan<THREADS>((uint32_t)__popc(m_gt) | ((uint32_t)__popc(m_eq) << 16), sh.w_ac + 5 * W);
+        const int gt_excl = (int)(upto & 0xffffu), eq_excl = (int)(upto >> 16);
+        // of this thread's keys on the threshold, the first (ties - eq_excl) are still wanted
+        take = m_gt;
         int want = min(max(ties - eq_excl, 0), __popc(m_eq));
         uint32_t rest = m_eq;
         while (want > 0) { const uint32_t low = rest & (0u - rest); take |= low; rest ^= low; --want; }
+        opos = gt_excl + min(ties, eq_excl);
     }
-    int opos = gt_excl + min(ties, eq_excl);
     while (take) {
         const int sel = base + __ffs((int)take) - 1;
         out[opos] = sel;
-        publish(opos, sel);
         ++opos;
         take &= take - 1u;
     }
