@@ -38,10 +38,14 @@ __device__ __forceinline__ uint32_t lds_address(const void *p)
 // The grid has W workgroups (at most one per compute unit).  With sequences of equal length every
 // sequence gets W / batch ranges.  In a ragged batch an equal split would leave the chip waiting
 // for the longest sequence's few workgroups, so the ranges are dealt in proportion to the sequences'
-// token counts: the smallest T with  sum_b max(base_b, ceil(S_b / T)) <= W  (found by bisection) gives sequence b
-// nr_b = max(base_b, ceil(S_b / T)) workgroups (base_b = what its image span needs at the most
+// token counts: the smallest T, in tiles, with  sum_b max(base_b, ceil(tiles_b / T)) <= W  gives sequence b
+// nr_b = max(base_b, ceil(tiles_b / T)) workgroups (base_b = what its image span needs at the most
 // tiles a wave can park).  Every wave computes the same table from the device-side lengths (the
-// host only knows their maxima): lane l looks after sequences 4l .. 4l+3, so batch <= 256.
+// host only knows their maxima): lane l looks after sequences l, l + 64, l + 128 and l + 192.
+// No row is requested before the table is there, so its instructions count: T lies a few per cent above the mean, from where it is
+// searched in growing steps, in tiles, with one float product per sequence (32 sequences, the last wave's geometry known after 2.7 us, where
+// bisecting T in tokens from the longest sequence down, four integer divisions a step, took 11.8: layer and top-k, 28/4 heads, paged, up to 16384
+// tokens, 125.8 -> 120.1 us, 16 sequences 83.7 -> 76.0; scoring, top-k and pruned attention 94.3 -> 86.9).
 struct RangeAlloc {
     int b, rng, nr, wg0;       // sequence, range within it, its range count, its first workgroup
     int R;                     // image tokens per range (a multiple of `unit`)
@@ -55,25 +59,23 @@ __device__ __forceinline__ RangeAlloc resident_alloc(const BatchDev &bv, int bat
                                                      int unit, int w)
 {
     const int lane = threadIdx.x & 63;
-    const int cap_tokens = kResTmax * unit;
+    const int rounds = (batch + 63) >> 6;                         // of 64 sequences
     int S[4], V0[4], N[4];
     bool same = true;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const int bb = 4 * lane + j;
         S[j] = 0; V0[j] = 0; N[j] = 0;
-        if (bb < batch) {
-            const SeqGeom g = seq_geom(bv, bb);
+        if (j < rounds) {
+            const SeqGeom g = seq_geom(bv, min(lane + 64 * j, batch - 1));
             S[j] = g.S; V0[j] = g.v0; N[j] = g.N;
         }
     }
     const int S0 = __builtin_amdgcn_readlane(S[0], 0), N0 = __builtin_amdgcn_readlane(N[0], 0);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) same = same && (4 * lane + j >= batch || (S[j] == S0 && N[j] == N0));
+    for (int j = 0; j < 4; ++j) same = same && (j >= rounds || (S[j] == S0 && N[j] == N0));
     const bool uniform = __builtin_amdgcn_ballot_w64(!same) == 0ull;
 
     RangeAlloc ra;
-    int start[4], cnt[4];
     if (uniform) {
         ra.b = w / nr_uniform;
         ra.rng = w - ra.b * nr_uniform;
@@ -82,64 +84,68 @@ __device__ __forceinline__ RangeAlloc resident_alloc(const BatchDev &bv, int bat
         ra.R = R_uniform;
         ra.active = ra.b < batch;
     } else {
+        // lengths in tiles (in multiples of a tile beyond 2^25 tokens, so that they stay below 2^20: the quotients below are then exact)
+        const int sh = 5 + max(0, 7 - (int)__builtin_clz((uint32_t)bv.max_seq_len | 1u));
+        static_assert(kResTile == 32, "a tile is 1 << 5 tokens");
+        const int cap = 31 - (int)__builtin_clz((uint32_t)(kResTmax * unit));              // log2: unit is 32, 64, 128 or 256
         int wt[4], base[4], part = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const bool live = 4 * lane + j < batch;
-            wt[j] = live ? max(S[j], 1) : 0;
-            base[j] = live ? max(1, (N[j] + cap_tokens - 1) / cap_tokens) : 0;
+            const bool live = lane + 64 * j < batch;
+            wt[j] = live ? max((int)(((uint32_t)S[j] + (1u << sh) - 1u) >> sh), 1) : 0;
+            base[j] = live ? max(1, (int)(((uint32_t)N[j] + (1u << cap) - 1u) >> cap)) : 0;
             part += wt[j];
         }
         const int total = wave_total(part);
+        // ceil(tiles / T): below 2^21, half a unit away from any whole number, the product's rounding decides nothing
+        auto count = [&](int j, int T, float inv) { return wt[j] > 0 ? max(base[j], (int)(((float)(wt[j] + T - 1) + 0.5f) * inv)) : 0; };
         auto need = [&](int T) {
-            int f = 0;
+            const float inv = __builtin_amdgcn_rcpf((float)T);
+            int f = count(0, T, inv);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) f += wt[j] > 0 ? max(base[j], (wt[j] + T - 1) / T) : 0;
+            for (int j = 1; j < 4; ++j) if (j < rounds) f += count(j, T, inv);
             return wave_total(f);
         };
-        // T = max_seq_len always fits (every sequence then takes base_b workgroups, and the host has
-        // checked that batch * max base <= W); bisect down from there to the smallest T that fits
-        int lo = max(1, (total + W - 1) / W) - 1, hi = max(bv.max_seq_len, 1);
-        if (lo + 1 <= hi && need(lo + 1) <= W) hi = lo + 1;
+        // a T below the mean never fits; the longest sequence's always does (every sequence then takes base_b workgroups, and the
+        // host has checked that batch * max base <= W)
+        const int top = max(1, (int)(((uint32_t)bv.max_seq_len + (1u << sh) - 1u) >> sh));
+        int lo = max(1, (total + W - 1) / W) - 1, hi = lo + 1, step = 1;
+        while (hi < top && need(hi) > W) { lo = hi; hi += step; step += step; }
+        hi = min(hi, top);
         while (hi - lo > 1) {
             const int mid = lo + (hi - lo) / 2;
             if (need(mid) <= W) hi = mid; else lo = mid;
         }
-        const int T = hi;
-        const bool fits = true;
-        int mine = 0;
+        const float inv = __builtin_amdgcn_rcpf((float)hi);
+        int before = 0;
+        ra.active = false;
+        ra.b = 0; ra.rng = 0; ra.nr = 0; ra.wg0 = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            cnt[j] = wt[j] > 0 ? (fits ? max(base[j], (wt[j] + T - 1) / T) : base[j]) : 0;
-            start[j] = mine;
-            mine += cnt[j];
+            if (j >= rounds) continue;
+            const int cnt = count(j, hi, inv), incl = wave_scan_incl(cnt), s0 = before + incl - cnt;
+            const unsigned long long who = __builtin_amdgcn_ballot_w64(w >= s0 && w < s0 + cnt);
+            if (who != 0ull) {
+                const int owner = __builtin_amdgcn_readfirstlane(__ffsll((long long)who) - 1);
+                ra.active = true;
+                ra.b = 64 * j + owner;
+                ra.wg0 = __builtin_amdgcn_readlane(s0, owner);
+                ra.rng = w - ra.wg0;
+                ra.nr = __builtin_amdgcn_readlane(cnt, owner);
+            }
+            before += __builtin_amdgcn_readlane(incl, 63);
         }
-        const int before = wave_scan_incl(mine) - mine;
-        int fb = 0, fr = 0, fn = 0, f0 = 0;
-        bool found = false;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int s0 = before + start[j];
-            if (cnt[j] > 0 && w >= s0 && w < s0 + cnt[j]) { found = true; fb = 4 * lane + j; fr = w - s0; fn = cnt[j]; f0 = s0; }
-        }
-        const unsigned long long who = __builtin_amdgcn_ballot_w64(found);
-        ra.active = who != 0ull;
-        const int owner = ra.active ? __builtin_amdgcn_readfirstlane(__ffsll((long long)who) - 1) : 0;
-        ra.b = __builtin_amdgcn_readlane(fb, owner);
-        ra.rng = __builtin_amdgcn_readlane(fr, owner);
-        ra.nr = __builtin_amdgcn_readlane(fn, owner);
-        ra.wg0 = __builtin_amdgcn_readlane(f0, owner);
         ra.R = 0;
     }
     // the sequence's geometry from the lane that loaded it
-    const int ol = __builtin_amdgcn_readfirstlane(min(ra.b, 255) >> 2), oj = ra.b & 3;
+    const int ol = ra.b & 63, oj = ra.b >> 6;
     const int ps = oj == 0 ? S[0] : (oj == 1 ? S[1] : (oj == 2 ? S[2] : S[3]));
     const int pv = oj == 0 ? V0[0] : (oj == 1 ? V0[1] : (oj == 2 ? V0[2] : V0[3]));
     const int pn = oj == 0 ? N[0] : (oj == 1 ? N[1] : (oj == 2 ? N[2] : N[3]));
     ra.S = __builtin_amdgcn_readlane(ps, ol);
     ra.v0 = __builtin_amdgcn_readlane(pv, ol);
     ra.N = __builtin_amdgcn_readlane(pn, ol);
-    if (!uniform) ra.R = max(unit, ((ra.N + ra.nr - 1) / max(ra.nr, 1) + unit - 1) / unit * unit);
+    if (!uniform) ra.R = max(unit, ((ra.N + ra.nr - 1) / max(ra.nr, 1) + unit - 1) & ~(unit - 1));
     return ra;
 }
 
