@@ -125,11 +125,13 @@ __device__ __forceinline__ int wave_scan_incl(int x)
     return x;
 }
 
-// Data-parallel-primitive moves within a row of 16 lanes (full-rate VALU, no LDS traffic).
+// Data-parallel-primitive moves within a row of 16 lanes (full-rate VALU, no LDS traffic).  None of the moves below has a lane
+// without a source; said so (bound_ctrl), the compiler makes the move a modifier of the instruction that uses it, one
+// instruction where a zero, the move and the operation were three.
 template <int CTRL>
 __device__ __forceinline__ float dpp_move(float x)
 {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
 }
 constexpr int kDppXor1 = 0xB1;          // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;          // quad_perm [2,3,0,1]

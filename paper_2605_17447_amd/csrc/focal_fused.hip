@@ -17,9 +17,15 @@
 //     tile of each is always in flight while the other is being consumed;
 //   - logits are produced transposed, C[token][column]: columns 0..7 are the group's heads for
 //     the tile's first 16 tokens, columns 8..15 the same heads for its last 16 (two accumulators,
-//     one select), so every lane holds 4 logits of ONE head; they stay in 4 VGPRs named for the
-//     tile until the normalisers are known;
-//   - the same layout serves P*V: with P masked to "first-half tokens in columns 0..7, second-half
+//     one select), so every lane holds 4 logits of ONE head.  Their softmax weights, which P*V needs anyway, stay in 4 VGPRs named
+//     for the tile until the normalisers are known, relative to the running maximum of their time, which LDS keeps.  (Parked logits, whose
+//     exponentials were taken behind the exchange, where nothing hides them, and lane moves of three instructions each: 64/8 heads,
+//     16 x 16384, 6.2 us from the statistics to the sums over the heads, now 4.1);
+//   - head_dim 64 has the registers and the idle matrix cores to produce the logits a second time with the operands exchanged,
+//     C[head][token]: 4 heads of one token per lane, in the scoring kernel's arithmetic step by step, so that both kernels' scores
+//     are the same bits and a set never depends on which of them a focal layer ran.  The sum over a token's heads is then four
+//     products in the lane instead of lane moves (behind the exchange, 64/8 heads, 16 x 16384: 7 -> 2.7 us);
+//   - the first layout serves P*V: with P masked to "first-half tokens in columns 0..7, second-half
 //     tokens in columns 8..15" one v_mfma_f32_16x16x32_bf16 per 16 output dims accumulates
 //     O^T[dim][column]; columns n and n+8 are the two halves' partial sums of head n and are added
 //     at the end.  The running maximum of a head is uniform over the wave (it scales whole
@@ -57,7 +63,7 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     uint32_t *__restrict__ gave_up_flag)
 {
     static_assert(sizeof(unsigned char[kResWaves][2][8192]) >= (size_t)kSelLdsBytes, "the select reuses the tile buffers");
-    __shared__ __align__(16) unsigned char smem[kResWaves][2][8192];      // [wave][K, V][slot]
+    __shared__ __align__(256) unsigned char smem[kResWaves][2][8192];     // [wave][K, V][slot]
 
     static_assert(D == 128 || D == 64, "head_dim 128 or 64");
     constexpr int KS = D / 32;             // k-steps of a logit
@@ -69,6 +75,7 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     constexpr int NSLOT = 128 / D;         // tiles of K (and of V) in flight: 8 KB each way, whatever the head_dim
     constexpr int NV = D == 128 ? 4 : 2;   // distinct chunk permutations over the loads of a K tile
     __shared__ float sm_m[kResWaves][8], sm_z[kResWaves][8];
+    __shared__ __align__(16) float sm_ref[D == 128 ? kResWaves : 1][kResTmax][8];
     __shared__ float sm_red[kResWaves];
     __shared__ int sm_met, sm_last;
 
@@ -129,9 +136,10 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     const uint32_t stride_b = (uint32_t)kv.stride_token * 2u;            // bytes; 32 rows fit 32 bits (host-checked)
     const uint32_t rowoff_row = (uint32_t)lrow * stride_b;
     const int fl = D == 128 ? lrow : (lrow >> 1);
-    uint32_t chunk_k[NV];
-#pragma unroll
-    for (int k = 0; k < NV; ++k) chunk_k[k] = 16u * (uint32_t)((lslot ^ fl) ^ (4 * k));
+    const uint32_t chunk_k0 = 16u * (uint32_t)(lslot ^ fl);
+    // (the permutations differ by an exclusive or with 4 (e & NV - 1) chunks; formed where they are used, they would live in registers
+    // that the loop does not have)
+    auto chunk_k = [&](int e) { return chunk_k0 ^ (uint32_t)(64 * (e & (NV - 1))); };
     const uint32_t chunk_v = 16u * (uint32_t)lslot;
     const unsigned char *kbytes = reinterpret_cast<const unsigned char *>(kv.k);
     const unsigned char *vbytes = reinterpret_cast<const unsigned char *>(kv.v);
@@ -153,14 +161,14 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
             for (int e = 0; e < NL; ++e) {
                 const uint32_t ro = min(rowoff_row + (uint32_t)(RPL * e) * stride_b, limit);
                 const unsigned char *base = ro >= split ? base_b : base_a;
-                lds_dma16(reinterpret_cast<const uint16_t *>(base + (ro + (isv ? chunk_v : chunk_k[e & (NV - 1)]))), dst + 1024 * e);
+                lds_dma16(reinterpret_cast<const uint16_t *>(base + (ro + (isv ? chunk_v : chunk_k(e)))), dst + 1024 * e);
             }
         } else {
             const unsigned char *base = bytes + 2 * (seq_base + (int64_t)first_tok * kv.stride_token);
 #pragma unroll
             for (int e = 0; e < NL; ++e) {
                 const uint32_t ro = min(rowoff_row + (uint32_t)(RPL * e) * stride_b, limit);
-                lds_dma16(reinterpret_cast<const uint16_t *>(base + (ro + (isv ? chunk_v : chunk_k[e & (NV - 1)]))), dst + 1024 * e);
+                lds_dma16(reinterpret_cast<const uint16_t *>(base + (ro + (isv ? chunk_v : chunk_k(e)))), dst + 1024 * e);
             }
         }
     };
@@ -186,7 +194,7 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
         for (int e = 0; e < NL; ++e) {
             const int tc = min(tf + RPL * e + lrow, Tn - 1);
             const int tok = tc < v0 ? tc : tc + N;
-            lds_dma16(base + row_offset<PAGED>(kv, b, tok, kvh) + (isv ? chunk_v : chunk_k[e & (NV - 1)]) / 2, dst + 1024 * e);
+            lds_dma16(base + row_offset<PAGED>(kv, b, tok, kvh) + (isv ? chunk_v : chunk_k(e)) / 2, dst + 1024 * e);
         }
     };
     // tile number n of the wave (text tiles first, then image tiles), or the dummy past the end
@@ -196,22 +204,22 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     };
 
     const int tt0 = 16 * (li >> 3) + 4 * lg;        // tile-relative token of this lane's first logit
-    float m = kMinusHuge, z = 0.f;                  // running max (uniform over the head's lanes), this lane's sum (D 128)
-    // D 64: what is parked is not the logit but its softmax weight, in the scoring kernel's arithmetic step by step
-    // (score_resident.hip: per token slot of the tile a reference fixed by the slot's first live logit,
-    // the sums joined in the same order), so that both kernels' scores are the same bits and a set never
-    // depends on which of them a focal layer ran.  Head_dim 128 has no registers for the references.
+    // Running max, uniform over the head's lanes (lane li: head li & 7).  Head_dim 128: z is this lane's sum; the weights
+    // parked so far stay as they are when m grows -- there are no registers to bring 128 of them along -- and m is noted in LDS for
+    // every image tile; bit J of moved_at says that it grew there (or that tile J is the first).
+    float m = kMinusHuge, z = 0.f;
+    uint32_t moved_at = 1u;
+    // Head_dim 64: the scoring kernel's references and sums (score_resident.hip) of heads 4 (lg & 1) .. + 3, this lane's token of a tile
+    const int tok_in_tile = li + 16 * (lg >> 1);
     float ref[4] = {kMinusHuge, kMinusHuge, kMinusHuge, kMinusHuge}, zr[4] = {0.f, 0.f, 0.f, 0.f};
-    f32x32 park0, park1, park2, park3;              // logit (D 64: weight) r of image tile J in park<r>[J]
+    f32x32 park0, park1, park2, park3;              // the weight of token r (D 64: head r) of the lane in image tile J: park<r>[J]
     f32x4 acc[NACC];
 #pragma unroll
     for (int t = 0; t < NACC; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // LDS byte addresses in slot 0: K rows li and 16 + li as the A operand, V rows 4lg.. and 16 + 4lg..
-    uint32_t rd_addr[KS];
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk)
-        rd_addr[kk] = lds_address(&smem[wave][0][0]) + li * ROWB + ((((4 * kk + lg) ^ (D == 128 ? li : (li >> 1))) & (CPR - 1)) << 4);
+    // (chunk 4 kk + lg of a row, permuted: an exclusive or with 64 kk bytes)
+    const uint32_t rd_k = lds_address(&smem[wave][0][0]) + li * ROWB + (((lg ^ (D == 128 ? li : (li >> 1))) & (CPR - 1)) << 4);
     const uint32_t rd_v = lds_address(&smem[wave][1][0]) + (4 * lg) * ROWB + (li & (CPR - 1)) * 16;
 
     // Loads are sent in the order K(n), V(n), K(n+1), ..; when K(n) is wanted the newest ones outstanding
@@ -230,7 +238,7 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
                 "ds_read_b128 %1, %3\n\t"
                 "s_waitcnt lgkmcnt(0)"
                 : "=&v"(kb[0]), "=&v"(kb[1])
-                : "v"(rd_addr[0] + so), "v"(rd_addr[1] + so)
+                : "v"(rd_k + so), "v"((rd_k ^ 64u) + so)
                 : "memory");
         else asm volatile(
             "s_waitcnt vmcnt(8)\n\t"
@@ -240,7 +248,7 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
             "ds_read_b128 %3, %7\n\t"
             "s_waitcnt lgkmcnt(0)"
             : "=&v"(kb[0]), "=&v"(kb[1]), "=&v"(kb[2]), "=&v"(kb[3])
-            : "v"(rd_addr[0]), "v"(rd_addr[1]), "v"(rd_addr[2]), "v"(rd_addr[3])
+            : "v"(rd_k), "v"(rd_k ^ 64u), "v"(rd_k ^ 128u), "v"(rd_k ^ 192u)
             : "memory");
     };
     auto read_k_hi = [&](uint32_t so, u32x4(&kb)[KS]) {
@@ -250,7 +258,7 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
                 "ds_read_b128 %1, %3 offset:2048\n\t"
                 "s_waitcnt lgkmcnt(0)"
                 : "=&v"(kb[0]), "=&v"(kb[1])
-                : "v"(rd_addr[0] + so), "v"(rd_addr[1] + so)
+                : "v"(rd_k + so), "v"((rd_k ^ 64u) + so)
                 : "memory");
         else asm volatile(
             "ds_read_b128 %0, %4 offset:4096\n\t"
@@ -259,7 +267,7 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
             "ds_read_b128 %3, %7 offset:4096\n\t"
             "s_waitcnt lgkmcnt(0)"
             : "=&v"(kb[0]), "=&v"(kb[1]), "=&v"(kb[2]), "=&v"(kb[3])
-            : "v"(rd_addr[0]), "v"(rd_addr[1]), "v"(rd_addr[2]), "v"(rd_addr[3])
+            : "v"(rd_k), "v"(rd_k ^ 64u), "v"(rd_k ^ 128u), "v"(rd_k ^ 192u)
             : "memory");
     };
     // vv[e]: chunk li (D 64: li & 7) of the row of token 4lg + e (e < 4) or 16 + 4lg + e - 4 of the tile
@@ -295,44 +303,92 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
             : "memory");
     };
 
-    // One tile: logits, online softmax, P*V.  nlive = tokens of the tile that exist (may exceed 32).
-    // Returns this lane's 4 logits (log2 domain; -inf for tokens past the end), for D 64 their weights.
+    // One tile: logits, online softmax, P*V.  nlive = tokens of the tile that exist (may exceed 32).  Returns the weights to park.
     auto tile_step = [&](int n, int nlive, auto &&next_k, auto &&next_v) -> f32x4 {
+        f32x4 weights;
         const uint32_t so = (uint32_t)(n & (NSLOT - 1)) * (8192 / NSLOT);
         u32x4 kb[KS];
-        f32x4 c0 = f32x4{0.f, 0.f, 0.f, 0.f}, c1 = c0;
+        f32x4 c0 = f32x4{0.f, 0.f, 0.f, 0.f}, c1 = c0, t0 = c0, t1 = c0;
         read_k_lo(so, kb);
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk)
+        for (int kk = 0; kk < KS; ++kk) {
             c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kb[kk]),
                                                          __builtin_bit_cast(bf16x8, qq[kk]), c0, 0, 0, 0);
+            if constexpr (D == 64)
+                t0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qq[kk]),
+                                                             __builtin_bit_cast(bf16x8, kb[kk]), t0, 0, 0, 0);
+        }
         read_k_hi(so, kb);
         next_k();
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk)
+        for (int kk = 0; kk < KS; ++kk) {
             c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kb[kk]),
                                                          __builtin_bit_cast(bf16x8, qq[kk]), c1, 0, 0, 0);
-        f32x4 s;
+            if constexpr (D == 64)
+                t1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qq[kk]),
+                                                             __builtin_bit_cast(bf16x8, kb[kk]), t1, 0, 0, 0);
+        }
+        if constexpr (D == 64) {
+            const bool live = tok_in_tile < nlive;
+            f32x4 w;
+            bool moved = false;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float x = lg >= 2 ? t1[r] : t0[r];
+                w[r] = live ? x * scale_log2 : -INFINITY;
+                if (ref[r] == kMinusHuge) ref[r] = fmaxf(w[r], kMinusHuge);          // the first live logit
+                moved = moved || w[r] - ref[r] > kRefSlack;
+            }
+            if (__builtin_amdgcn_ballot_w64(moved) != 0ull) {
+                float a[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const bool mv = w[r] - ref[r] > kRefSlack;
+                    a[r] = mv ? fast_exp2(ref[r] - w[r]) : 1.f;
+                    ref[r] = mv ? w[r] : ref[r];
+                    zr[r] *= a[r];
+                }
+                // (tile by tile: as whole vectors they would be copied)
+                for (int x = 0; x < n - ntext; ++x) {
+                    park0[x] *= a[0];
+                    park1[x] *= a[1];
+                    park2[x] *= a[2];
+                    park3[x] *= a[3];
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                w[r] = fast_exp2(w[r] - ref[r]);
+                zr[r] += w[r];
+            }
+            weights = w;
+        }
+        float p[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const float x = hi ? c1[r] : c0[r];
-            s[r] = (tt0 + r < nlive) ? x * scale_log2 : -INFINITY;
+            p[r] = (tt0 + r < nlive) ? x * scale_log2 : -INFINITY;
         }
-        float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+        float mx = fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3]));
         mx = fmaxf(mx, dpp_move<kDppRor8>(mx));
         mx = rows_max(mx);
         const float m_new = fmaxf(m, mx);
         if (__builtin_amdgcn_ballot_w64(m_new != m) != 0ull) {
             const float alpha = fast_exp2(m - m_new);
-            if constexpr (D == 128) z *= alpha;
 #pragma unroll
             for (int t = 0; t < NACC; ++t) acc[t] *= alpha;
+            if constexpr (D == 128) {
+                z *= alpha;
+                if (n >= ntext) moved_at |= 1u << (n - ntext);
+            }
             m = m_new;
         }
-        float p[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) p[r] = fast_exp2(s[r] - m);
-        if constexpr (D == 128) z += (p[0] + p[1]) + (p[2] + p[3]);
+        for (int r = 0; r < 4; ++r) p[r] = fast_exp2(p[r] - m);
+        if constexpr (D == 128) {
+            z += (p[0] + p[1]) + (p[2] + p[3]);
+            weights = f32x4{p[0], p[1], p[2], p[3]};
+        }
         const uint32_t w0 = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)p[0], (__bf16)p[1]});
         const uint32_t w1 = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)p[2], (__bf16)p[3]});
         // contraction slots of lane group lg: tokens 4lg..4lg+3, then 16+4lg..16+4lg+3
@@ -353,37 +409,10 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
             acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
                                                              __builtin_bit_cast(bf16x8, pb), acc[t], 0, 0, 0);
         }
-        if constexpr (D == 64) {
-            bool moved = false;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                if (ref[r] == kMinusHuge) ref[r] = fmaxf(s[r], kMinusHuge);          // the first live logit
-                moved = moved || s[r] - ref[r] > kRefSlack;
-            }
-            if (__builtin_amdgcn_ballot_w64(moved) != 0ull) {
-                float a[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const bool mv = s[r] - ref[r] > kRefSlack;
-                    a[r] = mv ? fast_exp2(ref[r] - s[r]) : 1.f;
-                    ref[r] = mv ? s[r] : ref[r];
-                    zr[r] *= a[r];
-                }
-                park0 *= a[0];
-                park1 *= a[1];
-                park2 *= a[2];
-                park3 *= a[3];
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                s[r] = fast_exp2(s[r] - ref[r]);
-                zr[r] += s[r];
-            }
-        }
-        return s;
+        return weights;
     };
 
-    // ---- stream: text tiles, then image tiles (logits parked in registers) ----------------------
+    // ---- stream: text tiles, then image tiles (weights parked in registers) ----------------------
     if (ntext + nimg > 0) {
         issue_any(0, false);
         issue_any(0, true);
@@ -391,11 +420,12 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
         for (int x = 0; x < ntext; ++x)
             (void)tile_step(x, Tn - text_first(x), [&]() { issue_any(x + NSLOT, false); }, [&]() { issue_any(x + NSLOT, true); });
         for (int J = 0; J < nimg; ++J) {
-            const f32x4 s = tile_step(ntext + J, r1 - img_first(J), [&]() { issue_img(J + NSLOT, false); }, [&]() { issue_img(J + NSLOT, true); });
-            park0[J] = s[0];
-            park1[J] = s[1];
-            park2[J] = s[2];
-            park3[J] = s[3];
+            const f32x4 w = tile_step(ntext + J, r1 - img_first(J), [&]() { issue_img(J + NSLOT, false); }, [&]() { issue_img(J + NSLOT, true); });
+            park0[J] = w[0];
+            park1[J] = w[1];
+            park2[J] = w[2];
+            park3[J] = w[3];
+            if constexpr (D == 128) sm_ref[wave][J][hcol] = m;
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the trailing refills must not land later
@@ -404,31 +434,37 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     // they would occupy registers it has no room for.
     int tx_p = threadIdx.x;
     asm volatile("" : "+v"(tx_p));
-    const int lane_p = tx_p & 63, li_p = lane_p & 15, lg_p = lane_p >> 4, hcol_p = li_p & 7;
-    const int tt0_p = 16 * (li_p >> 3) + 4 * lg_p;
+    const int lane_p = tx_p & 63, li_p = lane_p & 15, lg_p = lane_p >> 4, hcol_p = li_p & 7, hbase_p = 4 * (lg_p & 1);
 
-    // ---- attention partial of this wave: O^T columns n and n + 8 are the same head's halves -----
-    // mref, zref: what the sums are relative to and their total, per head (lanes li and li + 8, all lane groups)
-    float mref = m, zref;
+    // ---- the wave's statistics per head: what the weights are relative to, and their sum ----------------------
     if constexpr (D == 128) {
         z += dpp_move<kDppRor8>(z);
         z = rows_sum(z);
-        zref = z;
+        if (lane_p < 8) { sm_m[wave][lane_p] = m; sm_z[wave][lane_p] = z; }
     } else {
-        mref = fmaxf(fmaxf(ref[0], ref[1]), fmaxf(ref[2], ref[3]));
-        mref = rows_max(mref);
-        mref = fmaxf(mref, dpp_move<kDppRor8>(mref));
-        // the scoring kernel's first step adds a product to its neighbour's rounded one, and the lane whose total
-        // counts meets the odd quads of a half mirrored (reductions over score_resident.hip's lanes li)
-        float e[4];
+        // in the scoring kernel's steps and roundings
 #pragma unroll
-        for (int r = 0; r < 4; ++r) e[r] = fast_exp2(ref[r] - mref);
-        zref = (lg_p & 1) ? fmaf(zr[3], e[3], zr[2] * e[2]) + fmaf(zr[1], e[1], zr[0] * e[0])
-                          : fmaf(zr[0], e[0], zr[1] * e[1]) + fmaf(zr[2], e[2], zr[3] * e[3]);
-        zref = rows_sum(zref);
-        zref += dpp_move<kDppRor8>(zref);
-        z = zref * fast_exp2(mref - m);             // the same sum relative to the running maximum, as the partial has it
+        for (int r = 0; r < 4; ++r) {
+            float M = ref[r];
+            M = fmaxf(M, dpp_move<kDppXor1>(M));
+            M = fmaxf(M, dpp_move<kDppXor2>(M));
+            M = fmaxf(M, dpp_move<kDppHalfMirror>(M));
+            M = fmaxf(M, dpp_move<kDppRowMirror>(M));
+            M = with_lane_xor32(M, [](float a, float b) { return fmaxf(a, b); });
+            const float e = fast_exp2(ref[r] - M);
+            float Z = fmaf(zr[r], e, dpp_move<kDppXor1>(zr[r] * e));
+            Z += dpp_move<kDppXor2>(Z);
+            Z += dpp_move<kDppHalfMirror>(Z);
+            Z += dpp_move<kDppRowMirror>(Z);
+            Z = with_lane_xor32(Z, [](float a, float b) { return a + b; });
+            if (li_p == 0 && lg_p < 2) { sm_m[wave][hbase_p + r] = M; sm_z[wave][hbase_p + r] = Z; }
+        }
+        wave_lds_fence();
+        // relative to the running maximum, as the partial has it (a reference lies at most kRefSlack below)
+        z = sm_z[wave][li_p & 7] * fast_exp2(sm_m[wave][li_p & 7] - m);
     }
+
+    // ---- attention partial of this wave: O^T columns n and n + 8 are the same head's halves -----
 #pragma unroll
     for (int t = 0; t < NACC; ++t)
 #pragma unroll
@@ -472,8 +508,6 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
         if (lg_p == 0) {
             att_ml[2 * row] = m;
             att_ml[2 * row + 1] = z;
-            sm_m[wave][li_p] = mref;
-            sm_z[wave][li_p] = zref;
         }
     }
     if (threadIdx.x == 0) sm_met = 1;
@@ -485,17 +519,15 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     // ranges end together, the first answer comes back incomplete and a second round trip follows.)
     unsigned long long *stats = g_fus_stats[sync_slot] + (int64_t)wg0 * Hq;
     resident_publish(stats + (int64_t)rng * Hq, sm_m, sm_z, Hq, G, Hkv, wpk);
-    // the log-sum-exp of this wave's heads over the whole sequence (lane 8s + x: head x of the group)
-    float lh;
+    // (reference, sum) of this wave's heads over the whole sequence (lane 8s + x: head x of the group)
+    float Mh, Zh;
     {
-        float M, Z;
-        const bool ok = resident_heads_gather<4>(stats, rng, nranges, Hq, G, Hkv, wpk, kvh, sm_m, sm_z, spin_ticks, M, Z);
+        const bool ok = resident_heads_gather<4>(stats, rng, nranges, Hq, G, Hkv, wpk, kvh, sm_m, sm_z, spin_ticks, Mh, Zh);
         if (!ok && lane_p == 0) {
             sm_met = 0;
             __hip_atomic_fetch_add(&g_fus_timeouts, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (gave_up_flag) __hip_atomic_store(gave_up_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
-        lh = (hcol_p < G && Z > 0.f) ? M + log2f(Z) : (hcol_p < G ? -INFINITY : INFINITY);
     }
     __syncthreads();      // whether every wave has met its ranges
     // This range is done reading: count it out.  The last one of the sequence clears the
@@ -517,50 +549,34 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
         leave();
         return;
     }
-    if (lse_out && rng == 0 && sub == 0 && lane_p < G) lse_out[(int64_t)b * Hq + kvh * G + lane_p] = lh * kLn2;
+    if (lse_out && rng == 0 && sub == 0 && lane_p < G) lse_out[(int64_t)b * Hq + kvh * G + lane_p] = resident_lse(Mh, Zh);
 
-    // ---- probabilities of the parked logits, summed over the heads of each token ---------------
-    // D 128: one row of sums per kv head, [Hkv][R], at most 32 KB; D 64: one per four heads, [2 Hkv][R], at most 64 KB
+    // ---- the parked weights brought to the normalisers, summed over the heads of each token: one row of sums per four heads,
+    // [2 Hkv][R], at most 64 KB -----------------------------------------------------------------------
     float *red = reinterpret_cast<float *>(&smem[0][0][0]);
     if constexpr (D == 128) {
+        const float Mx = __shfl(Mh, hcol_p), ix = 1.0f / __shfl(Zh, hcol_p);
+        const float Mc = hcol_p < G ? Mx : INFINITY, ic = hcol_p < G ? ix : 0.f;
+        float c = 0.f;
+        float *to = red + (2 * kvh + ((li_p >> 2) & 1)) * R - r0 + 16 * (li_p >> 3) + 4 * lg_p + (li_p & 3);
+        const bool odd = (li_p & 1) != 0, high = (li_p & 2) != 0;
+#pragma unroll 2
         for (int J = 0; J < nimg; ++J) {
-            // this lane_p's 4 tokens of tile J, one head each on 8 neighbouring lanes
-            f32x4 v = f32x4{park0[J], park1[J], park2[J], park3[J]};
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                float x = fast_exp2(v[r] - lh);
-                x += dpp_move<kDppXor1>(x);
-                x += dpp_move<kDppXor2>(x);
-                x += dpp_move<kDppHalfMirror>(x);
-                v[r] = x;
-            }
-            if ((li_p & 7) == 0) *reinterpret_cast<f32x4 *>(&red[kvh * R + img_first(J) - r0 + tt0_p]) = v;
+#pragma clang fp contract(off)
+            if ((moved_at >> J) & 1u) c = fast_exp2(sm_ref[wave][J][hcol_p] - Mc) * ic;
+            // 4 tokens of tile J in each of 4 neighbouring lanes, a head each: lane k ends up with the sum of token k
+            const float v0 = park0[J] * c, v1 = park1[J] * c, v2 = park2[J] * c, v3 = park3[J] * c;
+            const float y0 = (odd ? v1 : v0) + dpp_move<kDppXor1>(odd ? v0 : v1);
+            const float y1 = (odd ? v3 : v2) + dpp_move<kDppXor1>(odd ? v2 : v3);
+            to[img_first(J)] = (high ? y1 : y0) + dpp_move<kDppXor2>(high ? y0 : y1);
         }
     } else {
-        // from the slot's reference to the head's normaliser (lane x's for head x, as in the scoring kernel: the lanes of
-        // a head agree only up to the rounding of the gather's last merges), for the four heads of this lane's quad
-        lh = __shfl(lh, hcol_p);
-        float cf[4][4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float c = hcol_p < G ? fast_exp2(ref[r] - lh) : 0.f;
-            cf[r][0] = dpp_move<kDppQuad0>(c);
-            cf[r][1] = dpp_move<kDppQuad1>(c);
-            cf[r][2] = dpp_move<kDppQuad2>(c);
-            cf[r][3] = dpp_move<kDppQuad3>(c);
-        }
+        float cf[4];
+        resident_factors(Mh, Zh, ref, hbase_p, G, cf);
+        float *to = red + (2 * kvh + (lg_p & 1)) * R - r0 + li_p + 16 * (lg_p >> 1);
         for (int J = 0; J < nimg; ++J) {
-            f32x4 v = f32x4{park0[J], park1[J], park2[J], park3[J]};
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float w = v[r];
-                float x = dpp_move<kDppQuad0>(w) * cf[r][0];
-                x = fmaf(dpp_move<kDppQuad1>(w), cf[r][1], x);
-                x = fmaf(dpp_move<kDppQuad2>(w), cf[r][2], x);
-                x = fmaf(dpp_move<kDppQuad3>(w), cf[r][3], x);
-                v[r] = x;
-            }
-            if ((li_p & 3) == 0) *reinterpret_cast<f32x4 *>(&red[(2 * kvh + ((li_p >> 2) & 1)) * R + img_first(J) - r0 + tt0_p]) = v;
+            const f32x4 w = f32x4{park0[J], park1[J], park2[J], park3[J]};
+            to[img_first(J)] = resident_head_sum(w, cf);
         }
     }
     __syncthreads();
@@ -573,7 +589,7 @@ __global__ __launch_bounds__(kResThreads) void focal_fused_kernel(
     asm volatile(".p2align 6\n\t.rept 9\n\ts_nop 0\n\t.endr");
     float local = 0.f;
     const float inv = 1.0f / (float)Hq;
-    const int rows = D == 128 ? Hkv : 2 * Hkv;
+    const int rows = 2 * Hkv;
     for (int i = threadIdx.x; i < r1 - r0; i += kResThreads) {
         float a = 0.f;
         for (int g = 0; g < rows; ++g) a += red[g * R + i];

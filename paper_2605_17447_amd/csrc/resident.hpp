@@ -273,6 +273,26 @@ __device__ __forceinline__ bool resident_heads_gather(const unsigned long long *
     return true;
 }
 
+// What the gathered (M, Z) of a wave's heads (lane x: head x) are used for.  From a lane's references to the sequence's normalisers, for
+// its heads hbase .. hbase + 3: 2^(ref - M) / Z.  (ref - M is a small difference of numbers of like size; subtracting M + log2 Z instead rounds at
+// that sum's own size, up to 1e-6 of the weight: error of the scores against 64 bits 3.3e-7 -> 1.4e-7 at 64/8 heads, 16 x 16384.)
+__device__ __forceinline__ void resident_factors(float M, float Z, const float (&ref)[4], int hbase, int G, float (&cf)[4])
+{
+    const float inv = 1.0f / Z;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        auto of = [&](float x, int h) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), h)); };
+        const float Mr = hbase ? of(M, 4 + r) : of(M, r), ir = hbase ? of(inv, 4 + r) : of(inv, r);
+        cf[r] = hbase + r < G ? fast_exp2(ref[r] - Mr) * ir : 0.f;
+    }
+}
+// a token's four weights of one lane, summed (spelt out: both kernels have the same roundings)
+__device__ __forceinline__ float resident_head_sum(const f32x4 &w, const float (&cf)[4])
+{
+    return fmaf(w[3], cf[3], fmaf(w[2], cf[2], fmaf(w[1], cf[1], w[0] * cf[0])));
+}
+__device__ __forceinline__ float resident_lse(float M, float Z) { return (Z > 0.f ? M + log2f(Z) : -INFINITY) * kLn2; }
+
 // Called by every thread when the workgroup is done reading (after a __syncthreads): `last` says
 // whether this range was the sequence's last to finish reading; it then clears the sequence's words
 // and the count.

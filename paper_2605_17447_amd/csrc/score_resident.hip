@@ -54,9 +54,7 @@ constexpr int kResGatherGroup = 8;      // ranges whose statistics a wave asks f
 // tile would cost more than the second row does in the final sum)
 #define RES_FINISH_STEP(J)                                                                          \
     {                                                                                               \
-        float v = 0.f;                                                                              \
-        _Pragma("unroll") for (int r = 0; r < 4; ++r) v += park_##J[r] * cf[r];                     \
-        red[(2 * kvh + (lg & 1)) * R + img_first(J) - r0 + tok_in_tile] = v;                        \
+        red[(2 * kvh + (lg & 1)) * R + img_first(J) - r0 + tok_in_tile] = resident_head_sum(park_##J, cf);    \
         if ((J) + 1 >= nimg) goto fin_done;                                                         \
     }
 
@@ -431,10 +429,9 @@ img_done:
     // publish this range's statistics (resident.hpp: every word is its own "ready" flag)
     resident_publish(stats + (int64_t)rng * Hq, sm_m, sm_z, Hq, G, Hkv, wpk);
 
-    // ---- the log-sum-exp of this wave's heads over the whole sequence (lane 8s + x: head x of the group) ----
-    float l2;
+    // ---- (reference, sum) of this wave's heads over the whole sequence (lane 8s + x: head x of the group) ----
+    float M, Z;
     {
-        float M, Z;
         const bool ok = resident_heads_gather<kResGatherGroup>(stats, rng, nranges, Hq, G, Hkv, wpk, kvh, sm_m, sm_z, spin_ticks,
                                                                M, Z, &early);
         if (!ok && lane == 0) {
@@ -442,7 +439,6 @@ img_done:
             __hip_atomic_fetch_add(&g_res_timeouts, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (gave_up_flag) __hip_atomic_store(gave_up_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
-        l2 = Z > 0.f ? M + log2f(Z) : -INFINITY;
     }
     __syncthreads();      // whether every wave has met its ranges; the tile buffers are free for the head sums
     // This range is done reading: count it out.  The last one of the sequence (it has seen every
@@ -465,16 +461,11 @@ img_done:
         leave();
         return;
     }
-    if (lse_out && rng == 0 && sub == 0 && lane < G) lse_out[(int64_t)b * Hq + kvh * G + lane] = l2 * kLn2;
+    if (lse_out && rng == 0 && sub == 0 && lane < G) lse_out[(int64_t)b * Hq + kvh * G + lane] = resident_lse(M, Z);
 
     // ---- the parked weights brought to the normalisers, summed over the heads of each token ------
     float cf[4];          // from "relative to the lane's reference" to "relative to the head's normaliser"
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const float la = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, l2), r));
-        const float lb = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, l2), 4 + r));
-        cf[r] = (hbase + r < G) ? fast_exp2(ref[r] - (hbase ? lb : la)) : 0.f;
-    }
+    resident_factors(M, Z, ref, hbase, G, cf);
     float *red = reinterpret_cast<float *>(&smem[0][0][0]);          // [2 Hkv][R], at most 64 KB
     if (nimg > 0) {
         RES_EACH_TILE(RES_FINISH_STEP)

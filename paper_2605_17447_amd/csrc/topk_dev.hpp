@@ -107,7 +107,7 @@ __device__ uint32_t radix_select(const uint32_t *keys, int n, int k, uint32_t (*
 // the two counts of the prefix sum share a word and the second one is seldom needed (1.7 -> 0.8 us), and keys of scores without a
 // sign bit take one instruction each.
 
-#define FASTOCR_ROW_STEP(OP, X, CTRL) X = OP(X, (uint32_t)__builtin_amdgcn_update_dpp((int)(X), (int)(X), CTRL, 0xf, 0xf, false))
+#define FASTOCR_ROW_STEP(OP, X, CTRL) X = OP(X, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(X), CTRL, 0xf, 0xf, true))
 // the maximum over each row of 16 lanes, in all of them
 __device__ __forceinline__ uint32_t row_max_u32(uint32_t x)
 {
