@@ -204,6 +204,18 @@ int fastocr_sparse_decode_attn(const fastocr_kv_view *kv, const fastocr_batch_vi
                                size_t ws_bytes, void *hip_stream);
 
 /*
+ * fastocr_sparse_decode_attn for n_layers layers that attend the same set, kv[l], q[l] and out[l] each: what the calls one after the
+ * other give, up to the rounding that their range counts make, in one launch per 32 layers where the caches differ in their places
+ * alone, run on the bf16 matrix-core kernels, and no output overlaps another layer's query or output; else those calls.  For programs that
+ * hold the queries of several layers at once.  All arguments are checked before anything is enqueued.  ws: as the largest layer needs.
+ * Kernels are timed as FASTOCR_KERNEL_SPARSE_ATTN, a launch of several layers once.
+ */
+int fastocr_sparse_decode_attn_layers(int n_layers, const fastocr_kv_view *kv, const fastocr_batch_view *bv,
+                                      const void *const *q, int n_q_heads, float scale, const int32_t *sel_idx,
+                                      const int32_t *sel_cnt, int64_t kmax, void *const *out, void *ws,
+                                      size_t ws_bytes, void *hip_stream);
+
+/*
  * Eq. 2, focal branch: the same with J_b = [0, seq_len[b]).
  *   lse  fp32 [batch, n_q_heads] natural-log sum-exp of the logits, or NULL
  */

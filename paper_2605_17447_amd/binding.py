@@ -9,7 +9,7 @@ from __future__ import annotations
 import ctypes
 import os
 from dataclasses import dataclass
-from typing import Optional
+from typing import List, Optional
 
 import torch
 
@@ -27,7 +27,7 @@ OP_FOCAL_SCORE_TOPK, OP_FOCAL_ATTN_SCORE_TOPK = 5, 6
 
 EXPORTS = (
     "fastocr_keep_count", "fastocr_workspace_bytes", "fastocr_focal_score", "fastocr_topk_fixation",
-    "fastocr_sparse_decode_attn", "fastocr_dense_decode_attn", "fastocr_dense_decode_attn_static", "fastocr_focal_attn_score",
+    "fastocr_sparse_decode_attn", "fastocr_sparse_decode_attn_layers", "fastocr_dense_decode_attn", "fastocr_dense_decode_attn_static", "fastocr_focal_attn_score",
     "fastocr_focal_score_topk", "fastocr_focal_attn_score_topk", "fastocr_kernel_timer_enable",
     "fastocr_kernel_timer_read", "fastocr_select_focal_layers", "fastocr_stream_probe", "fastocr_set_tuning", "fastocr_exchange_timeouts", "fastocr_stream_release", "fastocr_strerror", "fastocr_version",
 )
@@ -82,6 +82,8 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib.fastocr_topk_fixation.argtypes = [P, BV, D, P, P, P, P, I64, P, SZ, P]
     lib.fastocr_sparse_decode_attn.restype = I
     lib.fastocr_sparse_decode_attn.argtypes = [KV, BV, P, I, F, P, P, I64, P, P, SZ, P]
+    lib.fastocr_sparse_decode_attn_layers.restype = I
+    lib.fastocr_sparse_decode_attn_layers.argtypes = [I, KV, BV, P, I, F, P, P, I64, P, P, SZ, P]
     lib.fastocr_dense_decode_attn.restype = I
     lib.fastocr_dense_decode_attn.argtypes = [KV, BV, P, I, F, P, P, P, SZ, P]
     lib.fastocr_dense_decode_attn_static.restype = I
@@ -127,6 +129,7 @@ def _bind_call(lib) -> None:
              "focal_attn_score_topk")
     call.bind(KvCache, SeqBatch, _current_device, _raw_stream, torch.cuda.is_initialized,
               *(ctypes.cast(getattr(lib, "fastocr_" + n), ctypes.c_void_p).value for n in names))
+    call.bind_layers(ctypes.cast(lib.fastocr_sparse_decode_attn_layers, ctypes.c_void_p).value)
     _call = call
 
 
@@ -330,6 +333,30 @@ def sparse_decode_attn(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scale: 
                                           float(scale), sel_idx.data_ptr(), sel_cnt.data_ptr(), sel_idx.size(1),
                                           out.data_ptr(), ws.data_ptr(), ws.numel(), _stream_handle(stream)),
            "fastocr_sparse_decode_attn")
+
+
+def sparse_decode_attn_layers(caches: List[KvCache], batch: SeqBatch, queries: List[torch.Tensor], scale: float, sel_idx: torch.Tensor,
+                              sel_cnt: torch.Tensor, outs: List[torch.Tensor], ws: torch.Tensor, stream=None) -> None:
+    """fastocr_sparse_decode_attn_layers: sparse_decode_attn of several layers with one set, queries[l] and outs[l] each."""
+    caches, queries, outs = list(caches), list(queries), list(outs)
+    assert len(caches) == len(queries) == len(outs)
+    if not caches:
+        return
+    if _call is not None:
+        rc = _call.sparse_layers(caches, batch, queries, scale, sel_idx, sel_cnt, outs, ws, stream)
+        if rc is not None:
+            return _check(rc, "fastocr_sparse_decode_attn_layers")
+    lib = _lib or load_library()
+    n, bv = len(caches), batch.view()
+    for q, out in zip(queries, outs):
+        assert q.is_contiguous() and out.is_contiguous() and out.shape == q.shape and out.dtype == q.dtype
+        assert q.size(1) == queries[0].size(1)
+    assert sel_idx.dtype == torch.int32 and sel_idx.is_contiguous() and sel_cnt.dtype == torch.int32
+    views = (KvView * n)(*(c.view() for c in caches))
+    at = lambda ts: (ctypes.c_void_p * n)(*(t.data_ptr() for t in ts))          # noqa: E731
+    _check(lib.fastocr_sparse_decode_attn_layers(n, views, ctypes.byref(bv), at(queries), queries[0].size(1), float(scale),
+                                                 sel_idx.data_ptr(), sel_cnt.data_ptr(), sel_idx.size(1), at(outs), ws.data_ptr(), ws.numel(),
+                                                 _stream_handle(stream)), "fastocr_sparse_decode_attn_layers")
 
 
 def dense_decode_attn(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scale: float, out: torch.Tensor,

@@ -104,6 +104,20 @@ class FixationController:
             raise RuntimeError("the focal layer set is chosen at the last warm-up step: run steps 1..warmup first")
         if post_warmup and self.kept_from is not None:
             self.kept_from = "F_last"             # what the previous step left behind
+        # Pruned layers between two that select attend one set: they are enqueued together where every layer's query and output are at
+        # hand.  (Sequences of any other kind may compute a layer's query when it is asked for.)
+        together = getattr(ops, "sparse_decode_attn_layers", None)
+        if not (isinstance(queries, (list, tuple)) and isinstance(outs, (list, tuple))):
+            together = None
+        waiting = []
+
+        def enqueue_waiting():
+            if waiting:
+                ls = list(waiting)
+                waiting.clear()
+                together([self.caches[x] for x in ls], batch, [queries[x] for x in ls], self.scale, self.kept_idx, self.kept_cnt,
+                         [outs[x] for x in ls], self._ws, stream=stream)
+
         for l, cache in enumerate(self.caches):
             ws = self._workspace(cache, batch)
             q, out = queries[l], outs[l]
@@ -119,6 +133,7 @@ class FixationController:
                 continue
             selects = (l in self.focal) or (l == 0 and self.kept_from is None)
             if selects:
+                enqueue_waiting()
                 # the layer's own output over the full cache, the scores its successors are pruned by and
                 # their top-k, from one call (its last launch merges the output's partials and selects)
                 warm = self.kept_from is not None
@@ -130,9 +145,13 @@ class FixationController:
                     on_select(l, self.scores, self.kept_idx, self.kept_cnt)
                 trace.append((l, "full+select", None))
             else:
-                ops.sparse_decode_attn(cache, batch, q, self.scale, self.kept_idx, self.kept_cnt, out, ws,
-                                       stream=stream)
+                if together is not None:
+                    waiting.append(l)
+                else:
+                    ops.sparse_decode_attn(cache, batch, q, self.scale, self.kept_idx, self.kept_cnt, out, ws,
+                                           stream=stream)
                 trace.append((l, "pruned", self.kept_from))
+        enqueue_waiting()
         if self.focal is None and t == self.warmup:
             # Focal Layer Selection: one read-back of warmup x layers x batch ratios, ranked on the host
             self.focal = ops.select_focal_layers(self.ratios.cpu().numpy(), self.focal_ratio, self.focal_gap)

@@ -700,6 +700,70 @@ int fastocr_sparse_decode_attn(const fastocr_kv_view *kv, const fastocr_batch_vi
                        out, nullptr, ws, ws_bytes, hip_stream);
 }
 
+// Whether two layers' caches differ in their places alone.
+static bool alike(const fastocr_kv_view &a, const fastocr_kv_view &b)
+{
+    return a.dtype == b.dtype && a.n_kv_heads == b.n_kv_heads && a.head_dim == b.head_dim && a.stride_token == b.stride_token &&
+           a.stride_head == b.stride_head && a.stride_seq == b.stride_seq && a.page_tokens == b.page_tokens &&
+           a.stride_page == b.stride_page && a.max_pages_per_seq == b.max_pages_per_seq;
+}
+
+int fastocr_sparse_decode_attn_layers(int n_layers, const fastocr_kv_view *kv, const fastocr_batch_view *bv, const void *const *q,
+                                      int n_q_heads, float scale, const int32_t *sel_idx, const int32_t *sel_cnt, int64_t kmax,
+                                      void *const *out, void *ws, size_t ws_bytes, void *hip_stream)
+{
+    if (n_layers < 0 || (n_layers > 0 && (!kv || !q || !out))) return FASTOCR_EINVAL;
+    bool together = n_layers > 1;
+    for (int l = 0; l < n_layers; ++l) {
+        int rc = check_views(&kv[l], bv, n_q_heads);
+        if (rc != FASTOCR_OK) return rc;
+        if (!out[l] || !sel_idx || !sel_cnt || kmax < 1) return FASTOCR_EINVAL;
+        rc = check_qo(&kv[l], q[l], out[l], scale);
+        if (rc != FASTOCR_OK) return rc;
+        rc = check_ws(ws, ws_bytes, fastocr_workspace_bytes(FASTOCR_OP_SPARSE_DECODE_ATTN, &kv[l], bv, n_q_heads, kmax));
+        if (rc != FASTOCR_OK) return rc;
+        together = together && alike(kv[0], kv[l]) && make_shape(&kv[l], bv, n_q_heads).fast;
+    }
+    if (n_layers == 0 || bv->batch == 0) return FASTOCR_OK;
+    const bool merges = g_tune_attn_merge.load(std::memory_order_relaxed) != 0;
+    if (together && merges && g_tune_splits[FASTOCR_OP_SPARSE_DECODE_ATTN].load(std::memory_order_relaxed) == 0) {
+        // no output where another layer's query or output lies: layers one after the other read and write in their order
+        const size_t bytes = (size_t)bv->batch * n_q_heads * kv[0].head_dim * (kv[0].dtype == FASTOCR_BF16 ? 2 : 4);
+        auto apart = [&](const void *a, const void *b) {
+            const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+            return x + bytes <= y || y + bytes <= x;
+        };
+        for (int i = 0; i < n_layers && together; ++i)
+            for (int j = 0; j < n_layers && together; ++j)
+                together = i == j || (apart(out[i], q[j]) && apart(out[i], out[j]));
+    } else {
+        together = false;
+    }
+    for (int l = 0; l < n_layers;) {
+        int n = together ? std::min({kLayerSet, n_layers - l, 65535 / bv->batch}) : 1;
+        if (n < 2) {
+            const int rc = fastocr_sparse_decode_attn(&kv[l], bv, q[l], n_q_heads, scale, sel_idx, sel_cnt, kmax, out[l], ws, ws_bytes, hip_stream);
+            if (rc != FASTOCR_OK) return rc;
+            ++l;
+            continue;
+        }
+        Shape s = make_shape(&kv[l], bv, n_q_heads);
+        LayerPtrs at[kLayerSet];
+        for (int i = 0; i < n; ++i) at[i] = LayerPtrs{kv[l + i].k, kv[l + i].v, q[l + i], out[l + i], kv[l + i].block_table};
+        // ranges as for that many sequences, where they merge inside the launch
+        Shape all = s;
+        all.batch = s.batch * n;
+        int nsplit = choose_splits(FASTOCR_OP_SPARSE_DECODE_ATTN, all, sparse_positions(bv, kmax), nullptr, 0), slot = -1;
+        uint32_t *flag = nullptr;
+        if (nsplit > 1 && attn_merges_in_kernel(all, nsplit) && exchange_trusted()) slot = exchange_slot(EX_MERGE, (hipStream_t)hip_stream, &flag);
+        if (slot < 0) nsplit = 1;
+        const hipError_t e = launch_attn_layers(s, n, at, scale, sel_idx, sel_cnt, kmax, nsplit, slot < 0 ? 0 : slot, flag, (hipStream_t)hip_stream);
+        if (e != hipSuccess) return FASTOCR_EHIP;
+        l += n;
+    }
+    return FASTOCR_OK;
+}
+
 int fastocr_dense_decode_attn(const fastocr_kv_view *kv, const fastocr_batch_view *bv, const void *q,
                               int n_q_heads, float scale, void *out, float *lse, void *ws, size_t ws_bytes,
                               void *hip_stream)

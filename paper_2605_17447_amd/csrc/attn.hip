@@ -19,6 +19,8 @@
 // coalesced (16 lanes x 16 B = one 256 B row) and transposed in registers with v_perm_b32.
 // K is loaded the same coalesced way and re-laid to the A layout through a wave-private,
 // XOR-swizzled LDS tile.
+#include <type_traits>
+
 #include "kernels.hpp"
 #include "combine.hpp"
 
@@ -92,17 +94,28 @@ __device__ __forceinline__ int tile_row(int lg, int e) { return (e < 4) ? (4 * l
 // load the k-block's first four tokens, lanes li >= 8 its last four, and the halves swap through
 // a data-parallel-primitive move (lane ^ 8), so every V byte is still fetched once.
 // -----------------------------------------------------------------------------------------
+// Layers: OneLayer, or LayerSet: pruned attention of several layers whose caches are shaped alike and whose kept set is the same, in one launch;
+// blockIdx.z is batch * layer + sequence.  A pruned layer of some hundred rows is a chain of look-ups, one or two tiles per wave and
+// a join, 8 - 9 us in which most of the chip waits; the layers' chains pass at the same time (28/4 heads, batch 8, 15 tiles per stream,
+// 28 layers of which 2 focal: 278 us with 26 launches for the others, 98 with 3; batch 1, 244 and 55).
 // kWaves waves per workgroup walk the range.  Dense: the workgroup's tiles are dealt to its waves
 // in turn.  Gather: the attended list is cut into nsplit * kWaves contiguous pieces, one per wave,
 // of equal length to within one token (or one tile, for short lists: see below) -- with a
 // handful of tiles per wave, whole tiles would leave some waves a quarter more bytes than others.
-template <int D, bool GATHER, bool PAGED, int kWaves, int MODE>
+struct OneLayer {};
+struct LayerSet {
+    struct { const void *k, *v; const uint16_t *q; uint16_t *out; const int32_t *block_table; } at[kLayerSet];
+    int batch;
+    float inv_batch;
+};
+
+template <int D, bool GATHER, bool PAGED, int kWaves, int MODE, typename Layers = OneLayer>
 __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
     KvDev kv, BatchDev bv, const uint16_t *__restrict__ q, int Hq, int G, float scale_log2,
     const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt, int64_t kmax,
     float *__restrict__ part_o, float *__restrict__ part_ml, int nsplit, uint16_t *__restrict__ out,
     float *__restrict__ lse, int merge_slot, long long spin_ticks, uint32_t *__restrict__ gave_up_flag,
-    float *__restrict__ logits, int64_t pitch, float *__restrict__ part_zi, uint32_t *__restrict__ zero)
+    float *__restrict__ logits, int64_t pitch, float *__restrict__ part_zi, uint32_t *__restrict__ zero, Layers layers)
 {
     constexpr bool PARK = MODE == kParked || MODE == kLogits, PV = MODE != kLogits;
     static_assert(!(GATHER && PARK), "scores are those of the whole cache");
@@ -116,9 +129,20 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
     constexpr int NL = D / 16;            // 1 KB load instructions per 32-token K (or V) tile
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int li = lane & 15, lg = lane >> 4;
-    const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
+    const int split = blockIdx.x, kvh = blockIdx.y;
+    int b = blockIdx.z;
 
     const int stream_id = b * gridDim.y + kvh;
+    if constexpr (!std::is_same_v<Layers, OneLayer>) {
+        // (z below 2^16, half a unit away from any whole number: the product's rounding decides nothing)
+        const int l = __builtin_amdgcn_readfirstlane((int)(((float)b + 0.5f) * layers.inv_batch));
+        b -= l * layers.batch;
+        kv.k = layers.at[l].k;
+        kv.v = layers.at[l].v;
+        kv.block_table = layers.at[l].block_table;
+        q = layers.at[l].q;
+        out = layers.at[l].out;
+    }
     if (PARK && zero && split == 0 && kvh == 0 && threadIdx.x == 0) zero[b] = 0u;
     // this workgroup's ticket (see kMerge above), requested before anything else; the tag is only
     // needed after the tile loop and is put into LDS once the geometry (requested after it) is there
@@ -734,7 +758,7 @@ static void launch_mfma(int kid, const Shape &s, const void *q, float scale_log2
     const long long spin_ticks = tune_spin_ticks();
 #define FASTOCR_ATTN(DD, W, MODE) FASTOCR_LAUNCH(kid, (attn_mfma_kernel<DD, GATHER, PAGED, W, MODE>), grid, dim3(64 * W), 0, stream, \
         s.kv, s.bv, (const uint16_t *)q, s.n_q_heads, G, scale_log2, sel_idx, sel_cnt, kmax, part_o, part_ml, nsplit, \
-        (uint16_t *)out, lse, slot, spin_ticks, flag, nullptr, 0, nullptr, nullptr)
+        (uint16_t *)out, lse, slot, spin_ticks, flag, nullptr, 0, nullptr, nullptr, OneLayer{})
     if (s.kv.head_dim == 64) {
         if (nsplit == 1) FASTOCR_ATTN(64, 8, kDirect);
         else if (merge) FASTOCR_ATTN(64, 8, kMerge);
@@ -756,12 +780,44 @@ hipError_t launch_attn_parked(int kid, const Shape &s, const void *q, float scal
     const float scale_log2 = scale * kLog2e;
 #define FASTOCR_PARK(DD, P, MODE) FASTOCR_LAUNCH(kid, (attn_mfma_kernel<DD, false, P, 4, MODE>), grid, dim3(256), 0, stream, \
         s.kv, s.bv, (const uint16_t *)q, s.n_q_heads, G, scale_log2, nullptr, nullptr, 0, part_o, part_ml, nsplit, \
-        nullptr, nullptr, 0, 0, nullptr, logits, pitch, part_zi, zero)
+        nullptr, nullptr, 0, 0, nullptr, logits, pitch, part_zi, zero, OneLayer{})
 #define FASTOCR_PARK_D(DD, P) do { if (part_o) FASTOCR_PARK(DD, P, kParked); else FASTOCR_PARK(DD, P, kLogits); } while (0)
     if (s.kv.head_dim == 64) { if (s.paged) FASTOCR_PARK_D(64, true); else FASTOCR_PARK_D(64, false); }
     else                     { if (s.paged) FASTOCR_PARK_D(128, true); else FASTOCR_PARK_D(128, false); }
 #undef FASTOCR_PARK_D
 #undef FASTOCR_PARK
+    return hipGetLastError();
+}
+
+hipError_t launch_attn_layers(const Shape &s, int n, const LayerPtrs *at, float scale, const int32_t *sel_idx, const int32_t *sel_cnt,
+                              int64_t kmax, int nsplit, int merge_slot, uint32_t *flag, hipStream_t stream)
+{
+    const int G = s.n_q_heads / s.kv.n_kv_heads, streams = s.batch * s.kv.n_kv_heads * n;
+    dim3 grid(nsplit, s.kv.n_kv_heads, s.batch * n);
+    LayerSet set{};
+    for (int l = 0; l < n; ++l) {
+        set.at[l].k = at[l].k;
+        set.at[l].v = at[l].v;
+        set.at[l].q = (const uint16_t *)at[l].q;
+        set.at[l].out = (uint16_t *)at[l].out;
+        set.at[l].block_table = at[l].block_table;
+    }
+    set.batch = s.batch;
+    set.inv_batch = 1.0f / (float)s.batch;
+    const float scale_log2 = scale * kLog2e;
+    const long long spin_ticks = tune_spin_ticks();
+#define FASTOCR_LAYERS(DD, P, W, MODE) FASTOCR_LAUNCH(K_SPARSE_ATTN, (attn_mfma_kernel<DD, true, P, W, MODE, LayerSet>), grid, dim3(64 * W), 0, stream, \
+        s.kv, s.bv, nullptr, s.n_q_heads, G, scale_log2, sel_idx, sel_cnt, kmax, nullptr, nullptr, nsplit, \
+        nullptr, nullptr, merge_slot, spin_ticks, flag, nullptr, 0, nullptr, nullptr, set)
+    // more streams than compute units: two workgroups of four waves on each, so that one's look-ups and join pass behind the other's rows
+#define FASTOCR_LAYERS_D(DD, P) do { \
+        if (nsplit > 1) FASTOCR_LAYERS(DD, P, 8, kMerge); \
+        else if (streams <= plan_cu_count()) FASTOCR_LAYERS(DD, P, 8, kDirect); \
+        else FASTOCR_LAYERS(DD, P, 4, kDirect); } while (0)
+    if (s.kv.head_dim == 64) { if (s.paged) FASTOCR_LAYERS_D(64, true); else FASTOCR_LAYERS_D(64, false); }
+    else                     { if (s.paged) FASTOCR_LAYERS_D(128, true); else FASTOCR_LAYERS_D(128, false); }
+#undef FASTOCR_LAYERS_D
+#undef FASTOCR_LAYERS
     return hipGetLastError();
 }
 

@@ -102,6 +102,12 @@ bool attn_merges_in_kernel(const Shape &s, int nsplit);
 hipError_t launch_attn(const Shape &s, const void *q, float scale, const int32_t *sel_idx,
                        const int32_t *sel_cnt, int64_t kmax, void *out, float *lse, void *ws,
                        int nsplit, int merge_slot, uint32_t *gave_up_flag, hipStream_t stream);
+// Pruned attention of n <= kLayerSet layers in one launch: caches shaped like s.kv at their own places, one kept set, s.fast.  nsplit: 1, or a range
+// count that merges inside the launch (attn_merges_in_kernel of a shape with n times the sequences, merge_slot then >= 0).
+constexpr int kLayerSet = 32;
+struct LayerPtrs { const void *k, *v, *q; void *out; const int32_t *block_table; };
+hipError_t launch_attn_layers(const Shape &s, int n, const LayerPtrs *at, float scale, const int32_t *sel_idx, const int32_t *sel_cnt,
+                              int64_t kmax, int nsplit, int merge_slot, uint32_t *flag, hipStream_t stream);
 // Dense attention whose logits of the image tokens stay behind in `logits` (fp32, log2 domain, [sequence][query head][pitch]);
 // always partials.  part_o == nullptr: logits and statistics alone.  part_zi: the image tokens' part of every range's sum-exp,
 // [rows], or null.  zero: [batch] words the launch clears, or null.  Shapes with parks_by_head.

@@ -5,6 +5,9 @@
 // Every function returns the library's status, or None when something is not as the plain case has it -- an object of another
 // class, a tensor of the wrong type, shape or layout, no CUDA context yet, an exception: the caller then takes the
 // Python path, which does the same call or raises what it always raised.  Nothing is kept from one call to the next.
+#include <deque>
+#include <vector>
+
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "fastocr.h"
@@ -20,6 +23,7 @@ struct Library {
     decltype(&fastocr_focal_score_topk) score_topk;
     decltype(&fastocr_focal_attn_score_topk) layer_topk;
 } g_lib;
+decltype(&fastocr_sparse_decode_attn_layers) g_sparse_layers = nullptr;
 PyTypeObject *g_cache_type = nullptr, *g_batch_type = nullptr;
 PyObject *g_device = nullptr, *g_raw_stream = nullptr, *g_initialized = nullptr;
 PyObject *s_k, *s_v, *s_layout, *s_block_table, *s_seq_len, *s_vis_start, *s_vis_len, *s_max_seq_len, *s_max_vis_len, *s_cuda_stream;
@@ -271,6 +275,47 @@ PyObject *sparse(PyObject *, PyObject *const *a, Py_ssize_t n)               // 
     });
 }
 
+PyObject *sparse_layers(PyObject *, PyObject *const *a, Py_ssize_t n)        // caches, batch, queries, scale, sel_idx, sel_cnt, outs, ws, stream
+{
+    FASTOCR_ARGS(9)
+    return call([&]() {
+        require(g_sparse_layers != nullptr && a[7] != Py_None && PyList_CheckExact(a[0]) && PyList_CheckExact(a[2]) && PyList_CheckExact(a[6]));
+        const Py_ssize_t m = PyList_GET_SIZE(a[0]);
+        require(m > 0 && PyList_GET_SIZE(a[2]) == m && PyList_GET_SIZE(a[6]) == m);
+        const Batch b(a[1]);
+        const float scale = (float)number(a[3]);
+        const Sets k(a[4], a[5]);
+        const Scratch ws(a[7]);
+        void *s = stream_of(a[8]);
+        std::deque<Cache> caches;
+        std::vector<fastocr_kv_view> views;
+        std::vector<const void *> q;
+        std::vector<void *> out;
+        int hq = 0;
+        for (Py_ssize_t l = 0; l < m; ++l) {
+            views.push_back(caches.emplace_back(PyList_GET_ITEM(a[0], l)).view);
+            const at::Tensor &t = tensor(PyList_GET_ITEM(a[2], l));
+            require(l == 0 || query_heads(t) == hq);
+            hq = query_heads(t);
+            q.push_back(t.data_ptr());
+            out.push_back(output(PyList_GET_ITEM(a[6], l), t));
+        }
+        return unlocked([&]() {
+            return g_sparse_layers((int)m, views.data(), &b.view, q.data(), hq, scale, k.idx, k.cnt, k.kmax, out.data(), ws.p, ws.bytes, s);
+        });
+    });
+}
+
+// bind_layers(address of fastocr_sparse_decode_attn_layers)
+PyObject *bind_layers(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    FASTOCR_ARGS(1)
+    void *f = PyLong_AsVoidPtr(a[0]);
+    if (PyErr_Occurred()) return nullptr;
+    g_sparse_layers = (decltype(g_sparse_layers))f;
+    Py_RETURN_NONE;
+}
+
 PyObject *dense(PyObject *, PyObject *const *a, Py_ssize_t n)                // cache, batch, q, scale, out, ws, lse, stream
 {
     FASTOCR_ARGS(8)
@@ -373,7 +418,8 @@ PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
 
 #define FASTOCR_METHOD(NAME) {#NAME, (PyCFunction)(void (*)(void))NAME, METH_FASTCALL, nullptr}
 PyMethodDef g_methods[] = {FASTOCR_METHOD(bind), FASTOCR_METHOD(focal_score), FASTOCR_METHOD(topk), FASTOCR_METHOD(sparse), FASTOCR_METHOD(dense),
-                           FASTOCR_METHOD(layer), FASTOCR_METHOD(score_topk), FASTOCR_METHOD(layer_topk), {nullptr, nullptr, 0, nullptr}};
+                           FASTOCR_METHOD(layer), FASTOCR_METHOD(score_topk), FASTOCR_METHOD(layer_topk),
+                           FASTOCR_METHOD(sparse_layers), FASTOCR_METHOD(bind_layers), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_fastocr_call", nullptr, -1, g_methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
