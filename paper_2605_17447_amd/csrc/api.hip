@@ -686,8 +686,10 @@ static int attn_common(int op, const fastocr_kv_view *kv, const fastocr_batch_vi
     uint32_t *flag = nullptr;
     // (never for the static-workspace entry point: the first in-launch merge on a device allocates
     // the pinned "gave up" word)
-    if (!static_ws && !partials && ((op == FASTOCR_OP_SPARSE_DECODE_ATTN && mode != 0) || mode == 2) && attn_merges_in_kernel(s, nsplit) && exchange_trusted())
-        merge_slot = exchange_slot(EX_MERGE, (hipStream_t)hip_stream, &flag);
+    if (!static_ws && !partials && ((op == FASTOCR_OP_SPARSE_DECODE_ATTN && mode != 0) || mode == 2) && attn_merges_in_kernel(s, nsplit)) {
+        if (exchange_trusted()) merge_slot = exchange_slot(EX_MERGE, (hipStream_t)hip_stream, &flag);
+        if (merge_slot < 0) merge_slot = kNoMergeSlot;
+    }
     hipError_t e = launch_attn(s, q, scale, sel_idx, sel_cnt, kmax, out, lse, ws, nsplit, merge_slot, flag, (hipStream_t)hip_stream);
     return e == hipSuccess ? FASTOCR_OK : FASTOCR_EHIP;
 }

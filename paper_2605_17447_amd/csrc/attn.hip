@@ -99,21 +99,25 @@ __device__ __forceinline__ int tile_row(int lg, int e) { return (e < 4) ? (4 * l
 // a join, 8 - 9 us in which most of the chip waits; the layers' chains pass at the same time (28/4 heads, batch 8, 15 tiles per stream,
 // 28 layers of which 2 focal: 278 us with 26 launches for the others, 98 with 3; batch 1, 244 and 55).
 // kWaves waves per workgroup walk the range.  Dense: the workgroup's tiles are dealt to its waves
-// in turn.  Gather: the attended list is cut into nsplit * kWaves contiguous pieces, one per wave,
-// of equal length to within one token (or one tile, for short lists: see below) -- with a
-// handful of tiles per wave, whole tiles would leave some waves a quarter more bytes than others.
+// in turn.  Gather: short lists likewise, over all ranges' waves; from three tiles per wave on, nsplit * kWaves contiguous pieces of
+// equal length to within one token -- with a handful of tiles per wave, whole tiles would leave some waves a quarter more bytes than others.
+//
+// Before a short list's first row there was a chain of four round trips: arguments, lengths, set entries, rows (wave 0: the ticket
+// as well).  Now two: the pointers that lengths and entries are read through come first, so that they are in scalar registers when a wave starts
+// (-amdgpu-kernarg-preload-count; 14 words at most, and only arguments that are no structures), and the set comes
+// first in the attended list, so that a wave knows which entries are its own before it knows a length.  Pruned attention, 12 sequences of 838 attended rows,
+// 12/2 heads: 9.05 -> 8.27 us; a layer-step at batch 1, 4096 tokens: 19.5 -> 18.5; dense attention, 4 x 9216, 16/2: 12.3 -> 12.0.
 struct OneLayer {};
 struct LayerSet {
     struct { const void *k, *v; const uint16_t *q; uint16_t *out; const int32_t *block_table; } at[kLayerSet];
-    int batch;
-    float inv_batch;
 };
 
 template <int D, bool GATHER, bool PAGED, int kWaves, int MODE, typename Layers = OneLayer>
 __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
-    KvDev kv, BatchDev bv, const uint16_t *__restrict__ q, int Hq, int G, float scale_log2,
-    const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt, int64_t kmax,
-    float *__restrict__ part_o, float *__restrict__ part_ml, int nsplit, uint16_t *__restrict__ out,
+    const int32_t *__restrict__ seq_len, const int32_t *__restrict__ vis_start, const int32_t *__restrict__ vis_len,
+    const int32_t *__restrict__ sel_cnt, const int32_t *__restrict__ sel_idx, int64_t kmax, int nsplit, int batch,
+    KvDev kv, int max_seq_len, int max_vis_len, const uint16_t *__restrict__ q, int Hq, int G, int n_kv, float scale_log2,
+    float *__restrict__ part_o, float *__restrict__ part_ml, uint16_t *__restrict__ out,
     float *__restrict__ lse, int merge_slot, long long spin_ticks, uint32_t *__restrict__ gave_up_flag,
     float *__restrict__ logits, int64_t pitch, float *__restrict__ part_zi, uint32_t *__restrict__ zero, Layers layers)
 {
@@ -132,11 +136,11 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
     const int split = blockIdx.x, kvh = blockIdx.y;
     int b = blockIdx.z;
 
-    const int stream_id = b * gridDim.y + kvh;
+    const int stream_id = b * n_kv + kvh;
     if constexpr (!std::is_same_v<Layers, OneLayer>) {
         // (z below 2^16, half a unit away from any whole number: the product's rounding decides nothing)
-        const int l = __builtin_amdgcn_readfirstlane((int)(((float)b + 0.5f) * layers.inv_batch));
-        b -= l * layers.batch;
+        const int l = __builtin_amdgcn_readfirstlane((int)(((float)b + 0.5f) * __builtin_amdgcn_rcpf((float)batch)));
+        b -= l * batch;
         kv.k = layers.at[l].k;
         kv.v = layers.at[l].v;
         kv.block_table = layers.at[l].block_table;
@@ -144,41 +148,39 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
         out = layers.at[l].out;
     }
     if (PARK && zero && split == 0 && kvh == 0 && threadIdx.x == 0) zero[b] = 0u;
-    // this workgroup's ticket (see kMerge above), requested before anything else; the tag is only
-    // needed after the tile loop and is put into LDS once the geometry (requested after it) is there
-    unsigned long long ticket = 0;
-    if (MODE == kMerge && threadIdx.x == 0)
-        ticket = __hip_atomic_fetch_add(&g_merge_ticket[merge_slot][stream_id], kTicketUnit / (unsigned long long)nsplit,
-                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-
-    const SeqGeom geo = seq_geom(bv, b);
-    int cnt = 0;
-    const int32_t *sel = nullptr;
-    if (GATHER) {
-        cnt = min(max(sel_cnt[b], 0), (int)min((int64_t)geo.N, kmax));
-        sel = sel_idx + (int64_t)b * kmax;
-    }
+    const BatchDev bv{seq_len, vis_start, vis_len, max_seq_len, max_vis_len};
+    const int gw = split * kWaves + wave, nw = nsplit * kWaves;
+    const int32_t *sel = GATHER ? sel_idx + (int64_t)b * kmax : nullptr;
+    // The geometry, the set's entries of this wave's first two tiles where they are dealt in turn (below; their place needs no
+    // length) and the other arguments are requested together.
+    const int s_len = seq_len[b], v_start = vis_start[b], v_len = vis_len[b], s_cnt = GATHER ? sel_cnt[b] : 0;
+    int first_entry = 0;
+    if (GATHER) first_entry = sel[min((int64_t)((gw + nw * (lane >> 5)) * kTile + (lane & 31)), kmax - 1)];
+    asm volatile("" :: "s"(s_len), "s"(v_start), "s"(v_len), "s"(s_cnt), "s"(kv.k), "s"(kv.v), "s"(kv.stride_token), "s"(kv.stride_head),
+                 "s"(kv.stride_seq), "s"(q), "s"(Hq), "s"(G), "s"(n_kv), "s"(scale_log2), "s"(max_seq_len), "s"(max_vis_len) : "memory");
+    const SeqGeom geo = seq_geom_of(bv, s_len, v_start, v_len);
+    const int cnt = GATHER ? min(max(s_cnt, 0), (int)min((int64_t)geo.N, kmax)) : 0;
     const int L = GATHER ? (geo.S - geo.N + cnt) : geo.S;
-    if (MODE == kMerge && threadIdx.x == 0) {
-        const uint32_t t = (uint32_t)(ticket / kTicketUnit) + 1u;
-        sm_tag = t ? t : 1u;                  // zero is what never-written words hold
-    }
     // this wave's tiles: tile i starts at position tile_pos(i) and ends before pend
-    int wp0 = 0, pend = L, nt, tfirst = 0;
+    int wp0 = 0, wstep = kTile, pend = L, nt, tfirst = 0;
+    bool by_token = false;
     if (GATHER) {
-        // piece gw of nw: x units each, the first `rem` pieces one more.  A unit is a token when
-        // that leaves a wave three tiles or more (the stream is then bound by memory and equal byte
-        // counts matter), else a whole tile: a partial tile costs the load path as many
-        // instructions as a full one, which is what bounds a short list.
-        const int gw = split * kWaves + wave, nw = nsplit * kWaves;
+        // Tiles in turn, or, where that leaves a wave three tiles or more (the stream is then bound by memory and equal byte
+        // counts matter), contiguous pieces of equal length to within a token.  Short lists are not cut finer than tiles: a partial
+        // tile costs the load path as many instructions as a full one, which is what bounds them.
         const int ntile = (L + kTile - 1) / kTile;
-        const bool by_token = ntile >= 3 * nw;
-        const int units = by_token ? L : ntile;
-        const int x = units / nw, rem = units - x * nw;
-        const int u0 = gw * x + min(gw, rem), u1 = u0 + x + (gw < rem ? 1 : 0);
-        wp0 = by_token ? u0 : u0 * kTile;
-        pend = by_token ? u1 : min(L, u1 * kTile);
-        nt = (pend - wp0 + kTile - 1) / kTile;
+        by_token = ntile >= 3 * nw;
+        if (by_token) {
+            const int x = L / nw, rem = L - x * nw;
+            wp0 = gw * x + min(gw, rem);
+            pend = wp0 + x + (gw < rem ? 1 : 0);
+            nt = (pend - wp0 + kTile - 1) / kTile;
+        } else {
+            wp0 = gw * kTile;
+            wstep = nw * kTile;
+            nt = gw < ntile ? (ntile - 1 - gw >= nw ? 2 : 1) : 0;
+            if (nt == 2 && ntile - 1 - gw >= 2 * nw) nt = 3;
+        }
     } else {
         // ranges of equal length to within one tile
         const int ntile = (L + kTile - 1) / kTile;
@@ -187,18 +189,14 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
         tfirst = split * x + min(split, rem) + wave;
         nt = tfirst < t1 ? (t1 - 1 - tfirst) / kWaves + 1 : 0;
     }
-    auto tile_pos = [&](int i) { return GATHER ? wp0 + i * kTile : (tfirst + i * kWaves) * kTile; };
+    auto tile_pos = [&](int i) { return GATHER ? wp0 + i * wstep : (tfirst + i * kWaves) * kTile; };
 
     // Q as the B operand: lane (head li, k-block lg) holds dims 8*(4kk+lg) .. +7 for step kk.
+    // (lanes past the group's heads hold its last one again; nothing reads their columns)
     u32x4 qreg[KS];
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-        qreg[kk] = u32x4{0u, 0u, 0u, 0u};
-        if (li < G) {
-            const uint16_t *qp = q + ((int64_t)b * Hq + (int64_t)kvh * G + li) * D + 8 * (4 * kk + lg);
-            qreg[kk] = *reinterpret_cast<const u32x4 *>(qp);
-        }
-    }
+    for (int kk = 0; kk < KS; ++kk)
+        qreg[kk] = *reinterpret_cast<const u32x4 *>(q + ((int64_t)b * Hq + (int64_t)kvh * G + min(li, G - 1)) * D + 8 * (4 * kk + lg));
 
     const uint16_t *kbase = reinterpret_cast<const uint16_t *>(kv.k);
     const uint16_t *vbase = reinterpret_cast<const uint16_t *>(kv.v);
@@ -206,12 +204,13 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
     // Row look-up of the wave's tiles i and i + 1 by this lane (row lane % 32 of tile i + lane / 32; rows past the
     // end repeat the last one), in stages of one load each: the entry of the set, the page, the element offset.
     auto pos_of = [&](int i) { return min(tile_pos(i + (lane >> 5)) + (lane & 31), pend - 1); };
-    auto set_entry = [&](int i) -> int { return GATHER ? sel[min(max(pos_of(i) - geo.v0, 0), max(cnt - 1, 0))] : 0; };
+    // (the attended list: the set, the text before the image span, the text after it)
+    auto set_entry = [&](int i) -> int { return GATHER ? sel[min(pos_of(i), max(cnt - 1, 0))] : 0; };
     auto token_of = [&](int i, int entry) -> int {
         const int p = pos_of(i);
         if (!GATHER) return p;
-        const int mid = geo.v0 + min(max(entry, 0), max(geo.N - 1, 0));
-        return p < geo.v0 ? p : (p < geo.v0 + cnt ? mid : p - cnt + geo.N);
+        const int mid = geo.v0 + min(max(entry, 0), max(geo.N - 1, 0)), t = p - cnt;
+        return t < 0 ? mid : (t < geo.v0 ? t : t + geo.N);
     };
     auto page_of = [&](int tok) -> int {
         return PAGED ? kv.block_table[(int64_t)b * kv.max_pages + min((int)((uint32_t)tok / (uint32_t)kv.page_tokens), kv.max_pages - 1)] : 0;
@@ -221,10 +220,6 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
         const int in = tok - (int)((uint32_t)tok / (uint32_t)kv.page_tokens) * kv.page_tokens;
         return (int64_t)page * kv.stride_page + (int64_t)in * kv.stride_token + (int64_t)kvh * kv.stride_head;
     };
-    auto rowoff_of = [&](int i) -> int64_t {
-        const int tok = token_of(i, set_entry(i));
-        return offset_of(tok, page_of(tok));
-    };
     const int64_t seq_base = row_offset<false>(kv, b, 0, kvh);
 
     // D = 64: which of the k-block's halves this lane loads of V, and its chunk of a row
@@ -232,25 +227,37 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
     // K first: its products and the exponentials run while V is still arriving
     // (off: what rowoff_of looked up for the pair of tiles that i belongs to, h: which of the two i is)
     auto load_tile = [&](int i, int64_t off, int h, u32x4(&K)[NL], u32x4(&V)[PV ? NL : 1]) {
-        auto row = [&](int r) -> int64_t {
-            if (GATHER || PAGED) return __shfl(off, 32 * h + r);
+        // row at / 4 + c of the tile.  at differs from lane to lane, c does not and goes into the lane move's own offset (at passes as
+        // made anew for each tile: the compiler would keep every sum of the two in a register of its own over the loop).
+        auto row = [&](int at, int c) -> int64_t {
+            const int r = at / 4 + c;
+            if (GATHER || PAGED) {
+                const uint32_t lo = __builtin_amdgcn_ds_bpermute(at + 4 * (32 * h + c), (int)off);
+                const uint32_t hi = __builtin_amdgcn_ds_bpermute(at + 4 * (32 * h + c), (int)(off >> 32));
+                return (int64_t)((uint64_t)hi << 32 | lo);
+            }
             return seq_base + (int64_t)min(tile_pos(i) + r, L - 1) * kv.stride_token;
         };
         if constexpr (D == 128) {
             int64_t ro[NL];
+            int at = 16 * lg;
+            if (GATHER || PAGED) asm volatile("" : "+v"(at));
 #pragma unroll
-            for (int e = 0; e < NL; ++e) { ro[e] = row(tile_row(lg, e)); K[e] = stream_load(kbase + ro[e] + 8 * li); }
+            for (int e = 0; e < NL; ++e) { ro[e] = row(at, tile_row(0, e)); K[e] = stream_load(kbase + ro[e] + 8 * li); }
             if constexpr (PV) {
+                if (GATHER || PAGED) __builtin_amdgcn_sched_barrier(0);      // (else the addresses of both cost registers that there are not)
 #pragma unroll
                 for (int e = 0; e < NL; ++e) V[e] = stream_load(vbase + ro[e] + 8 * li);
             }
         } else {
             // V: row 16 vh + 4 lg + e (the k-block's tokens); K: rows 8e .. 8e+7, one per 8 lanes
+            int at_k = 4 * (lane >> 3), at_v = 64 * vh + 16 * lg;
+            if (GATHER || PAGED) asm volatile("" : "+v"(at_k), "+v"(at_v));
 #pragma unroll
-            for (int e = 0; e < NL; ++e) K[e] = stream_load(kbase + row(8 * e + (lane >> 3)) + 8 * lc);
+            for (int e = 0; e < NL; ++e) K[e] = stream_load(kbase + row(at_k, 8 * e) + 8 * lc);
             if constexpr (PV) {
 #pragma unroll
-                for (int e = 0; e < NL; ++e) V[e] = stream_load(vbase + row(16 * vh + 4 * lg + e) + 8 * lc);
+                for (int e = 0; e < NL; ++e) V[e] = stream_load(vbase + row(at_v, e) + 8 * lc);
             }
         }
         // nothing of the tile before may be moved in between: it would wait for that tile's rows
@@ -380,6 +387,20 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
         }
     };
 
+    // This workgroup's ticket (see kMerge above), requested behind the first tile's rows and first needed after the last tile.  The last
+    // wave, which has the fewest tiles, draws it.  (The address passes as one that lanes may differ in: the compiler combines what
+    // the lanes add to one address and waits for the answer at once.)
+    constexpr int kDraws = 64 * (kWaves - 1);
+    unsigned long long ticket;
+    auto draw_ticket = [&]() {
+        if (MODE == kMerge && (int)threadIdx.x == kDraws) {
+            int at = stream_id;
+            asm volatile("" : "+v"(at));
+            ticket = __hip_atomic_fetch_add(&g_merge_ticket[merge_slot][at], (uint32_t)kTicketUnit / (uint32_t)nsplit,
+                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    };
+    if (nt <= 0) draw_ticket();
     if (nt > 0) {
         // Two register buffers, software pipelined: a tile is requested before the one ahead of it is computed, and
         // nothing is requested past the wave's last tile.  The loop has one exit, at its end, and always leaves
@@ -393,9 +414,21 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
         // Row offsets that come from memory (selected indices, block table): each stage of a pair's look-up is sent
         // half a pair or more before it is used and BEFORE the rows of the tiles until then: loads return in
         // order, so waiting for it never waits for a tile requested after it.
-        int64_t off = kLookUp ? rowoff_of(0) : 0;
-        int entry = kLookUp ? set_entry(2) : 0;
+        int64_t off = 0;
+        int entry = 0;
+        if (kLookUp) {
+            int tok;
+            if (by_token) {
+                tok = token_of(0, set_entry(0));
+                asm volatile("" : "+v"(tok));        // (its own wait: the entries asked for above don't wait for the query behind them)
+            } else {
+                tok = token_of(0, first_entry);
+            }
+            off = offset_of(tok, page_of(tok));
+            entry = set_entry(2);
+        }
         load_tile(0, off, 0, KA, VA);
+        draw_ticket();
         int i = 0;
         while (nt - i > 2) {
             const int tok = kLookUp ? token_of(i + 2, entry) : 0, page = kLookUp ? page_of(tok) : 0;
@@ -455,6 +488,10 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
             buf[li * D + join_slot<D>(li, dim)] = acc[t][r];
         }
     if (lg == 0) { sm_m[wave][li] = m; sm_z[wave][li] = zl; }
+    if (MODE == kMerge && (int)threadIdx.x == kDraws) {
+        const uint32_t t = (uint32_t)(ticket / kTicketUnit) + 1u;
+        sm_tag = t ? t : 1u;                  // zero is what never-written words hold
+    }
     __syncthreads();
     const uint32_t tag = MODE == kMerge ? sm_tag : 0u;
 
@@ -532,11 +569,10 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
 #pragma unroll
             for (int x = 0; x < NP; ++x)
                 if (x < np) Mt = fmaxf(Mt, __uint_as_float((uint32_t)wm[u][x]));
+            // (in the merge kernel's order and with its roundings, so that a call without an exchange slot gives the same bits)
             float ot = 0.f, Zt = 0.f;
             if (Mt > -INFINITY) {
-                const float f = fast_exp2(M[u] - Mt);
-                ot = f * o[u];
-                Zt = f * Z[u];
+#pragma clang fp contract(off)
 #pragma unroll
                 for (int x = 0; x < NP; ++x) {
                     if (x < np) {
@@ -545,6 +581,9 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
                         Zt += fx * __uint_as_float((uint32_t)wz[u][x]);
                     }
                 }
+                const float f = fast_exp2(M[u] - Mt);
+                ot += f * o[u];
+                Zt += f * Z[u];
             }
             // a range that never published: no number is better than a wrong one
             out[bh * D + c] = ok ? f32_to_bf16_bits(Zt > 0.f ? ot / Zt : 0.f) : (uint16_t)0x7fc0;
@@ -753,21 +792,23 @@ static void launch_mfma(int kid, const Shape &s, const void *q, float scale_log2
     dim3 grid(nsplit, s.kv.n_kv_heads, s.batch);
     const bool merge = merge_slot >= 0 && nsplit > 1;
     const int slot = merge ? merge_slot : 0;
+    // (a call that would have merged: the same waves for the same tiles)
+    const bool wide = tune_attn_waves() == 8 || merge_slot == kNoMergeSlot;
     // the stream's last range waits at most this long for the others (they run concurrently and
     // finish within microseconds of each other); past it the outputs are NaN but the call ends
     const long long spin_ticks = tune_spin_ticks();
 #define FASTOCR_ATTN(DD, W, MODE) FASTOCR_LAUNCH(kid, (attn_mfma_kernel<DD, GATHER, PAGED, W, MODE>), grid, dim3(64 * W), 0, stream, \
-        s.kv, s.bv, (const uint16_t *)q, s.n_q_heads, G, scale_log2, sel_idx, sel_cnt, kmax, part_o, part_ml, nsplit, \
-        (uint16_t *)out, lse, slot, spin_ticks, flag, nullptr, 0, nullptr, nullptr, OneLayer{})
+        s.bv.seq_len, s.bv.vis_start, s.bv.vis_len, sel_cnt, sel_idx, kmax, nsplit, s.batch, s.kv, s.bv.max_seq_len, s.bv.max_vis_len, \
+        (const uint16_t *)q, s.n_q_heads, G, s.kv.n_kv_heads, scale_log2, part_o, part_ml, (uint16_t *)out, lse, slot, spin_ticks, flag, nullptr, 0, nullptr, nullptr, OneLayer{})
     if (s.kv.head_dim == 64) {
         if (nsplit == 1) FASTOCR_ATTN(64, 8, kDirect);
         else if (merge) FASTOCR_ATTN(64, 8, kMerge);
-        else if (tune_attn_waves() == 8) FASTOCR_ATTN(64, 8, kPartial);
+        else if (wide) FASTOCR_ATTN(64, 8, kPartial);
         else FASTOCR_ATTN(64, 4, kPartial);
     }
     else if (nsplit == 1) FASTOCR_ATTN(128, 8, kDirect);       // one range per stream: eight waves, final output
     else if (merge) FASTOCR_ATTN(128, 8, kMerge);         // the stream's last range merges inside the launch
-    else if (tune_attn_waves() == 8) FASTOCR_ATTN(128, 8, kPartial);
+    else if (wide) FASTOCR_ATTN(128, 8, kPartial);
     else FASTOCR_ATTN(128, 4, kPartial);
 #undef FASTOCR_ATTN
 }
@@ -779,8 +820,8 @@ hipError_t launch_attn_parked(int kid, const Shape &s, const void *q, float scal
     dim3 grid(nsplit, s.kv.n_kv_heads, s.batch);
     const float scale_log2 = scale * kLog2e;
 #define FASTOCR_PARK(DD, P, MODE) FASTOCR_LAUNCH(kid, (attn_mfma_kernel<DD, false, P, 4, MODE>), grid, dim3(256), 0, stream, \
-        s.kv, s.bv, (const uint16_t *)q, s.n_q_heads, G, scale_log2, nullptr, nullptr, 0, part_o, part_ml, nsplit, \
-        nullptr, nullptr, 0, 0, nullptr, logits, pitch, part_zi, zero, OneLayer{})
+        s.bv.seq_len, s.bv.vis_start, s.bv.vis_len, nullptr, nullptr, 0, nsplit, s.batch, s.kv, s.bv.max_seq_len, s.bv.max_vis_len, \
+        (const uint16_t *)q, s.n_q_heads, G, s.kv.n_kv_heads, scale_log2, part_o, part_ml, nullptr, nullptr, 0, 0, nullptr, logits, pitch, part_zi, zero, OneLayer{})
 #define FASTOCR_PARK_D(DD, P) do { if (part_o) FASTOCR_PARK(DD, P, kParked); else FASTOCR_PARK(DD, P, kLogits); } while (0)
     if (s.kv.head_dim == 64) { if (s.paged) FASTOCR_PARK_D(64, true); else FASTOCR_PARK_D(64, false); }
     else                     { if (s.paged) FASTOCR_PARK_D(128, true); else FASTOCR_PARK_D(128, false); }
@@ -802,13 +843,11 @@ hipError_t launch_attn_layers(const Shape &s, int n, const LayerPtrs *at, float 
         set.at[l].out = (uint16_t *)at[l].out;
         set.at[l].block_table = at[l].block_table;
     }
-    set.batch = s.batch;
-    set.inv_batch = 1.0f / (float)s.batch;
     const float scale_log2 = scale * kLog2e;
     const long long spin_ticks = tune_spin_ticks();
 #define FASTOCR_LAYERS(DD, P, W, MODE) FASTOCR_LAUNCH(K_SPARSE_ATTN, (attn_mfma_kernel<DD, true, P, W, MODE, LayerSet>), grid, dim3(64 * W), 0, stream, \
-        s.kv, s.bv, nullptr, s.n_q_heads, G, scale_log2, sel_idx, sel_cnt, kmax, nullptr, nullptr, nsplit, \
-        nullptr, nullptr, merge_slot, spin_ticks, flag, nullptr, 0, nullptr, nullptr, set)
+        s.bv.seq_len, s.bv.vis_start, s.bv.vis_len, sel_cnt, sel_idx, kmax, nsplit, s.batch, s.kv, s.bv.max_seq_len, s.bv.max_vis_len, \
+        nullptr, s.n_q_heads, G, s.kv.n_kv_heads, scale_log2, nullptr, nullptr, nullptr, nullptr, merge_slot, spin_ticks, flag, nullptr, 0, nullptr, nullptr, set)
     // more streams than compute units: two workgroups of four waves on each, so that one's look-ups and join pass behind the other's rows
 #define FASTOCR_LAYERS_D(DD, P) do { \
         if (nsplit > 1) FASTOCR_LAYERS(DD, P, 8, kMerge); \
@@ -839,7 +878,7 @@ hipError_t launch_attn(const Shape &s, const void *q, float scale, const int32_t
 {
     const bool gather = sel_idx != nullptr;
     const bool merge = merge_slot >= 0 && attn_merges_in_kernel(s, nsplit);
-    if (!merge) merge_slot = -1;
+    if (!merge && merge_slot >= 0) merge_slot = -1;
     const int d = s.kv.head_dim;
     float *part_o = reinterpret_cast<float *>(ws);
     float *part_ml = part_o + (size_t)s.batch * s.n_q_heads * nsplit * d;

@@ -98,6 +98,9 @@ size_t attn_workspace_bytes(const Shape &s, size_t rows);             // rows = 
 // (attn_merges_in_kernel) and an exchange slot is given; otherwise partials go to the workspace
 // and a merge kernel follows.
 bool attn_merges_in_kernel(const Shape &s, int nsplit);
+// merge_slot of a call whose ranges would merge inside the launch if a slot were left: partials and the merge kernel, with the
+// merging kernel's tiles and roundings, so that the outputs' bits do not depend on how many streams are in use.
+constexpr int kNoMergeSlot = -2;
 // merge_slot: exchange slot for the in-launch merge (EX_MERGE), or -1 = partials + merge kernel.
 hipError_t launch_attn(const Shape &s, const void *q, float scale, const int32_t *sel_idx,
                        const int32_t *sel_cnt, int64_t kmax, void *out, float *lse, void *ws,
