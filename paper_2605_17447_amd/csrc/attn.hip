@@ -418,7 +418,7 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
         int entry = 0;
         if (kLookUp) {
             int tok;
-            if (by_token) {
+            if (by_token || geo.S == geo.N) {            // (no text: rows past the end are to repeat the set's last one, never another)
                 tok = token_of(0, set_entry(0));
                 asm volatile("" : "+v"(tok));        // (its own wait: the entries asked for above don't wait for the query behind them)
             } else {
