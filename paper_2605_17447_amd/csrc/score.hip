@@ -69,10 +69,11 @@ constexpr int kFinThreads = 256;
 __host__ __device__ inline int fin_lanes_per_token(int Gp) { return Gp == 8 ? 2 : (Gp == 16 ? 4 : 1); }
 
 __global__ __launch_bounds__(kFinThreads) void score_finalize_kernel(
-    BatchDev bv, int Hq, int n_kv_heads, const float *__restrict__ logits, int64_t pitch,
-    const float *__restrict__ part_ml, int nsplit, float *__restrict__ scores,
-    float *__restrict__ lse, float *__restrict__ mass_part)
+    const float *__restrict__ part_ml, const float *__restrict__ logits, const int32_t *__restrict__ seq_len,
+    const int32_t *__restrict__ vis_start, const int32_t *__restrict__ vis_len, int64_t pitch, int Hq, int nsplit,
+    int n_kv_heads, int max_seq_len, int max_vis_len, float *__restrict__ scores, float *__restrict__ lse, float *__restrict__ mass_part)
 {
+    const BatchDev bv{seq_len, vis_start, vis_len, max_seq_len, max_vis_len};
     // [Hq][2]: a head's maximum M and 1/Z over the sequence.  A weight is 2^(logit - M) / Z: the difference of two
     // logits of like size is nearly exact, where logit - (M + log2 Z) would carry the rounding of that sum
     extern __shared__ float norm[];
@@ -153,10 +154,11 @@ __global__ void mass_reduce_kernel(const float *__restrict__ mass_part, int nblk
 constexpr int kFinTokens = 64;
 
 // (M, Z) of NU heads hg, hg + 16, .. over their nsplit ranges, and the image tokens' part of Z with MASS, in all 16 lanes of a row.
-// NS: ranges per lane requested at a time, 16 NS in all (1: up to 16 ranges in one round trip, 4: up to 64).
-template <int NU, int NS, bool MASS>
+// NS: ranges per lane requested at a time, 16 NS in all (1: up to 16 ranges in one round trip, 4: up to 64).  meanwhile(): what is
+// done while they are on their way.
+template <int NU, int NS, bool MASS, typename F>
 __device__ __forceinline__ void parked_stats(const float *__restrict__ part_ml, const float *__restrict__ part_zi, int64_t bh0, int h0, int Hq,
-                                             int nsplit, float (&M)[NU], float (&Z)[NU], float (&Zi)[NU])
+                                             int nsplit, float (&M)[NU], float (&Z)[NU], float (&Zi)[NU], F meanwhile)
 {
     const int tq = threadIdx.x & 15;
 #pragma unroll
@@ -176,6 +178,8 @@ __device__ __forceinline__ void parked_stats(const float *__restrict__ part_ml, 
                 ii[u][k] = MASS ? (s < nsplit ? part_zi[at] : 0.f) : 0.f;
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
+        meanwhile();
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             float mx = M[u];
@@ -231,13 +235,23 @@ __device__ __forceinline__ void parked_scores(const BatchDev &bv, int b, int blk
     const int p0 = blk * kFinTokens + 4 * tq;                    // tokens of the sequence
     const int at = parked_token(p0, pitch);
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int h0 = hg; h0 < Hq + hg; h0 += 16 * NU) {             // (every lane walks every round)
+    // The geometry is read through the scalar cache while logits and statistics come.  (Named where it is used, behind the sums, the compiler asks for
+    // it there: one more round trip before the store.)
+    int s_len = 0, v_start = 0, v_len = 0;
+    auto geometry = [&]() {
+        s_len = bv.seq_len[b];
+        v_start = bv.vis_start[b];
+        v_len = bv.vis_len[b];
+        asm volatile("" : "+s"(s_len), "+s"(v_start), "+s"(v_len));
+    };
+    for (int r0 = 0; r0 < Hq; r0 += 16 * NU) {                   // (every lane walks every round)
+        const int h0 = r0 + hg;
         f32x4 l[NU];
 #pragma unroll
         for (int u = 0; u < NU; ++u)
             l[u] = *reinterpret_cast<const f32x4 *>(logits + (bh0 + min(h0 + 16 * u, Hq - 1)) * pitch + at);
         float M[NU], Z[NU], unused[NU];
-        parked_stats<NU, NS, false>(part_ml, nullptr, bh0, h0, Hq, nsplit, M, Z, unused);
+        parked_stats<NU, NS, false>(part_ml, nullptr, bh0, h0, Hq, nsplit, M, Z, unused, geometry);
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             const bool there = h0 + 16 * u < Hq;
@@ -251,7 +265,7 @@ __device__ __forceinline__ void parked_scores(const BatchDev &bv, int b, int blk
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[e] = rows_sum(acc[e]);       // the wave's four head groups
     if ((t & 63) < 16) *reinterpret_cast<f32x4 *>(&sm[wave * kFinTokens + 4 * tq]) = acc;
-    const SeqGeom geo = seq_geom(bv, b);
+    const SeqGeom geo = seq_geom_of(bv, s_len, v_start, v_len);
     __syncthreads();
     if (t < kFinTokens) {
         const int i = blk * kFinTokens + t - geo.v0;
@@ -273,7 +287,7 @@ __device__ __forceinline__ void parked_mass(const BatchDev &bv, int b, int Hq, c
     float sum = 0.f;
     for (int h0 = hg; h0 < Hq + hg; h0 += 16 * NU) {
         float M[NU], Z[NU], Zi[NU];
-        parked_stats<NU, NS, true>(part_ml, part_zi, (int64_t)b * Hq, h0, Hq, nsplit, M, Z, Zi);
+        parked_stats<NU, NS, true>(part_ml, part_zi, (int64_t)b * Hq, h0, Hq, nsplit, M, Z, Zi, []() {});
 #pragma unroll
         for (int u = 0; u < NU; ++u) sum += h0 + 16 * u < Hq ? Zi[u] / Z[u] : 0.f;
     }
@@ -285,10 +299,12 @@ __device__ __forceinline__ void parked_mass(const BatchDev &bv, int b, int Hq, c
 
 template <int NU, int NS>
 __global__ __launch_bounds__(kFinThreads) void parked_finish_kernel(
-    BatchDev bv, int Hq, const float *__restrict__ logits, int64_t pitch, const float *__restrict__ part_ml,
-    const float *__restrict__ part_zi, int nsplit, float *__restrict__ scores, float *__restrict__ lse, float *__restrict__ img_mass,
-    int nblk, const float *__restrict__ part_o, int d, uint16_t *__restrict__ out)
+    const float *__restrict__ logits, const float *__restrict__ part_ml, const float *__restrict__ part_o, const float *__restrict__ part_zi,
+    int64_t pitch, int Hq, int nsplit, int nblk, int d, const int32_t *__restrict__ seq_len, const int32_t *__restrict__ vis_start,
+    const int32_t *__restrict__ vis_len, int max_seq_len, int max_vis_len, float *__restrict__ scores, float *__restrict__ lse,
+    float *__restrict__ img_mass, uint16_t *__restrict__ out)
 {
+    const BatchDev bv{seq_len, vis_start, vis_len, max_seq_len, max_vis_len};
     __shared__ float sm_max[4];
     __shared__ float sm_z[256];
     __shared__ __align__(16) float sm_o[1024];
@@ -308,10 +324,12 @@ constexpr int kFinSelThreads = 1024;
 constexpr int kFinSelBlocks = kFinSelThreads / 256;          // 64-token blocks per workgroup
 
 __global__ __launch_bounds__(kFinSelThreads) void parked_select_kernel(
-    BatchDev bv, int Hq, const float *__restrict__ logits, int64_t pitch, const float *__restrict__ part_ml,
+    const int32_t *__restrict__ seq_len, const int32_t *__restrict__ vis_start, const int32_t *__restrict__ vis_len, int max_seq_len, int max_vis_len,
+    int Hq, const float *__restrict__ logits, int64_t pitch, const float *__restrict__ part_ml,
     const float *__restrict__ part_zi, int nsplit, float *__restrict__ scores, float *__restrict__ lse, float *__restrict__ img_mass,
     int nwg, const float *__restrict__ part_o, int d, uint16_t *__restrict__ out, SelectArgs sel, uint32_t *__restrict__ done)
 {
+    const BatchDev bv{seq_len, vis_start, vis_len, max_seq_len, max_vis_len};
     __shared__ uint32_t hist[kWinBins];
     __shared__ __align__(16) uint32_t list[kWinListWords];
     __shared__ int s_pick[4];
@@ -376,7 +394,8 @@ static hipError_t launch_finalize(const Shape &s, const float *logits, int64_t p
     const int nblk = fin_blocks(s);
     dim3 fgrid(nblk, s.batch), fblock(kFinThreads);
     FASTOCR_LAUNCH(K_SCORE_FINALIZE, score_finalize_kernel, fgrid, fblock, (size_t)s.n_q_heads * 2 * sizeof(float), stream,
-        s.bv, s.n_q_heads, s.kv.n_kv_heads, logits, pitch, part_ml, nsplit, scores, lse, img_mass ? mass_part : nullptr);
+        part_ml, logits, s.bv.seq_len, s.bv.vis_start, s.bv.vis_len, pitch, s.n_q_heads, nsplit, s.kv.n_kv_heads, s.bv.max_seq_len, s.bv.max_vis_len,
+        scores, lse, img_mass ? mass_part : nullptr);
     return hipGetLastError();
 }
 
@@ -388,7 +407,7 @@ static hipError_t launch_parked_finish(const Shape &s, const float *logits, int6
     if (select) {
         const int nwg = std::max(1, (s.bv.max_seq_len + kFinSelBlocks * kFinTokens - 1) / (kFinSelBlocks * kFinTokens));
         const dim3 grid(nwg + (img_mass ? 1 : 0) + (out ? s.n_q_heads : 0), s.batch), block(kFinSelThreads);
-        FASTOCR_LAUNCH(K_PARKED_FINISH, parked_select_kernel, grid, block, 0, stream, s.bv, s.n_q_heads, logits, pitch, part_ml, part_zi, nsplit, scores, lse,
+        FASTOCR_LAUNCH(K_PARKED_FINISH, parked_select_kernel, grid, block, 0, stream, s.bv.seq_len, s.bv.vis_start, s.bv.vis_len, s.bv.max_seq_len, s.bv.max_vis_len, s.n_q_heads, logits, pitch, part_ml, part_zi, nsplit, scores, lse,
                        img_mass, nwg, part_o, s.kv.head_dim, (uint16_t *)out, *select, done);
         return hipGetLastError();
     }
@@ -396,8 +415,8 @@ static hipError_t launch_parked_finish(const Shape &s, const float *logits, int6
     // words that nobody wrote and drop what they make of them.
     const int nblk = std::max(1, (s.bv.max_seq_len + kFinTokens - 1) / kFinTokens);
     const dim3 grid(nblk + (img_mass ? 1 : 0) + (out ? s.n_q_heads : 0), s.batch), block(kFinThreads);
-#define FASTOCR_FINISH_N(NU, NS) FASTOCR_LAUNCH(K_PARKED_FINISH, (parked_finish_kernel<NU, NS>), grid, block, 0, stream, s.bv, s.n_q_heads, logits, pitch, \
-        part_ml, part_zi, nsplit, scores, lse, img_mass, nblk, part_o, s.kv.head_dim, (uint16_t *)out)
+#define FASTOCR_FINISH_N(NU, NS) FASTOCR_LAUNCH(K_PARKED_FINISH, (parked_finish_kernel<NU, NS>), grid, block, 0, stream, logits, part_ml, part_o, part_zi, \
+        pitch, s.n_q_heads, nsplit, nblk, s.kv.head_dim, s.bv.seq_len, s.bv.vis_start, s.bv.vis_len, s.bv.max_seq_len, s.bv.max_vis_len, scores, lse, img_mass, (uint16_t *)out)
 #define FASTOCR_FINISH(NU) do { if (nsplit <= 16) FASTOCR_FINISH_N(NU, 1); else FASTOCR_FINISH_N(NU, 4); } while (0)
     if (s.n_q_heads <= 16) FASTOCR_FINISH(1);
     else if (s.n_q_heads <= 32) FASTOCR_FINISH(2);

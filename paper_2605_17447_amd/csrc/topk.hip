@@ -211,9 +211,10 @@ constexpr int kTopkRegKeys = kTopkThreads * kTopkPer;
 // four times the work).
 template <bool VEC, int PER>
 __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(
-    const float *__restrict__ scores, BatchDev bv, double tau, const int32_t *prev_idx,
-    const int32_t *prev_cnt, int32_t *sel_idx, int32_t *sel_cnt, int64_t kmax)
+    const float *__restrict__ scores, const int32_t *prev_idx, const int32_t *seq_len, const int32_t *vis_start, const int32_t *vis_len,
+    int64_t kmax, int max_vis_len, int max_seq_len, double tau, const int32_t *prev_cnt, int32_t *sel_idx, int32_t *sel_cnt)
 {
+    const BatchDev bv{seq_len, vis_start, vis_len, max_seq_len, max_vis_len};
     __shared__ uint32_t hist[kWinBins];
     __shared__ __align__(16) uint32_t list[kWinListWords];
     __shared__ int s_pick[4];
@@ -230,9 +231,10 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(
 // (a template parameter: the argument's load and a branch in front of every merge cost 3 us at 2048 merges).
 template <typename T, bool VEC, int PER, bool MASS>
 __global__ __launch_bounds__(kTopkThreads) void focal_tail_kernel(
-    const float *__restrict__ scores, BatchDev bv, double tau, const int32_t *prev_idx,
-    const int32_t *prev_cnt, int32_t *sel_idx, int32_t *sel_cnt, int64_t kmax, int batch, CombineArgs c)
+    const float *__restrict__ scores, const int32_t *prev_idx, const int32_t *seq_len, const int32_t *vis_start, const int32_t *vis_len,
+    int64_t kmax, int max_vis_len, int batch, int max_seq_len, double tau, const int32_t *prev_cnt, int32_t *sel_idx, int32_t *sel_cnt, CombineArgs c)
 {
+    const BatchDev bv{seq_len, vis_start, vis_len, max_seq_len, max_vis_len};
     __shared__ uint32_t hist[kWinBins];
     __shared__ __align__(16) uint32_t list[kWinListWords];
     __shared__ int s_pick[4];
@@ -300,11 +302,11 @@ hipError_t launch_topk(const float *scores, const BatchDev &bv, int batch, doubl
     if (bv.max_vis_len <= kTopkRegKeys) {
         const bool vec = (reinterpret_cast<uintptr_t>(scores) & 15u) == 0 && (bv.max_vis_len & 3) == 0;
 #define FASTOCR_TOPK_REG(V, P) FASTOCR_LAUNCH(K_TOPK, (topk_reg_kernel<V, P>), dim3(batch), dim3(kTopkThreads), 0, stream, scores, \
-                                              bv, tau, prev_idx, prev_cnt, sel_idx, sel_cnt, kmax)
+        prev_idx, bv.seq_len, bv.vis_start, bv.vis_len, kmax, bv.max_vis_len, bv.max_seq_len, tau, prev_cnt, sel_idx, sel_cnt)
         if (combine) {
             const dim3 grid(batch + batch * combine->n_q_heads + (combine->mass.out ? batch : 0));
 #define FASTOCR_TAIL_M(T, V, P, M) FASTOCR_LAUNCH(K_TOPK, (focal_tail_kernel<T, V, P, M>), grid, dim3(kTopkThreads), 0, stream, scores, \
-                                          bv, tau, prev_idx, prev_cnt, sel_idx, sel_cnt, kmax, batch, *combine)
+        prev_idx, bv.seq_len, bv.vis_start, bv.vis_len, kmax, bv.max_vis_len, batch, bv.max_seq_len, tau, prev_cnt, sel_idx, sel_cnt, *combine)
 #define FASTOCR_TAIL_T(T, V, P) do { if (combine->mass.out) FASTOCR_TAIL_M(T, V, P, true); else FASTOCR_TAIL_M(T, V, P, false); } while (0)
 #define FASTOCR_TAIL(V, P) do { if (combine->out_f32) FASTOCR_TAIL_T(float, V, P); else FASTOCR_TAIL_T(uint16_t, V, P); } while (0)
             if (bv.max_vis_len <= kTopkThreads * 4) { if (vec) FASTOCR_TAIL(true, 4); else FASTOCR_TAIL(false, 4); }

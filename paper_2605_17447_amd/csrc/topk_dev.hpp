@@ -387,6 +387,7 @@ __device__ __forceinline__ void topk_reg_body(
     }
 
     const int e_seq = bv.seq_len[b], e_start = bv.vis_start[b], e_vis = bv.vis_len[b];
+    if constexpr (!COHERENT) asm volatile("" :: "s"(e_seq), "s"(e_start), "s"(e_vis));        // (all three before anything waits for the arguments below)
     const int e_prev = (prev_cnt ? prev_cnt : bv.vis_len)[b];
     const SeqGeom geo = seq_geom_of(bv, e_seq, e_start, e_vis);
     const int N = geo.N;
