@@ -6,6 +6,7 @@
 
 namespace fastocr {
 
+constexpr int kCombineWalk = 12;       // up to this many every thread walks their maxima
 constexpr int kCombineFew = 32;        // up to this many partials per head the merge takes its one-round-trip form
 
 // What the partials are added up in: fp64 for fp32 outputs (up to 32 and more fp32 partials in an fp32 chain were the
@@ -65,12 +66,17 @@ __device__ __forceinline__ void combine_wide_body(const float *__restrict__ part
     Ax4 o = Ax4{0, 0, 0, 0};
     if (nsplit <= kCombineFew && nsplit <= 4 * SL) {
         // A handful of partials (a short list cut fine): one memory round trip instead of two.  The
-        // thread's (at most four) accumulators are requested first, from clamped addresses; then every
-        // thread reads all the maxima itself -- the same addresses across the workgroup, requests that
-        // travel together with the others -- instead of waiting for a reduction through LDS.
+        // thread's (at most four) accumulators are requested from clamped addresses, and by every
+        // lane one of the maxima, which meet by lane moves instead of a reduction through LDS.  A loop over the maxima that every
+        // thread reads is one scalar load and one wait per partial: hidden behind the accumulators up to a dozen of them (10 ranges, scores, mass and
+        // merge of a warm-up layer: the layer 16.13 us against 16.37 by lanes), not beyond (32 ranges, dense attention 4 x 9216 tokens, 16/2 heads: 11.95 us
+        // against 11.67; 16, a focal layer of 16 x 17152, 64/8: 194.0 against 191.4, head_dim 64 103.6 against 101.1).
+        static_assert(kCombineFew <= 64, "a lane per partial");
         f32x4 a[4];
         float mm[4], zz[4];
         const int dc = dl < nd4 ? dl : nd4 - 1;
+        const bool by_lane = nsplit > kCombineWalk;
+        M = by_lane ? ml[min(t & 63, nsplit - 1) * ml_step] : -INFINITY;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int sk = sl + k * SL < nsplit ? sl + k * SL : 0;
@@ -78,8 +84,14 @@ __device__ __forceinline__ void combine_wide_body(const float *__restrict__ part
             mm[k] = ml[sk * ml_step];
             zz[k] = ml[sk * ml_step + 1];
         }
-        M = -INFINITY;
-        for (int x = 0; x < nsplit; ++x) M = fmaxf(M, ml[x * ml_step]);
+        if (by_lane) {
+            M = fmaxf(M, dpp_move<kDppXor1>(M));
+            M = fmaxf(M, dpp_move<kDppXor2>(M));
+            M = fmaxf(M, dpp_move<kDppHalfMirror>(M));
+            M = fmaxf(rows_max(fmaxf(M, dpp_move<kDppRowMirror>(M))), -INFINITY);
+        } else {
+            for (int x = 0; x < nsplit; ++x) M = fmaxf(M, ml[x * ml_step]);
+        }
         if (M > -INFINITY && live) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
