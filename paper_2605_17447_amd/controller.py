@@ -105,18 +105,18 @@ class FixationController:
         if post_warmup and self.kept_from is not None:
             self.kept_from = "F_last"             # what the previous step left behind
         # Pruned layers between two that select attend one set: they are enqueued together where every layer's query and output are at
-        # hand.  (Sequences of any other kind may compute a layer's query when it is asked for.)
+        # hand, in plain lists and tuples.  Sequences of any other kind, classes derived from those two among them, may make a layer's query
+        # when it is asked for, from what the layer before left: each is asked for once, after the call before it.
         together = getattr(ops, "sparse_decode_attn_layers", None)
-        if not (isinstance(queries, (list, tuple)) and isinstance(outs, (list, tuple))):
+        if not (type(queries) in (list, tuple) and type(outs) in (list, tuple)):
             together = None
-        waiting = []
+        waiting = []                              # (cache, query, output)
 
         def enqueue_waiting():
             if waiting:
-                ls = list(waiting)
+                caches, qs, os = (list(x) for x in zip(*waiting))
                 waiting.clear()
-                together([self.caches[x] for x in ls], batch, [queries[x] for x in ls], self.scale, self.kept_idx, self.kept_cnt,
-                         [outs[x] for x in ls], self._ws, stream=stream)
+                together(caches, batch, qs, self.scale, self.kept_idx, self.kept_cnt, os, self._ws, stream=stream)
 
         for l, cache in enumerate(self.caches):
             ws = self._workspace(cache, batch)
@@ -146,7 +146,7 @@ class FixationController:
                 trace.append((l, "full+select", None))
             else:
                 if together is not None:
-                    waiting.append(l)
+                    waiting.append((cache, q, out))
                 else:
                     ops.sparse_decode_attn(cache, batch, q, self.scale, self.kept_idx, self.kept_cnt, out, ws,
                                            stream=stream)
