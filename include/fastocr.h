@@ -206,8 +206,10 @@ int fastocr_sparse_decode_attn(const fastocr_kv_view *kv, const fastocr_batch_vi
 /*
  * fastocr_sparse_decode_attn for n_layers layers that attend the same set, kv[l], q[l] and out[l] each: what the calls one after the
  * other give, up to the rounding that their range counts make, in one launch per 32 layers where the caches differ in their places
- * alone, run on the bf16 matrix-core kernels, and no output overlaps another layer's query or output; else those calls.  For programs that
- * hold the queries of several layers at once.  All arguments are checked before anything is enqueued.  ws: as the largest layer needs.
+ * alone, run on the bf16 matrix-core kernels, and no output overlaps another output, another layer's query, a contiguous cache, a block
+ * table, the set or the lengths; else those calls.  How far the pool of a paged cache reaches is not known here: no output may lie in the pages
+ * of any layer's cache.  For programs that hold the queries of several layers at once.  All arguments are checked before anything is
+ * enqueued.  ws: as the largest layer needs.
  * Kernels are timed as FASTOCR_KERNEL_SPARSE_ATTN, a launch of several layers once.
  */
 int fastocr_sparse_decode_attn_layers(int n_layers, const fastocr_kv_view *kv, const fastocr_batch_view *bv,

@@ -45,7 +45,7 @@ def _call_command(out: str, hipcc: str, host_sanitize: bool):
         compiler = [clang, "-O1", "-g", "-fsanitize=address", "-fsanitize=undefined", "-fno-sanitize-recover=undefined",
                     "-fno-sanitize=vptr,function", "-fno-omit-frame-pointer", "-shared-libsan"]
     return [*compiler, "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-            "-I", INCLUDE, "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+            "-I", INCLUDE, "-I", CSRC, "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
             "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "pycall.cpp"), "-o", out,
             "-L", os.path.join(home, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
 

@@ -335,9 +335,22 @@ def sparse_decode_attn(cache: KvCache, batch: SeqBatch, q: torch.Tensor, scale: 
            "fastocr_sparse_decode_attn")
 
 
+def _bytes_of(t: torch.Tensor):
+    """The addresses [first, last) between which a tensor's elements lie."""
+    lo = t.data_ptr()
+    return lo, lo if t.numel() == 0 else lo + (1 + sum((n - 1) * s for n, s in zip(t.shape, t.stride()))) * t.element_size()
+
+
+def _meets_pages(caches: List[KvCache], outs: List[torch.Tensor]) -> bool:
+    """Whether an output lies in the pool of a paged cache, whose reach the library does not know."""
+    at = [_bytes_of(t) for t in outs]
+    return any(lo < hi2 and lo2 < hi for c in caches if c.block_table is not None for lo, hi in map(_bytes_of, (c.k, c.v)) for lo2, hi2 in at)
+
+
 def sparse_decode_attn_layers(caches: List[KvCache], batch: SeqBatch, queries: List[torch.Tensor], scale: float, sel_idx: torch.Tensor,
                               sel_cnt: torch.Tensor, outs: List[torch.Tensor], ws: torch.Tensor, stream=None) -> None:
-    """fastocr_sparse_decode_attn_layers: sparse_decode_attn of several layers with one set, queries[l] and outs[l] each."""
+    """fastocr_sparse_decode_attn_layers: sparse_decode_attn of several layers with one set, queries[l] and outs[l] each.  Layers with an
+    output in the pool of a paged cache go one after the other."""
     caches, queries, outs = list(caches), list(queries), list(outs)
     assert len(caches) == len(queries) == len(outs)
     if not caches:
@@ -346,6 +359,10 @@ def sparse_decode_attn_layers(caches: List[KvCache], batch: SeqBatch, queries: L
         rc = _call.sparse_layers(caches, batch, queries, scale, sel_idx, sel_cnt, outs, ws, stream)
         if rc is not None:
             return _check(rc, "fastocr_sparse_decode_attn_layers")
+    if _meets_pages(caches, outs):
+        for cache, q, out in zip(caches, queries, outs):
+            sparse_decode_attn(cache, batch, q, scale, sel_idx, sel_cnt, out, ws, stream)
+        return
     lib = _lib or load_library()
     n, bv = len(caches), batch.view()
     for q, out in zip(queries, outs):

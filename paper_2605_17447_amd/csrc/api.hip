@@ -10,6 +10,7 @@
 #include <mutex>
 #include <vector>
 
+#include "apart.hpp"
 #include "fastocr.h"
 #include "kernels.hpp"
 
@@ -710,6 +711,33 @@ static bool alike(const fastocr_kv_view &a, const fastocr_kv_view &b)
            a.stride_page == b.stride_page && a.max_pages_per_seq == b.max_pages_per_seq;
 }
 
+// Layers one after the other read and write in their order: no output may lie in anything that is read by the layers (its own query apart), nor in another
+// output.  (The pages of a paged cache are not looked at: how far its pool reaches is not known here.)
+static bool layers_apart(int n, const fastocr_kv_view *kv, const fastocr_batch_view *bv, const void *const *q, int n_q_heads,
+                         const int32_t *sel_idx, const int32_t *sel_cnt, int64_t kmax, void *const *out)
+{
+    const int64_t B = bv->batch, es = kv[0].dtype == FASTOCR_BF16 ? 2 : 4, row = (int64_t)kv[0].head_dim * es, io = B * n_q_heads * row;
+    Outputs<kLayerSet> outs;
+    Span spans[kLayerSet];
+    for (int i = 0; i < n; ++i) spans[i] = span_of(out[i], io);
+    if (!outs.set(spans, n)) return false;
+    for (const int32_t *p : {bv->seq_len, bv->vis_start, bv->vis_len, sel_cnt})
+        if (!outs.apart(span_of(p, B * 4), -1)) return false;
+    if (!outs.apart(span_of(sel_idx, B * kmax * 4), -1)) return false;
+    const uint64_t last = (uint64_t)(B - 1) * kv[0].stride_seq + (uint64_t)(kv[0].n_kv_heads - 1) * kv[0].stride_head +
+                          (uint64_t)std::max(bv->max_seq_len - 1, 0) * kv[0].stride_token;          // the farthest row
+    const int64_t cache = (int64_t)(last * es) + row;
+    for (int i = 0; i < n; ++i) {
+        if (!outs.apart(span_of(q[i], io), i)) return false;
+        if (kv[i].page_tokens > 0) {
+            if (!outs.apart(span_of(kv[i].block_table, B * kv[i].max_pages_per_seq * 4), -1)) return false;
+        } else if (!outs.apart(span_of(kv[i].k, cache), -1) || !outs.apart(span_of(kv[i].v, cache), -1)) {
+            return false;
+        }
+    }
+    return true;
+}
+
 int fastocr_sparse_decode_attn_layers(int n_layers, const fastocr_kv_view *kv, const fastocr_batch_view *bv, const void *const *q,
                                       int n_q_heads, float scale, const int32_t *sel_idx, const int32_t *sel_cnt, int64_t kmax,
                                       void *const *out, void *ws, size_t ws_bytes, void *hip_stream)
@@ -727,26 +755,15 @@ int fastocr_sparse_decode_attn_layers(int n_layers, const fastocr_kv_view *kv, c
         together = together && alike(kv[0], kv[l]) && make_shape(&kv[l], bv, n_q_heads).fast;
     }
     if (n_layers == 0 || bv->batch == 0) return FASTOCR_OK;
-    const bool merges = g_tune_attn_merge.load(std::memory_order_relaxed) != 0;
-    if (together && merges && g_tune_splits[FASTOCR_OP_SPARSE_DECODE_ATTN].load(std::memory_order_relaxed) == 0) {
-        // no output where another layer's query or output lies: layers one after the other read and write in their order
-        const size_t bytes = (size_t)bv->batch * n_q_heads * kv[0].head_dim * (kv[0].dtype == FASTOCR_BF16 ? 2 : 4);
-        auto apart = [&](const void *a, const void *b) {
-            const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
-            return x + bytes <= y || y + bytes <= x;
-        };
-        for (int i = 0; i < n_layers && together; ++i)
-            for (int j = 0; j < n_layers && together; ++j)
-                together = i == j || (apart(out[i], q[j]) && apart(out[i], out[j]));
-    } else {
-        together = false;
-    }
+    together = together && g_tune_attn_merge.load(std::memory_order_relaxed) != 0 &&
+               g_tune_splits[FASTOCR_OP_SPARSE_DECODE_ATTN].load(std::memory_order_relaxed) == 0;
     for (int l = 0; l < n_layers;) {
         int n = together ? std::min({kLayerSet, n_layers - l, 65535 / bv->batch}) : 1;
-        if (n < 2) {
-            const int rc = fastocr_sparse_decode_attn(&kv[l], bv, q[l], n_q_heads, scale, sel_idx, sel_cnt, kmax, out[l], ws, ws_bytes, hip_stream);
-            if (rc != FASTOCR_OK) return rc;
-            ++l;
+        if (n < 2 || !layers_apart(n, kv + l, bv, q + l, n_q_heads, sel_idx, sel_cnt, kmax, out + l)) {
+            for (n = std::max(n, 1); n > 0; --n, ++l) {
+                const int rc = fastocr_sparse_decode_attn(&kv[l], bv, q[l], n_q_heads, scale, sel_idx, sel_cnt, kmax, out[l], ws, ws_bytes, hip_stream);
+                if (rc != FASTOCR_OK) return rc;
+            }
             continue;
         }
         Shape s = make_shape(&kv[l], bv, n_q_heads);

@@ -5,11 +5,13 @@
 // Every function returns the library's status, or None when something is not as the plain case has it -- an object of another
 // class, a tensor of the wrong type, shape or layout, no CUDA context yet, an exception: the caller then takes the
 // Python path, which does the same call or raises what it always raised.  Nothing is kept from one call to the next.
+#include <algorithm>
 #include <deque>
 #include <vector>
 
 #include <torch/csrc/autograd/python_variable.h>
 
+#include "apart.hpp"
 #include "fastocr.h"
 
 namespace {
@@ -275,6 +277,14 @@ PyObject *sparse(PyObject *, PyObject *const *a, Py_ssize_t n)               // 
     });
 }
 
+// the bytes between which a tensor's elements lie
+fastocr::Span reach(const at::Tensor &t)
+{
+    int64_t last = 1;
+    for (int64_t i = 0; i < t.dim(); ++i) last += (t.size(i) - 1) * t.stride(i);
+    return fastocr::span_of(t.data_ptr(), t.numel() ? last * (int64_t)t.element_size() : 0);
+}
+
 PyObject *sparse_layers(PyObject *, PyObject *const *a, Py_ssize_t n)        // caches, batch, queries, scale, sel_idx, sel_cnt, outs, ws, stream
 {
     FASTOCR_ARGS(9)
@@ -299,6 +309,19 @@ PyObject *sparse_layers(PyObject *, PyObject *const *a, Py_ssize_t n)        // 
             hq = query_heads(t);
             q.push_back(t.data_ptr());
             out.push_back(output(PyList_GET_ITEM(a[6], l), t));
+        }
+        // an output in the pool of a paged cache, whose reach the library does not know, is left to the Python path
+        std::vector<fastocr::Span> pools;
+        for (const Cache &c : caches) if (c.table.p != Py_None) for (PyObject *t : {c.k.p, c.v.p}) pools.push_back(reach(tensor(t)));
+        if (!pools.empty()) {
+            std::sort(pools.begin(), pools.end(), [](const fastocr::Span &x, const fastocr::Span &y) { return x.lo < y.lo; });
+            // (pools that share memory: a span up to the farthest end so far)
+            for (size_t i = 1; i < pools.size(); ++i) pools[i].hi = std::max(pools[i].hi, pools[i - 1].hi);
+            for (Py_ssize_t l = 0; l < m; ++l) {
+                const fastocr::Span o = reach(tensor(PyList_GET_ITEM(a[6], l)));
+                const auto p = std::partition_point(pools.begin(), pools.end(), [&](const fastocr::Span &x) { return x.lo < o.hi; });
+                require(p == pools.begin() || std::prev(p)->hi <= o.lo);
+            }
         }
         return unlocked([&]() {
             return g_sparse_layers((int)m, views.data(), &b.view, q.data(), hq, scale, k.idx, k.cnt, k.kmax, out.data(), ws.p, ws.bytes, s);
