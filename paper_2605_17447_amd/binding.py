@@ -349,8 +349,8 @@ def _meets_pages(caches: List[KvCache], outs: List[torch.Tensor]) -> bool:
 
 def sparse_decode_attn_layers(caches: List[KvCache], batch: SeqBatch, queries: List[torch.Tensor], scale: float, sel_idx: torch.Tensor,
                               sel_cnt: torch.Tensor, outs: List[torch.Tensor], ws: torch.Tensor, stream=None) -> None:
-    """fastocr_sparse_decode_attn_layers: sparse_decode_attn of several layers with one set, queries[l] and outs[l] each.  Layers with an
-    output in the pool of a paged cache go one after the other."""
+    """fastocr_sparse_decode_attn_layers: sparse_decode_attn of several layers with one set, queries[l] and outs[l] each.  Layers of unlike
+    query heads, or with an output in the pool of a paged cache, go one after the other."""
     caches, queries, outs = list(caches), list(queries), list(outs)
     assert len(caches) == len(queries) == len(outs)
     if not caches:
@@ -359,7 +359,7 @@ def sparse_decode_attn_layers(caches: List[KvCache], batch: SeqBatch, queries: L
         rc = _call.sparse_layers(caches, batch, queries, scale, sel_idx, sel_cnt, outs, ws, stream)
         if rc is not None:
             return _check(rc, "fastocr_sparse_decode_attn_layers")
-    if _meets_pages(caches, outs):
+    if any(q.size(1) != queries[0].size(1) for q in queries) or _meets_pages(caches, outs):
         for cache, q, out in zip(caches, queries, outs):
             sparse_decode_attn(cache, batch, q, scale, sel_idx, sel_cnt, out, ws, stream)
         return
@@ -367,7 +367,6 @@ def sparse_decode_attn_layers(caches: List[KvCache], batch: SeqBatch, queries: L
     n, bv = len(caches), batch.view()
     for q, out in zip(queries, outs):
         assert q.is_contiguous() and out.is_contiguous() and out.shape == q.shape and out.dtype == q.dtype
-        assert q.size(1) == queries[0].size(1)
     assert sel_idx.dtype == torch.int32 and sel_idx.is_contiguous() and sel_cnt.dtype == torch.int32
     views = (KvView * n)(*(c.view() for c in caches))
     at = lambda ts: (ctypes.c_void_p * n)(*(t.data_ptr() for t in ts))          # noqa: E731

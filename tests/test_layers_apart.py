@@ -123,3 +123,15 @@ def test_an_output_in_the_pool_of_a_paged_cache(recorded, monkeypatch, native, w
         monkeypatch.setattr(fb, "_call", call)
     fb.sparse_decode_attn_layers(caches, batch, qs, 0.125, i32(B, 4), i32(B), outs, torch.zeros(256, dtype=torch.uint8))
     assert seen == goes
+
+
+@pytest.mark.parametrize("native", [True, False])
+def test_layers_of_unlike_query_heads_go_one_by_one(recorded, monkeypatch, native):
+    seen, call = recorded
+    monkeypatch.setattr(fb, "_call", call if native else None)
+    i32 = lambda *s: torch.zeros(*s, dtype=torch.int32)                  # noqa: E731
+    caches = [fb.KvCache(*(torch.zeros(2, 2, 40, 64, dtype=torch.bfloat16) for _ in range(2))) for _ in range(3)]
+    qs = [torch.zeros(2, h, 64, dtype=torch.bfloat16) for h in (4, 8, 4)]
+    fb.sparse_decode_attn_layers(caches, fb.SeqBatch(i32(2), i32(2), i32(2), 40, 20), qs, 0.125, i32(2, 4), i32(2), [torch.zeros_like(q) for q in qs],
+                                 torch.zeros(256, dtype=torch.uint8))
+    assert seen == ["one"] * 3
