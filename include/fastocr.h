@@ -209,7 +209,9 @@ int fastocr_sparse_decode_attn(const fastocr_kv_view *kv, const fastocr_batch_vi
  * alone, run on the bf16 matrix-core kernels, and no output overlaps another output, another layer's query, a contiguous cache, a block
  * table, the set or the lengths; else those calls.  How far the pool of a paged cache reaches is not known here: no output may lie in the pages
  * of any layer's cache.  For programs that hold the queries of several layers at once.  All arguments are checked before anything is
- * enqueued.  ws: as the largest layer needs.
+ * enqueued.  ws: as the largest layer needs.  Ranges of a stream merge inside the launch, and wait for each other, as in
+ * fastocr_sparse_decode_attn; without an exchange slot, or once the exchange is distrusted, each layer leaves the same ranges' partials in ws
+ * and a merge launch follows: the same bits.  fastocr_set_tuning("graph_replay", 1) has no effect on layers in one launch.
  * Kernels are timed as FASTOCR_KERNEL_SPARSE_ATTN, a launch of several layers once.
  */
 int fastocr_sparse_decode_attn_layers(int n_layers, const fastocr_kv_view *kv, const fastocr_batch_view *bv,

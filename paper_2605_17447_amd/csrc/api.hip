@@ -757,28 +757,46 @@ int fastocr_sparse_decode_attn_layers(int n_layers, const fastocr_kv_view *kv, c
     if (n_layers == 0 || bv->batch == 0) return FASTOCR_OK;
     together = together && g_tune_attn_merge.load(std::memory_order_relaxed) != 0 &&
                g_tune_splits[FASTOCR_OP_SPARSE_DECODE_ATTN].load(std::memory_order_relaxed) == 0;
-    for (int l = 0; l < n_layers;) {
-        int n = together ? std::min({kLayerSet, n_layers - l, 65535 / bv->batch}) : 1;
+    auto one_by_one = [&](int from, int n) {
+        for (int l = from; l < from + n; ++l) {
+            const int rc = fastocr_sparse_decode_attn(&kv[l], bv, q[l], n_q_heads, scale, sel_idx, sel_cnt, kmax, out[l], ws, ws_bytes, hip_stream);
+            if (rc != FASTOCR_OK) return rc;
+        }
+        return (int)FASTOCR_OK;
+    };
+    for (int l = 0, n; l < n_layers; l += n) {
+        n = together ? std::min({kLayerSet, n_layers - l, 65535 / bv->batch}) : 1;
         if (n < 2 || !layers_apart(n, kv + l, bv, q + l, n_q_heads, sel_idx, sel_cnt, kmax, out + l)) {
-            for (n = std::max(n, 1); n > 0; --n, ++l) {
-                const int rc = fastocr_sparse_decode_attn(&kv[l], bv, q[l], n_q_heads, scale, sel_idx, sel_cnt, kmax, out[l], ws, ws_bytes, hip_stream);
-                if (rc != FASTOCR_OK) return rc;
-            }
+            const int rc = one_by_one(l, n);
+            if (rc != FASTOCR_OK) return rc;
             continue;
         }
-        Shape s = make_shape(&kv[l], bv, n_q_heads);
-        LayerPtrs at[kLayerSet];
-        for (int i = 0; i < n; ++i) at[i] = LayerPtrs{kv[l + i].k, kv[l + i].v, q[l + i], out[l + i], kv[l + i].block_table};
+        const Shape s = make_shape(&kv[l], bv, n_q_heads);
         // ranges as for that many sequences, where they merge inside the launch
         Shape all = s;
         all.batch = s.batch * n;
-        int nsplit = choose_splits(FASTOCR_OP_SPARSE_DECODE_ATTN, all, sparse_positions(bv, kmax), nullptr, 0), slot = -1;
+        const int positions = sparse_positions(bv, kmax);
+        int nsplit = choose_splits(FASTOCR_OP_SPARSE_DECODE_ATTN, all, positions, nullptr, 0), slot = -1;
         uint32_t *flag = nullptr;
-        if (nsplit > 1 && attn_merges_in_kernel(all, nsplit) && exchange_trusted()) slot = exchange_slot(EX_MERGE, (hipStream_t)hip_stream, &flag);
-        if (slot < 0) nsplit = 1;
+        if (nsplit > 1 && !attn_merges_in_kernel(all, nsplit)) {
+            nsplit = 1;
+        } else if (nsplit > 1) {
+            if (exchange_trusted()) slot = exchange_slot(EX_MERGE, (hipStream_t)hip_stream, &flag);
+            if (slot < 0) {
+                // The same ranges as each layer's partials and a merge launch (kNoMergeSlot): the outputs' bits do not depend on how many streams
+                // are in use.  (ws holds them: a layer's own streams times nsplit are at most a chip, and nsplit at most a range per four tiles.)
+                for (int i = l; i < l + n; ++i) {
+                    const hipError_t e = launch_attn(make_shape(&kv[i], bv, n_q_heads), q[i], scale, sel_idx, sel_cnt, kmax, out[i], nullptr, ws,
+                                                     nsplit, kNoMergeSlot, nullptr, (hipStream_t)hip_stream);
+                    if (e != hipSuccess) return FASTOCR_EHIP;
+                }
+                continue;
+            }
+        }
+        LayerPtrs at[kLayerSet];
+        for (int i = 0; i < n; ++i) at[i] = LayerPtrs{kv[l + i].k, kv[l + i].v, q[l + i], out[l + i], kv[l + i].block_table};
         const hipError_t e = launch_attn_layers(s, n, at, scale, sel_idx, sel_cnt, kmax, nsplit, slot < 0 ? 0 : slot, flag, (hipStream_t)hip_stream);
         if (e != hipSuccess) return FASTOCR_EHIP;
-        l += n;
     }
     return FASTOCR_OK;
 }
