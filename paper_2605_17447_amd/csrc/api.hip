@@ -779,6 +779,16 @@ int fastocr_sparse_decode_attn_layers(int n_layers, const fastocr_kv_view *kv, c
         int nsplit = choose_splits(FASTOCR_OP_SPARSE_DECODE_ATTN, all, positions, nullptr, 0), slot = -1;
         uint32_t *flag = nullptr;
         if (nsplit > 1 && !attn_merges_in_kernel(all, nsplit)) {
+            // Few streams of long lists in groups of more heads than that merge takes (9 to 16 per kv head, beyond 64 tiles): one range per
+            // stream lasts as long as its list, whatever the layers; their own calls, cut into many ranges and merged by a launch, add up.
+            // Measured in us, together / one by one, batch 1 to 8: 69 tiles, 2 layers 17.5 - 25.7 / 15.9 - 23.1, 3 22.2 - 26.4 / 24.4 - 34.4,
+            // 6 23.5 - 28.9 / 48.8 - 69.9; 125 tiles, 3 36.9 - 43.2 / 25.0 - 38.0, 6 38.7 - 47.5 / 49.7 - 78.1; 250 tiles, 6 71 - 90 / 63 - 112, 13
+            // 76 - 92 / 135 - 169
+            if ((positions + 31) / 32 > 24 * n) {
+                const int rc = one_by_one(l, n);
+                if (rc != FASTOCR_OK) return rc;
+                continue;
+            }
             nsplit = 1;
         } else if (nsplit > 1) {
             if (exchange_trusted()) slot = exchange_slot(EX_MERGE, (hipStream_t)hip_stream, &flag);

@@ -1,5 +1,5 @@
 """Layers enqueued together whose ranges merge inside the launch, and the same without an exchange slot, on a distrusted exchange, on more streams
-than there are slots and from a graph: the same bits everywhere, and the oracle's results."""
+than there are slots and from a graph: the same bits everywhere, and the oracle's results.  Lists whose ranges don't merge inside a launch."""
 import numpy as np
 import pytest
 import torch
@@ -115,3 +115,17 @@ def test_a_captured_set_of_layers_replays_like_the_eager_one(L, B, Hq, Hkv, d, n
     finally:
         fb.set_tuning("exchange_fallback", 0)
 
+
+@pytest.mark.parametrize("L,rows,launches", [(2, 70, 2), (3, 70, 1), (3, 90, 3), (6, 140, 1)])
+def test_long_lists_in_groups_of_more_heads_than_the_merge_takes(L, rows, launches):
+    """16 query heads per kv head: one range per stream in one launch up to 24 tiles a layer, the layers' own calls beyond that."""
+    text = 32 * rows - 50
+    problem = _layers(L, 2, 16, 1, 128, 1000, text, ragged=False, seed=rows)
+    batch, caches, qs, idx, cnt, ws, scale = problem
+    assert text + idx.size(1) <= 32 * rows and text + idx.size(1) > 32 * (rows - 1)
+    want = _one_by_one(batch, caches, qs, idx, cnt, ws, scale, [torch.zeros_like(q) for q in qs])
+    outs = [torch.full_like(q, 5.0) for q in qs]
+    assert _launches(lambda: fb.sparse_decode_attn_layers(caches, batch, qs, scale, idx, cnt, outs, ws)) == launches
+    if launches == L:
+        assert all(torch.equal(a, b) for a, b in zip(outs, want))
+    _against_oracle(problem, outs, {0, L - 1})
