@@ -13,7 +13,7 @@ SOURCES = ["api.hip", "attn.hip", "attn_f32.hip", "score.hip", "score_resident.h
 
 # Packed-FP32 VALU forms are switched off for all device code (they have given silently wrong
 # results on these machines); hipcc's host pass does not know the feature and says so.
-# The first arguments of a kernel (up to 16 words, before the first structure) are in scalar registers when its waves start.
+# The first arguments of a kernel (16 words with the two of their own address, so 14; before the first structure) are in scalar registers when its waves start.
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-mllvm", "-amdgpu-kernarg-preload-count=16",

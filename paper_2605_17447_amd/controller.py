@@ -63,7 +63,8 @@ class FixationController:
         self._bound_seq, self._bound_vis = int(max_seq_len), int(max_vis_len)
         self._need = {}
         # set while a step is being captured into a HIP graph: the library is then told that its launches
-        # will follow each other closely (fastocr_set_tuning("graph_replay", 1)) for the calls of that step
+        # will follow each other closely (fastocr_set_tuning("graph_replay", 1)) for the calls of that step (pruned layers that share
+        # a launch are not looked at: it fills the chip without a finer cut)
         self.graph_replay = False
 
     def _workspace(self, cache, batch):

@@ -225,7 +225,7 @@ __global__ __launch_bounds__(64 * kWaves, 8 / kWaves) void attn_mfma_kernel(
     // D = 64: which of the k-block's halves this lane loads of V, and its chunk of a row
     const int vh = li >> 3, lc = lane & 7;
     // K first: its products and the exponentials run while V is still arriving
-    // (off: what rowoff_of looked up for the pair of tiles that i belongs to, h: which of the two i is)
+    // (off: the row offsets looked up for the pair of tiles that i belongs to, h: which of the two i is)
     auto load_tile = [&](int i, int64_t off, int h, u32x4(&K)[NL], u32x4(&V)[PV ? NL : 1]) {
         // row at / 4 + c of the tile.  at differs from lane to lane, c does not and goes into the lane move's own offset (at passes as
         // made anew for each tile: the compiler would keep every sum of the two in a register of its own over the loop).
@@ -848,7 +848,12 @@ hipError_t launch_attn_layers(const Shape &s, int n, const LayerPtrs *at, float 
 #define FASTOCR_LAYERS(DD, P, W, MODE) FASTOCR_LAUNCH(K_SPARSE_ATTN, (attn_mfma_kernel<DD, true, P, W, MODE, LayerSet>), grid, dim3(64 * W), 0, stream, \
         s.bv.seq_len, s.bv.vis_start, s.bv.vis_len, sel_cnt, sel_idx, kmax, nsplit, s.batch, s.kv, s.bv.max_seq_len, s.bv.max_vis_len, \
         nullptr, s.n_q_heads, G, s.kv.n_kv_heads, scale_log2, nullptr, nullptr, nullptr, nullptr, merge_slot, spin_ticks, flag, nullptr, 0, nullptr, nullptr, set)
-    // more streams than compute units: two workgroups of four waves on each, so that one's look-ups and join pass behind the other's rows
+    // More streams than compute units: two workgroups of four waves on each, so that one's look-ups and join pass behind the other's rows; up to
+    // one per compute unit eight waves, which halve a stream's tiles per wave (us, eight / four waves, lists of 200, 420 and 840 rows; 28/4 heads:
+    // 192 streams 8.7 / 8.0, 10.2 / 11.4, 16.9 / 16.9; 256 8.2 / 8.1, 12.4 / 13.2, 21.1 / 21.6; 320 13.1 / 11.2, 19.4 / 18.0, 32.9 / 29.4; 416
+    // 13.8 / 11.5, 20.8 / 19.5, 35.0 / 31.7; 832 25.8 / 19.7, 40.6 / 34.4, 70.9 / 62.2; 16/2 and 64/8 heads and lists of unlike length alike;
+    // head_dim 64, 64/8, where four waves do no worse below the line either: 256 8.3 / 7.9, 10.6 / 10.2, 15.4 / 14.0; 320 14.2 / 10.0, 17.8 / 14.4,
+    // 25.9 / 19.4; 832 26.6 / 15.9, 34.9 / 25.3, 52.5 / 37.3)
 #define FASTOCR_LAYERS_D(DD, P) do { \
         if (nsplit > 1) FASTOCR_LAYERS(DD, P, 8, kMerge); \
         else if (streams <= plan_cu_count()) FASTOCR_LAYERS(DD, P, 8, kDirect); \

@@ -70,7 +70,10 @@ __device__ __forceinline__ void combine_wide_body(const float *__restrict__ part
         // lane one of the maxima, which meet by lane moves instead of a reduction through LDS.  A loop over the maxima that every
         // thread reads is one scalar load and one wait per partial: hidden behind the accumulators up to a dozen of them (10 ranges, scores, mass and
         // merge of a warm-up layer: the layer 16.13 us against 16.37 by lanes), not beyond (32 ranges, dense attention 4 x 9216 tokens, 16/2 heads: 11.95 us
-        // against 11.67; 16, a focal layer of 16 x 17152, 64/8: 194.0 against 191.4, head_dim 64 103.6 against 101.1).
+        // against 11.67; 16, a focal layer of 16 x 17152, 64/8: 194.0 against 191.4, head_dim 64 103.6 against 101.1).  From ten to sixteen the two are
+        // within 0.5 us of each other (4608 tokens, 10 / 12 / 14 / 16 ranges, walk then lanes: dense attention, batch 4, 16/2 heads 11.29 / 10.44 /
+        // 10.14 / 9.97, 11.91 / 10.80 / 10.50 / 10.16; 28/4 11.98 / 11.47 / 11.63 / 11.57, 12.33 / 11.86 / 11.89 / 11.82; 64/8 19.34 / 17.76 / 17.36 / 17.13,
+        // 19.10 / 17.59 / 16.97 / 16.94; batch 12, 16/2 14.34 / 16.87 / 15.85 / 14.92, 14.28 / 16.63 / 15.59 / 14.68; a warm-up layer of them within 0.3).
         static_assert(kCombineFew <= 64, "a lane per partial");
         f32x4 a[4];
         float mm[4], zz[4];

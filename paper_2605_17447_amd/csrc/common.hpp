@@ -138,7 +138,6 @@ constexpr int kDppXor2 = 0x4E;          // quad_perm [2,3,0,1]
 constexpr int kDppHalfMirror = 0x141;   // lane i <-> 7 - i within each 8 lanes
 constexpr int kDppRowMirror = 0x140;    // lane i <-> 15 - i within each 16 lanes
 constexpr int kDppRor8 = 0x128;         // lane i <- lane i ^ 8
-constexpr int kDppQuad0 = 0x00, kDppQuad1 = 0x55, kDppQuad2 = 0xAA, kDppQuad3 = 0xFF;      // quad_perm: lane k of each quad to its four lanes
 
 // A lane's value together with that of the lane 16 (32) away, for commutative reductions: gfx950 swaps
 // rows of 16 lanes (halves of 32) between two registers in one VALU instruction, where a general
